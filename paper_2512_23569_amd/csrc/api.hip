@@ -926,7 +926,6 @@ htsvd_status htsvd_set_basis(htsvd_ctx *ctx, int32_t ps, int32_t c, const double
     //   S0 = s0' + 2re', S1 = s0' - re' - im', S2 = s0' - re' + im'  (c = 1: identities).
     std::vector<uint16_t> frag;
     {
-        const int NP = c == 3 ? 40 : 8;
         std::vector<double> Lxi((size_t)P * P, 0.0), LSi((size_t)P * P, 0.0);
         if (c == 3) {
             // inverses of [[1,1,1],[2,-1,-1],[0,-1,1]] and [[1,2,0],[1,-1,-1],[1,-1,1]]
@@ -960,32 +959,9 @@ htsvd_status htsvd_set_basis(htsvd_ctx *ctx, int32_t ps, int32_t c, const double
         };
         const std::vector<double> Ff = mul(mul(LSi, T, false), Lxi, false);
         const std::vector<double> Fi = mul(mul(LSi, T, true), Lxi, false);
-        for (int n = 0; n < P; ++n)
-            for (int k = 0; k < P; ++k)
-                if ((n < 64) != (k < 64) && (std::fabs(Ff[(size_t)n * P + k]) > 1e-12 || std::fabs(Fi[(size_t)n * P + k]) > 1e-12))
-                    return fail(HTSVD_EINVAL, "per-slice transform is not block diagonal");
-        auto f16 = host_f16;
-        auto f16v = host_f16_value;
-        frag.assign((size_t)2 * 2 * NP * 64 * 8, 0);
-        for (int dir = 0; dir < 2; ++dir) {
-            const std::vector<double> &M = dir == 0 ? Ff : Fi;
-            int pr = 0;
-            for (int t = 0; t < 2 * c; ++t)
-                for (int st = 0; st < 4 * c; ++st) {
-                    const bool blk0 = t < 2, kin0 = st < 4;
-                    if (blk0 != kin0) continue;   // zero blocks are skipped
-                    for (int l = 0; l < 64; ++l)
-                        for (int jj = 0; jj < 8; ++jj) {
-                            const int k = 16 * st + 8 * (l / 32) + jj, n = 32 * t + (l % 32);
-                            const double v = M[(size_t)n * P + k];
-                            const uint16_t hi = f16(v), lo = f16(v - f16v(hi));
-                            frag[((size_t)((dir * 2 + 0) * NP + pr) * 64 + l) * 8 + jj] = hi;
-                            frag[((size_t)((dir * 2 + 1) * NP + pr) * 64 + l) * 8 + jj] = lo;
-                        }
-                    ++pr;
-                }
-            if (pr != NP) return fail(HTSVD_EINVAL, "internal: fragment table size");
-        }
+        frag.assign(filter_mfma_table_halves(c), 0);
+        if (!filter_mfma_tables(c, Ff.data(), Fi.data(), host_f16, host_f16_value, frag.data()))
+            return fail(HTSVD_EINVAL, "per-slice transform has not the expected structure");
     }
     const int slot = c == 3;
     hipError_t e = hipSetDevice(ctx->device);
@@ -1003,7 +979,7 @@ htsvd_status htsvd_set_basis(htsvd_ctx *ctx, int32_t ps, int32_t c, const double
         return hip_fail(e, "basis upload");
     if (!ctx->basis[slot].frag) {
         void *fp = nullptr;
-        if ((e = hipMalloc(&fp, sizeof(uint16_t) * 2 * 2 * 40 * 64 * 8)) != hipSuccess)
+        if ((e = hipMalloc(&fp, sizeof(uint16_t) * frag.size())) != hipSuccess)
             return fail(HTSVD_ENOMEM, "basis allocation");
         ctx->basis[slot].frag = fp;
     }

@@ -66,17 +66,24 @@ struct TileGeom {
     int TY, TX;          // references per tile
     int tiles_y, tiles_x;
     int RH, RW;          // region capacity (rows, cols) per tile
-    int RP;              // row pitch of a region plane in floats (>= RW, RP % 16 == 8)
+    int RP;              // row pitch of a region in pixels (>= RW, see region_pitch)
     int FS;              // fixed-point shift of the LDS accumulation (sums in int32 units of 2^-FS)
     int R;               // search radius (W-1)/2
 };
 
-// A tile's region is C + 1 planes of RH x RP floats: the channel sums, then the number of
-// patches covering each pixel.  Planar, with the pitch chosen so that the 4 x 8 pixels of a
-// patch half fall on 32 distinct LDS banks.  In LDS the planes hold int32 (fixed point for the
+// A tile's region is RH x RP pixels: the channel sums (C per pixel, interleaved), then a plane
+// with the number of patches covering each pixel.  In LDS it holds int32 (fixed point for the
 // sums, see FS); the global copy is float.
-__host__ __device__ inline int region_plane(const TileGeom &tg) { return tg.RH * tg.RP; }
-__host__ __device__ inline int region_elems(const TileGeom &tg, int C) { return (C + 1) * tg.RH * tg.RP; }
+__host__ __device__ inline int region_plane(const TileGeom &tg) { return (tg.RH * tg.RP + 3) & ~3; }
+__host__ __device__ inline int region_elems(const TileGeom &tg, int C) { return (C + 1) * region_plane(tg); }
+// Row pitch of a region of w columns: a filter instruction adds to 8 rows x 2 columns 4 apart of a
+// patch (16 lanes; the other three groups of lanes hold other patches), C = 1 or 3 words a pixel.
+// The smallest pitch >= w for which these 16 words lie in distinct banks (of 32 or of 64):
+// pitch = 3, 5, 11, 13, 19, 21, 27 or 29 modulo 32.
+inline int region_pitch(int w) {
+    while (!(((w & 7) == 3) || ((w & 7) == 5))) ++w;
+    return w;
+}
 
 // One image of a batched call, as the persistent kernels see it.
 struct BatchItem {
@@ -280,6 +287,9 @@ int filter_lds_bytes_for(const TileGeom &tg, int C, int K);
 int filter_mfma_lds_bytes(const TileGeom &tg, int C);
 int filter_mfma_group_bytes(int C);  // LDS besides the region
 int filter_mfma_static_bytes();
+size_t filter_mfma_table_halves(int C);   // fp16 values of the operand tables
+bool filter_mfma_tables(int C, const double *fwd, const double *inv, uint16_t (*h16)(double), double (*h16v)(uint16_t),
+                        uint16_t *out);
 // ra_d (n_ref x 64C, may be NULL) and ra_flag (n_ref): RA-Haar-tSVD corrections of the first Haar
 // row, applied to the groups whose flag is set.
 hipError_t launch_filter_mfma(const ImageGeom &g, const TileGeom &tg, int K, const BasisDev &b, const int32_t *idx,

@@ -36,9 +36,11 @@ __device__ __forceinline__ void gather_px(const ImageGeom &g, const TileGeom &tg
             int c0, c1;
             region_cols(g, tg, tx, &c0, &c1);
             if (x < c0 || x > c1) continue;
-            const float *src = regions + (int64_t)(ty * tg.tiles_x + tx) * elems + (y - r0) * tg.RP + (x - c0);
+            const float *src = regions + (int64_t)(ty * tg.tiles_x + tx) * elems;
+            const int e0 = (y - r0) * tg.RP + (x - c0);
 #pragma unroll
-            for (int k = 0; k < CH; ++k) acc[k] += src[k * plane];
+            for (int k = 0; k < C; ++k) acc[k] += src[e0 * C + k];
+            acc[C] += src[C * plane + e0];
         }
     }
     float *o = out + (int64_t)y * out_stride + (int64_t)x * C;
@@ -67,10 +69,6 @@ __global__ void gather_kernel_batched(const BatchItem *__restrict__ items, int n
     gather_px<C>(it.g, alt ? it.tg_alt : it.tg, it.regions, it.out, it.out_stride, e - pix_start[i]);
 }
 
-// Smallest pitch >= w with pitch % 16 == 8: four consecutive rows then start 8 banks apart
-// (mod 32), so the 4 x 8 pixels one half-wave adds to hit distinct banks.
-int region_pitch(int w) { return w + ((8 - w % 16) + 16) % 16; }
-
 // Largest reference tile (side <= max_side) whose region and the filter's other buffers fit in LDS.
 TileGeom plan_tiles(const ImageGeom &g, int W, int lds_budget, int max_side) {
     TileGeom tg;
@@ -82,7 +80,7 @@ TileGeom plan_tiles(const ImageGeom &g, int W, int lds_budget, int max_side) {
     for (; T > 1; --T) {
         const int RH = min((T - 1) * g.s + 2 * tg.R + PS, g.h);
         const int RW = min((T - 1) * g.s + 2 * tg.R + PS, g.w);
-        if (CH * RH * region_pitch(RW) * 4 + other <= lds_budget) break;
+        if (CH * ((RH * region_pitch(RW) + 3) & ~3) * 4 + other <= lds_budget) break;
     }
     tg.TY = tg.TX = T;
     tg.RH = min((T - 1) * g.s + 2 * tg.R + PS, g.h);

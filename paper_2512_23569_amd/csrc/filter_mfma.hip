@@ -1,25 +1,34 @@
 // Collaborative filtering (Eq. 19-21) and aggregation (Algorithm 1) on the matrix cores of gfx950.
 //
 // The per-patch transform S = U^T * G * V is linear in the patch, and with the 3-point DFT along
-// the channel mode (Eq. 4-5) it splits into a real 64 x 64 map on the channel sum and a real
-// 128 x 128 map on the (real, imaginary) pair of the first Fourier slice; the third slice is the
-// conjugate of the second.  Thirty-two patches at a time are contracted against these matrices
-// with v_mfma_f32_32x32x16_f16:
+// the channel mode (Eq. 4-5) it splits into a real 64 x 64 map on the channel sum and a complex
+// 64 x 64 map on the first Fourier slice; the third slice is the conjugate of the second.  The
+// Haar transform along the group (Eq. 7-8) is a 32 x 32 map on the patches (block diagonal for
+// groups of 4, 8 or 16).  A wavefront takes 32 patches (32 / K groups) per step through a chain of
+// matrix products in which every result is already the operand layout of the next product
+// (lane = Haar row or pixel, registers = the index summed over next), so that nothing is
+// transposed through LDS:
 //
-//   forward   [s0'; re'; im'] (32 patches x 192) = [a0, ar, ai] (32 x 192) . F^T
-//             a0 = R+G+B, ar = 2R-G-B, ai = B-G are integers, exact in fp16; F is split into
-//             fp16 hi + lo (two products, ~22-bit matrix); accumulation in fp32.
-//             S0 = s0' + 2 re', S1 = s0' - re' - im', S2 = s0' - re' + im'  (1/3 and sqrt3 folded into F)
-//   Haar      along the group (Eq. 7-8), in registers: the result layout of the MFMA puts 16
-//             patches of one coefficient column in one lane, the other 16 in lane + 32.
-//             Unnormalised butterflies; the threshold of a coefficient produced by l butterflies
-//             is tau * 2^(l/2), and the inverse scales kept values by 2^-l (exact).
-//   threshold keep |s| >= tau (Eq. 20); values within 0.05 of tau are re-decided in FP64 from the
-//             uint8 group and the FP64 transform.
-//   inverse   the kept coefficients, recombined as s0 = S0+S1+S2, sr = 2S0-S1-S2, d = S2-S1,
-//             are split into fp16 hi (nearest) + lo, transposed through LDS into the A-operand
-//             layout and multiplied by the inverse matrix with three products
-//             (hi.hi + hi.lo + lo.hi); R, G, B follow as above.
+//   1  first Haar level    D = X^T H^T: A = 16 pixels x 32 patches (bytes as fp16 1024 + b),
+//      B = the scaled sums (tile 0) and differences (tile 1) of the 16 pairs of patches.
+//      Chaining B, G, R in one accumulator gives a0 = R+G+B; p = a0 - 1.5 (G+B) = R - (G+B)/2
+//      and q = B - G follow.  All of it is exact, and has at most 11 significant bits.
+//   2  forward t-product      S = F [a0; p; q]: A = F (fp16 hi + lo, ~22-bit matrix), B = the pair
+//      rows of the pixels, exact in fp16.  With re' = A p + B q and im' = 1.5 A q - 2 B p only
+//      three 64 x 64 matrices are needed for both slices.
+//      S0 = s0' + 2 re', S1 = s0' - re' - im', S2 = s0' - re' + im'  (1/3 and sqrt3 folded into F).
+//      The further Haar levels are butterflies between the lanes of tile 0 (one multiply-add with
+//      a moved operand per value and level; see HaarRow).
+//   3  threshold              keep |s| >= tau (Eq. 20), with tau scaled per lane (a lane is one
+//      Haar row); values within 0.05 of tau are re-decided in FP64 from the uint8 group and the
+//      FP64 transform.
+//   4  inverse t-product      A = the kept coefficients s0 = S0+S1+S2, sr = 2S0-S1-S2, dn = S1-S2,
+//      split into fp16 hi + lo, B = F^T (hi + lo): all four products, in two instructions of
+//      depth 32 = 16 coefficients x (hi, lo).  A (16 coefficients x 16 Haar rows) block that
+//      thresholding killed is skipped.
+//   5  inverse Haar           A = H (entries 0, +- powers of two), B = the Haar rows of the reconstructed pixels,
+//      split into fp16 hi + lo; the result has 16 pixels along the lanes and the patches in
+//      registers.
 //   Algorithm 1: every reconstructed patch is added (sums and a count) into an LDS copy of the
 //             image region the tile's groups reach; the region goes to the tile's slot of a
 //             global buffer and the gather kernel divides.  Groups whose members lie anywhere
@@ -32,86 +41,165 @@
 namespace htsvd {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+typedef short v4s __attribute__((ext_vector_type(4)));
 
 namespace {
 
 constexpr int MW = 8;          // wavefronts per workgroup (two per SIMD)
 constexpr int MNEAR = 64;      // near-threshold list capacity per wavefront
 constexpr float MGUARD = 0.05f;
-constexpr int XS = 33;         // words per row of the per-wave transpose buffer (32 + 1 pad)
-constexpr int XWORDS = 32 * XS;
 
 struct MfmaShared {
     int r0, c0;
     int near_n[MW];
-    int near_a[MW][MNEAR];     // lane | tile << 6 | reg << 9 | group << 13
-    int near_b[MW][MNEAR];     // haar row k | coefficient q << 8
+    int near_a[MW][MNEAR];     // lane | bit of the lane's coefficient << 6
+    int near_b[MW][MNEAR];     // coefficient q
     int near_kill[MW][MNEAR];
 };
 
-// Number of pairs of fragment tables: c = 3: forward/inverse x hi/lo x 40 (tile, k-step) blocks.
-template <int C>
-struct Frag {
-    static constexpr int NPAIR = C == 3 ? 40 : 8;
+// Per-wave scratch: the address of every patch of the step and its offset in the region.
+struct WaveScratch {
+    uint64_t addr[32];
+    int off[32];
 };
 
-// Pair index of (output tile t, k-step s) in the block-diagonal fragment table.
+// Operand tables (BasisDev::frag): the maps M0, A, B (c = 1: M0), each [coefficient tile 4][k-step
+// 2][hi, lo][half of the k-step 2][lane][4 halves].  Entry j of lane 16 g + m is coefficient m of
+// the tile against pixel 4 g + j of pixel set q = 2 (k-step) + half; pixel p of set q is row p / 2,
+// column 4 (p % 2) + q of the patch.  The forward products read a lane's two halves of a k-step
+// (lane = coefficient); the inverse products read 16 coefficients x 16 pixels of one set with the
+// transposing LDS load (lane = pixel), so one copy in LDS serves both directions, without bank
+// conflicts either way.
 template <int C>
-__device__ __host__ constexpr int pair_of(int t, int s) {
-    return (C == 1 || t < 2) ? t * 4 + s : 8 + (t - 2) * 8 + (s - 4);
+struct Frag {
+    static constexpr int NM = C == 3 ? 3 : 1;           // 64 x 64 maps
+    static constexpr int MAP = 4 * 2 * 2 * 64;          // 16-byte words per map
+};
+// LDS besides the region: the maps, the two Haar operands, the waves' scratch.
+constexpr int HAAR_V8 = 4 * 64;   // [forward tile 2, inverse tile 2][lane]
+template <int C>
+__host__ __device__ constexpr int fixed_lds_bytes() {
+    return (Frag<C>::NM * Frag<C>::MAP + HAAR_V8) * 16 + 16 * 32 + MW * (int)sizeof(WaveScratch);
 }
 
-__device__ inline v8h ldfrag(const v8h *__restrict__ base, int dir, int term, int pair, int npair, int lane) {
-    return base[((dir * 2 + term) * npair + pair) * 64 + lane];
+// Haar rows of a step's 32 patches.  Tile 1, lane n: the difference of pair n (patches 2n, 2n + 1),
+// times 1/2.  Tile 0 starts as the pair sums, times 2^-5, and each further level l = 2 .. log2 K
+// makes a sum and a difference of two lanes: v += s v(partner), s = 1 in the lane that keeps the
+// sum, -1 in the one that keeps the difference (its own side minus the partner's), 0 in lanes
+// whose row is finished.  The partners n ^ 1, n ^ 2, n ^ 7, n ^ 15 are the lane permutations that
+// an operand can take within a row of 16 lanes, so the sums stay in lanes that they pair: after
+// level 2 in positions 0 and 2 of an even quad of lanes and 1 and 3 of an odd one, then in lanes
+// 0, 7, 8, 15, then 0 and 15, then 0.
+// The row of a lane covers patches first .. first + 2^l - 1: their sum, or the half that holds pair
+// n minus the other.
+struct HaarRow {
+    int l, first;
+    bool sum;
+};
+// s of lane n at level l (2 .. 5), before the levels past log2 K are dropped.
+__device__ inline int haar_step(int l, int n) {
+    const int odd = (n >> 2) & 1;                       // quad of lanes
+    const bool sum2 = (n & 1) == odd;
+    if (l == 2) return sum2 ? 1 : -1;
+    const bool sum3 = sum2 && (n & 3) == 3 * odd;
+    if (l == 3) return sum2 ? (sum3 ? 1 : -1) : 0;
+    const bool sum4 = sum3 && (n == 0 || n == 15);
+    if (l == 4) return sum3 ? (sum4 ? 1 : -1) : 0;
+    return sum4 ? (n == 0 ? 1 : -1) : 0;
 }
-
-// 8*C bytes of one patch row starting at p (dword loads + byte alignment when in bounds).
+__device__ inline HaarRow haar_row_of(int K, int ht, int n) {
+    if (ht == 1) return {1, 2 * n, false};
+    int l = 2;
+    while ((1 << l) < K && haar_step(l, n) == 1) ++l;   // the level the lane ends at
+    return {l, (2 * n >> l) << l, haar_step(l, n) == 1};
+}
+__device__ inline float haar_sign(const HaarRow &r, int n, int mu, bool pair) {
+    if ((mu >> r.l) != (r.first >> r.l)) return 0.f;
+    if (pair) return (mu & 1) ? -1.f : 1.f;             // tile 1: first minus second
+    return r.sum || ((mu ^ (2 * n)) >> (r.l - 1) & 1) == 0 ? 1.f : -1.f;
+}
+// 2^(e/2)
+__device__ inline float root2(int e) {
+    return __uint_as_float((uint32_t)(127 + (e >> 1)) << 23) * ((e & 1) ? 1.41421356237309505f : 1.f);
+}
+// The butterflies of levels 2 .. 5 on 4 C values per lane; s[l - 2] as above (0 past log2 K).  In one
+// block of assembly because the moved operand is part of the multiply-add; a value is read by the
+// move no sooner than 4 C - 1 instructions after it was written, and the block starts with the two
+// wait states a move needs after the values' own instructions, which must be vector ones.
 template <int C>
-__device__ inline void load_row_u8(const uint8_t *p, const uint8_t *end, uint32_t (&out)[2 * C]) {
-    constexpr int ND = 2 * C + 1;
-    const uintptr_t a = (uintptr_t)p;
-    const uint32_t *base = reinterpret_cast<const uint32_t *>(a & ~(uintptr_t)3);
-    const int sh = (int)(a & 3);
-    if ((const uint8_t *)(base + ND) <= end) {
-        uint32_t d[ND];
-#pragma unroll
-        for (int i = 0; i < ND; ++i) d[i] = base[i];
-#pragma unroll
-        for (int i = 0; i < 2 * C; ++i) out[i] = __builtin_amdgcn_alignbyte(d[i + 1], d[i], sh * 1u);
+__device__ inline void haar_lanes(v4f (&v)[C], const float (&s)[4]) {
+#define HB_ROW(x, y, z, w, cof, ctl)                                          \
+    "v_fmac_f32_dpp %" #x ", %" #x ", %" #cof " " ctl " row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #y ", %" #y ", %" #cof " " ctl " row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #z ", %" #z ", %" #cof " " ctl " row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #w ", %" #w ", %" #cof " " ctl " row_mask:0xf bank_mask:0xf\n"
+    if constexpr (C == 3) {
+#define HB_LEVEL(cof, ctl) HB_ROW(0, 1, 2, 3, cof, ctl) HB_ROW(4, 5, 6, 7, cof, ctl) HB_ROW(8, 9, 10, 11, cof, ctl)
+        asm("s_nop 1\n" HB_LEVEL(12, "quad_perm:[1,0,3,2]") HB_LEVEL(13, "quad_perm:[2,3,0,1]")
+                HB_LEVEL(14, "row_half_mirror") HB_LEVEL(15, "row_mirror")
+            : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[0][3]), "+v"(v[1][0]), "+v"(v[1][1]), "+v"(v[1][2]),
+              "+v"(v[1][3]), "+v"(v[2][0]), "+v"(v[2][1]), "+v"(v[2][2]), "+v"(v[2][3])
+            : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
+#undef HB_LEVEL
     } else {
-#pragma unroll
-        for (int i = 0; i < 2 * C; ++i)
-            out[i] = (uint32_t)p[4 * i] | ((uint32_t)p[4 * i + 1] << 8) | ((uint32_t)p[4 * i + 2] << 16) |
-                     ((uint32_t)p[4 * i + 3] << 24);
+#define HB_LEVEL(cof, ctl) HB_ROW(0, 1, 2, 3, cof, ctl)
+        asm("s_nop 1\n" HB_LEVEL(4, "quad_perm:[1,0,3,2]") HB_LEVEL(5, "quad_perm:[2,3,0,1]")
+                HB_LEVEL(6, "row_half_mirror") HB_LEVEL(7, "row_mirror")
+            : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[0][3])
+            : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
+#undef HB_LEVEL
+    }
+#undef HB_ROW
+}
+
+// 4 pixels (4 C bytes) of global memory, any alignment.
+template <int C>
+__device__ inline void load_seg(uint64_t addr, uint32_t (&out)[C]) {
+    typedef uint32_t u32x __attribute__((ext_vector_type(C == 3 ? 3 : 2)));
+    if constexpr (C == 3) {
+        typedef u32x __attribute__((aligned(1))) u32xu;
+        const u32x s = *(const __attribute__((address_space(1))) u32xu *)addr;
+        out[0] = s[0];
+        out[1] = s[1];
+        out[2] = s[2];
+    } else {
+        typedef uint32_t __attribute__((aligned(1))) u32u;
+        out[0] = *(const __attribute__((address_space(1))) u32u *)addr;
     }
 }
 
-__device__ inline int byte_of(const uint32_t *w, int i) { return (int)((w[i >> 2] >> (8 * (i & 3))) & 0xffu); }
-
-// Byte i of the words as a float (one byte-to-float conversion).
-__device__ inline float byte_f(const uint32_t *w, int i) { return (float)((w[i >> 2] >> (8 * (i & 3))) & 0xffu); }
-
-// Two floats as a packed pair of fp16 (round toward zero), low half first.
+// Two floats as a packed pair of fp16: round toward zero, and round to nearest even.
 __device__ inline uint32_t pack_rtz(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
 }
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t pack_rne(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){lo, hi}, v2h));
+}
+// The parts of (a, b) that the packed pair h leaves, rounded to nearest, packed.
+__device__ inline uint32_t pack_rest(float a, float b, uint32_t h) {
+    const v2h hv = __builtin_bit_cast(v2h, h);
+    float m1 = -1.f;
+    asm("" : "+s"(m1));   // not a plain subtraction, so that it becomes one mixed-precision instruction
+    v2h r;
+    r[0] = (_Float16)__builtin_fmaf((float)hv[0], m1, a);
+    r[1] = (_Float16)__builtin_fmaf((float)hv[1], m1, b);
+    return __builtin_bit_cast(uint32_t, r);
+}
 
-// Entry (k, m) of the orthonormal Haar matrix H_n of Eq. 8.
-__device__ inline double haar_w(int k, int m, int n) {
-    const double r2 = 0.70710678118654752440;
-    double w = 1.0;
-    while (n > 1) {
-        if (k < n / 2) {
-            w *= r2;
-            m >>= 1;
-            n >>= 1;
-        } else {
-            const int i = k - n / 2;
-            return m == 2 * i ? w * r2 : (m == 2 * i + 1 ? -w * r2 : 0.0);
-        }
-    }
-    return w;
+__device__ inline v8h as_v8h(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    return __builtin_bit_cast(v8h, make_uint4(a, b, c, d));
+}
+
+__device__ inline v4f mfma(v8h a, v8h b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// Transposing LDS load: each block of 16 lanes reads four rows of 16 halves (a lane points at
+// halves 4 (i % 4) .. of row i / 4), and lane i receives column i of the four rows.
+__device__ inline v4h lds_read_tr(const v4h *p) {
+    return __builtin_bit_cast(v4h, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)p));
 }
 
 __device__ inline void wave_lds_fence() {
@@ -125,111 +213,172 @@ __device__ inline double wave_sum64(double v) {
     return v;
 }
 
-// Value of the same register in lane l ^ 32.
-__device__ inline float swap_half(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
+// Keeps the values of v with |v| > lo and zeroes the others; the lanes that kept one are added to
+// `kept`, those with a kept one below hi to `band`.  In assembly so that the masks live for one
+// call only (left to the compiler, the masks of a whole pass stay live and spill); every mask is
+// read two or more vector instructions after it was written.
+__device__ inline void threshold4(v4f &v, float lo, float hi, uint64_t &kept, uint64_t &band) {
+    uint64_t m0, m1, m2, m3, n0, n1, n2, n3;
+    asm("v_cmp_gt_f32_e64 %4, |%0|, %12\n"
+        "v_cmp_gt_f32_e64 %5, |%1|, %12\n"
+        "v_cmp_gt_f32_e64 %6, |%2|, %12\n"
+        "v_cmp_gt_f32_e64 %7, |%3|, %12\n"
+        "v_cmp_lt_f32_e64 %8, |%0|, %13\n"
+        "v_cmp_lt_f32_e64 %9, |%1|, %13\n"
+        "v_cmp_lt_f32_e64 %10, |%2|, %13\n"
+        "v_cmp_lt_f32_e64 %11, |%3|, %13\n"
+        "v_cndmask_b32_e64 %0, 0, %0, %4\n"
+        "v_cndmask_b32_e64 %1, 0, %1, %5\n"
+        "v_cndmask_b32_e64 %2, 0, %2, %6\n"
+        "v_cndmask_b32_e64 %3, 0, %3, %7\n"
+        "s_and_b64 %8, %8, %4\n"
+        "s_and_b64 %9, %9, %5\n"
+        "s_and_b64 %10, %10, %6\n"
+        "s_and_b64 %11, %11, %7\n"
+        "s_or_b64 %8, %8, %9\n"
+        "s_or_b64 %10, %10, %11\n"
+        "s_or_b64 %4, %4, %5\n"
+        "s_or_b64 %6, %6, %7\n"
+        "s_or_b64 %8, %8, %10\n"
+        "s_or_b64 %4, %4, %6\n"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3), "=&s"(n0),
+          "=&s"(n1), "=&s"(n2), "=&s"(n3)
+        : "v"(lo), "v"(hi)
+        : "scc");
+    kept |= m0;
+    band |= n0;
 }
 
-// Butterfly count l of the coefficient left in register r (group size K, 16 registers per lane).
-template <int K>
-__device__ __host__ constexpr int haar_level(int r) {
-    constexpr int KL = K < 16 ? K : 16;
-    constexpr int LK = K == 32 ? 5 : (K == 16 ? 4 : (K == 8 ? 3 : 2));
-    const int i = r % KL;
-    if (i == 0) return LK;
-    int l = 1;
-    while (!((i >> (l - 1)) & 1)) ++l;
-    return l;
+// Contribution in fixed point (round to nearest even) plus the bits of MAGIC; |v| is clamped to
+// 1024 (four times the 8-bit range) so that no region sum can overflow (see the accumulation
+// shift of the tiling).  The scale 2^FS (FS <= 12) is applied here, after the fp16 products,
+// whose range it would exceed.  |v| scale <= 2^22, so v scale + 1.5 * 2^23 lies in [2^23, 2^24],
+// where floats are the integers: one fused multiply-add rounds to nearest even and the bits
+// give the integer.  Sums of n such words hold n times the bits of MAGIC modulo 2^32; the flush
+// of a tile, which knows n, takes them out.
+constexpr float MAGIC = 12582912.0f;   // 1.5 * 2^23
+constexpr uint32_t MAGIC_BITS = 0x4b400000u;
+__device__ inline uint32_t to_fixed_biased(float v, float scale) {
+    return __float_as_uint(fmaf(__builtin_amdgcn_fmed3f(v, -1024.f, 1024.f), scale, MAGIC));
 }
-
-// Haar row k (Eq. 8 order) of the coefficient in register r of lane half h.
-template <int K>
-__device__ inline int haar_row(int r, int h) {
-    constexpr int KL = K < 16 ? K : 16;
-    const int i = r % KL;
-    if (i == 0) return K == 32 ? h : 0;
-    const int l = haar_level<K>(r);
-    const int mu0 = (K == 32 ? 16 * h : 0) + i - (1 << (l - 1));
-    return (K >> l) + (mu0 >> l);
-}
-
-// Contribution in fixed point (round to nearest even); |v| is clamped to 1024 (four times the
-// 8-bit range) so that no region sum can overflow (see the accumulation shift of the tiling).
-// The scale 2^FS (FS <= 12) is applied here, after the fp16 products, whose range it would
-// exceed.  |v| scale <= 2^22, so v scale + 1.5 * 2^23 lies in [2^23, 2^24], where floats are
-// the integers: one fused multiply-add rounds to nearest even and the bits give the integer.
-__device__ inline int to_fixed(float v, float scale) {
-    constexpr float MAGIC = 12582912.0f;   // 1.5 * 2^23
-    const float t = fmaf(fminf(fmaxf(v, -1024.f), 1024.f), scale, MAGIC);
-    return __float_as_int(t) - __float_as_int(MAGIC);
-}
+__device__ inline int to_fixed(float v, float scale) { return (int)(to_fixed_biased(v, scale) - MAGIC_BITS); }
 
 // Fixed-point shift of the global aggregation.  Its 64-bit sums cannot overflow; the int32 slot
 // regions of a tile receive at most TY TX K contributions per pixel (one per member of each of
 // the tile's groups), each of |v| <= 1024, so a tiling uses the largest shift <= GA_FS that
 // keeps TY TX K 1024 2^FS below 2^31, and only tilings with a shift of at least GA_MIN_FS.
 constexpr int GA_FS = 12;
-constexpr int GA_MIN_FS = 9;
+constexpr int GA_MIN_FS = 10;
 constexpr int GA_MAX_TILE = 8;   // largest tile side of the slot regions
 
 // Geometry of a video for the global aggregation: frames of h_frame rows stacked vertically,
 // ny_frame reference rows each; with slot regions (GA == 2) a tile's references lie in one
-// frame t and its LDS region holds, per channel, the frames f_lo .. f_lo + nslot - 1 (f_lo =
-// max(0, t - radius)) as nslot blocks of RH x RP int32 (columns RW used).
+// frame t and its LDS region holds the frames f_lo .. f_lo + nslot - 1 (f_lo =
+// max(0, t - radius)) as nslot blocks of RH x RP pixels (columns RW used).
 struct VideoTiling {
     int T = 1, h_frame = 0, ny_frame = 0, radius = 0, nslot = 1;
     int RH = 0, RW = 0, RP = 0;
 };
 
-// 2^e for a small integer exponent (exact).
-__device__ inline float exp2i(int e) { return __int_as_float((e + 127) << 23); }
+// What a lane (by its place n in a row of 16) knows of its row of tile 0: the butterfly factors (0
+// past log2 K), the factor of tau, the group, and whether it is a row of sums.  Rows are scaled by
+// 2^-5 (in tile 1 by 2^-1), times the orthonormal 2^(l/2).  Kept in LDS and read once a step, so
+// that nothing of it occupies registers between steps.
+struct alignas(16) LaneRow {
+    float hs[4];
+    float rs;
+    int gi, sum, pad;
+};
 
-// Fragments of the slice-0 pairs (pair < 8: the 64 x 64 map) of both directions and terms,
-// kept in LDS: [dir][term][pair][lane].
-constexpr int F0_PAIRS = 8;
-constexpr int F0_BYTES = 2 * 2 * F0_PAIRS * 64 * 16;
+// The LDS of a workgroup: tables (filled once), wave scratch, then the region.
+template <int C>
+struct FilterLds {
+    const v4h *F;       // maps
+    v8h *H;             // Haar operands
+    LaneRow *rows;
+    WaveScratch *ws;
+    int *region;
+};
 
-__device__ inline v8h ldfrag0(const v8h *FL0, int dir, int term, int pair, int lane) {
-    return FL0[((dir * 2 + term) * F0_PAIRS + pair) * 64 + lane];
+// Fills the tables for group size K (the caller's barrier follows).
+template <int C>
+__device__ __forceinline__ FilterLds<C> filter_lds_init(float *smem, const v8h *__restrict__ FG, const int K) {
+    FilterLds<C> L;
+    v8h *F8 = reinterpret_cast<v8h *>(smem);
+    L.F = reinterpret_cast<const v4h *>(smem);
+    L.H = F8 + Frag<C>::NM * Frag<C>::MAP;
+    L.rows = reinterpret_cast<LaneRow *>(L.H + HAAR_V8);
+    L.ws = reinterpret_cast<WaveScratch *>(L.rows + 16);
+    if (threadIdx.x < 16) {
+        const int n = threadIdx.x, lk = 31 - __builtin_clz(K);
+        const HaarRow r = haar_row_of(K, 0, n);
+        LaneRow w;
+        for (int l = 2; l <= 5; ++l) w.hs[l - 2] = l <= lk ? (float)haar_step(l, n) : 0.f;
+        w.rs = root2(r.l - 10);
+        w.gi = r.first >> lk;
+        w.sum = r.sum;
+        w.pad = 0;
+        L.rows[n] = w;
+    }
+    L.region = reinterpret_cast<int *>(L.ws + MW);
+    for (int e = threadIdx.x; e < Frag<C>::NM * Frag<C>::MAP; e += MW * 64) F8[e] = FG[e];
+    for (int e = threadIdx.x; e < HAAR_V8; e += MW * 64) {
+        const int l = e & 63, n = l & 15, g = l >> 4, t = (e >> 6) & 1;
+        v8h v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (e < 128) {   // first level: pair n of tile t, patch 8g + j
+                const int mu = 8 * g + j;
+                v[j] = (_Float16)((mu >> 1) != n ? 0.f : (t == 0 ? 0.03125f : ((mu & 1) ? -0.5f : 0.5f)));
+            } else {         // inverse: patch 16t + n, lane row 4g + j%4 of tile j/4
+                const int m = 4 * g + (j & 3);
+                const HaarRow r = haar_row_of(K, j >> 2, m);
+                v[j] = (_Float16)(haar_sign(r, m, 16 * t + n, j >= 4) * (j >= 4 ? 1.f : (float)(1 << (5 - r.l))));
+            }
+        }
+        L.H[e] = v;
+    }
+    return L;
 }
 
 // One reference tile: every group of the tile, 32 patches (32/K groups) per wavefront step.
-//   FL0: LDS copy of the slice-0 fragments (the 64 x 64 map, both directions); FG: the whole
-//   tables (forward at dir 0, inverse at dir 1), read through the caches for the other slices.
-//   The eight wavefronts of a workgroup share both and the tile's LDS region.
 //   GA: global aggregation into gacc[pix*C + ch] (units of 2^-tg.FS) and ghist[pix] (patches by
 //   top-left pixel).  GA == 1: every contribution goes to gacc, the tile only schedules
-//   references and region is unused; GA == 2: the tile (references of one frame) adds into its
-//   LDS slot region, which then goes to the tile's slot of a global region buffer (at gacc,
+//   references and the region is unused; GA == 2: the tile (references of one frame) adds into
+//   its LDS slot region, which then goes to the tile's slot of a global region buffer (at gacc,
 //   C * plane int32 per tile) for ga_gather_kernel.
-template <int C, int K, bool RA = false, int GA = 0>
-__device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileGeom &tg, const v8h *FL0,
+//
+// What bounds it, per 32-patch step at C = 3, two waves sharing a SIMD: 24 + 160 + at most 320 (106
+// on the 12 MP image, where most blocks die) + 48 matrix instructions of 16 cycles, about 1,800
+// vector instructions of 4, and the waits between a wave's phases that its one neighbour does not
+// fill; the vector instructions lead.  Measured on the 12 MP image (stride 3, window 31, K 32,
+// estimated noise level): 16.1 -> 9.0 ms against a form that transposed the coefficients through
+// LDS, ran all Haar levels in registers on both sides and read its tables through the caches (3,840
+// vector and 143 matrix instructions of twice the size per step); 0.57 -> 0.24 ms for 509 x 763 at
+// sigma 10, K 16.  Of these, 1.5 and 0.18 ms are the FP64 re-decisions, which read the patches of a
+// row side by side instead of one after the other.
+template <int C, bool RA = false, int GA = 0>
+__device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileGeom &tg, const FilterLds<C> &L,
                                                  const v8h *__restrict__ FG, const double *__restrict__ T64,
-                                                 const int32_t *__restrict__ idx, const int idx_stride,
+                                                 const int K, const int32_t *__restrict__ idx, const int idx_stride,
                                                  const double *__restrict__ tau_ref, const double tau_mul,
                                                  float *__restrict__ regions,
                                                  unsigned long long *__restrict__ guard_count, const int tile,
-                                                 float *region, uint32_t *xbuf_all, MfmaShared &sh,
-                                                 const float *__restrict__ ra_d = nullptr,
+                                                 MfmaShared &sh, const float *__restrict__ ra_d = nullptr,
                                                  const uint8_t *__restrict__ ra_flag = nullptr,
                                                  unsigned long long *__restrict__ gacc = nullptr,
                                                  int *__restrict__ ghist = nullptr,
                                                  const VideoTiling &vt = VideoTiling{}) {
     constexpr int P = 64 * C;
-    constexpr int CH = C + 1;
-    constexpr int NT = 2 * C;            // 32-column tiles of the 64C coefficients
-    constexpr int NPAIR = Frag<C>::NPAIR;
-    constexpr int G = 32 / K;            // groups per step
-    constexpr int KL = K < 16 ? K : 16;  // group members per lane-half block
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c32 = lane & 31, h = lane >> 5;
+    const int lk = 31 - __builtin_clz(K);   // log2 K
+    const int G = 32 >> lk;                 // groups per step
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ty = tile / tg.tiles_x, tx = tile % tg.tiles_x;
-    uint32_t *xbuf = xbuf_all + wave * XWORDS;
+    WaveScratch &ws = L.ws[wave];
     const int plane = region_plane(tg), relems = region_elems(tg, C);
     // LDS accumulation in int32 (float atomics in LDS are far slower than integer ones):
     // channel sums in units of 2^-FS, then patches by top-left pixel, which become the count.
-    int *iregion = reinterpret_cast<int *>(region);
+    int *iregion = L.region;
     int *hist = iregion + C * plane;
     const float fscale = (float)(1 << tg.FS);
     // references of the tile: rows iy0 .. iy0 + ny_t - 1 of the grid; with slot regions the
@@ -261,256 +410,294 @@ __device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileG
     }
     __syncthreads();
     const int r0 = sh.r0, c0 = sh.c0;
-    const uint8_t *img_end = g.img + (int64_t)(g.h - 1) * g.stride + (int64_t)g.w * C;
     const int ix0 = tx * tg.TX;
     const int nx_t = min(tg.TX, g.nx - ix0);
     const int nref = ny_t * nx_t;
-
-    // pixel of patch position 32 tq + c held by this lane in the output layout
     const int rp = GA == 1 ? g.w : tg.RP;   // row pitch of the aggregation target
-    const int lane_off[2] = {(c32 >> 3) * rp + (c32 & 7), (4 + (c32 >> 3)) * rp + (c32 & 7)};
-    // MFMA row rho = lane % 32 holds group member mu_in of this step's 32 patches
-    const int rho = c32;
-    const int mu_in = 16 * ((rho >> 2) & 1) + 4 * (rho >> 3) + (rho & 3);
 
+    // Patch positions: lane mu (and mu + 32) looks up patch mu of a step; the position of the next
+    // step's patch is loaded one step ahead, and its pixels while the last phase runs.
+    const uint32_t w_inv = (uint32_t)(0xffffffffu / (uint32_t)g.w) + 1u;   // lin / w = mulhi(lin, w_inv), or one more
+    const uint32_t nx_inv = 65535u / (uint32_t)nx_t + 1u;                  // t / nx_t = t nx_inv >> 16 for t < 256
+    auto ref_at = [&](int b, int gi) -> int64_t {
+        const int t = min(b + gi, nref - 1), q = (int)((uint32_t)t * nx_inv >> 16);
+        return (int64_t)(iy0 + q) * g.nx + (ix0 + t - q * nx_t);
+    };
+    auto position = [&](int b) { return idx[ref_at(b, (tid & 31) >> lk) * idx_stride + (tid & (K - 1))]; };
+    int off_own = 0;
+    uint32_t raw[8][C];   // 4 pixels of patches 8 gq .. 8 gq + 7
+    auto fetch = [&](int32_t lin, int lane) {
+        const int n16 = lane & 15, gq = lane >> 4;
+        // bytes of this lane's 4 pixels of a patch: row n16/2, columns 4 (n16 % 2) ..
+        const int64_t seg = (int64_t)(n16 >> 1) * g.stride + (n16 & 1) * 4 * C;
+        int yin = (int)__umulhi((uint32_t)lin, w_inv);
+        if (yin * g.w > lin) --yin;
+        const int xin = lin - yin * g.w;
+        if constexpr (GA == 1) {
+            off_own = lin;
+        } else if constexpr (GA == 2) {
+            const int f = yin / vt.h_frame;   // stacked row -> frame, slot and row in the frame
+            off_own = ((f - f_lo) * vt.RH + (yin - f * vt.h_frame - r0)) * rp + (xin - c0);
+        } else {
+            off_own = (yin - r0) * rp + (xin - c0);
+        }
+        wave_lds_fence();   // earlier reads of the scratch are done
+        if (lane < 32) {
+            ws.addr[lane] = (uint64_t)(uintptr_t)(g.img + (int64_t)yin * g.stride + (int64_t)xin * C);
+            ws.off[lane] = off_own;
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) load_seg<C>(ws.addr[8 * gq + j] + seg, raw[j]);
+    };
+    int32_t lin_next = 0;
+    if (wave * G < nref) {
+        lin_next = position(wave * G);
+        fetch(lin_next, tid & 63);
+    }
     for (int base = wave * G; base < nref; base += MW * G) {
         const bool full = base + G <= nref;
-        auto ref_of = [&](int gi) -> int64_t {
-            const int t = min(base + gi, nref - 1);
-            return (int64_t)(iy0 + t / nx_t) * g.nx + (ix0 + t % nx_t);
-        };
-        // ---- this lane's patch: A operands of the forward products (pixel rows 2 sp + h) ----
-        uint32_t raw[4][2 * C];   // pixel rows 2 sp + h of this lane's patch (8 C bytes each)
-        int off_in;   // region offset of the patch (for the aggregation, shared by lane shuffles)
+        auto ref_of = [&](int gi) { return ref_at(base, gi); };
+        // everything that depends on the lane alone is made anew in each step (an opaque copy), so
+        // that it does not hold registers across the product loop
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
+        const int n16 = lane & 15, gq = lane >> 4;
+        if (lane < 32 && (full || base + (lane >> lk) < nref)) {
+            if constexpr (GA != 0)
+                atomicAdd(ghist + lin_next, 1);
+            else
+                atomicAdd(hist + off_own, 1);
+        }
+        lin_next = position(base + MW * G);
+        // ---- 1: pair sums and differences of the pixels ----
+        // bh[sl][s][ht]: B operands of the forward products (pair n16 of tile ht, 32 pixels per k-step s)
+        v8h bh[C][2][2];
         {
-            const int64_t r_in = ref_of(mu_in / K);
-            const int32_t lin_in = idx[r_in * idx_stride + (mu_in % K)];
-            const int yin = lin_in / g.w, xin = lin_in % g.w;
-            if constexpr (GA == 1) {
-                off_in = lin_in;
-                if (h == 0 && (full || base + mu_in / K < nref)) atomicAdd(ghist + lin_in, 1);
-            } else if constexpr (GA == 2) {
-                const int f = yin / vt.h_frame;   // stacked row -> frame, slot and row in the frame
-                off_in = ((f - f_lo) * vt.RH + (yin - f * vt.h_frame - r0)) * tg.RP + (xin - c0);
-                if (h == 0 && (full || base + mu_in / K < nref)) atomicAdd(ghist + lin_in, 1);
-            } else {
-                off_in = (yin - r0) * tg.RP + (xin - c0);
-                if (h == 0 && (full || base + mu_in / K < nref)) atomicAdd(hist + off_in, 1);
-            }
-            const uint8_t *pin = g.img + (int64_t)yin * g.stride + (int64_t)xin * C;
+            // A operands: pixel byte t of patches 8 gq .. 8 gq + 7 as fp16 1024 + b
+            uint32_t a[4 * C][4];
 #pragma unroll
-            for (int sp = 0; sp < 4; ++sp) load_row_u8<C>(pin + (int64_t)(2 * sp + h) * g.stride, img_end, raw[sp]);
-        }
-        // ---- thresholds of the groups this lane half holds ----
-        // per (group slot, butterfly count l): keep-or-undecided above lo, undecided below hi
-        // (the guard band (tau - g, tau + g) scaled by 2^(l/2)); without a guard band lo is the
-        // float just below the threshold and hi = lo (empty band)
-        constexpr int NS = 16 / KL;
-        constexpr int LK = K == 32 ? 5 : (K == 16 ? 4 : (K == 8 ? 3 : 2));
-        float tau_l[NS], lo_t[NS][LK + 1], hi_t[NS][LK + 1];
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int gs = 0; gs < NS; ++gs) {
-            const int gi = K == 32 ? 0 : (16 * h + gs * KL) / K;
-            const bool valid = base + gi < nref;
-            const double tau = tau_ref[ref_of(gi)] * tau_mul;
-            tau_l[gs] = valid ? (float)tau : __builtin_inff();
-            const bool guard = valid && tau > (double)MGUARD;
-#pragma unroll
-            for (int l = 1; l <= LK; ++l) {
-                const float sc = l == 1 ? 1.41421356237309505f : (l == 2 ? 2.f : (l == 3 ? 2.82842712474619010f
-                                 : (l == 4 ? 4.f : 5.65685424949238019f)));
-                const float tl = tau_l[gs] * sc;
-                // a >= tl  <=>  a > (the float just below tl); tl = 0 keeps everything
-                const float below = tl > 0.f ? __int_as_float(__float_as_int(tl) - 1) : -1.f;
-                lo_t[gs][l] = guard ? tl - MGUARD * sc : below;
-                hi_t[gs][l] = guard ? tl + MGUARD * sc : lo_t[gs][l];
-            }
-        }
-        // RA-Haar-tSVD: the forward products of every member of a refined group start from
-        // -ra_d(q) (in the accumulators' (s0', re', im') form) instead of 0.  The Haar rows past
-        // the first sum to zero over the group, so only the first row changes, to
-        // sum - K ra_d(q) = K (T p_est)(q); ramask marks the registers that hold it, which are
-        // kept without threshold.
-        uint32_t ramask = 0, raflag = 0;
-        int64_t ra_row[NS];
-        if constexpr (RA) {
-#pragma unroll
-            for (int gs = 0; gs < NS; ++gs) {
-                const int gi = K == 32 ? 0 : (16 * h + gs * KL) / K;
-                ra_row[gs] = ref_of(gi) * P;
-                if (base + gi < nref && ra_flag[ref_of(gi)]) {
-                    raflag |= 1u << gs;
-                    if (K < 32 || h == 0) ramask |= 1u << (gs * KL);
+                for (int d = 0; d < C; ++d) {
+                    const uint32_t x = raw[2 * i][d], y = raw[2 * i + 1][d];
+                    const uint32_t lo = __builtin_amdgcn_perm(y, x, 0x05010400u);   // x0 y0 x1 y1
+                    const uint32_t hi = __builtin_amdgcn_perm(y, x, 0x07030602u);   // x2 y2 x3 y3
+                    const uint32_t k64 = 0x64646464u;
+                    a[4 * d][i] = __builtin_amdgcn_perm(k64, lo, 0x04010400u);
+                    a[4 * d + 1][i] = __builtin_amdgcn_perm(k64, lo, 0x04030402u);
+                    a[4 * d + 2][i] = __builtin_amdgcn_perm(k64, hi, 0x04010400u);
+                    a[4 * d + 3][i] = __builtin_amdgcn_perm(k64, hi, 0x04030402u);
                 }
-            }
-        }
-
-        v16f out[NT];
+            const v4f zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < NT; ++t) out[t] = (v16f){};
-
-        // two passes over the coefficient positions 32 tp + c (tp = 0, 1)
-#pragma unroll 1
-        for (int tp = 0; tp < 2; ++tp) {
-            // the raw bytes are converted again in each pass (keeps the converted operands short-lived)
+            for (int ht = 0; ht < 2; ++ht) {
+                const v8h hb = L.H[ht * 64 + lane];
+                uint32_t ph[C][2][4];
 #pragma unroll
-            for (int sp = 0; sp < 4; ++sp)
+                for (int q = 0; q < 4; ++q) {   // pixel q of the lane's four: D rows 4 gq + r
+                    v4f v[C];
+                    if constexpr (C == 3) {
+                        const v4f bb = mfma(as_v8h(a[3 * q + 2][0], a[3 * q + 2][1], a[3 * q + 2][2], a[3 * q + 2][3]), hb, zero);
+                        const v4f t = mfma(as_v8h(a[3 * q + 1][0], a[3 * q + 1][1], a[3 * q + 1][2], a[3 * q + 1][3]), hb, bb);
+                        const v4f s = mfma(as_v8h(a[3 * q][0], a[3 * q][1], a[3 * q][2], a[3 * q][3]), hb, t);
 #pragma unroll
-                for (int i = 0; i < 2 * C; ++i) asm volatile("" : "+v"(raw[sp][i]));
-            // ---- forward products for the tiles (slice, tp) ----
-            v16f acc[C];
-#pragma unroll
-            for (int sl = 0; sl < C; ++sl) acc[sl] = (v16f){};
-            if constexpr (RA) {
-#pragma unroll
-                for (int gs = 0; gs < NS; ++gs)
-                    if ((raflag >> gs) & 1u) {
-                        float d[C], a[C];
-#pragma unroll
-                        for (int sl = 0; sl < C; ++sl) d[sl] = ra_d[ra_row[gs] + 64 * sl + 32 * tp + c32];
-                        if (C == 3) {   // inverse of S0 = s0' + 2re', S1 = s0' - re' - im', S2 = s0' - re' + im'
-                            a[0] = -(d[0] + d[1] + d[2]) * (1.f / 3.f);
-                            a[1] = -(2.f * d[0] - d[1] - d[2]) * (1.f / 6.f);
-                            a[2] = -(d[2] - d[1]) * 0.5f;
-                        } else {
-                            a[0] = -d[0];
+                        for (int r = 0; r < 4; ++r) {
+                            v[0][r] = ht == 0 ? s[r] - 192.f : s[r];   // 6 x 1024 / 32
+                            v[1][r] = fmaf(-1.5f, t[r], s[r]);
+                            v[2][r] = fmaf(2.f, bb[r], -t[r]);
                         }
-#pragma unroll
-                        for (int sl = 0; sl < C; ++sl)
-#pragma unroll
-                            for (int r = gs * KL; r < gs * KL + KL; ++r) acc[sl][r] = a[sl];
-                    }
-            }
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-                // bytes straight to float, the channel DFT in float, pairs packed to fp16 with
-                // round-toward-zero (all values are integers below 2^11, exact either way)
-                uint32_t w0[4], wr[4], wi[4];
-#pragma unroll
-                for (int b = 0; b < 8; b += 2) {
-                    if (C == 3) {
-                        const float R0 = byte_f(raw[sp], 3 * b), G0 = byte_f(raw[sp], 3 * b + 1), B0 = byte_f(raw[sp], 3 * b + 2);
-                        const float R1 = byte_f(raw[sp], 3 * b + 3), G1 = byte_f(raw[sp], 3 * b + 4), B1 = byte_f(raw[sp], 3 * b + 5);
-                        const float t0 = G0 + B0, t1 = G1 + B1;
-                        w0[b / 2] = pack_rtz(R0 + t0, R1 + t1);
-                        wr[b / 2] = pack_rtz(fmaf(2.f, R0, -t0), fmaf(2.f, R1, -t1));
-                        wi[b / 2] = pack_rtz(B0 - G0, B1 - G1);
                     } else {
-                        w0[b / 2] = pack_rtz(byte_f(raw[sp], b), byte_f(raw[sp], b + 1));
+                        v[0] = mfma(as_v8h(a[q][0], a[q][1], a[q][2], a[q][3]), hb, zero);
+                        if (ht == 0) v[0] -= 64.f;   // 2 x 1024 / 32
                     }
-                }
-                const v8h a0 = __builtin_bit_cast(v8h, make_uint4(w0[0], w0[1], w0[2], w0[3]));
-                const v8h ar = C == 3 ? __builtin_bit_cast(v8h, make_uint4(wr[0], wr[1], wr[2], wr[3])) : a0;
-                const v8h ai = C == 3 ? __builtin_bit_cast(v8h, make_uint4(wi[0], wi[1], wi[2], wi[3])) : a0;
-                const int p0 = pair_of<C>(tp, sp);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, ldfrag0(FL0, 0, 0, p0, lane), acc[0], 0, 0, 0);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, ldfrag0(FL0, 0, 1, p0, lane), acc[0], 0, 0, 0);
-                if (C == 3) {
 #pragma unroll
-                    for (int sl = 1; sl < C; ++sl) {
-                        const int t = 2 * sl + tp;
-                        const int pr = pair_of<C>(t, 4 + sp), pi = pair_of<C>(t, 8 + sp);
-                        acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ar, ldfrag(FG, 0, 0, pr, NPAIR, lane), acc[sl], 0, 0, 0);
-                        acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ar, ldfrag(FG, 0, 1, pr, NPAIR, lane), acc[sl], 0, 0, 0);
-                        acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ai, ldfrag(FG, 0, 0, pi, NPAIR, lane), acc[sl], 0, 0, 0);
-                        acc[sl] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ai, ldfrag(FG, 0, 1, pi, NPAIR, lane), acc[sl], 0, 0, 0);
+                    for (int sl = 0; sl < C; ++sl)
+#pragma unroll
+                        for (int r2 = 0; r2 < 2; ++r2) {
+                            ph[sl][q >> 1][2 * (q & 1) + r2] = pack_rtz(v[sl][2 * r2], v[sl][2 * r2 + 1]);
+                        }
+                }
+#pragma unroll
+                for (int sl = 0; sl < C; ++sl)
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        bh[sl][s][ht] = as_v8h(ph[sl][s][0], ph[sl][s][1], ph[sl][s][2], ph[sl][s][3]);
                     }
+            }
+        }
+        // ---- thresholds of this lane's Haar rows: keep-or-undecided above lo, undecided below hi
+        // (the guard band (tau - g, tau + g) scaled alike); without a guard band lo is the
+        // float just below the threshold and hi = lo (empty band)
+        const LaneRow row0 = L.rows[n16];
+        const int gi_row[2] = {row0.gi, (2 * n16) >> lk};
+        const float rs[2] = {row0.rs, 0.70710678118654752f};
+        const float (&hs)[4] = row0.hs;
+        float tau_l[2], lo_t[2], hi_t[2];
+        uint32_t rafl = 0;   // bit ht: this lane's row of tile ht is the first row of a refined group
+        int64_t ra_row = 0;
+#pragma unroll
+        for (int ht = 0; ht < 2; ++ht) {
+            const int gi = gi_row[ht];
+            const bool valid = base + gi < nref;
+            const int64_t rr = ref_of(gi);
+            const double tau = tau_ref[rr] * tau_mul;
+            const float tf = valid ? (float)tau : __builtin_inff();
+            const bool guard = valid && tau > (double)MGUARD;
+            const float tl = tf * rs[ht];
+            // a >= tl  <=>  a > (the float just below tl); tl = 0 keeps everything
+            const float below = tl > 0.f ? __int_as_float(__float_as_int(tl) - 1) : -1.f;
+            tau_l[ht] = tl;
+            lo_t[ht] = guard ? tl - MGUARD * rs[ht] : below;
+            hi_t[ht] = guard ? tl + MGUARD * rs[ht] : lo_t[ht];
+            if constexpr (RA) {
+                // RA-Haar-tSVD: the row of sums of a refined group, K times the transform of the mean,
+                // becomes K T p_est by taking off K ra_d(q), and is kept without threshold
+                if (ht == 0 && row0.sum != 0 && valid && ra_flag[rr]) {
+                    rafl = 1;
+                    ra_row = rr * P;
+                    lo_t[0] = hi_t[0] = -1.f;
                 }
             }
-            // ---- inverse channel DFT: (s0', re', im') -> S0, S1, S2 ----
-            if (C == 3) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float s0 = acc[0][r], re = acc[1][r], im = acc[2][r];
-                    const float t0 = s0 - re;
-                    acc[0][r] = s0 + 2.f * re;
-                    acc[1][r] = t0 - im;
-                    acc[2][r] = t0 + im;
-                }
-            }
+        }
 
-            // ---- Haar along the group; threshold; guard-band values kept for now ----
-            bool any_near = false;
+        const v4h *FL = L.F + lane;                                      // forward operands
+        const v4h *FT = L.F + (4 * gq + (n16 >> 2)) + 16 * (n16 & 3);    // transposing reads
+        v4f out[C][4][2];   // [p0, 2 pr, pi][pixel set][Haar tile]
 #pragma unroll
-            for (int sl = 0; sl < C; ++sl) {
-                float v[16];
+        for (int sl = 0; sl < C; ++sl)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) v[r] = acc[sl][r];
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int st = 1; st < KL; st <<= 1)
+                for (int ht = 0; ht < 2; ++ht) out[sl][t][ht] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+        // four passes over the coefficients 16 ct + 4 gq + r of every slice
+#pragma unroll 1
+        for (int ct = 0; ct < 4; ++ct) {
+            // ---- 2: forward products ----
+            // acc[.][ht]: s0'; A p + B q; B p; A q
+            constexpr int NA = C == 3 ? 4 : 1;
+            v4f acc[NA][2];
 #pragma unroll
-                    for (int i = 0; i < 16; i += 2 * st) {
-                        const float a = v[i], b = v[i + st];
-                        v[i] = a + b;
-                        v[i + st] = a - b;
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int ht = 0; ht < 2; ++ht) acc[i][ht] = (v4f){0.f, 0.f, 0.f, 0.f};
+            // The maps' operands of k-step 1 take the registers of k-step 0 as soon as those are used,
+            // so their LDS latency passes under the products in between; the barriers keep the
+            // compiler from moving the loads back to their uses.
+            auto table = [&](int m, int s, int term) {
+                const v4h *f = FL + m * 2 * Frag<C>::MAP + ((ct * 2 + s) * 2 + term) * 128;
+                const v4h lo = f[0], hi = f[64];
+                return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            };
+            constexpr int NM = Frag<C>::NM;
+            v8h f[NM][2];
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int term = 0; term < 2; ++term) f[m][term] = table(m, 0, term);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+#pragma unroll
+                    for (int term = 0; term < 2; ++term)
+#pragma unroll
+                        for (int ht = 0; ht < 2; ++ht) {
+                            if (m == 0) acc[0][ht] = mfma(f[0][term], bh[0][s][ht], acc[0][ht]);
+                            if constexpr (C == 3) {
+                                if (m == 1) {
+                                    acc[1][ht] = mfma(f[1][term], bh[1][s][ht], acc[1][ht]);
+                                    acc[3][ht] = mfma(f[1][term], bh[2][s][ht], acc[3][ht]);
+                                }
+                                if (m == 2) {
+                                    acc[1][ht] = mfma(f[2][term], bh[2][s][ht], acc[1][ht]);
+                                    acc[2][ht] = mfma(f[2][term], bh[1][s][ht], acc[2][ht]);
+                                }
+                            }
+                        }
+                    if (s == 0) {
+                        f[m][0] = table(m, 1, 0);
+                        f[m][1] = table(m, 1, 1);
                     }
-                if (K == 32) {
-                    const float o = swap_half(v[0]);
-                    v[0] = h ? o - v[0] : v[0] + o;
                 }
+            }
+            // ---- inverse channel DFT, threshold ----
+            v4f S[2][C];
+            bool any[2], near[2];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int l = haar_level<K>(r);
-                    const int gs = r / KL;
-                    const float a = fabsf(v[r]);
-                    bool keep = a > lo_t[gs][l];
-                    bool near = keep && a < hi_t[gs][l];
+            for (int ht = 0; ht < 2; ++ht) {
+                if constexpr (C == 3) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float s0 = acc[0][ht][r], re = acc[1][ht][r];
+                        const float u = fmaf(-0.75f, acc[3][ht][r], acc[2][ht][r]);   // -im'/2
+                        const float t0 = s0 - re;
+                        S[ht][0][r] = fmaf(2.f, re, s0);
+                        S[ht][1][r] = fmaf(2.f, u, t0);
+                        S[ht][2][r] = fmaf(-2.f, u, t0);
+                    }
+                } else {
+                    // by a vector instruction: the assembly below must not read a matrix result directly
+                    float one = 1.f;
+                    asm("" : "+s"(one));
+                    S[ht][0] = acc[0][ht] * one;
+                }
+                if (ht == 0) {
+                    haar_lanes<C>(S[0], hs);
                     if constexpr (RA) {
-                        if (r % KL == 0 && ((ramask >> r) & 1u)) {
-                            keep = true;
-                            near = false;
+                        if (rafl) {
+                            const float kd = (float)K * 0.03125f;
+#pragma unroll
+                            for (int sl = 0; sl < C; ++sl) {
+                                const float4 d = *reinterpret_cast<const float4 *>(ra_d + ra_row + 64 * sl + 16 * ct + 4 * gq);
+                                S[0][sl][0] = fmaf(-kd, d.x, S[0][sl][0]);
+                                S[0][sl][1] = fmaf(-kd, d.y, S[0][sl][1]);
+                                S[0][sl][2] = fmaf(-kd, d.z, S[0][sl][2]);
+                                S[0][sl][3] = fmaf(-kd, d.w, S[0][sl][3]);
+                            }
                         }
                     }
-                    any_near |= near;
-                    v[r] = keep ? v[r] * exp2i(-l) : 0.f;   // kept values scaled by 2^-l (inverse Haar)
                 }
+                uint64_t kept = 0, band = 0;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[sl][r] = v[r];
+                for (int sl = 0; sl < C; ++sl) threshold4(S[ht][sl], lo_t[ht], hi_t[ht], kept, band);
+                any[ht] = kept != 0;
+                near[ht] = band != 0;
             }
+            if (!(any[0] | any[1])) continue;
 
             // ---- FP64 re-decision of the coefficients inside the guard band (rare) ----
-            if (__ballot(any_near)) {
-                // rebuild the band membership from the kept (scaled) values
-                uint32_t nearbits[C];
-#pragma unroll
-                for (int sl = 0; sl < C; ++sl) {
-                    uint32_t nb = 0;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int l = haar_level<K>(r);
-                        const int gs = r / KL;
-                        const float a = fabsf(acc[sl][r]) * exp2i(l);
-                        nb |= (uint32_t)(a > lo_t[gs][l] && a < hi_t[gs][l]) << r;
-                    }
-                    nearbits[sl] = RA ? nb & ~ramask : nb;
-                }
+            if (near[0] | near[1]) {
                 if (lane == 0) sh.near_n[wave] = 0;
                 wave_lds_fence();
-                uint32_t kill[C];
+                // the comparisons are made again (opaque copies keep the masks of the threshold short-lived)
+                float lo_o[2] = {lo_t[0], lo_t[1]}, hi_o[2] = {hi_t[0], hi_t[1]};
+                asm volatile("" : "+v"(lo_o[0]), "+v"(lo_o[1]), "+v"(hi_o[0]), "+v"(hi_o[1]));
+                uint32_t kill = 0, bits = 0;   // bit (ht * C + sl) * 4 + r
 #pragma unroll
-                for (int sl = 0; sl < C; ++sl) {
-                    kill[sl] = 0;
-                    uint32_t bits = nearbits[sl];
-                    while (bits) {
-                        const int r = __builtin_ctz(bits);
-                        bits &= bits - 1;
-                        const int e = atomicAdd(&sh.near_n[wave], 1);
-                        const int gi = K == 32 ? 0 : (16 * h + r) / K;
-                        if (e < MNEAR) {
-                            sh.near_a[wave][e] = lane | (sl << 6) | (r << 9) | (gi << 13);
-                            sh.near_b[wave][e] = haar_row<K>(r, h) | ((32 * (2 * sl + tp) + c32) << 8);
-                        } else {   // list full: the FP32 value decides
-                            const int l = haar_level<K>(r);
-                            const float sc = l == 1 ? 1.41421356237309505f : (l == 2 ? 2.f : (l == 3 ? 2.82842712474619010f
-                                             : (l == 4 ? 4.f : 5.65685424949238019f)));
-                            float vr = 0.f;
+                for (int ht = 0; ht < 2; ++ht)
 #pragma unroll
-                            for (int rr = 0; rr < 16; ++rr) vr = rr == r ? acc[sl][rr] : vr;
-                            float tauv = tau_l[0];
+                    for (int sl = 0; sl < C; ++sl)
 #pragma unroll
-                            for (int gs = 0; gs < NS; ++gs) tauv = gs == r / KL ? tau_l[gs] : tauv;
-                            if (!(fabsf(vr) * exp2i(l) >= tauv * sc)) kill[sl] |= 1u << r;
+                        for (int r = 0; r < 4; ++r) {
+                            const float av = fabsf(S[ht][sl][r]);
+                            bits |= (uint32_t)(av > lo_o[ht] && av < hi_o[ht]) << ((ht * C + sl) * 4 + r);
                         }
+                while (bits) {
+                    const int bit = __builtin_ctz(bits), r = bit & 3, ht = bit >= 4 * C, sl = (bit >> 2) - ht * C;
+                    bits &= bits - 1;
+                    const int e = atomicAdd(&sh.near_n[wave], 1);
+                    if (e < MNEAR) {
+                        sh.near_a[wave][e] = lane | (bit << 6);
+                        sh.near_b[wave][e] = 64 * sl + 16 * ct + 4 * gq + r;
+                    } else {   // list full: the FP32 value decides
+                        float av = 0.f;
+#pragma unroll
+                        for (int i = 0; i < 8 * C; ++i)
+                            if (i == bit) av = fabsf(S[i / (4 * C)][(i >> 2) % C][i & 3]);
+                        if (!(av >= (ht ? tau_l[1] : tau_l[0]))) kill |= 1u << bit;
                     }
                 }
                 wave_lds_fence();
@@ -521,21 +708,35 @@ __device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileG
                     if (n_all > nn) atomicAdd(guard_count + 1, (unsigned long long)(n_all - nn));
                 }
                 for (int e = 0; e < nn; ++e) {
-                    const int ia = sh.near_a[wave][e], ib = sh.near_b[wave][e];
-                    const int gi = (ia >> 13) & 7, k = ib & 255, q = ib >> 8;
-                    const int64_t rr = ref_of(gi);
-                    double part = 0.0;
-                    for (int p = lane; p < P; p += 64) {
-                        const int ch = p / 64, i = (p / 8) % 8, j = p % 8;
-                        double accp = 0.0;
-                        for (int m = 0; m < K; ++m) {
-                            const double w = haar_w(k, m, K);
-                            if (w == 0.0) continue;
-                            const int32_t l2 = idx[rr * idx_stride + m];
-                            accp += w * (double)g.img[(int64_t)(l2 / g.w + i) * g.stride + (int64_t)(l2 % g.w + j) * C + ch];
+                    // sum over the patches of the row (signs +-1, exact in integers) at this lane's
+                    // pixel, then against row q of the transform; eight patches' bytes in flight
+                    const int ia = sh.near_a[wave][e], q = sh.near_b[wave][e];
+                    const int n = ia & 15, ht = (ia >> 6) >= 4 * C;
+                    const HaarRow hr = haar_row_of(K, ht, n);
+                    const int cnt = 1 << hr.l;
+                    const int64_t pix = (int64_t)(lane >> 3) * g.stride + (lane & 7) * C;
+                    int sum[C] = {};
+                    for (int m0 = 0; m0 < cnt; m0 += 8) {
+                        int b[8][C];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const uint64_t a = ws.addr[hr.first + min(m0 + i, cnt - 1)] + pix;
+#pragma unroll
+                            for (int ch = 0; ch < C; ++ch)
+                                b[i][ch] = ((const __attribute__((address_space(1))) uint8_t *)a)[ch];
                         }
-                        part += T64[(int64_t)q * P + p] * accp;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const int w = m0 + i < cnt ? (int)haar_sign(hr, n, hr.first + m0 + i, ht) : 0;
+#pragma unroll
+                            for (int ch = 0; ch < C; ++ch) sum[ch] += w * b[i][ch];
+                        }
                     }
+                    double part = 0.0;
+#pragma unroll
+                    for (int ch = 0; ch < C; ++ch) part += T64[(int64_t)q * P + 64 * ch + lane] * (double)sum[ch];
+                    part *= ((hr.l & 1) ? 0.70710678118654752440 : 1.0) / (double)(1 << (hr.l >> 1));
+                    const int64_t rr = ref_of(hr.first >> lk);
                     const double sv = wave_sum64(part);
                     const double tau = tau_ref[rr] * tau_mul;
                     if (lane == 0) sh.near_kill[wave][e] = !(fabs(sv) >= tau);
@@ -543,147 +744,155 @@ __device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileG
                 wave_lds_fence();
                 for (int e = 0; e < nn; ++e) {
                     const int ia = sh.near_a[wave][e];
-                    if ((ia & 63) == lane && sh.near_kill[wave][e]) {
-                        const int sl = (ia >> 6) & 7, r = (ia >> 9) & 15;
-#pragma unroll
-                        for (int ss = 0; ss < C; ++ss)
-                            if (ss == sl) kill[ss] |= 1u << r;
-                    }
+                    if ((ia & 63) == lane && sh.near_kill[wave][e]) kill |= 1u << (ia >> 6);
                 }
 #pragma unroll
-                for (int sl = 0; sl < C; ++sl)
+                for (int ht = 0; ht < 2; ++ht)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if ((kill[sl] >> r) & 1u) acc[sl][r] = 0.f;
+                    for (int sl = 0; sl < C; ++sl)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if ((kill >> ((ht * C + sl) * 4 + r)) & 1u) S[ht][sl][r] = 0.f;
             }
 
-            // ---- inverse Haar (transposed butterfly network) ----
+            // ---- 4: inverse products ----
 #pragma unroll
-            for (int sl = 0; sl < C; ++sl) {
-                float v[16];
+            for (int ht = 0; ht < 2; ++ht) {
+                if (!any[ht]) continue;   // wave-uniform: nothing kept, the products are zero
+                // A operands [hi, hi] and [lo, lo] (coefficients 4 gq + j%4)
+                auto split = [&](const v4f x, v8h &hh, v8h &ll) {
+                    const uint32_t h0 = pack_rne(x[0], x[1]), h1 = pack_rne(x[2], x[3]);
+                    const uint32_t l0 = pack_rest(x[0], x[1], h0), l1 = pack_rest(x[2], x[3], h1);
+                    hh = as_v8h(h0, h1, h0, h1);
+                    ll = as_v8h(l0, l1, l0, l1);
+                };
+                v8h xh[4], xl[4];   // s0, sr, 2 dn, -1.5 dn
+                if constexpr (C == 3) {
+                    v4f s0, sr, d2, d3;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) v[r] = acc[sl][r];
-                if (K == 32) {
-                    const float o = swap_half(v[0]);
-                    v[0] = h ? o - v[0] : v[0] + o;
-                }
-#pragma unroll
-                for (int st = KL / 2; st >= 1; st >>= 1)
-#pragma unroll
-                    for (int i = 0; i < 16; i += 2 * st) {
-                        const float a = v[i], b = v[i + st];
-                        v[i] = a + b;
-                        v[i + st] = a - b;
+                    for (int r = 0; r < 4; ++r) {
+                        const float a0 = S[ht][0][r], b0 = S[ht][1][r], c0v = S[ht][2][r];
+                        const float u = b0 + c0v;
+                        s0[r] = a0 + u;
+                        sr[r] = fmaf(2.f, a0, -u);
+                        const float dn = b0 - c0v;
+                        d2[r] = dn + dn;
+                        d3[r] = -1.5f * dn;
                     }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[sl][r] = v[r];
-            }
-            // ---- channel DFT of the kept coefficients: s0, 2 re, d ----
-            if (C == 3) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float a = acc[0][r], b = acc[1][r], cc = acc[2][r];
-                    const float u = b + cc;
-                    acc[0][r] = a + u;
-                    acc[1][r] = 2.f * a - u;
-                    acc[2][r] = cc - b;
-                }
-            }
-
-            // ---- inverse products: each 32-coefficient tile is transposed through LDS ----
-#pragma unroll
-            for (int sl = 0; sl < C; ++sl) {
-                const int j = 2 * sl + tp;   // tile of the k dimension
-                constexpr int NTMAX = C == 3 ? 4 : 2;
-                const int tlo = sl == 0 ? 0 : 2, ntile = sl == 0 ? 2 : 4;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    // hi = v rounded to fp16 (nearest), lo = the rest (toward zero), one word.
-                    // Rounding keeps |lo| <= 2^-11 |v|; a hi cut toward zero (one AND) doubles the
-                    // residual and missed the pixel bar on the large refined rows of RA-Haar-tSVD.
-                    const float v = acc[sl][r];
-                    const float hf = (float)(_Float16)v;
-                    xbuf[(16 * h + r) * XS + c32] = pack_rtz(hf, v - hf);
-                }
-                wave_lds_fence();
-#pragma unroll
-                for (int ss = 0; ss < 2; ++ss) {
-                    v8h ahi, alo;
-                    uint32_t any = 0;
-#pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) {
-                        const uint32_t wd = xbuf[mu_in * XS + 16 * ss + 8 * h + jj];
-                        any |= wd;
-                        ahi[jj] = __builtin_bit_cast(_Float16, (uint16_t)(wd & 0xffffu));
-                        alo[jj] = __builtin_bit_cast(_Float16, (uint16_t)(wd >> 16));
-                    }
-                    // a block of 16 coefficient positions that thresholding killed in all 32 patches
-                    // adds nothing: its products are skipped (wave-uniform; the sums are unchanged)
-                    if (!__builtin_amdgcn_ballot_w64(any != 0u)) continue;
-#pragma unroll
-                    for (int tt = 0; tt < ntile; ++tt) {
-                        const int t = tlo + tt;
-                        const int pr = pair_of<C>(t, 2 * j + ss);
-                        const v8h fbh = sl == 0 ? ldfrag0(FL0, 1, 0, pr, lane) : ldfrag(FG, 1, 0, pr, NPAIR, lane);
-                        const v8h fbl = sl == 0 ? ldfrag0(FL0, 1, 1, pr, lane) : ldfrag(FG, 1, 1, pr, NPAIR, lane);
-                        out[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi, fbh, out[t], 0, 0, 0);
-                        out[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi, fbl, out[t], 0, 0, 0);
-                        out[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo, fbh, out[t], 0, 0, 0);
-                    }
-                }
-                wave_lds_fence();
-            }
-        }
-
-        // ---- aggregation into the LDS region ----
-        // patch offsets of the MFMA rows 8(r/4) + 4h + r%4 through the (now free) transpose
-        // buffer: one store per lane, four 16-byte reads
-        xbuf[lane] = (uint32_t)off_in;
-        wave_lds_fence();
-        int offs[16];
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const uint4 o4 = *reinterpret_cast<const uint4 *>(xbuf + 8 * q4 + 4 * h);
-            offs[4 * q4] = (int)o4.x;
-            offs[4 * q4 + 1] = (int)o4.y;
-            offs[4 * q4 + 2] = (int)o4.z;
-            offs[4 * q4 + 3] = (int)o4.w;
-        }
-        wave_lds_fence();
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int mu = 16 * h + r;
-            const int gi = mu / K;
-            const int off = offs[r];
-            if (!full && base + gi >= nref) continue;
-#pragma unroll
-            for (int tq = 0; tq < 2; ++tq) {
-                if constexpr (GA == 1) {
-                    unsigned long long *dst = gacc + (int64_t)(off + lane_off[tq]) * C;
-                    auto add = [&](int ch, float v) {
-                        atomicAdd(dst + ch, (unsigned long long)(long long)to_fixed(v, fscale));
-                    };
-                    if (C == 3) {
-                        const float p0 = out[tq][r], pr = out[2 + tq][r], pi = out[4 + tq][r];
-                        const float t0 = p0 - pr;
-                        add(0, p0 + 2.f * pr);
-                        add(1, t0 - pi);
-                        add(2, t0 + pi);
-                    } else {
-                        add(0, out[tq][r]);
-                    }
-                    continue;
-                }
-                int *dst = iregion + off + lane_off[tq];
-                if (C == 3) {
-                    const float p0 = out[tq][r], pr = out[2 + tq][r], pi = out[4 + tq][r];
-                    const float t0 = p0 - pr;
-                    atomicAdd(dst, to_fixed(p0 + 2.f * pr, fscale));
-                    atomicAdd(dst + plane, to_fixed(t0 - pi, fscale));
-                    atomicAdd(dst + 2 * plane, to_fixed(t0 + pi, fscale));
+                    split(s0, xh[0], xl[0]);
+                    split(sr, xh[1], xl[1]);
+                    split(d2, xh[2], xl[2]);
+                    split(d3, xh[3], xl[3]);
                 } else {
-                    atomicAdd(dst, to_fixed(out[tq][r], fscale));
+                    split(S[ht][0], xh[0], xl[0]);
                 }
+                // [hi | lo] of coefficients 4 gq + j against pixel n16 of set t; the operands of the next
+                // set are loaded before the products of this one
+                auto table_t = [&](int m, int t) {
+                    const v4h *f = FT + m * 2 * Frag<C>::MAP + (ct * 2 + (t >> 1)) * 256 + (t & 1) * 64;
+                    const v4h hi = lds_read_tr(f), lo = lds_read_tr(f + 128);
+                    return __builtin_shufflevector(hi, lo, 0, 1, 2, 3, 4, 5, 6, 7);
+                };
+                v8h f[2][NM];
+#pragma unroll
+                for (int m = 0; m < NM; ++m) f[0][m] = table_t(m, 0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (t < 3) {
+#pragma unroll
+                        for (int m = 0; m < NM; ++m) f[(t + 1) & 1][m] = table_t(m, t + 1);
+                    }
+                    const v8h (&ft)[NM] = f[t & 1];
+                    out[0][t][ht] = mfma(xh[0], ft[0], out[0][t][ht]);
+                    if constexpr (C == 3) {
+                        out[1][t][ht] = mfma(xh[1], ft[1], out[1][t][ht]);
+                        out[2][t][ht] = mfma(xh[3], ft[1], out[2][t][ht]);
+                    }
+                    out[0][t][ht] = mfma(xl[0], ft[0], out[0][t][ht]);
+                    if constexpr (C == 3) {
+                        out[1][t][ht] = mfma(xl[1], ft[1], out[1][t][ht]);
+                        out[2][t][ht] = mfma(xl[3], ft[1], out[2][t][ht]);
+                        out[1][t][ht] = mfma(xh[2], ft[2], out[1][t][ht]);
+                        out[2][t][ht] = mfma(xh[1], ft[2], out[2][t][ht]);
+                        out[1][t][ht] = mfma(xl[2], ft[2], out[1][t][ht]);
+                        out[2][t][ht] = mfma(xl[1], ft[2], out[2][t][ht]);
+                    }
+                }
+            }
+        }
+
+        // ---- 5: inverse Haar and aggregation, one pixel set (16 pixels) at a time ----
+        const v8h hi0 = L.H[128 + lane], hi1 = L.H[192 + lane];
+        int offs[2][4];   // patches 16 mt + 4 gq + r: word of this lane's pixel of set 0
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int4 o4 = *reinterpret_cast<const int4 *>(&ws.off[16 * mt + 4 * gq]);
+            const int lp = (n16 >> 1) * rp + 4 * (n16 & 1);
+            offs[mt][0] = o4.x + lp;
+            offs[mt][1] = o4.y + lp;
+            offs[mt][2] = o4.z + lp;
+            offs[mt][3] = o4.w + lp;
+            if constexpr (GA != 1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    offs[mt][r] *= C;
+                    asm volatile("" : "+v"(offs[mt][r]));   // computed once, not per pixel set
+                }
+        }
+        if (base + MW * G < nref) fetch(lin_next, lane);
+        uint32_t skip = 0;   // patches (bit 4 mt + r) of groups past the tile's last
+        if (!full) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                skip |= (uint32_t)(base + ((16 * (i >> 2) + 4 * gq + (i & 3)) >> lk) >= nref) << i;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            v4f px[C][2];   // R, G, B: [patch tile], patches 4 gq + r
+#pragma unroll
+            for (int ht = 0; ht < 2; ++ht)
+                if constexpr (C == 3) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float p0 = out[0][t][ht][r], pr = out[1][t][ht][r], pi = out[2][t][ht][r];
+                        const float t0 = fmaf(-0.5f, pr, p0);   // pr is twice the real part
+                        out[0][t][ht][r] = p0 + pr;
+                        out[1][t][ht][r] = t0 - pi;
+                        out[2][t][ht][r] = t0 + pi;
+                    }
+                }
+#pragma unroll
+            for (int ch = 0; ch < C; ++ch) {
+                const v4f a = out[ch][t][0], b = out[ch][t][1];
+                const uint32_t h0 = pack_rne(a[0], a[1]), h1 = pack_rne(a[2], a[3]);
+                const uint32_t h2 = pack_rne(b[0], b[1]), h3 = pack_rne(b[2], b[3]);
+                const v8h xh = as_v8h(h0, h1, h2, h3);
+                const v8h xl = as_v8h(pack_rest(a[0], a[1], h0), pack_rest(a[2], a[3], h1), pack_rest(b[0], b[1], h2),
+                                      pack_rest(b[2], b[3], h3));
+                const v4f zero = {0.f, 0.f, 0.f, 0.f};
+                px[ch][0] = mfma(hi0, xl, mfma(hi0, xh, zero));
+                px[ch][1] = mfma(hi1, xl, mfma(hi1, xh, zero));
+            }
+            auto add = [&](int i) {
+                const int mt = i >> 2, r = i & 3;
+#pragma unroll
+                for (int ch = 0; ch < C; ++ch) {
+                    if constexpr (GA == 1)
+                        atomicAdd(gacc + (int64_t)offs[mt][r] * C + (t * C + ch),
+                                  (unsigned long long)(long long)to_fixed(px[ch][mt][r], fscale));
+                    else if constexpr (GA == 2)
+                        atomicAdd(iregion + offs[mt][r] + (t * C + ch), to_fixed(px[ch][mt][r], fscale));
+                    else
+                        atomicAdd(iregion + offs[mt][r] + (t * C + ch), (int)to_fixed_biased(px[ch][mt][r], fscale));
+                }
+            };
+            if (full) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) add(i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (!((skip >> i) & 1u)) add(i);
             }
         }
     }
@@ -733,16 +942,24 @@ __device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileG
         }
     }
     __syncthreads();
+    // sums (the bits of MAGIC taken out once per contribution), then counts
     float *dst = regions + (int64_t)tile * relems;
     const float unscale = 1.f / fscale;
-    for (int e = tid; e < relems; e += MW * 64) dst[e] = (float)iregion[e] * (e < C * plane ? unscale : 1.f);
+    for (int e = tid; e < plane; e += MW * 64) {
+        const int cnt = hist[e];
+#pragma unroll
+        for (int ch = 0; ch < C; ++ch)
+            dst[e * C + ch] = (float)(int)((uint32_t)iregion[e * C + ch] - (uint32_t)cnt * MAGIC_BITS) * unscale;
+        dst[C * plane + e] = (float)cnt;
+    }
 }
 
 // Persistent over the tiles of one image: workgroup b takes tiles b, b + grid, ... in an
 // XCD-aware order (consecutive ids go round-robin over the 8 XCDs; with grid a multiple of 8
 // each workgroup stays in one class, whose tiles form a contiguous run).
-template <int C, int K, bool RA>
-__global__ __launch_bounds__(MW * 64) void filter_mfma_kernel(ImageGeom g, TileGeom tg, const v8h *__restrict__ F,
+template <int C, bool RA>
+__global__ __launch_bounds__(MW * 64) void filter_mfma_kernel(ImageGeom g, TileGeom tg, int K,
+                                                             const v8h *__restrict__ F,
                                                              const double *__restrict__ T64,
                                                              const int32_t *__restrict__ idx,
                                                              const double *__restrict__ tau_ref,
@@ -752,30 +969,23 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_kernel(ImageGeom g, TileG
                                                              const uint8_t *__restrict__ ra_flag) {
     extern __shared__ __align__(16) float smem[];
     __shared__ MfmaShared sh;
-    v8h *FL0 = reinterpret_cast<v8h *>(smem);
-    for (int e = threadIdx.x; e < F0_BYTES / 16; e += MW * 64) {
-        const int dt = e / (F0_PAIRS * 64), pl = e % (F0_PAIRS * 64);
-        FL0[e] = F[(dt * Frag<C>::NPAIR) * 64 + pl];
-    }
+    const FilterLds<C> L = filter_lds_init<C>(smem, F, K);
     __syncthreads();
-    float *region = smem + F0_BYTES / 4;
-    uint32_t *xb = reinterpret_cast<uint32_t *>(region + region_elems(tg, C));
     const int n_tiles = tg.tiles_y * tg.tiles_x;
     const int per = (n_tiles + 7) / 8;
     for (int v = blockIdx.x; v < 8 * per; v += gridDim.x) {
         const int tile = (v & 7) * per + (v >> 3);
         if (tile >= n_tiles) continue;
-        filter_tile_mfma<C, K, RA>(g, tg, FL0, F, T64, idx, K, tau_ref, 1.0, regions, guard_count, tile, region, xb,
-                                   sh, ra_d, ra_flag);
+        filter_tile_mfma<C, RA>(g, tg, L, F, T64, K, idx, K, tau_ref, 1.0, regions, guard_count, tile, sh, ra_d,
+                                ra_flag);
         __syncthreads();
     }
 }
 
 // Groups anywhere in the image (video), global aggregation: GA == 1 the tiles only schedule the
-// work (LDS: the slice-0 fragments and the transpose buffers); GA == 2 each tile also has its
-// slot region after them.
-template <int C, int K, bool RA, int GA>
-__global__ __launch_bounds__(MW * 64) void filter_mfma_ga_kernel(ImageGeom g, TileGeom tg, VideoTiling vt,
+// work; GA == 2 each tile also has its slot region.
+template <int C, bool RA, int GA>
+__global__ __launch_bounds__(MW * 64) void filter_mfma_ga_kernel(ImageGeom g, TileGeom tg, VideoTiling vt, int K,
                                                                 const v8h *__restrict__ F,
                                                                 const double *__restrict__ T64,
                                                                 const int32_t *__restrict__ idx,
@@ -787,21 +997,15 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_ga_kernel(ImageGeom g, Ti
                                                                 const uint8_t *__restrict__ ra_flag) {
     extern __shared__ __align__(16) float smem[];
     __shared__ MfmaShared sh;
-    v8h *FL0 = reinterpret_cast<v8h *>(smem);
-    for (int e = threadIdx.x; e < F0_BYTES / 16; e += MW * 64) {
-        const int dt = e / (F0_PAIRS * 64), pl = e % (F0_PAIRS * 64);
-        FL0[e] = F[(dt * Frag<C>::NPAIR) * 64 + pl];
-    }
+    const FilterLds<C> L = filter_lds_init<C>(smem, F, K);
     __syncthreads();
-    uint32_t *xb = reinterpret_cast<uint32_t *>(smem + F0_BYTES / 4);
-    float *region = GA == 2 ? reinterpret_cast<float *>(xb + MW * XWORDS) : nullptr;
     const int n_tiles = tg.tiles_y * tg.tiles_x;
     const int per = (n_tiles + 7) / 8;   // XCD-aware order, as in filter_mfma_kernel
     for (int v = blockIdx.x; v < 8 * per; v += gridDim.x) {
         const int tile = (v & 7) * per + (v >> 3);
         if (tile >= n_tiles) continue;
-        filter_tile_mfma<C, K, RA, GA>(g, tg, FL0, F, T64, idx, K, tau_ref, 1.0, nullptr, guard_count, tile,
-                                       region, xb, sh, ra_d, ra_flag, gacc, ghist, vt);
+        filter_tile_mfma<C, RA, GA>(g, tg, L, F, T64, K, idx, K, tau_ref, 1.0, nullptr, guard_count, tile, sh, ra_d,
+                                    ra_flag, gacc, ghist, vt);
         __syncthreads();
     }
 }
@@ -848,7 +1052,7 @@ __global__ void ga_gather_kernel(const int *__restrict__ regions, TileGeom tg, V
         for (int ch = 0; ch < C; ++ch) o[ch] = (float)px[ch];
         return;
     }
-    const int plane = tg.RH * tg.RP;
+    const int plane = region_plane(tg);
     const int tyf = (vt.ny_frame + tg.TY - 1) / tg.TY;
     const int span_y = tg.TY * s, span_x = tg.TX * s;
     // tiles whose region rows r0 .. r0 + RH - 1 can hold y: r0 = max(0, first reference row - R)
@@ -866,9 +1070,9 @@ __global__ void ga_gather_kernel(const int *__restrict__ regions, TileGeom tg, V
                 const int c0 = max(0, ref_pos(tx * tg.TX, nx, w, s) - tg.R);
                 if (x < c0 || x >= c0 + vt.RW) continue;
                 const int *src = regions + ((int64_t)(t * tyf + tyl) * tg.tiles_x + tx) * C * plane +
-                                 (slot * vt.RH + (y - r0)) * tg.RP + (x - c0);
+                                 ((slot * vt.RH + (y - r0)) * tg.RP + (x - c0)) * C;
 #pragma unroll
-                for (int ch = 0; ch < C; ++ch) acc[ch] += src[ch * plane];
+                for (int ch = 0; ch < C; ++ch) acc[ch] += src[ch];
             }
         }
     }
@@ -877,8 +1081,8 @@ __global__ void ga_gather_kernel(const int *__restrict__ regions, TileGeom tg, V
     for (int ch = 0; ch < C; ++ch) o[ch] = (float)((double)acc[ch] * inv);
 }
 
-template <int C, int K>
-__global__ __launch_bounds__(MW * 64) void filter_mfma_kernel_batched(const BatchItem *__restrict__ items,
+template <int C>
+__global__ __launch_bounds__(MW * 64) void filter_mfma_kernel_batched(const BatchItem *__restrict__ items, int K,
                                                                      int n_items, const int *__restrict__ unit_start,
                                                                      const v8h *__restrict__ F,
                                                                      const double *__restrict__ T64,
@@ -887,13 +1091,8 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_kernel_batched(const Batc
     extern __shared__ __align__(16) float smem[];
     __shared__ MfmaShared sh;
     __shared__ int s_u;
-    v8h *FL0 = reinterpret_cast<v8h *>(smem);
-    for (int e = threadIdx.x; e < F0_BYTES / 16; e += MW * 64) {
-        const int dt = e / (F0_PAIRS * 64), pl = e % (F0_PAIRS * 64);
-        FL0[e] = F[(dt * Frag<C>::NPAIR) * 64 + pl];
-    }
+    const FilterLds<C> L = filter_lds_init<C>(smem, F, K);
     __syncthreads();
-    float *region = smem + F0_BYTES / 4;
     const int total = unit_start[n_items];
     for (;;) {
         // thread 0 claims the next unit of an image filtered with this group size; units of an
@@ -918,33 +1117,70 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_kernel_batched(const Batc
         if (u >= total) break;
         const int i = find_unit(unit_start, n_items, u);
         const BatchItem it = items[i];
-        uint32_t *xb = reinterpret_cast<uint32_t *>(region + region_elems(it.tg, C));
-        filter_tile_mfma<C, K>(it.g, it.tg, FL0, F, T64, it.idx, it.idx_stride, it.tau, it.tau_mul, it.regions,
-                               guard_count, u - unit_start[i], region, xb, sh);
+        filter_tile_mfma<C>(it.g, it.tg, L, F, T64, K, it.idx, it.idx_stride, it.tau, it.tau_mul, it.regions,
+                            guard_count, u - unit_start[i], sh);
         __syncthreads();
     }
 }
 
 }  // namespace
 
-int filter_mfma_lds_bytes(const TileGeom &tg, int C) {
-    return F0_BYTES + region_elems(tg, C) * 4 + MW * XWORDS * 4;
-}
+int filter_mfma_group_bytes(int C) { return C == 3 ? fixed_lds_bytes<3>() : fixed_lds_bytes<1>(); }
 
-int filter_mfma_group_bytes(int C) {
-    (void)C;
-    return F0_BYTES + MW * XWORDS * 4;
+int filter_mfma_lds_bytes(const TileGeom &tg, int C) { return filter_mfma_group_bytes(C) + region_elems(tg, C) * 4; }
+
+size_t filter_mfma_table_halves(int C) { return (size_t)(C == 3 ? 3 : 1) * Frag<1>::MAP * 8; }
+
+// Fills the operand tables from the FP64 maps fwd and inv (64 C x 64 C, row-major; the forward map
+// of (a0, ar, ai) to (s0', re', im') and its inverse on (s0, sr, d)), h16 rounding to fp16 bits and
+// h16v giving their value.  Returns false if the maps have not the structure the kernel relies on:
+// slice 0 apart, re' = A ar + B ai, im' = -B ar + 3 A ai, and the inverse its transpose.
+bool filter_mfma_tables(int C, const double *fwd, const double *inv, uint16_t (*h16)(double), double (*h16v)(uint16_t),
+                        uint16_t *out) {
+    const int P = 64 * C, NM = C == 3 ? 3 : 1;
+    auto F = [&](int n, int k) { return fwd[(size_t)n * P + k]; };
+    auto I = [&](int n, int k) { return inv[(size_t)n * P + k]; };
+    auto far = [](double a, double b) { return !(fabs(a - b) <= 1e-12); };
+    if (C == 3)
+        for (int n = 0; n < 64; ++n)
+            for (int k = 0; k < 64; ++k) {
+                for (int a = 1; a < 3; ++a)
+                    if (far(F(n, 64 * a + k), 0) || far(F(64 * a + n, k), 0)) return false;
+                if (far(F(128 + n, 64 + k), -F(64 + n, 128 + k)) || far(F(128 + n, 128 + k), 3 * F(64 + n, 64 + k)))
+                    return false;
+            }
+    // the inverse is the transposed forward map, so the kernel reads one table both ways
+    for (int n = 0; n < P; ++n)
+        for (int k = 0; k < P; ++k)
+            if (far(F(n, k), I(k, n))) return false;
+    auto map = [&](int m, int n, int k) {   // p = ar / 2 doubles A
+        return m == 0 ? F(n, k) : (m == 1 ? 2 * F(64 + n, 64 + k) : F(64 + n, 128 + k));
+    };
+    uint16_t *o = out;
+    for (int m = 0; m < NM; ++m)
+        for (int ct = 0; ct < 4; ++ct)
+            for (int s = 0; s < 2; ++s)
+                for (int term = 0; term < 2; ++term)
+                    for (int q = 2 * s; q < 2 * s + 2; ++q)
+                        for (int l = 0; l < 64; ++l)
+                            for (int j = 0; j < 4; ++j) {
+                                const int px = 4 * (l >> 4) + j;   // of set q
+                                const double v = map(m, 16 * ct + (l & 15), 8 * (px >> 1) + 4 * (px & 1) + q);
+                                const uint16_t hi = h16(v);
+                                *o++ = term == 0 ? hi : h16(v - h16v(hi));
+                            }
+    return true;
 }
 
 int filter_mfma_static_bytes() { return (int)sizeof(MfmaShared) + 16; }
 
-template <int C, int K, bool RA>
-static hipError_t launch_mfma_t(const ImageGeom &g, const TileGeom &tg, const BasisDev &b, const int32_t *idx,
+template <int C, bool RA>
+static hipError_t launch_mfma_t(const ImageGeom &g, const TileGeom &tg, int K, const BasisDev &b, const int32_t *idx,
                                 const double *tau_ref, float *regions, unsigned long long *gc, const float *ra_d,
                                 const uint8_t *ra_flag, hipStream_t st) {
     const int n_tiles = tg.tiles_y * tg.tiles_x;
     const int lds = filter_mfma_lds_bytes(tg, C);
-    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_kernel<C, K, RA>, lds, (int)sizeof(MfmaShared));
+    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_kernel<C, RA>, lds, (int)sizeof(MfmaShared));
     if (e != hipSuccess) return e;
     int dev = 0, n_cu = 0;
     (void)hipGetDevice(&dev);
@@ -952,7 +1188,7 @@ static hipError_t launch_mfma_t(const ImageGeom &g, const TileGeom &tg, const Ba
     if (n_cu < 8) n_cu = 8;
     const int per = (n_tiles + 7) / 8;
     const int grid = min(8 * per, (n_cu / 8) * 8);
-    hipLaunchKernelGGL((filter_mfma_kernel<C, K, RA>), dim3(grid), dim3(MW * 64), lds, st, g, tg, (const v8h *)b.frag,
+    hipLaunchKernelGGL((filter_mfma_kernel<C, RA>), dim3(grid), dim3(MW * 64), lds, st, g, tg, K, (const v8h *)b.frag,
                        b.T64, idx, tau_ref, regions, gc, ra_d, ra_flag);
     return hipGetLastError();
 }
@@ -960,24 +1196,23 @@ static hipError_t launch_mfma_t(const ImageGeom &g, const TileGeom &tg, const Ba
 hipError_t launch_filter_mfma(const ImageGeom &g, const TileGeom &tg, int K, const BasisDev &b, const int32_t *idx,
                               const double *tau_ref, float *regions, unsigned long long *gc, hipStream_t st,
                               const float *ra_d, const uint8_t *ra_flag) {
-    if (!b.frag) return hipErrorInvalidValue;
-#define HM_CASE(CC, KK)                                                                                          \
-    if (g.c == CC && K == KK)                                                                                    \
-        return ra_d ? launch_mfma_t<CC, KK, true>(g, tg, b, idx, tau_ref, regions, gc, ra_d, ra_flag, st)         \
-                    : launch_mfma_t<CC, KK, false>(g, tg, b, idx, tau_ref, regions, gc, nullptr, nullptr, st);
-    HM_CASE(1, 4) HM_CASE(1, 8) HM_CASE(1, 16) HM_CASE(1, 32)
-    HM_CASE(3, 4) HM_CASE(3, 8) HM_CASE(3, 16) HM_CASE(3, 32)
-#undef HM_CASE
+    if (!b.frag || !(K == 4 || K == 8 || K == 16 || K == 32)) return hipErrorInvalidValue;
+    if (g.c == 3)
+        return ra_d ? launch_mfma_t<3, true>(g, tg, K, b, idx, tau_ref, regions, gc, ra_d, ra_flag, st)
+                    : launch_mfma_t<3, false>(g, tg, K, b, idx, tau_ref, regions, gc, nullptr, nullptr, st);
+    if (g.c == 1)
+        return ra_d ? launch_mfma_t<1, true>(g, tg, K, b, idx, tau_ref, regions, gc, ra_d, ra_flag, st)
+                    : launch_mfma_t<1, false>(g, tg, K, b, idx, tau_ref, regions, gc, nullptr, nullptr, st);
     return hipErrorInvalidValue;
 }
 
-template <int C, int K, bool RA, int GA>
-static hipError_t launch_mfma_ga_t(const ImageGeom &g, const TileGeom &tg, const VideoTiling &vt, int lds,
+template <int C, bool RA, int GA>
+static hipError_t launch_mfma_ga_t(const ImageGeom &g, const TileGeom &tg, const VideoTiling &vt, int K, int lds,
                                    const BasisDev &b, const int32_t *idx, const double *tau_ref,
                                    unsigned long long *gacc, int *ghist, unsigned long long *gc, const float *ra_d,
                                    const uint8_t *ra_flag, hipStream_t st) {
     const int n_tiles = tg.tiles_y * tg.tiles_x;
-    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_ga_kernel<C, K, RA, GA>, lds, (int)sizeof(MfmaShared));
+    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_ga_kernel<C, RA, GA>, lds, (int)sizeof(MfmaShared));
     if (e != hipSuccess) return e;
     int dev = 0, n_cu = 0;
     (void)hipGetDevice(&dev);
@@ -985,7 +1220,7 @@ static hipError_t launch_mfma_ga_t(const ImageGeom &g, const TileGeom &tg, const
     if (n_cu < 8) n_cu = 8;
     const int per = (n_tiles + 7) / 8;
     const int grid = min(8 * per, (n_cu / 8) * 8);
-    hipLaunchKernelGGL((filter_mfma_ga_kernel<C, K, RA, GA>), dim3(grid), dim3(MW * 64), lds, st, g, tg, vt,
+    hipLaunchKernelGGL((filter_mfma_ga_kernel<C, RA, GA>), dim3(grid), dim3(MW * 64), lds, st, g, tg, vt, K,
                        (const v8h *)b.frag, b.T64, idx, tau_ref, gacc, ghist, gc, ra_d, ra_flag);
     return hipGetLastError();
 }
@@ -1005,8 +1240,8 @@ static int video_tile_side(int C, int K, int h_frame, int w, int s, int W, int n
     for (int side = GA_MAX_TILE; side >= 1; --side) {
         if (ga_shift(side, K) < GA_MIN_FS) continue;
         const int RH = min((side - 1) * s + 2 * R + PS, h_frame), RW = min((side - 1) * s + 2 * R + PS, w);
-        const int RP = RW + ((8 - RW % 16) + 16) % 16;   // pitch % 16 == 8, as for the image regions
-        const int bytes = filter_mfma_group_bytes(C) + C * nslot * RH * RP * 4;
+        const int RP = region_pitch(RW);
+        const int bytes = filter_mfma_group_bytes(C) + C * ((nslot * RH * RP + 3) & ~3) * 4;
         if (bytes <= filter_lds_budget()) {
             vt->RH = RH;
             vt->RW = RW;
@@ -1064,7 +1299,8 @@ hipError_t launch_filter_mfma_global(const ImageGeom &g, int T, int radius, int 
                                      const int32_t *idx, const double *tau_ref, void *accum, int *ghist,
                                      unsigned long long *gc, float *out, int64_t out_stride, hipStream_t st,
                                      const float *ra_d, const uint8_t *ra_flag, bool force_direct) {
-    if (!b.frag || T < 1 || g.h % T || g.ny % T) return hipErrorInvalidValue;
+    if (!b.frag || T < 1 || g.h % T || g.ny % T || !(K == 4 || K == 8 || K == 16 || K == 32))
+        return hipErrorInvalidValue;
     VideoTiling vt;
     TileGeom tg;
     const int side = plan_video(g, T, radius, W, K, force_direct, &vt, &tg);
@@ -1077,21 +1313,14 @@ hipError_t launch_filter_mfma_global(const ImageGeom &g, int T, int radius, int 
         return e;
     }
     e = hipErrorInvalidValue;
-#define HG_CASE(CC, KK)                                                                                          \
-    if (g.c == CC && K == KK) {                                                                                  \
-        if (side > 0)                                                                                            \
-            e = ra_d ? launch_mfma_ga_t<CC, KK, true, 2>(g, tg, vt, lds, b, idx, tau_ref, gacc, ghist, gc, ra_d,  \
-                                                          ra_flag, st)                                           \
-                     : launch_mfma_ga_t<CC, KK, false, 2>(g, tg, vt, lds, b, idx, tau_ref, gacc, ghist, gc,       \
-                                                           nullptr, nullptr, st);                                \
-        else                                                                                                     \
-            e = ra_d ? launch_mfma_ga_t<CC, KK, true, 1>(g, tg, vt, lds, b, idx, tau_ref, gacc, ghist, gc, ra_d,  \
-                                                          ra_flag, st)                                           \
-                     : launch_mfma_ga_t<CC, KK, false, 1>(g, tg, vt, lds, b, idx, tau_ref, gacc, ghist, gc,       \
-                                                           nullptr, nullptr, st);                                \
-    }
-    HG_CASE(1, 4) HG_CASE(1, 8) HG_CASE(1, 16) HG_CASE(1, 32)
-    HG_CASE(3, 4) HG_CASE(3, 8) HG_CASE(3, 16) HG_CASE(3, 32)
+#define HG_CASE(CC, RR, GG) \
+    launch_mfma_ga_t<CC, RR, GG>(g, tg, vt, K, lds, b, idx, tau_ref, gacc, ghist, gc, ra_d, ra_flag, st)
+    if (g.c == 3)
+        e = side > 0 ? (ra_d ? HG_CASE(3, true, 2) : HG_CASE(3, false, 2))
+                     : (ra_d ? HG_CASE(3, true, 1) : HG_CASE(3, false, 1));
+    else if (g.c == 1)
+        e = side > 0 ? (ra_d ? HG_CASE(1, true, 2) : HG_CASE(1, false, 2))
+                     : (ra_d ? HG_CASE(1, true, 1) : HG_CASE(1, false, 1));
 #undef HG_CASE
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)g.h * g.w;
@@ -1113,14 +1342,14 @@ hipError_t launch_filter_mfma_global(const ImageGeom &g, int T, int radius, int 
     return hipGetLastError();
 }
 
-template <int C, int K>
-static hipError_t launch_mfma_batched_t(const BatchItem *items, int n_items, const int *unit_start, int lds,
+template <int C>
+static hipError_t launch_mfma_batched_t(int K, const BatchItem *items, int n_items, const int *unit_start, int lds,
                                         const BasisDev &b, unsigned long long *gc, int *queue, int grid,
                                         hipStream_t st) {
-    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_kernel_batched<C, K>, lds,
+    hipError_t e = prepare_dynamic_lds((const void *)filter_mfma_kernel_batched<C>, lds,
                                        (int)sizeof(MfmaShared) + 16);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((filter_mfma_kernel_batched<C, K>), dim3(grid), dim3(MW * 64), lds, st, items, n_items,
+    hipLaunchKernelGGL(filter_mfma_kernel_batched<C>, dim3(grid), dim3(MW * 64), lds, st, items, K, n_items,
                        unit_start, (const v8h *)b.frag, b.T64, gc, queue);
     return hipGetLastError();
 }
@@ -1128,12 +1357,9 @@ static hipError_t launch_mfma_batched_t(const BatchItem *items, int n_items, con
 hipError_t launch_filter_mfma_batched(int C, int K, const BatchItem *items, int n_items, const int *unit_start,
                                       int lds, const BasisDev &b, unsigned long long *gc, int *queue, int grid,
                                       hipStream_t st) {
-    if (!b.frag) return hipErrorInvalidValue;
-#define HMB_CASE(CC, KK) \
-    if (C == CC && K == KK) return launch_mfma_batched_t<CC, KK>(items, n_items, unit_start, lds, b, gc, queue, grid, st);
-    HMB_CASE(1, 4) HMB_CASE(1, 8) HMB_CASE(1, 16) HMB_CASE(1, 32)
-    HMB_CASE(3, 4) HMB_CASE(3, 8) HMB_CASE(3, 16) HMB_CASE(3, 32)
-#undef HMB_CASE
+    if (!b.frag || !(K == 4 || K == 8 || K == 16 || K == 32)) return hipErrorInvalidValue;
+    if (C == 3) return launch_mfma_batched_t<3>(K, items, n_items, unit_start, lds, b, gc, queue, grid, st);
+    if (C == 1) return launch_mfma_batched_t<1>(K, items, n_items, unit_start, lds, b, gc, queue, grid, st);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,66 @@
+"""The filter kernel at the edges of its 32-patch steps and tiles, against the FP64 oracle.
+
+Tolerance: a contribution is rounded to a multiple of 2^-9 or finer (at most 2^-10 off), and the
+fp16 hi/lo operands and FP32 sums leave about 2^-21 of values below 2^11 (2^-10) in each patch, so
+an averaged pixel is within 2^-9 + 2^-9 = 2^-8 of the oracle as long as every keep/kill decision
+agrees, which the FP64 re-decision of the values near the threshold ensures.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 2.0 ** -8
+
+
+@pytest.fixture(scope="module")
+def dn():
+    import paper_2512_23569_amd as ht
+    d = ht.Denoiser(0)
+    yield d
+    d.close()
+
+
+# (h, w): fewer groups than a step holds, one row or column of groups, steps and tiles cut short by
+# the last group, several tiles with remainders
+@pytest.mark.parametrize("h,w,stride,window", [
+    (12, 13, 4, 7), (15, 70, 5, 15), (71, 15, 3, 15), (33, 42, 4, 21), (64, 95, 3, 31), (53, 61, 2, 9),
+])
+@pytest.mark.parametrize("K", [4, 8, 16, 32])
+@pytest.mark.parametrize("c", [1, 3])
+# tau 0 keeps everything, 2 and 60 cross blocks that stay and blocks that die, 1e9 kills everything
+@pytest.mark.parametrize("tau", [0.0, 2.0, 60.0, 1e9])
+def test_step_and_tile_edges(dn, basis1, basis3, h, w, stride, window, K, c, tau):
+    reach = min((window - 1) // 2, min(h, w) - 8) + 1
+    if reach * reach < K:
+        pytest.skip("the corner window holds fewer than K candidates")
+    img = synth.add_awgn(synth.make_clean(h, w, c, 5 + K), 20.0, 11)
+    p = dn.params(c, stride=stride, window=window, K=K)
+    n_ref = len(oracle.ref_grid(h, 8, stride)) * len(oracle.ref_grid(w, 8, stride))
+    taus = tau * (0.75 + 0.5 * np.arange(n_ref) / n_ref)   # another threshold for every group
+    out = dn.denoise_tau(torch.from_numpy(img).cuda(), torch.from_numpy(taus).cuda(), p).cpu().numpy()
+    U, V = basis3 if c == 3 else basis1
+    ref = oracle.denoise(img, U, V, taus, s=stride, W=window, K=K)
+    assert np.abs(out - ref).max() <= TOL
+
+
+@pytest.mark.parametrize("c,K", [(3, 32), (3, 8), (1, 16)])
+def test_more_values_at_the_threshold_than_the_list_holds(dn, basis1, basis3, c, K):
+    """A flat image: every coefficient but the means is exactly 0, and with tau at 0.06 (guard band
+    0.01 .. 0.11) none of them counts; with a two-level pattern whole tiles of coefficients sit at
+    the same value, and tau there sends them all through the FP64 list."""
+    img = np.full((40, 44, c), 100, np.uint8)
+    img[::2, 1::2] = 104
+    img = img if c == 3 else img[:, :, 0]
+    U, V = basis3 if c == 3 else basis1
+    p = dn.params(c, stride=4, window=15, K=K)
+    n_ref = len(oracle.ref_grid(40, 8, 4)) * len(oracle.ref_grid(44, 8, 4))
+    for tau in (0.06, 1.0, 3.0):
+        taus = np.full(n_ref, tau)
+        out = dn.denoise_tau(torch.from_numpy(img).cuda(), torch.from_numpy(taus).cuda(), p).cpu().numpy()
+        ref = oracle.denoise(img, U, V, taus, s=4, W=15, K=K)
+        assert np.abs(out - ref).max() <= TOL
