@@ -16,10 +16,6 @@
 #include "hevd.h"
 
 namespace htsvd {
-hipError_t launch_filter(const ImageGeom &g, int W, int K, const BasisDev &b, const int32_t *idx,
-                         const double *tau_ref, float *regions, unsigned long long *gc, float *out, int64_t out_stride,
-                         hipStream_t st, bool gather, const float *ra_d = nullptr, const uint8_t *ra_flag = nullptr);
-size_t filter_region_bytes(const ImageGeom &g, int W, int K);
 hipError_t launch_fill_const(double *p, int n, double v, hipStream_t st);
 int bm_lds_bytes(int s, int W, int h, int w);
 }  // namespace htsvd
@@ -260,11 +256,13 @@ struct Ws {
     int32_t *use_plain;
     double *sig_plain;
     int32_t *mom;      // per (sub-image, channel) moments of the plain estimator
+    TileGeom tg;       // reference tiles of the filter
     size_t total;
 };
 
-Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile) {
+Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile, bool compact = false) {
     Ws w;
+    w.tg = plan_filter_tiles(g, W, K, 0, 1.0, compact);
     const int64_t n_ref = (int64_t)g.ny * g.nx;
     const int64_t n_tiles = (int64_t)((g.h + tile - 1) / tile) * ((g.w + tile - 1) / tile);
     size_t off = 0;
@@ -274,7 +272,7 @@ Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile) {
         return (char *)base + o;
     };
     w.idx = (int32_t *)take(sizeof(int32_t) * n_ref * K);
-    w.regions = (float *)take(filter_region_bytes(g, W, K));
+    w.regions = (float *)take(filter_region_bytes(w.tg, g.c));
     w.tau = (double *)take(sizeof(double) * n_ref);
     w.sig_est = (double *)take(sizeof(double) * n_tiles);
     w.sig_hat = (double *)take(sizeof(double) * n_tiles);
@@ -508,14 +506,13 @@ htsvd_status run_filter(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &
     }
     {
         StageScope sc(ctx, HTSVD_STAGE_FILTER, st);
-        if ((e = launch_filter(g, mp.W, mp.K, ctx->basis[g.c == 3], w.idx, tau, w.regions, ctx->d_guard, d_out,
-                               out_stride, st, false, ra_d, ra_flag)) != hipSuccess)
+        if ((e = launch_filter_mfma(g, w.tg, mp.K, ctx->basis[g.c == 3], w.idx, tau, w.regions, ctx->d_guard, st, ra_d,
+                                    ra_flag)) != hipSuccess)
             return hip_fail(e, "filtering");
     }
     {
         StageScope sc(ctx, HTSVD_STAGE_NORMALIZE, st);
-        if ((e = launch_filter(g, mp.W, mp.K, ctx->basis[g.c == 3], w.idx, tau, w.regions, ctx->d_guard, d_out,
-                               out_stride, st, true)) != hipSuccess)
+        if ((e = launch_gather(g, w.tg, w.regions, d_out, out_stride, st)) != hipSuccess)
             return hip_fail(e, "aggregation");
     }
     return HTSVD_OK;
@@ -1120,9 +1117,12 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
     const size_t off_ra = align256(w0.total);
     void *base = fixed_ws;
+    bool compact = false;
     if (fixed_ws) {
         if (learned) return fail(HTSVD_ENOTSUP, "the no-allocation call takes the plain estimator or a known sigma");
         if (p->ra) return fail(HTSVD_ENOTSUP, "the no-allocation call does not run RA-Haar-tSVD");
+        // the tiles that take the least memory where the fastest ones do not fit
+        if (w0.total > fixed_cap) w0 = plan_ws(nullptr, g, mp.W, mp.K, tile, compact = true);
         if (w0.total > fixed_cap)
             return fail(HTSVD_ENOMEM, "the image needs " + std::to_string(w0.total) + " bytes of scratch; the "
                                       "fixed array holds " + std::to_string(fixed_cap));
@@ -1130,7 +1130,7 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
         if ((s = ensure_ws(ctx, off_ra + (p->ra ? ra_ws_bytes(g) : 0))) != HTSVD_OK) return s;
         base = ctx->ws;
     }
-    Ws wk = plan_ws(base, g, mp.W, mp.K, tile);
+    Ws wk = plan_ws(base, g, mp.W, mp.K, tile, compact);
     const double mult = p->tau_mult > 0.0 ? p->tau_mult : default_mult(c, mp.K);
     hipStream_t st = (hipStream_t)stream;
     const float *zmap = nullptr;
@@ -1195,7 +1195,7 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
         if (!it.d_out) return fail(HTSVD_EINVAL, "null sweep output");
         if (it.out_stride < (int64_t)w * c) return fail(HTSVD_EINVAL, "out_stride < w*c");
         need_prefix |= it.K < mp.K;
-        region_max = std::max(region_max, filter_region_bytes(g, mp.W, it.K));
+        region_max = std::max(region_max, filter_region_bytes(plan_filter_tiles(g, mp.W, it.K, 0), c));
     }
     const int tile = p->subimage;
     const int64_t n_ref = (int64_t)g.ny * g.nx;
@@ -1218,6 +1218,7 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
         mpi.K = it.K;
         Ws wi = wk;
         wi.regions = regions;
+        wi.tg = plan_filter_tiles(g, mp.W, it.K, 0);
         if (it.K < mp.K) {
             if (pre_k != it.K) {
                 if ((e = launch_idx_prefix(wk.idx, mp.K, idx_pre, it.K, n_ref, st)) != hipSuccess)
@@ -1499,14 +1500,23 @@ htsvd_status plan_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *imgs, cons
         b.out_stride = x.out_stride;
         b.bm_tiles_x = (b.g.nx + REF_TILE - 1) / REF_TILE;
         b.bm_tiles = ((b.g.ny + REF_TILE - 1) / REF_TILE) * b.bm_tiles_x;
-        b.tg = plan_filter_tiles(b.g, b.mp.W, b.mp.K, tile_side);
-        b.tg_alt = plan_filter_tiles(b.g, b.mp.W, 16, tile_side);
         b.n_ref = (int64_t)b.g.ny * b.g.nx;
         b.n_tiles_sigma = (int64_t)((b.g.h + T - 1) / T) * ((b.g.w + T - 1) / T);
         b.learned = x.sigma == HTSVD_SIGMA_AUTO && p->estimator == 1;
         b.off_z = 0;
         P.any_auto |= (x.sigma == HTSVD_SIGMA_AUTO) || p->adaptive;
         P.im.push_back(b);
+    }
+    // tiles sized for the image's share of the work that its launch covers (an image whose group size
+    // is chosen on the device counts in both launches it may take part in)
+    int64_t work_k[33] = {};
+    for (const BatchImage &b : P.im) {
+        work_k[b.mp.K] += b.n_ref;
+        if (b.auto_k) work_k[16] += b.n_ref;
+    }
+    for (BatchImage &b : P.im) {
+        b.tg = plan_filter_tiles(b.g, b.mp.W, b.mp.K, tile_side, (double)b.n_ref / work_k[b.mp.K]);
+        b.tg_alt = plan_filter_tiles(b.g, b.mp.W, 16, tile_side, (double)b.n_ref / std::max(work_k[16], b.n_ref));
     }
     // largest images first: their units enter the work queues first and the tail is short
     std::stable_sort(P.im.begin(), P.im.end(), [](const BatchImage &a, const BatchImage &b) {

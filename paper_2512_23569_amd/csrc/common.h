@@ -279,9 +279,13 @@ hipError_t launch_select_k(const BatchItem *items, const int *auto_list, int n_a
                            const double *mult, double cutoff, int *ksel, hipStream_t st);
 hipError_t launch_fill_tau_batched(const BatchItem *items, int n_items, const int *ref_start, int total_refs,
                                    const double *sigma, const double *mult, hipStream_t st);
-// Reference tiling of the filter: the largest square tile (side <= max_side, 0 = 16) whose
-// region and group buffers fit in LDS.
-TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side);
+// Reference tiling of the filter: square tiles (side <= max_side, 0 = 16) for `share` of the GPU,
+// or (compact) those with the smallest regions.
+TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share = 1.0, bool compact = false);
+double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share);
+size_t filter_region_bytes(const TileGeom &tg, int c);
+hipError_t launch_gather(const ImageGeom &g, const TileGeom &tg, const float *regions, float *out, int64_t out_stride,
+                         hipStream_t st);
 int filter_lds_bytes_for(const TileGeom &tg, int C, int K);
 // matrix-core filter (filter_mfma.hip)
 int filter_mfma_lds_bytes(const TileGeom &tg, int C);

@@ -69,26 +69,22 @@ __global__ void gather_kernel_batched(const BatchItem *__restrict__ items, int n
     gather_px<C>(it.g, alt ? it.tg_alt : it.tg, it.regions, it.out, it.out_stride, e - pix_start[i]);
 }
 
-// Largest reference tile (side <= max_side) whose region and the filter's other buffers fit in LDS.
-TileGeom plan_tiles(const ImageGeom &g, int W, int lds_budget, int max_side) {
+// Tiling with T x T references per tile (tight: no padding of the region's rows).
+TileGeom tiles_of(const ImageGeom &g, int W, int T, bool tight) {
     TileGeom tg;
     tg.FS = 0;
     tg.R = (W - 1) / 2;
-    const int CH = g.c + 1;
-    const int other = filter_mfma_group_bytes(g.c);
-    int T = max(1, min(16, max_side));
-    for (; T > 1; --T) {
-        const int RH = min((T - 1) * g.s + 2 * tg.R + PS, g.h);
-        const int RW = min((T - 1) * g.s + 2 * tg.R + PS, g.w);
-        if (CH * ((RH * region_pitch(RW) + 3) & ~3) * 4 + other <= lds_budget) break;
-    }
     tg.TY = tg.TX = T;
     tg.RH = min((T - 1) * g.s + 2 * tg.R + PS, g.h);
     tg.RW = min((T - 1) * g.s + 2 * tg.R + PS, g.w);
-    tg.RP = region_pitch(tg.RW);
+    tg.RP = tight ? tg.RW : region_pitch(tg.RW);
     tg.tiles_y = (g.ny + T - 1) / T;
     tg.tiles_x = (g.nx + T - 1) / T;
     return tg;
+}
+
+size_t region_bytes(const TileGeom &tg, int c) {
+    return (size_t)tg.tiles_y * tg.tiles_x * region_elems(tg, c) * sizeof(float);
 }
 
 }  // namespace
@@ -117,18 +113,48 @@ int accumulation_shift(int T, int K) {
     return fs;
 }
 
-TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side) {
-    int side = max_side > 0 ? max_side : 16;
-    while (side > 1 && accumulation_shift(side, K) < FX_MIN_SHIFT) --side;
-    TileGeom tg = plan_tiles(g, W, filter_lds_budget(), side);
-    tg.FS = accumulation_shift(tg.TY, K);
-    return tg;
+// Estimated microseconds of the filter over n_tiles tiles of refs references (K members each), on
+// `share` of the 256 CUs: one workgroup of 8 waves per CU takes whole tiles, a wave takes 32
+// patches per step, and a tile costs a fixed time besides (clearing and writing its region, the
+// first loads of its patches, waves that wait for the last one).  Measured with the tile side
+// forced: 512 x 512 RGB, stride 4, window 31, K 32: 187, 188, 164, 146, 203 us at side 4, 5, 6, 8,
+// 10, which is rounds (steps 14.5 + 18); 1536 x 2048 gray, K 16: 538, 412, 332, 320 us at side
+// 4, 6, 8, 11, rounds (steps 4.6 + 9).
+double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share) {
+    const int64_t cu = max((int64_t)1, (int64_t)(256 * share + 0.5));
+    const double steps = max(1.0, (double)refs * K / 32 / 8);
+    return (double)((n_tiles + cu - 1) / cu) * (c == 3 ? 14.5 * steps + 18.0 : 4.6 * steps + 9.0);
 }
 
-size_t filter_region_bytes(const ImageGeom &g, int W, int K) {
-    const TileGeom tg = plan_filter_tiles(g, W, K, 0);
-    return (size_t)tg.tiles_y * tg.tiles_x * region_elems(tg, g.c) * sizeof(float);
+// The tile side with the lowest estimated time among those whose region fits in LDS beside the
+// tables and whose sums keep FX_MIN_SHIFT: small images take small tiles, so that every CU has
+// one, large ones the largest, whose regions overlap least.  The regions' way through memory
+// (written and read once, about 2.5 bytes per nanosecond and direction over the whole GPU at
+// these sizes) is added.  64 x 72 RGB at K 16: 108 us at the largest side (one tile), 29 at side 4;
+// 256 x 256 gray: 49 against 20.  compact: the side whose regions, without
+// padding, take the least memory instead (for the fixed scratch of the no-allocation call).
+TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share, bool compact) {
+    TileGeom best = tiles_of(g, W, 1, compact);
+    double best_cost = 0.0;
+    const int top = min(max_side > 0 ? min(max_side, 16) : 16, max(g.ny, g.nx));
+    for (int T = 1; T <= top; ++T) {
+        const TileGeom tg = tiles_of(g, W, T, compact);
+        if (T > 1 && (accumulation_shift(T, K) < FX_MIN_SHIFT || filter_mfma_lds_bytes(tg, g.c) > filter_lds_budget()))
+            break;
+        const double bytes = (double)region_bytes(tg, g.c);
+        const double cost = compact ? bytes
+                                    : filter_tiles_cost(g.c, K, (int64_t)tg.tiles_y * tg.tiles_x, T * T, share) +
+                                          bytes / 2.5e6;
+        if (T == 1 || cost <= best_cost) {
+            best = tg;
+            best_cost = cost;
+        }
+    }
+    best.FS = accumulation_shift(best.TY, K);
+    return best;
 }
+
+size_t filter_region_bytes(const TileGeom &tg, int c) { return region_bytes(tg, c); }
 
 hipError_t launch_filter_batched(int C, int K, const BatchItem *items, int n_items, const int *unit_start, int lds,
                                  const BasisDev &b, unsigned long long *gc, int *queue, int grid, hipStream_t st) {
@@ -145,11 +171,8 @@ hipError_t launch_gather_batched(int C, const BatchItem *items, int n_items, con
     return hipGetLastError();
 }
 
-hipError_t launch_filter(const ImageGeom &g, int W, int K, const BasisDev &b, const int32_t *idx,
-                         const double *tau_ref, float *regions, unsigned long long *gc, float *out, int64_t out_stride,
-                         hipStream_t st, bool gather, const float *ra_d, const uint8_t *ra_flag) {
-    const TileGeom tg = plan_filter_tiles(g, W, K, 0);
-    if (!gather) return launch_filter_mfma(g, tg, K, b, idx, tau_ref, regions, gc, st, ra_d, ra_flag);
+hipError_t launch_gather(const ImageGeom &g, const TileGeom &tg, const float *regions, float *out, int64_t out_stride,
+                         hipStream_t st) {
     const int64_t n = (int64_t)g.h * g.w;
     if (g.c == 3)
         hipLaunchKernelGGL(gather_kernel<3>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, tg, regions, out,

@@ -1232,24 +1232,31 @@ static int ga_shift(int side, int K) {
     return fs;
 }
 
-// Tiling of the video filter: the largest tile side (<= GA_MAX_TILE) whose fixed-point shift is
-// at least GA_MIN_FS and whose slot region fits in LDS beside the fragments and transpose
-// buffers; 0 when none does (direct global aggregation).
-static int video_tile_side(int C, int K, int h_frame, int w, int s, int W, int nslot, VideoTiling *vt) {
+// Tiling of the video filter: the tile side (<= GA_MAX_TILE) with the lowest estimated time among
+// those whose fixed-point shift is at least GA_MIN_FS and whose slot region fits in LDS beside the
+// tables; 0 when none does (direct global aggregation).
+static int video_tile_side(int C, int K, int T, int ny_frame, int nx, int h_frame, int w, int s, int W, int nslot,
+                           VideoTiling *vt) {
     const int R = (W - 1) / 2;
-    for (int side = GA_MAX_TILE; side >= 1; --side) {
-        if (ga_shift(side, K) < GA_MIN_FS) continue;
+    int best = 0;
+    double best_cost = 0.0;
+    for (int side = 1; side <= GA_MAX_TILE; ++side) {
         const int RH = min((side - 1) * s + 2 * R + PS, h_frame), RW = min((side - 1) * s + 2 * R + PS, w);
         const int RP = region_pitch(RW);
         const int bytes = filter_mfma_group_bytes(C) + C * ((nslot * RH * RP + 3) & ~3) * 4;
-        if (bytes <= filter_lds_budget()) {
+        if (ga_shift(side, K) < GA_MIN_FS || bytes > filter_lds_budget()) break;
+        const int64_t n_tiles = (int64_t)T * ((ny_frame + side - 1) / side) * ((nx + side - 1) / side);
+        const double cost = filter_tiles_cost(C, K, n_tiles, side * side, 1.0) +
+                            (double)n_tiles * nslot * RH * RP * C * 4 / 2.5e6;
+        if (best == 0 || cost <= best_cost) {
+            best = side;
+            best_cost = cost;
             vt->RH = RH;
             vt->RW = RW;
             vt->RP = RP;
-            return side;
         }
     }
-    return 0;
+    return best;
 }
 
 // Plan of the video filter: frame-aligned tiles with slot regions (side > 0), or the direct
@@ -1261,7 +1268,8 @@ static int plan_video(const ImageGeom &g, int T, int radius, int W, int K, bool 
     vt->ny_frame = g.ny / T;
     vt->radius = radius;
     vt->nslot = min(2 * radius + 1, T);
-    const int side = force_direct ? 0 : video_tile_side(g.c, K, vt->h_frame, g.w, g.s, W, vt->nslot, vt);
+    const int side = force_direct ? 0 : video_tile_side(g.c, K, T, vt->ny_frame, g.nx, vt->h_frame, g.w, g.s, W, vt->nslot,
+                                                        vt);
     *tg = TileGeom{};
     tg->R = (W - 1) / 2;
     tg->FS = side > 0 ? ga_shift(side, K) : GA_FS;

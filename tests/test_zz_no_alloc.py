@@ -67,3 +67,15 @@ def test_noalloc_refuses_what_it_cannot_hold(dn):
     assert _call_noalloc(dn, small, 25.0, p.replace(ra=1), out) == ht.HTSVD_ENOTSUP          # RA network
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0      # nothing was written
+
+
+def test_noalloc_takes_the_smallest_regions_where_the_fastest_do_not_fit(dn):
+    """900 x 1000 RGB: its scratch fits the fixed array only with the tiles of the smallest regions."""
+    import paper_2512_23569_amd as ht
+    h, w = 900, 1000
+    x = torch.from_numpy(synth.add_awgn(synth.make_clean(h, w, 3, 13), 30.0, 14)).cuda()
+    p = dn.params(3, stride=4, window=31, K=32)
+    out = torch.full((h, w, 3), -5.0, dtype=torch.float32, device="cuda")
+    assert _call_noalloc(dn, x, 30.0, p, out) == ht.HTSVD_OK, ht.htsvd_last_error()
+    want = dn.denoise(x, 30.0, p)
+    assert float((out - want).abs().max()) <= RUN_TOL
