@@ -226,3 +226,31 @@ def test_trained_network_beats_plain_estimate_on_varying_noise():
         assert np.mean(gains) > 0.0
     finally:
         d.close()
+
+
+# Crop sizes that leave the backward kernels with remainders everywhere: maps of one pixel or one
+# column, odd sides under stride 2 (parity classes of unequal size), fewer pixels than one tile of
+# 32, chunks and pairs cut by the end of the batch, more than one workgroup.  The bar per tensor is
+# a relative L2 error of 2e-2: an activation that the other summation order moves across a bf16
+# rounding boundary changes its terms by 2^-8, and a few of them may meet in a small map.
+@pytest.mark.parametrize("n,h,w,c", [(1, 8, 8, 3), (1, 9, 17, 3), (2, 8, 70, 1), (3, 33, 21, 3), (5, 67, 130, 3),
+                                     (2, 41, 8, 1)])
+def test_gradients_on_ragged_sizes(dn, n, h, w, c):
+    import paper_2512_23569_amd as ht
+    p = _params(c, 70 + h)
+    ht.htsvd_cnn_set_weights(dn.ctx, c, p)
+    X = np.stack([synth.add_awgn(synth.make_clean(h, w, c, 80 + i), 25.0, 90 + i).reshape(h, w, c) for i in range(n)])
+    z_ref, _ = cnn.forward(to_bf16(p), X, c, act_round=to_bf16)
+    rng = np.random.default_rng(h * w)
+    Y = (z_ref + np.where(rng.random(z_ref.shape) < 0.5, -0.5, 0.5)).astype(np.float32)
+    g = torch.zeros(ht.htsvd_cnn_param_count(c), dtype=torch.float32, device="cuda")
+    loss = ht.htsvd_cnn_gradients(dn.ctx, torch.from_numpy(X).cuda(), n, h, w, c, torch.from_numpy(Y).cuda(), g)
+    gg = g.cpu().numpy().astype(np.float64)
+    ref_loss, ref_g = cnn.loss_and_grad(to_bf16(p), X, Y.astype(np.float64), c, act_round=to_bf16)
+    assert abs(loss - ref_loss) <= 1e-4 * max(1.0, ref_loss)
+    off = 0
+    for ci, co, st, relu in cnn.layer_shapes(c):
+        for size_t in (co * 9 * ci, co):
+            a, r = gg[off:off + size_t], ref_g[off:off + size_t]
+            assert np.linalg.norm(a - r) <= 2e-2 * np.linalg.norm(r) + 1e-12, (off, size_t)
+            off += size_t
