@@ -112,6 +112,7 @@ struct htsvd_ctx {
     RaState ra[2];                          // RA-Haar-tSVD networks, [0]: c=1, [1]: c=3
     int bands = 0;                          // band count of the hyperspectral basis (0: none)
     double *d_band_maps = nullptr;          // its D, Dinv and slice maps (FP64)
+    size_t band_maps_n = 0;                 // its capacity (doubles)
     int64_t band_cap = (int64_t)4 << 30;    // bytes per patch matrix of one pass of the band filter
     // Optional per-stage timing with HIP events recorded on the call's stream.
     bool timing = false;
@@ -593,29 +594,34 @@ htsvd_status build_band_maps(int B, const double *h_U, const double *h_V, std::v
 }
 
 // Uploads maps into *d (replacing what it held).  Synchronises the device first.
-htsvd_status upload_maps(htsvd_ctx *ctx, const std::vector<double> &maps, double **d) {
+// The maps' buffer, for n doubles, with no call still using it.
+htsvd_status ensure_maps(htsvd_ctx *ctx, size_t n) {
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "synchronise before basis upload");
-    if (*d) (void)hipFree(*d);
-    *d = nullptr;
-    if (hipMalloc(d, sizeof(double) * maps.size()) != hipSuccess) {
-        *d = nullptr;
+    if (ctx->band_maps_n >= n) return HTSVD_OK;
+    if (ctx->d_band_maps) (void)hipFree(ctx->d_band_maps);
+    ctx->d_band_maps = nullptr;
+    ctx->band_maps_n = 0;
+    if (hipMalloc(&ctx->d_band_maps, sizeof(double) * n) != hipSuccess) {
+        ctx->d_band_maps = nullptr;
         (void)hipGetLastError();
         return fail(HTSVD_ENOMEM, "basis allocation");
     }
-    if ((e = hipMemcpy(*d, maps.data(), sizeof(double) * maps.size(), hipMemcpyHostToDevice)) != hipSuccess)
-        return hip_fail(e, "basis upload");
+    ctx->band_maps_n = n;
     return HTSVD_OK;
 }
 
-// Basis of the hyperspectral path (B bands).
+size_t band_maps_doubles(int B) { return (size_t)2 * band_nb(B) * band_nb(B) + (size_t)2 * (B / 2 + 1) * 512; }
+
 htsvd_status set_basis_bands(htsvd_ctx *ctx, int B, const double *h_U, const double *h_V) {
     std::vector<double> maps;
     htsvd_status s = build_band_maps(B, h_U, h_V, maps);
     if (s != HTSVD_OK) return s;
     ctx->bands = 0;
-    if ((s = upload_maps(ctx, maps, &ctx->d_band_maps)) != HTSVD_OK) return s;
+    if ((s = ensure_maps(ctx, maps.size())) != HTSVD_OK) return s;
+    const hipError_t e = hipMemcpy(ctx->d_band_maps, maps.data(), sizeof(double) * maps.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "basis upload");
     ctx->bands = B;
     return HTSVD_OK;
 }
@@ -1023,7 +1029,8 @@ htsvd_status htsvd_learn_basis(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
     if (s != HTSVD_OK) return s;
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-    const size_t gram_n = (size_t)2 * c * c * 64;
+    const bool on_device = c != 1 && c != 3;   // the hyperspectral basis never leaves the device
+    const size_t sums_n = (size_t)2 * c * c * 64, gram_n = sums_n + (on_device ? band_learn_words(c) : 0);
     if (ctx->d_gram_n < gram_n) {
         if (ctx->d_gram) {
             (void)hipDeviceSynchronize();
@@ -1039,8 +1046,26 @@ htsvd_status htsvd_learn_basis(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
         ctx->d_gram_n = std::max<size_t>(gram_n, 2 * 9 * 64);
     }
     hipStream_t st = (hipStream_t)stream;
+    if (on_device) {
+        if ((s = ensure_maps(ctx, band_maps_doubles(c))) != HTSVD_OK) return s;
+        ctx->bands = 0;
+    }
     if ((e = launch_gram(d_in, in_stride, h, w, c, stride, ctx->d_gram, st)) != hipSuccess)
         return hip_fail(e, "Gram sums");
+    if (on_device) {
+        double *uv = nullptr;
+        if ((e = launch_band_learn(ctx->d_gram, c, band_nb(c), ctx->d_gram + sums_n, ctx->d_band_maps, &uv, st)) !=
+            hipSuccess)
+            return hip_fail(e, "basis");
+        std::vector<double> UV((size_t)2 * 64 * c);
+        if ((e = hipMemcpyAsync(UV.data(), uv, sizeof(double) * UV.size(), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+            (e = hipStreamSynchronize(st)) != hipSuccess)
+            return hip_fail(e, "basis download");
+        ctx->bands = c;
+        if (h_U) memcpy(h_U, UV.data(), sizeof(double) * 64 * c);
+        if (h_V) memcpy(h_V, UV.data() + (size_t)64 * c, sizeof(double) * 64 * c);
+        return HTSVD_OK;
+    }
     std::vector<int64_t> gram((size_t)2 * c * c * 64);
     if ((e = hipMemcpyAsync(gram.data(), ctx->d_gram, sizeof(int64_t) * gram.size(), hipMemcpyDeviceToHost, st)) !=
         hipSuccess)

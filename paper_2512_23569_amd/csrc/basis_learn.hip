@@ -231,6 +231,189 @@ __global__ __launch_bounds__(256) void gram_bands_kernel(const uint8_t *__restri
         }
 }
 
+// ---- from the Gram sums of a cube to its basis, on the device (hyperspectral path) ----
+// The channel sums enter the slice covariances only through d = a - b mod c, so they are first added
+// over the diagonals, exactly; then every slice and side is one 8 x 8 Hermitian eigenproblem for
+// one wavefront, and the inverse channel DFT and the operands of the band filter follow from the
+// vectors.  On the host the same work took 3.0 ms for 31 bands (a covariance sum over all 961
+// channel pairs, cosines inside the loops, 32 eigenproblems one after another), here 80 us (the eigenproblems 57).
+
+// fold[(g*c + d)*64 + e] = sum_{a - b = d mod c} gram[((g*c + a)*c + b)*64 + e].
+__global__ __launch_bounds__(64) void gram_fold_kernel(const int64_t *__restrict__ gram, int c,
+                                                       int64_t *__restrict__ fold) {
+    const int g = blockIdx.x / c, d = blockIdx.x % c, e = threadIdx.x;
+    int64_t v = 0;
+    for (int a = 0; a < c; ++a) {
+        const int b = a >= d ? a - d : a - d + c;
+        v += gram[((int64_t)(g * c + a) * c + b) * 64 + e];
+    }
+    fold[(int64_t)blockIdx.x * 64 + e] = v;
+}
+
+struct cd {
+    double re, im;
+};
+__device__ inline cd mul(cd a, cd b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+
+// Eigenvectors of slice f (block f*2 + g; g = 0: C_row -> U, 1: C_col -> V) into vec[(f*2 + g)*64 + i*8 + j]
+// (column j: the j-th largest eigenvalue, the entry of largest modulus real and positive).  Jacobi's
+// method with the four disjoint rotations of a round at once (lane = entry (i, k); a tournament of
+// 7 rounds meets every pair), each with a complex rotation: a unit phase makes the pivot real, a
+// plane rotation removes it.
+__global__ __launch_bounds__(64) void band_evd_kernel(const int64_t *__restrict__ fold, int c, cd *__restrict__ vec) {
+    __shared__ cd A[64], V[64], W[64];
+    __shared__ double ev[8];
+    const int f = blockIdx.x >> 1, g = blockIdx.x & 1, lane = threadIdx.x, i = lane >> 3, k = lane & 7;
+    {
+        // C_row = sum_d w^(f d) fold_d, C_col the conjugate factors, w = exp(-2 pi i / c)
+        double re = 0.0, im = 0.0;
+        for (int d = 0; d < c; ++d) {
+            double sn, cs;
+            sincospi(2.0 * (double)((f * d) % c) / c, &sn, &cs);
+            const double v = (double)fold[((int64_t)g * c + d) * 64 + lane];
+            re += v * cs;
+            im += (g == 0 ? -v : v) * sn;
+        }
+        W[lane] = {re, im};
+        __syncthreads();
+        const cd t = W[k * 8 + i];
+        A[lane] = {0.5 * (re + t.re), i == k ? 0.0 : 0.5 * (im - t.im)};
+        V[lane] = {i == k ? 1.0 : 0.0, 0.0};
+        __syncthreads();
+    }
+    for (int sweep = 0; sweep < 100; ++sweep) {
+        const cd own = A[lane];
+        if (!__ballot(i < k && (own.re != 0.0 || own.im != 0.0))) break;
+        for (int r = 0; r < 7; ++r) {
+            auto partner = [&](int x) { return x == 7 ? r : (x == r ? 7 : (2 * r - x + 7) % 7); };
+            // rotation of the pair that holds x: J[p][p] = co, J[p][q] = sn, J[q][p] = -sn conj(e),
+            // J[q][q] = co conj(e)
+            struct Rot {
+                double co, sn;
+                cd e;
+                int p, q;
+            };
+            auto rotation = [&](int x) {
+                const int y = partner(x);
+                Rot t;
+                t.p = min(x, y);
+                t.q = max(x, y);
+                const cd z = A[t.p * 8 + t.q];
+                const double app = A[t.p * 9].re, aqq = A[t.q * 9].re;
+                const double m = sqrt(z.re * z.re + z.im * z.im);
+                // past the first sweeps a pivot below the last bit of both diagonal entries is
+                // dropped instead of rotated (the usual termination of the method)
+                const bool drop = m == 0.0 || (sweep > 3 && fabs(app) + 100.0 * m == fabs(app) &&
+                                               fabs(aqq) + 100.0 * m == fabs(aqq));
+                if (drop) {
+                    t.co = 1.0;
+                    t.sn = 0.0;
+                    t.e = {1.0, 0.0};
+                } else {
+                    t.e = {z.re / m, z.im / m};
+                    const double theta = (aqq - app) / (2.0 * m);
+                    double tn = 1.0 / (fabs(theta) + sqrt(1.0 + theta * theta));
+                    if (theta < 0.0) tn = -tn;
+                    t.co = 1.0 / sqrt(1.0 + tn * tn);
+                    t.sn = tn * t.co;
+                }
+                return t;
+            };
+            const Rot rk = rotation(k), ri = rotation(i);
+            // column k of J, and the conjugate column i: factors of the entries p and q of the pair
+            const cd kp = k == rk.p ? cd{rk.co, 0.0} : cd{rk.sn, 0.0};
+            const cd kq = k == rk.p ? cd{-rk.sn * rk.e.re, rk.sn * rk.e.im} : cd{rk.co * rk.e.re, -rk.co * rk.e.im};
+            const cd ip = i == ri.p ? cd{ri.co, 0.0} : cd{ri.sn, 0.0};
+            const cd iq = i == ri.p ? cd{-ri.sn * ri.e.re, -ri.sn * ri.e.im} : cd{ri.co * ri.e.re, ri.co * ri.e.im};
+            auto column = [&](const cd *M, int row) {
+                const cd x = mul(M[row * 8 + rk.p], kp), y = mul(M[row * 8 + rk.q], kq);
+                return cd{x.re + y.re, x.im + y.im};
+            };
+            const cd x = mul(ip, column(A, ri.p)), y = mul(iq, column(A, ri.q));
+            cd a = {x.re + y.re, i == k ? 0.0 : x.im + y.im};
+            if (k == partner(i)) a = {0.0, 0.0};
+            const cd v = column(V, i);
+            __syncthreads();
+            A[lane] = a;
+            V[lane] = v;
+            __syncthreads();
+        }
+    }
+    if (i == 0) ev[k] = A[k * 9].re;
+    __syncthreads();
+    int rank = 0;   // place of column k by descending eigenvalue, equal ones in order
+    for (int j = 0; j < 8; ++j) rank += ev[j] > ev[k] || (ev[j] == ev[k] && j < k);
+    int kmax = 0;
+    double amax = -1.0;
+    for (int j = 0; j < 8; ++j) {
+        const cd v = V[j * 8 + k];
+        const double m = sqrt(v.re * v.re + v.im * v.im);
+        if (m > amax) {
+            amax = m;
+            kmax = j;
+        }
+    }
+    const cd top = V[kmax * 8 + k], ph = amax > 0.0 ? cd{top.re / amax, -top.im / amax} : cd{1.0, 0.0};
+    vec[(int64_t)blockIdx.x * 64 + i * 8 + rank] = i == kmax ? cd{amax, 0.0} : mul(V[lane], ph);
+}
+
+// T(k) = (1/c) sum_f T_hat^(f) exp(2 pi i f k / c) with T_hat^(c-f) = conj T_hat^(f): band k = blockIdx.x of
+// U (threads 0 .. 63) and V into uv[(side*c + k)*64 + e].
+__global__ __launch_bounds__(128) void band_basis_kernel(const cd *__restrict__ vec, int c, double *__restrict__ uv) {
+    const int k = blockIdx.x, g = threadIdx.x >> 6, e = threadIdx.x & 63;
+    double acc = 0.0;
+    for (int f = 0; f <= c / 2; ++f) {
+        double sn, cs;
+        sincospi(2.0 * (double)((f * k) % c) / c, &sn, &cs);
+        const cd v = vec[(f * 2 + g) * 64 + e];
+        const double re = v.re * cs - v.im * sn;
+        acc += f == 0 || 2 * f == c ? re : 2.0 * re;
+    }
+    uv[(int64_t)(g * c + k) * 64 + e] = acc / c;
+}
+
+// The band filter's maps (BandMaps): blocks f < NF: the slice products' operands of frequency f, both
+// directions; block NF: the channel DFT D and its inverse.  Slice products: forward T = L P with
+// L(a, b) = conj(U(b, a)), then Y = T R with R = V; inverse L = U, R(a, b) = conj(V(b, a)).  Real
+// embeddings: L as [[Lr, -Li], [Li, Lr]] acting on [Pr; Pi], R as [[Rr, Ri], [-Ri, Rr]] acting on
+// [Tr | Ti] from the right; operand lanes of v_mfma_f64_16x16x4f64: A(m, k) in lane m + 16 (k mod 4),
+// B(k, n) in lane n + 16 (k mod 4).
+__global__ __launch_bounds__(256) void band_maps_kernel(const cd *__restrict__ vec, int c, int nb,
+                                                        double *__restrict__ maps) {
+    const int NF = c / 2 + 1, f = blockIdx.x;
+    double *D = maps, *Dinv = maps + nb * nb;
+    if (f == NF) {
+        for (int e = threadIdx.x; e < nb * nb; e += 256) {
+            const int row = e / nb, b = e % nb;   // D[row][b] and Dinv[b][row]
+            double d = 0.0, di = 0.0;
+            if (row < c && b < c) {
+                const int fr = (row + 1) / 2;
+                double sn, cs;
+                sincospi(2.0 * (double)((fr * b) % c) / c, &sn, &cs);
+                const bool real = row == 0 || 2 * fr == c;
+                d = real || (row & 1) ? cs : -sn;
+                di = (real ? 1.0 : 2.0) * d / c;
+            }
+            D[row * nb + b] = d;
+            Dinv[b * nb + row] = di;
+        }
+        return;
+    }
+    const cd *U = vec + (f * 2) * 64, *V = U + 64;
+    const int st = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int m = lane & 15, k = 4 * st + (lane >> 4), rm = m >> 3, rk = k >> 3;
+    for (int dir = 0; dir < 2; ++dir) {
+        double *fr = maps + (int64_t)2 * nb * nb + ((int64_t)dir * NF + f) * 512;
+        // left factor: row m = (rm, a), column k = (rk, b); right factor: row k = (rk, a), column m = (rm, b)
+        const cd lu = dir == 0 ? U[(k & 7) * 8 + (m & 7)] : U[(m & 7) * 8 + (k & 7)];
+        const cd l = {lu.re, dir == 0 ? -lu.im : lu.im};
+        const cd rv = dir == 0 ? V[(k & 7) * 8 + (m & 7)] : V[(m & 7) * 8 + (k & 7)];
+        const cd r = {rv.re, dir == 0 ? rv.im : -rv.im};
+        fr[st * 64 + lane] = rm == rk ? l.re : (rm == 0 ? -l.im : l.im);
+        fr[(4 + st) * 64 + lane] = rk == rm ? r.re : (rk == 0 ? r.im : -r.im);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_gram(const uint8_t *img, int64_t stride, int h, int w, int c, int s, int64_t *out, hipStream_t st) {
@@ -253,6 +436,22 @@ hipError_t launch_gram(const uint8_t *img, int64_t stride, int h, int w, int c, 
         hipLaunchKernelGGL(gram_kernel<3>, dim3(nb, 2), dim3(GR_THREADS), 0, st, img, stride, h, w, s, ny, nx, o);
     else
         hipLaunchKernelGGL(gram_kernel<1>, dim3(nb, 2), dim3(GR_THREADS), 0, st, img, stride, h, w, s, ny, nx, o);
+    return hipGetLastError();
+}
+
+size_t band_learn_words(int c) { return (size_t)2 * c * 64 + (size_t)(c / 2 + 1) * 2 * 64 * 2 + (size_t)2 * c * 64; }
+
+// Basis of a c-band cube from its Gram sums: maps (BandMaps layout) and uv = U then V, slice-major,
+// (in work, band_learn_words 8-byte words; *uv is set to their place there).
+hipError_t launch_band_learn(const int64_t *gram, int c, int nb, void *work, double *maps, double **uv,
+                             hipStream_t st) {
+    int64_t *fold = (int64_t *)work;
+    cd *vec = (cd *)(fold + (size_t)2 * c * 64);
+    *uv = (double *)(vec + (size_t)(c / 2 + 1) * 2 * 64);
+    hipLaunchKernelGGL(gram_fold_kernel, dim3(2 * c), dim3(64), 0, st, gram, c, fold);
+    hipLaunchKernelGGL(band_evd_kernel, dim3((c / 2 + 1) * 2), dim3(64), 0, st, fold, c, vec);
+    hipLaunchKernelGGL(band_basis_kernel, dim3(c), dim3(128), 0, st, vec, c, *uv);
+    hipLaunchKernelGGL(band_maps_kernel, dim3(c / 2 + 2), dim3(256), 0, st, vec, c, nb, maps);
     return hipGetLastError();
 }
 

@@ -389,5 +389,8 @@ hipError_t ra_adam(float *w, float *m, float *v, const float *g, int n, float lr
 
 // Channel Gram sums of the reference patches (rows, then columns) into out[2][c][c][8][8].
 hipError_t launch_gram(const uint8_t *img, int64_t stride, int h, int w, int c, int s, int64_t *out, hipStream_t st);
+size_t band_learn_words(int c);
+hipError_t launch_band_learn(const int64_t *gram, int c, int nb, void *work, double *maps, double **uv,
+                             hipStream_t st);
 
 }  // namespace htsvd

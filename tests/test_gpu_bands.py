@@ -222,3 +222,23 @@ def test_band_full_size_row_band_parity(dn):
     ref = oracle.filter_groups(noisy, idx[sel], U, V, tau)
     m = assert_pixel_parity(gpu[r0:r1], ref[r0:r1], clean[r0:r1])
     print("full-size band rows %d-%d, %d groups:" % (r0, r1 - 1, int(sel.sum())), m)
+
+
+@pytest.mark.parametrize("h,w,bands,stride", [(24, 31, 2, 3), (40, 29, 4, 4), (33, 36, 33, 5), (30, 41, 64, 4)])
+def test_learned_pair_at_the_ends_of_the_band_counts(dn, h, w, bands, stride):
+    """Even and odd counts, two bands (two real slices), the first count of the 64-wide maps and the
+    last: the pair against the oracle's at 1e-8, the bar of the other learned pairs, and the filter
+    with it against the filter with the same pair set from the host (which forms the maps there):
+    both within FP64 rounding of each other, so within an FP32 rounding (2^-16) and a fixed-point step
+    of the sums on the 0..255 scale; 1e-4 covers both."""
+    import paper_2512_23569_amd as ht
+    cube = synth.add_awgn(synth.make_hsi(h, w, bands, 40 + bands), 20.0, bands)
+    d = _dev(cube)
+    U, V = dn.learn_basis(d, stride=stride)
+    Uo, Vo = lb.learn(cube, 8, stride)
+    assert np.abs(np.moveaxis(U, 0, 2) - Uo).max() <= 1e-8
+    assert np.abs(np.moveaxis(V, 0, 2) - Vo).max() <= 1e-8
+    p = dn.params(1, stride=stride, window=9, K=8)
+    learned = dn.denoise_bands(d, 20.0, p)
+    ht.htsvd_set_basis(dn.ctx, 8, bands, U, V)
+    assert float((learned - dn.denoise_bands(d, 20.0, p)).abs().max()) <= 1e-4
