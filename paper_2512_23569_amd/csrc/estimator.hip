@@ -13,11 +13,10 @@
 //     channel) runs it on v_mfma_i32_16x16x64_i8 with 64 patches per k-step; the row sums
 //     come from the same instruction with an all-ones operand.  int32 partials are exact and
 //     go to a scratch buffer (mom_kernel).
-//   - The eigenvalues of the 64x64 FP64 covariance take one wavefront per (sub-image,
-//     channel) (eig_kernel): Householder reduction to tridiagonal form with lane i holding
-//     row i in registers, then Sturm-count bisection with lane i finding the i-th smallest
-//     eigenvalue.  Keeping this stage apart from the moments lets every SIMD run two such
-//     wavefronts, whose serial dependency chains would otherwise leave the CU idle.
+//   - The eigenvalues of the 64x64 FP64 covariance take one workgroup of four wavefronts per
+//     (sub-image, channel) (eig_kernel): Householder reduction to tridiagonal form with lane i
+//     of wave w holding columns 16 w .. of row i, then Sturm-count multisection with lane i
+//     finding the i-th smallest eigenvalue from one point per wave and step.
 //
 // Eq. 22-23 vote: for a few groups per sub-image the rank a of the alternating eigenvalue
 // lambda_hat = |sum_m (-1)^m p_m|^2 among the K eigenvalues of circ(G) circ(G)^T, whose
@@ -63,15 +62,6 @@ __device__ inline v4i frag16(const unsigned char *lds, int plane, int r, int col
     return f;
 }
 
-// 1/q: the hardware estimate refined by two Newton steps (each squares the relative error).
-__device__ inline double recip(double q) {
-    double r = __builtin_amdgcn_rcp(q);
-    double e = fma(-q, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-q, r, 1.0);
-    return fma(r, e, r);
-}
-
 // Sum over the 64 lanes of a wavefront (every lane gets the total; partners exchange by DPP
 // and row swaps, offsets 32, 16, ..., 1).
 __device__ __forceinline__ double wave_sum_d(double v) {
@@ -102,8 +92,10 @@ constexpr int MOM_INTS = 64 * 64 + 64;
 // Moments of one (sub-image, channel), one workgroup of 4 waves: exact integer second moments
 // of the shifted patches on the matrix cores, the sub-image staged band by band; written to
 // mom (MOM_INTS int32).
+// With `parts` > 1 the workgroup takes every parts-th band of rows from band `part` and adds its
+// share to mom (zero before): a few sub-images then fill the GPU (512 x 512 RGB: 95 -> 18 us).
 __device__ __forceinline__ void mom_tile(unsigned char *smem, const ImageGeom g, int T, int t, int ch,
-                                int32_t *__restrict__ mom) {
+                                int32_t *__restrict__ mom, int part, int parts) {
     int32_t *S2 = reinterpret_cast<int32_t *>(smem + COV_OFF_S2);
     int32_t *S1 = reinterpret_cast<int32_t *>(smem + COV_OFF_S1);
     unsigned char *stage = smem + COV_OFF_STAGE;
@@ -126,7 +118,7 @@ __device__ __forceinline__ void mom_tile(unsigned char *smem, const ImageGeom g,
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     const int i16 = lane & 15, kq = lane >> 4;
     const int xsteps = (nx + 63) / 64;
-    for (int b0 = 0; b0 < ny; b0 += COV_BAND) {
+    for (int b0 = part * COV_BAND; b0 < ny; b0 += parts * COV_BAND) {
         const int nb = min(COV_BAND, ny - b0);
         const int prow = nb + PS - 1;
         __syncthreads();   // previous band consumed
@@ -179,6 +171,14 @@ __device__ __forceinline__ void mom_tile(unsigned char *smem, const ImageGeom g,
     }
     __syncthreads();
     // only the blocks ib <= jb were accumulated: entry (r, c) of the full matrix is S2[min][max]
+    if (parts > 1) {
+        for (int e = tid; e < 64 * 64; e += 256) {
+            const int r = e >> 6, c = e & 63;
+            atomicAdd(mom + e, S2[min(r, c) * S2_PITCH + max(r, c)]);
+        }
+        if (tid < 64) atomicAdd(mom + 64 * 64 + tid, S1[tid]);
+        return;
+    }
     for (int e = tid; e < 64 * 64; e += 256) {
         const int r = e >> 6, c = e & 63;
         mom[e] = S2[min(r, c) * S2_PITCH + max(r, c)];
@@ -186,114 +186,156 @@ __device__ __forceinline__ void mom_tile(unsigned char *smem, const ImageGeom g,
     if (tid < 64) mom[64 * 64 + tid] = S1[tid];
 }
 
-// Householder steps k = 8B .. min(8B + 8, 62) - 1 on the rows held one per lane (lane i: row i).
-// The reflector vector v is zero at indices <= k, so for a step of this block the products and
-// updates of the columns below 8B are exact zeros for every entry read later (the tridiagonal
-// entries of the reduced rows, and v, w, p): those columns are left out.
-template <int B>
-__device__ __forceinline__ void hh_block(double (&row)[64], int i) {
-    constexpr int J0 = 8 * B;
-    constexpr int KEND = J0 + 8 < 62 ? J0 + 8 : 62;
-    for (int k = J0; k < KEND; ++k) {
-        double xk = 0.0;
-#pragma unroll
-        for (int j = J0; j < J0 + 8; ++j) xk = (j == k) ? row[j] : xk;   // lane i: A[i][k]
-        const double tail = wave_sum_d(i > k + 1 ? xk * xk : 0.0);
-        const double x0 = readlane_f64(xk, k + 1);
-        if (tail == 0.0) continue;                       // column already reduced (uniform)
-        const double nrm = sqrt(x0 * x0 + tail);
-        const double alpha = x0 > 0.0 ? -nrm : nrm;
-        const double v0 = x0 - alpha;
-        const double beta = 2.0 / (v0 * v0 + tail);
-        const double vi = i == k + 1 ? v0 : (i > k + 1 ? xk : 0.0);
-        // v and w are broadcast lane by lane as scalar operands (no LDS round trip)
-        double pi = 0.0;
-#pragma unroll
-        for (int j = J0 + 1; j < 64; ++j) pi += row[j] * readlane_f64(vi, j);
-        pi *= beta;
-        const double Kc = 0.5 * beta * wave_sum_d(pi * vi);
-        const double wi = pi - Kc * vi;
-#pragma unroll
-        for (int j = J0; j < 64; ++j) row[j] -= vi * readlane_f64(wi, j) + wi * readlane_f64(vi, j);
-    }
-}
+// LDS of the eigenvalue stage: vectors of a Householder step (two sets, so that a step may start
+// while a slow wave still reads the last one's), then the tridiagonal matrix and the counts.
+constexpr int EIG_WAVES = 4;
+struct EigShared {
+    double v[2][64], beta[2], part[2][EIG_WAVES][64];
+    double d[64], e2[64], sub[64], ev[64];
+    int cnt[2][EIG_WAVES][64];
+};
 
-// Eigenvalue stage of one (sub-image, channel), one wavefront: covariance rows in registers
-// (lane i holds row i), Householder reduction to tridiagonal form, eigenvalues by Sturm-count
-// bisection (lane i finds the i-th smallest), tail rule.  vec: 3 x 64 doubles of LDS for this
-// wave.  Writes sigma_c^2 to *out (lane 0).
-__device__ __forceinline__ void eig_tile(double *vec, const int32_t *__restrict__ mom, double n, double *__restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    // ---- phase 2: covariance row i = lane, in registers ----
-    const int i = lane;
+// Eigenvalue stage of one (sub-image, channel), one workgroup: covariance columns in registers (lane
+// i of wave w: row i, columns 16 w .. 16 w + 15), Householder reduction to tridiagonal form,
+// eigenvalues by Sturm counts, tail rule.  Writes sigma_c^2 to *out.
+//
+// It is bound by latency: 62 reflections and some 26 counts of 64 dependent steps one after the other.
+// With one wave per matrix (all 64 columns, three interleaved counts with divisions per step) it
+// took 272 us for the 48 matrices of a 512 x 512 RGB image and 698 us for the 2,304 of 12 MP, with
+// four 131 and 522.
+__device__ __forceinline__ void eig_tile(EigShared &sh, const int32_t *__restrict__ mom, double n,
+                                         double *__restrict__ out) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane, j0 = 16 * wave;
     const int32_t *S1 = mom + 64 * 64;
     const double s1i = (double)S1[i] / n;
-    double row[64];
+    double row[16];
 #pragma unroll
-    for (int j = 0; j < 64; ++j) row[j] = (double)mom[i * 64 + j] / n - s1i * ((double)S1[j] / n);
-    // Householder: step k annihilates column k below the subdiagonal; steps run in blocks of 8.
-    hh_block<0>(row, i);
-    hh_block<1>(row, i);
-    hh_block<2>(row, i);
-    hh_block<3>(row, i);
-    hh_block<4>(row, i);
-    hh_block<5>(row, i);
-    hh_block<6>(row, i);
-    hh_block<7>(row, i);
+    for (int q = 0; q < 4; ++q) {
+        const int4 m4 = *reinterpret_cast<const int4 *>(mom + i * 64 + j0 + 4 * q);
+        const int4 s4 = *reinterpret_cast<const int4 *>(S1 + j0 + 4 * q);
+        row[4 * q] = (double)m4.x / n - s1i * ((double)s4.x / n);
+        row[4 * q + 1] = (double)m4.y / n - s1i * ((double)s4.y / n);
+        row[4 * q + 2] = (double)m4.z / n - s1i * ((double)s4.z / n);
+        row[4 * q + 3] = (double)m4.w / n - s1i * ((double)s4.w / n);
+    }
+    // Householder: step k annihilates column k below the subdiagonal.  The wave with column k makes
+    // the reflector v; every wave adds its columns' share of p = beta A v and, with p complete,
+    // updates its columns by A -= v w^T + w v^T, w = p - (beta p.v / 2) v.  Columns below the
+    // current block of 16 only carry zeros for every entry read later and are left alone.
+    for (int k = 0; k < 62; ++k) {
+        const int buf = k & 1;
+        if (wave == (k >> 4)) {
+            double xk = 0.0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) xk = (j == (k & 15)) ? row[j] : xk;   // lane i: A[i][k]
+            const double tail = wave_sum_d(i > k + 1 ? xk * xk : 0.0);
+            const double x0 = readlane_f64(xk, k + 1);
+            const double nrm = sqrt(x0 * x0 + tail);
+            const double v0 = x0 > 0.0 ? x0 + nrm : x0 - nrm;                  // x0 - alpha
+            // a column that is already reduced (tail 0) gives beta 0: no reflection
+            if (lane == 0) sh.beta[buf] = tail == 0.0 ? 0.0 : 2.0 / (v0 * v0 + tail);
+            sh.v[buf][i] = i == k + 1 ? v0 : (i > k + 1 ? xk : 0.0);
+        }
+        __syncthreads();
+        const double beta = sh.beta[buf], vi = sh.v[buf][i];
+        const bool live = beta != 0.0 && j0 + 15 >= k;   // uniform
+        double vj[16], pi = 0.0;
+        if (live) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) vj[j] = sh.v[buf][j0 + j];
+            double p1 = 0.0;
+#pragma unroll
+            for (int j = 0; j < 16; j += 2) {
+                pi += row[j] * vj[j];
+                p1 += row[j + 1] * vj[j + 1];
+            }
+            pi += p1;
+        }
+        sh.part[buf][wave][i] = pi;
+        __syncthreads();
+        if (live) {
+            pi = beta * ((sh.part[buf][0][i] + sh.part[buf][1][i]) + (sh.part[buf][2][i] + sh.part[buf][3][i]));
+            const double wi = pi - 0.5 * beta * wave_sum_d(pi * vi) * vi;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) row[j] -= vi * readlane_f64(wi, j0 + j) + wi * vj[j];
+        }
+    }
     // tridiagonal: d_i = A[i][i], e_{i-1} = A[i][i-1]
-    double di = 0.0, sub = 0.0;
 #pragma unroll
-    for (int j = 0; j < 64; ++j) {
-        di = (j == i) ? row[j] : di;
-        sub = (j == i - 1) ? row[j] : sub;
+    for (int j = 0; j < 16; ++j) {
+        if (i == j0 + j) sh.d[i] = row[j];
+        if (i == j0 + j + 1) {
+            sh.e2[i] = row[j] * row[j];   // e2[i] = e_{i-1}^2
+            sh.sub[i] = row[j];
+        }
     }
-    double *dd = vec, *e2 = vec + 64, *ev = vec + 128;
-    __builtin_amdgcn_wave_barrier();
-    dd[i] = di;
-    e2[i] = i > 0 ? sub * sub : 0.0;    // e2[i] = e_{i-1}^2
+    if (threadIdx.x == 0) sh.e2[0] = sh.sub[0] = 0.0;
+    __syncthreads();
     // Gershgorin interval
-    const double se = fabs(sub) + fabs(__shfl(sub, (i + 1) & 63) * (i < 63 ? 1.0 : 0.0));
-    double lo = di - se, hi = di + se;
+    double lo, hi;
+    {
+        const double di = sh.d[i], se = fabs(sh.sub[i]) + (i < 63 ? fabs(sh.sub[i + 1]) : 0.0);
+        lo = di - se;
+        hi = di + se;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, o));
-        hi = fmax(hi, __shfl_xor(hi, o));
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+        }
     }
-    __builtin_amdgcn_wave_barrier();
-    // The i-th smallest eigenvalue by quadrisection: count(x) = #eigenvalues < x (Sturm sequence
-    // of the LDL^T pivots); three interior points per step, evaluated as three interleaved
-    // chains, so 30 steps narrow the interval by 2^60 like 60 bisection steps.
-    const double span = fmax(hi - lo, 1e-300);
-    lo -= 1e-12 * span;
-    hi += 1e-12 * span;
-    for (int it = 0; it < 30; ++it) {
-        const double qw = 0.25 * (hi - lo);
-        const double x1 = lo + qw, x2 = lo + 2.0 * qw, x3 = lo + 3.0 * qw;
-        double q1 = dd[0] - x1, q2 = dd[0] - x2, q3 = dd[0] - x3;
-        int c1 = q1 < 0.0, c2 = q2 < 0.0, c3 = q3 < 0.0;
+    // The i-th smallest eigenvalue by multisection: count(x) = #eigenvalues < x = the sign changes in
+    // the leading principal minors p_j(x) of A - x, p_j = (d_j - x) p_{j-1} - e_{j-1}^2 p_{j-2} (no
+    // division in the chain).  Matrix and interval are scaled to unit width, so a minor grows by at
+    // most a factor 2 per step, and every eight steps the pair is scaled back to exponent 0; a minor
+    // that is exactly 0 counts once either way (the next one has the opposite sign of the last).
+    // Four waves place four points, so 26 steps narrow the interval by 5^26 > 2^60.
+    const double span = fmax(hi - lo, 1e-290), scale = 1.0 / span;   // of the FP64 normal range
+    __syncthreads();
+    if (wave == 0) {
+        sh.d[i] = (sh.d[i] - lo) * scale;
+        sh.e2[i] = sh.e2[i] * scale * scale;
+    }
+    __syncthreads();
+    const double base = lo;
+    lo = -1e-12;
+    hi = 1.0 + 1e-12;
+    for (int it = 0; it < 26; ++it) {
+        const double q = 0.2 * (hi - lo), x = fma((double)(wave + 1), q, lo);
+        double p0 = 1.0, p1 = sh.d[0] - x;
+        uint32_t c = (uint32_t)(__double2hiint(p1)) >> 31;
+#pragma unroll 8
         for (int j = 1; j < 64; ++j) {
-            const double dj = dd[j], ej = e2[j];
-            q1 = (dj - x1) - ej * recip(q1 == 0.0 ? 1e-300 : q1);
-            q2 = (dj - x2) - ej * recip(q2 == 0.0 ? 1e-300 : q2);
-            q3 = (dj - x3) - ej * recip(q3 == 0.0 ? 1e-300 : q3);
-            c1 += q1 < 0.0;
-            c2 += q2 < 0.0;
-            c3 += q3 < 0.0;
+            const double p2 = fma(sh.d[j] - x, p1, -(sh.e2[j] * p0));
+            c += (uint32_t)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31;
+            p0 = p1;
+            p1 = p2;
+            if ((j & 7) == 7) {
+                const int e = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+                p0 = ldexp(p0, -e);
+                p1 = ldexp(p1, -e);
+            }
         }
-        if (c1 > i) {
-            hi = x1;
-        } else if (c2 > i) {
-            lo = x1;
-            hi = x2;
-        } else if (c3 > i) {
-            lo = x2;
-            hi = x3;
-        } else {
-            lo = x3;
-        }
+        sh.cnt[it & 1][wave][i] = (int)c;
+        __syncthreads();
+        // the first point with more than i eigenvalues below it closes the interval
+        double nlo = lo + 4.0 * q, nhi = hi;
+#pragma unroll
+        for (int w = EIG_WAVES - 1; w >= 0; --w)
+            if (sh.cnt[it & 1][w][i] > i) {
+                nhi = fma((double)(w + 1), q, lo);
+                nlo = w == 0 ? lo : fma((double)w, q, lo);
+            }
+        lo = nlo;
+        hi = nhi;
     }
+    if (wave != 0) return;
+    double *ev = sh.ev;
+    lo = base + span * lo;
+    hi = base + span * hi;
     const double lam = 0.5 * (lo + hi);   // ascending: lane i holds the i-th smallest
     ev[i] = lam;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
     // tail rule on the descending order: tail m = the 64 - m smallest values (lane m)
     const int m = lane, len = 64 - m;
@@ -318,51 +360,45 @@ __device__ inline double tile_patches(const ImageGeom &g, int T, int t) {
     return (double)(y1 - y0 + 1) * (double)(x1 - x0 + 1);
 }
 
-// One workgroup per (sub-image, channel): unit u = t * c + ch = unit0 + block.
-__global__ __launch_bounds__(256) void mom_kernel(ImageGeom g, int T, int unit0, int32_t *__restrict__ mom) {
+// `parts` workgroups per (sub-image, channel): unit u = t * c + ch = unit0 + block / parts.
+__global__ __launch_bounds__(256) void mom_kernel(ImageGeom g, int T, int unit0, int parts, int32_t *__restrict__ mom) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int u = unit0 + (int)blockIdx.x;
-    mom_tile(smem, g, T, u / g.c, u % g.c, mom + (int64_t)blockIdx.x * MOM_INTS);
+    const int v = (int)blockIdx.x / parts, u = unit0 + v;
+    mom_tile(smem, g, T, u / g.c, u % g.c, mom + (int64_t)v * MOM_INTS, (int)blockIdx.x % parts, parts);
 }
 
-// One wavefront per (sub-image, channel), EIG_WAVES per workgroup.
-constexpr int EIG_WAVES = 4;
-
-// Units unit0 .. unit0 + n_units - 1; mom and sigma2 indexed from unit0.
-__global__ __launch_bounds__(64 * EIG_WAVES, 2) void eig_kernel(ImageGeom g, int T, int unit0, int n_units,
+// One workgroup per (sub-image, channel): units unit0 + block; mom and sigma2 indexed from unit0.
+__global__ __launch_bounds__(64 * EIG_WAVES) void eig_kernel(ImageGeom g, int T, int unit0,
                                                              const int32_t *__restrict__ mom,
                                                              double *__restrict__ sigma2) {
-    __shared__ double vec[EIG_WAVES][3 * 64];
-    const int wave = threadIdx.x >> 6;
-    const int u = blockIdx.x * EIG_WAVES + wave;
-    if (u >= n_units) return;
-    eig_tile(vec[wave], mom + (int64_t)u * MOM_INTS, tile_patches(g, T, (unit0 + u) / g.c), sigma2 + u);
+    __shared__ EigShared sh;
+    const int u = blockIdx.x;
+    eig_tile(sh, mom + (int64_t)u * MOM_INTS, tile_patches(g, T, (unit0 + u) / g.c), sigma2 + u);
 }
 
 // Batched: units (item, sub-image, channel) of the list; mom is indexed by the global unit.
 __global__ __launch_bounds__(256) void mom_kernel_batched(const SigmaItem *__restrict__ items,
                                                           const int *__restrict__ sel, const int *__restrict__ start,
-                                                          int n, int T, int32_t *__restrict__ mom) {
+                                                          int n, int T, int parts, int32_t *__restrict__ mom) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int j = find_unit(start, n, blockIdx.x);
+    const int gu = (int)blockIdx.x / parts;
+    const int j = find_unit(start, n, gu);
     const ImageGeom g = items[sel[j]].g;
-    const int u = blockIdx.x - start[j];
-    mom_tile(smem, g, T, u / g.c, u % g.c, mom + (int64_t)blockIdx.x * MOM_INTS);
+    const int u = gu - start[j];
+    mom_tile(smem, g, T, u / g.c, u % g.c, mom + (int64_t)gu * MOM_INTS, (int)blockIdx.x % parts, parts);
 }
 
-__global__ __launch_bounds__(64 * EIG_WAVES, 2) void eig_kernel_batched(const SigmaItem *__restrict__ items,
+__global__ __launch_bounds__(64 * EIG_WAVES) void eig_kernel_batched(const SigmaItem *__restrict__ items,
                                                                      const int *__restrict__ sel,
-                                                                     const int *__restrict__ start, int n, int total,
-                                                                     int T, const int32_t *__restrict__ mom) {
-    __shared__ double vec[EIG_WAVES][3 * 64];
-    const int wave = threadIdx.x >> 6;
-    const int gu = blockIdx.x * EIG_WAVES + wave;
-    if (gu >= total) return;
+                                                                     const int *__restrict__ start, int n, int T,
+                                                                     const int32_t *__restrict__ mom) {
+    __shared__ EigShared sh;
+    const int gu = blockIdx.x;
     const int j = find_unit(start, n, gu);
     const SigmaItem &it = items[sel[j]];
     const ImageGeom g = it.g;
     const int u = gu - start[j];
-    eig_tile(vec[wave], mom + (int64_t)gu * MOM_INTS, tile_patches(g, T, u / g.c), it.cov + u);
+    eig_tile(sh, mom + (int64_t)gu * MOM_INTS, tile_patches(g, T, u / g.c), it.cov + u);
 }
 
 __global__ void combine_sigma_kernel(const double *sigma2, int c, int n_tiles, double *sigma_est) {
@@ -431,10 +467,11 @@ __device__ inline void ref_range(int n_ref, int n, int s, int lo, int hi, int *f
     *last = l;
 }
 
-// One workgroup (4 wavefronts) per sub-image: the sampled groups are spread over the waves;
+// One workgroup (8 wavefronts) per sub-image, its sampled groups spread over the waves;
 // per group the exact autocorrelations c_d, then lambda_k = sum_d c_d cos(2 pi k d / K) with
 // lane k computing lambda_k (same summation order for every k), the rank of lambda_hat, and
 // the majority over the groups.
+constexpr int VOTE_WAVES = 8;
 template <int K>
 struct VoteShared {
     int iy0, iy1, ix0, ix1, yes;
@@ -466,9 +503,8 @@ __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, 
         return;
     }
     const int nv = n_t <= n_vote ? (int)n_t : n_vote;
-    const int P = 64 * g.c;
     int yes = 0;
-    for (int i = wave; i < nv; i += 4) {
+    for (int i = wave; i < nv; i += VOTE_WAVES) {
         int64_t j;
         if (n_t <= n_vote) {
             j = i;
@@ -481,14 +517,17 @@ __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, 
         int64_t cd[K / 2 + 1];
 #pragma unroll
         for (int d = 0; d <= K / 2; ++d) cd[d] = 0;
-        for (int e = lane; e < P; e += 64) {
-            const int ch = e / 64, a = (e / 8) % 8, b = e % 8;
+        // lane m finds the address of member m, read from there as a scalar
+        const int32_t lin = idx[r * idx_stride + (lane & (K - 1))];
+        const int64_t at = (int64_t)(lin / g.w) * g.stride + (int64_t)(lin % g.w) * g.c;
+        const int64_t px = (int64_t)(lane >> 3) * g.stride + (int64_t)(lane & 7) * g.c;
+        for (int ch = 0; ch < g.c; ++ch) {
             int v[K];
 #pragma unroll
             for (int m = 0; m < K; ++m) {
-                const int32_t lin = idx[r * idx_stride + m];
-                const int y = lin / g.w, x = lin % g.w;
-                v[m] = g.img[(int64_t)(y + a) * g.stride + (int64_t)(x + b) * g.c + ch];
+                const uint32_t alo = __builtin_amdgcn_readlane((uint32_t)at, m);
+                const uint32_t ahi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)at >> 32), m);
+                v[m] = (g.img + (int64_t)(((uint64_t)ahi << 32) | alo))[px + ch];
             }
 #pragma unroll
             for (int d = 0; d <= K / 2; ++d) {
@@ -528,7 +567,7 @@ __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, 
 }
 
 template <int K>
-__global__ __launch_bounds__(256) void vote_kernel(ImageGeom g, const int32_t *__restrict__ idx, int T, int n_vote,
+__global__ __launch_bounds__(64 * VOTE_WAVES) void vote_kernel(ImageGeom g, const int32_t *__restrict__ idx, int T, int n_vote,
                                                    uint64_t seed, int gamma_rank, double beta,
                                                    const double *__restrict__ sigma_est, double *__restrict__ sigma_hat,
                                                    int32_t *__restrict__ votes) {
@@ -537,7 +576,7 @@ __global__ __launch_bounds__(256) void vote_kernel(ImageGeom g, const int32_t *_
 }
 
 template <int K>
-__global__ __launch_bounds__(256) void vote_kernel_batched(const SigmaItem *__restrict__ items,
+__global__ __launch_bounds__(64 * VOTE_WAVES) void vote_kernel_batched(const SigmaItem *__restrict__ items,
                                                            const int *__restrict__ sel,
                                                            const int *__restrict__ start, int n, int T, int n_vote,
                                                            uint64_t seed, int gamma_rank, double beta) {
@@ -554,6 +593,14 @@ __global__ __launch_bounds__(256) void vote_kernel_batched(const SigmaItem *__re
 }  // namespace
 
 int cov_lds_bytes() { return COV_LDS; }
+
+// Workgroups per (sub-image, channel) of the moments: up to the 8 bands of a full sub-image, as long as
+// all of them run at once (4 per CU by LDS).
+static int mom_parts(int n_units) {
+    int parts = 8;
+    while (parts > 1 && (int64_t)n_units * parts > 1024) parts >>= 1;
+    return parts;
+}
 int sigma_mom_ints() { return MOM_INTS; }
 
 hipError_t launch_sigma2_units(const ImageGeom &g, int tile, int unit0, int n_units, int32_t *mom, double *sigma2,
@@ -563,10 +610,12 @@ hipError_t launch_sigma2_units(const ImageGeom &g, int tile, int unit0, int n_un
     const int lds = cov_lds_bytes();
     hipError_t e = prepare_dynamic_lds((const void *)mom_kernel, lds, 0);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mom_kernel, dim3(n_units), dim3(256), lds, st, g, tile, unit0, mom);
+    const int parts = mom_parts(n_units);
+    if (parts > 1 && (e = launch_zero(mom, sizeof(int32_t) * MOM_INTS * n_units, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(mom_kernel, dim3(n_units * parts), dim3(256), lds, st, g, tile, unit0, parts, mom);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(eig_kernel, dim3((n_units + EIG_WAVES - 1) / EIG_WAVES), dim3(64 * EIG_WAVES), 0, st, g, tile,
-                       unit0, n_units, (const int32_t *)mom, sigma2);
+    hipLaunchKernelGGL(eig_kernel, dim3(n_units), dim3(64 * EIG_WAVES), 0, st, g, tile, unit0, (const int32_t *)mom,
+                       sigma2);
     return hipGetLastError();
 }
 
@@ -592,7 +641,7 @@ hipError_t launch_vote(const ImageGeom &g, const MethodParams &mp, const int32_t
     const int n_tiles = ((g.h + tile - 1) / tile) * ((g.w + tile - 1) / tile);
 #define HV_CASE(KK)                                                                                              \
     if (mp.K == KK) {                                                                                            \
-        hipLaunchKernelGGL(vote_kernel<KK>, dim3(n_tiles), dim3(256), 0, st, g, idx, tile, n_vote, seed, gamma_rank, \
+        hipLaunchKernelGGL(vote_kernel<KK>, dim3(n_tiles), dim3(64 * VOTE_WAVES), 0, st, g, idx, tile, n_vote, seed, gamma_rank, \
                            beta, sigma_est, sigma_hat, votes);                                                   \
         return hipGetLastError();                                                                                \
     }
@@ -608,10 +657,13 @@ hipError_t launch_sigma_est_batched(const SigmaItem *items, const int *sel, cons
     const int lds = cov_lds_bytes();
     hipError_t e = prepare_dynamic_lds((const void *)mom_kernel_batched, lds, 0);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mom_kernel_batched, dim3(total), dim3(256), lds, st, items, sel, start, n, tile, mom);
+    const int parts = mom_parts(total);
+    if (parts > 1 && (e = launch_zero(mom, sizeof(int32_t) * MOM_INTS * total, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(mom_kernel_batched, dim3(total * parts), dim3(256), lds, st, items, sel, start, n, tile, parts,
+                       mom);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(eig_kernel_batched, dim3((total + EIG_WAVES - 1) / EIG_WAVES), dim3(64 * EIG_WAVES), 0, st,
-                       items, sel, start, n, total, tile, (const int32_t *)mom);
+    hipLaunchKernelGGL(eig_kernel_batched, dim3(total), dim3(64 * EIG_WAVES), 0, st, items, sel, start, n, tile,
+                       (const int32_t *)mom);
     return hipGetLastError();
 }
 
@@ -628,7 +680,7 @@ hipError_t launch_vote_batched(int K, const SigmaItem *items, const int *sel, co
     if (n <= 0 || total <= 0) return hipSuccess;
 #define HVB_CASE(KK)                                                                                             \
     if (K == KK) {                                                                                               \
-        hipLaunchKernelGGL(vote_kernel_batched<KK>, dim3(total), dim3(256), 0, st, items, sel, start, n, tile,      \
+        hipLaunchKernelGGL(vote_kernel_batched<KK>, dim3(total), dim3(64 * VOTE_WAVES), 0, st, items, sel, start, n, tile,      \
                            n_vote, seed, gamma_rank, beta);                                                     \
         return hipGetLastError();                                                                                \
     }

@@ -86,3 +86,20 @@ def test_adaptive_known_sigma_denoise_parity(dn, basis3):
     ref = oracle.denoise(noisy, U, V, tau, s=4, W=31, K=32)
     m = assert_pixel_parity(gpu, ref, clean)
     print("adaptive known", m, sig)
+
+
+@pytest.mark.parametrize("h,w,c", [(11, 13, 1), (12, 140, 3), (139, 129, 3), (1030, 1100, 3), (1410, 1500, 3)])
+def test_sigma_est_for_every_split_of_the_moments(dn, h, w, c):
+    """Sub-images of one band of rows, of a cut last band, and images whose sub-images are split over
+    8, 4 and 2 workgroups, at the same bar as the other estimates (1e-9 relative; FP64 rounding of
+    eigenvalues up to 1e6 leaves 1e-10 absolute)."""
+    img = synth.add_awgn(synth.make_clean(h, w, c, 7), 20.0, 8)
+    n = ((h + 127) // 128) * ((w + 127) // 128)
+    est = torch.empty(n, dtype=torch.float64, device="cuda")
+    import paper_2512_23569_amd as ht
+    d = torch.from_numpy(np.ascontiguousarray(img)).cuda()
+    ht.htsvd_estimate_sigma(dn.ctx, d, h, w, c, w * c, -1.0, dn.params(c, K=4, window=9), d_sigma_est=est)
+    tiles = sorted({0, n // 3, n - 1})
+    ref = oracle.sigma_est_tiles(img, tiles=tiles)
+    got = est.cpu().numpy()
+    assert np.all(np.abs(got[tiles] - ref[tiles]) <= 1e-9 * ref[tiles] + 1e-10)
