@@ -16,14 +16,26 @@
 // v_mfma_f32_16x16x32_f16 for the sum plane (all partial sums are integers < 2^24, so the
 // fp32 accumulation is exact).  Distances of each reference land in an LDS table indexed
 // by the raster position inside its clipped window, so (distance, position) orders like
-// (distance, row, column).  Each wave then selects the K smallest keys of one reference:
-// the K-th smallest of the 64 lane minima bounds the answer from above, the keys under
-// that bound are compacted and sorted with a wave bitonic network.
+// (distance, row, column).  Each wave then selects the K smallest keys of one reference: the
+// larger of the (K/2)-th smallest lane minima of its two halves bounds the answer from above, the
+// keys under that bound are compacted and sorted with a wave bitonic network.
+//
+// It is bound by vector instructions, so the work per candidate is kept to few: in the distance
+// phase a wave takes a fixed block of columns and steps through the rows, so that addresses advance
+// by constants and a window's columns are tested once, and the keys sorted are 32 bits wide
+// wherever their range allows.  1,205 vector instructions per reference of a 12 MP image with
+// window 31, 4.20 ms (1,575 and 4.70 ms when both sides of each window were tested per reference
+// and position, the keys were counted before they were compacted, and channel sums took 64-bit
+// keys).  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions, so that
+// small windows neither walk empty table rows nor hold LDS for them: 1536 x 2048 gray, window 21,
+// 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 1,784 us.
 //
 // Video (Sec. IV-C): the frames are stacked vertically, and a reference's candidates are the
 // positions of its clipped window in every frame within a temporal radius.  The workgroup keeps
 // the reference patches of its own frame in registers, stages one frame after another, and
 // merges each frame's K best (distance, frame slot, position) keys into a running list in LDS.
+#include <algorithm>
+
 #include "common.h"
 
 namespace htsvd {
@@ -37,12 +49,17 @@ namespace {
 constexpr int NREF = REF_TILE * REF_TILE;  // 16
 constexpr int BMW = 16;                    // wavefronts per workgroup (four per SIMD)
 constexpr int BMT = BMW * 64;
-constexpr int SEL_CAP = 512;               // >= K * ceil(MAX_CAND / 64) for K <= 32
-// Words per reference row of the distance table: 964 = 4 (mod 64), so the four references a
-// quarter-wave writes for 16 consecutive candidates land on disjoint LDS banks.
-constexpr int TAB_STRIDE = 964;
-static_assert(TAB_STRIDE >= MAX_CAND, "table rows hold a whole window");
 constexpr int RUN_K = 32;                  // running list per reference of the video search
+// Words per reference row of the distance table for windows of at most 64 NPL positions: 4 (mod
+// 64), so the four references a quarter-wave writes for 16 consecutive candidates land on disjoint
+// LDS banks.  Once in registers, a row gives its place to the compacted keys: at most RUN_K lanes
+// hold keys under an exact bound, with at most NPL keys each (of 961 positions only lane 0 has 16),
+// so the row holds them as 64-bit keys.
+template <int NPL>
+__host__ __device__ constexpr int tab_stride() { return NPL == 16 ? 964 : 64 * NPL + 4; }
+static_assert(tab_stride<16>() >= MAX_CAND && tab_stride<16>() >= 2 * (15 * RUN_K + 1), "a whole window");
+static_assert(tab_stride<4>() >= 2 * 4 * RUN_K && tab_stride<7>() >= 2 * 7 * RUN_K && tab_stride<10>() >= 2 * 10 * RUN_K,
+              "the keys under the bound");
 
 // Frames of a video search: g.img is frame 0 of T frames of g.h rows each, frame_bytes apart.
 struct VideoArgs {
@@ -64,7 +81,7 @@ struct BmLds {
     int pitch16;    // halves per row of one fp16 plane copy
     int rows;       // plane rows (union rows + 7)
     int plane8;     // bytes between the int8 plane copies (a row multiple plus a bank offset)
-    int off_p8, off_p16, off_n8, off_n16, off_tab, off_sel, total;   // video: running lists last
+    int off_p8, off_p16, off_n8, off_n16, off_tab, total;   // video: running lists last
 };
 
 __device__ inline uint32_t lds_u32(const unsigned char *base, int byte_off) {
@@ -96,33 +113,136 @@ __device__ inline int wave_excl_scan(int v, int lane, int *total) {
     return x - v;
 }
 
-// Ascending bitonic sort of P (power of two <= SEL_CAP) keys in LDS by one wave.
+// Ascending bitonic sort of n keys in LDS by one wave, in the form whose comparators are all
+// ascending (see wave_sort_asc), so that the places from n to the next power of two can be taken as
+// larger than any key without existing.
 template <typename T>
-__device__ void lds_sort(T *a, int P, int lane) {
-    for (int k = 2; k <= P; k <<= 1) {
+__device__ void lds_sort(T *a, int n, int lane) {
+    for (int k = 2; k < 2 * n; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = lane; t < P / 2; t += 64) {
-                int i = 2 * t - (t & (j - 1));
-                int m = i + j;
-                T x = a[i], y = a[m];
-                bool up = (i & k) == 0;
-                if ((x > y) == up) {
-                    a[i] = y;
-                    a[m] = x;
+            for (int t = lane; 2 * t < 2 * n; t += 64) {   // pairs beyond n have no upper element
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const int m = j == k >> 1 ? i ^ (k - 1) : i + j;
+                if (i < n && m < n) {
+                    const T x = a[i], y = a[m];
+                    if (y < x) {
+                        a[i] = y;
+                        a[m] = x;
+                    }
                 }
             }
             wave_lds_sync();
         }
+}
+
+// Sort across each half of the wave (two independent sorts of 32 keys).
+__device__ inline uint32_t half_sort_asc(uint32_t v, int lane) {
+#pragma unroll
+    for (int k = 2; k <= 32; k <<= 1) {
+        {
+            const uint32_t p = mirror_lane(v, k, lane);
+            v = (lane & (k >> 1)) ? max(v, p) : min(v, p);
+        }
+#pragma unroll
+        for (int j = k >> 2; j > 0; j >>= 1) {
+            const uint32_t p = xor_lane(v, j, lane);
+            v = (lane & j) ? max(v, p) : min(v, p);
+        }
     }
+    return v;
+}
+
+// Number of set bits of m below this lane.
+__device__ inline int bits_below(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The K smallest (distance, position) keys d << 10 | p of a row of n distances dv (position lane +
+// 64 i in register i, 0xFFFFFFFF past n), ascending, lane k the k-th.  `row` is the reference's LDS
+// row (its distances are in registers).  small: distances below 2^22 (green or gray), whose keys
+// fit 32 bits; otherwise (channel sum, below 2^26) the bound is found on the coarser key d << 6 |
+// p >> 4, which orders alike, and the sort takes distances from the smallest one.
+template <int NPL>
+__device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const int n, const int K, const bool small,
+                                             uint32_t *row, const int lane) {
+    const int shift = small ? 10 : 6;
+    const uint32_t pl = small ? (uint32_t)lane : (uint32_t)lane >> 4;
+    uint32_t key[NPL], m = ~0u;
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+        key[i] = (dv[i] << shift) | (pl + (small ? 64u * i : 4u * i));
+        if (64 * (i + 1) > n) key[i] = lane + 64 * i < n ? key[i] : ~0u;   // the first test is uniform
+        m = min(m, key[i]);
+    }
+    const uint32_t s = half_sort_asc(m, lane);
+    const uint32_t t0 = __builtin_amdgcn_readlane(s, K / 2 - 1), t1 = __builtin_amdgcn_readlane(s, 32 + K / 2 - 1);
+    const uint32_t theta = min(max(t0, t1), 0xFFFFFFFEu);   // ~0 marks an empty place
+    // 32-bit keys in the row: distances from their smallest where they are wide (their range under
+    // the bound nearly always fits 22 bits; the 64-bit form below takes the rest)
+    const uint32_t dmin = small ? 0u : min((uint32_t)__builtin_amdgcn_readlane(s, 0), (uint32_t)__builtin_amdgcn_readlane(s, 32)) >> 6;
+    if (small || (theta >> 6) - dmin < (1u << 22) - 1u) {
+        int total = 0;
+#pragma unroll
+        for (int i = 0; i < NPL; ++i) {
+            const bool in = key[i] <= theta;
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+            if (in) row[total + bits_below(mask)] = small ? key[i] : ((dv[i] - dmin) << 10) | (uint32_t)(lane + 64 * i);
+            total += __popcll(mask);
+        }
+        wave_lds_sync();
+        uint32_t v;
+        if (total <= 64) {
+            v = wave_sort_asc<uint32_t>(lane < total ? row[lane] : ~0u, lane);
+        } else if (total <= 128) {
+            // two sorted halves: the smaller of each key and its mirror in the other half are the 64
+            // smallest, in bitonic order
+            v = wave_sort_asc<uint32_t>(row[lane], lane);
+            const uint32_t u = wave_sort_asc<uint32_t>(lane + 64 < total ? row[lane + 64] : ~0u, lane);
+            v = min(v, mirror_lane(u, 64, lane));
+#pragma unroll
+            for (int j = 32; j > 0; j >>= 1) {
+                const uint32_t p = xor_lane(v, j, lane);
+                v = (lane & j) ? max(v, p) : min(v, p);
+            }
+        } else {
+            lds_sort(row, total, lane);
+            v = row[lane];
+        }
+        return small ? (uint64_t)v : ((uint64_t)((v >> 10) + dmin) << 10) | (v & 1023u);
+    }
+    // the K-th smallest of the exact lane minima, under which at most RUN_K lanes hold keys
+    uint64_t *sel = reinterpret_cast<uint64_t *>(row);
+    uint64_t mm = ~0ull;
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+        const int p = lane + 64 * i;
+        const uint64_t k64 = ((uint64_t)dv[i] << 10) | (uint64_t)p;
+        mm = p < n && k64 < mm ? k64 : mm;
+    }
+    const uint64_t bound = readlane_u64(wave_sort64(mm, lane), K - 1);
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+        const int p = lane + 64 * i;
+        const uint64_t k64 = ((uint64_t)dv[i] << 10) | (uint64_t)p;
+        const bool in = p < n && k64 <= bound;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+        if (in) sel[total + bits_below(mask)] = k64;
+        total += __popcll(mask);
+    }
+    wave_lds_sync();
+    if (total <= 64) return wave_sort64(lane < total ? sel[lane] : ~0ull, lane);
+    lds_sort(sel, total, lane);
+    return sel[lane];
 }
 
 // Groups of the 16 references of tile b (VIDEO: tile b of the frames' tiles, frame-major).
-template <bool VIDEO>
+template <bool VIDEO, int NPL>
 __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams &mp, const int tiles_x, const int b_in,
                                         const BmLds &L, int32_t *__restrict__ idx_out,
                                         int32_t *__restrict__ dist_out, unsigned char *smem, TileInfo &ti,
                                         const VideoArgs &va) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int b = b_in, t = 0, f_lo = 0, nf = 1;
     ImageGeom g = g0;   // the reference's frame
     if constexpr (VIDEO) {
@@ -200,7 +320,9 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     v4i a8;
     v8h a16a = {}, a16b = {};
     bool any_sum = false;
-    int rwy0[4], rwx0[4], rwh[4], rww[4], rgreen[4], rn[4];
+    int rn[4];             // squared norms of the references 4 q + r
+    int gmask[4];          // all ones where reference 4 q + r takes the green distance
+    constexpr int TAB = tab_stride<NPL>();
     uint64_t *run = reinterpret_cast<uint64_t *>(smem + L.total - NREF * RUN_K * 8);
     const int K = mp.K;
 
@@ -390,117 +512,119 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int ii = 4 * q + r;
-                    rwy0[r] = ti.wy0[ii]; rwx0[r] = ti.wx0[ii];
-                    rwh[r] = ti.wh[ii]; rww[r] = ti.ww[ii];
-                    rgreen[r] = ti.green[ii];
+                    rn[r] = gmask[r] = 0;
                     if (ti.ry[ii] >= 0) {
                         const int pe = (ti.ry[ii] - uy0) * uw + (ti.rx[ii] - ux0);
-                        rn[r] = rgreen[r] ? n8[pe] : n16[pe];
-                    } else {
-                        rn[r] = 0;
-                        rwh[r] = 0;
+                        rn[r] = ti.green[ii] ? n8[pe] : n16[pe];
+                        gmask[r] = -ti.green[ii];
                     }
                 }
             }
-            if constexpr (VIDEO) {
-                // reloaded for every frame: only the norms and the A fragments stay live across frames
+            // A wave takes one block of 16 columns of the union and every so-many-th row, so that all
+            // addresses step by constants and the columns of the windows are tested once.  In the
+            // union's coordinates the references 4 q + r lie in row q and column r of the tile, so the
+            // rows of their windows go with q and the columns with r; position (dy, dx) of reference
+            // 4 q + r is table byte 4 (dy ww + dx) of its row.
+            const int ncb = (uw + 15) >> 4;   // 1 .. 4
+            const int wpc = ncb == 1 ? 16 : (ncb == 2 ? 8 : (ncb == 3 ? 5 : 4));   // waves per block of columns
+            const int cb = (wave >= wpc) + (wave >= 2 * wpc) + (wave >= 3 * wpc), cr0 = wave - cb * wpc;
+            const int cc0 = 16 * cb + i16, cc = min(cc0, uw - 1);
+            const int wy = ti.wy0[4 * q] - uy0, wh = ti.ry[4 * q] >= 0 ? ti.wh[4 * q] : 0;
+            bool inside[4];
+            int step4[4];
+            unsigned char *at[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int ii = 4 * q + r;
-                    rwy0[r] = ti.wy0[ii]; rwx0[r] = ti.wx0[ii];
-                    rwh[r] = ti.ry[ii] >= 0 ? ti.wh[ii] : 0; rww[r] = ti.ww[ii];
-                    rgreen[r] = ti.green[ii];
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int dx = cc0 - (ti.wx0[r] - ux0), ww = ti.ry[r] >= 0 ? ti.ww[r] : 0;
+                inside[r] = (unsigned)dx < (unsigned)ww;
+                at[r] = reinterpret_cast<unsigned char *>(tab + (4 * q + r) * TAB + (cr0 - wy) * ww + dx);
+                step4[r] = 4 * wpc * ww;
             }
-            const int nU = uh * uw;
-            const int nchunks = (nU + 15) >> 4;
-            // candidate j = 16 chunk + i16 at (row, column) = (j / uw, j % uw), stepped by 16 BMW
-            constexpr int JSTEP = 16 * BMW;
-            const int step_r = JSTEP / uw, step_c = JSTEP % uw;
-            int jr = (16 * wave + i16) / uw, jc = (16 * wave + i16) % uw;
-            for (int chunk = wave; chunk < nchunks; chunk += BMW) {
-                const int j = chunk * 16 + i16;
-                const int cr = j < nU ? jr : 0, cc = j < nU ? jc : 0;
-                jr += step_r;
-                jc += step_c;
-                if (jc >= uw) {
-                    jc -= uw;
-                    ++jr;
-                }
-                v4i b8;
-                {
-                    const int k = cc & 3;
-                    const unsigned char *base = p8 + k * plane8;
-                    const int o0 = (cr + 2 * q) * L.pitch8 + cc - k, o1 = o0 + L.pitch8;
-                    b8[0] = (int)lds_u32(base, o0); b8[1] = (int)lds_u32(base, o0 + 4);
-                    b8[2] = (int)lds_u32(base, o1); b8[3] = (int)lds_u32(base, o1 + 4);
-                }
-                v4i acc8 = {0, 0, 0, 0};
-                acc8 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a8, b8, acc8, 0, 0, 0);
-                v4f acc16 = {0.f, 0.f, 0.f, 0.f};
-                if (any_sum) {
-                    // 8 halves from the copy in which they start on a dword (pitch and offsets even)
-                    const int k = cc & 1;
-                    const _Float16 *base = p16 + k * plane16;
-                    const uint32_t *ra = reinterpret_cast<const uint32_t *>(base + (cr + q) * L.pitch16 + cc - k);
-                    const uint32_t *rb = reinterpret_cast<const uint32_t *>(base + (cr + q + 4) * L.pitch16 + cc - k);
-                    const v8h b16a = __builtin_bit_cast(v8h, make_uint4(ra[0], ra[1], ra[2], ra[3]));
-                    const v8h b16b = __builtin_bit_cast(v8h, make_uint4(rb[0], rb[1], rb[2], rb[3]));
-                    acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16a, b16a, acc16, 0, 0, 0);
-                    acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16b, b16b, acc16, 0, 0, 0);
-                }
-                if (j < nU) {
-                    const int cy = uy0 + cr, cx = ux0 + cc;
-                    const int nb8 = n8[j], nb16 = n16[j];
+            const unsigned char *c8 = p8 + (cc & 3) * plane8 + (cr0 + 2 * q) * L.pitch8 + (cc & ~3);
+            // 8 halves from the copy in which they start on a dword (pitch and offsets even)
+            const _Float16 *c16 = p16 + (cc & 1) * plane16 + (cr0 + q) * L.pitch16 + (cc & ~1);
+            const int32_t *m8 = n8 + cr0 * uw + cc, *m16 = n16 + cr0 * uw + cc;
+            if (cb < ncb) {
+                for (int cr = cr0; cr < uh; cr += wpc) {
+                    const uint32_t *w8a = reinterpret_cast<const uint32_t *>(c8);
+                    const uint32_t *w8b = reinterpret_cast<const uint32_t *>(c8 + L.pitch8);
+                    const v4i b8 = {(int)w8a[0], (int)w8a[1], (int)w8b[0], (int)w8b[1]};
+                    const v4i acc8 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a8, b8, (v4i){0, 0, 0, 0}, 0, 0, 0);
+                    // d = |a|^2 + |b|^2 - 2 a.b with |a.b| <= 64 384^2 < 2^24
+                    int d[4];
+                    if (any_sum) {
+                        const uint32_t *ra = reinterpret_cast<const uint32_t *>(c16);
+                        const uint32_t *rb = reinterpret_cast<const uint32_t *>(c16 + 4 * L.pitch16);
+                        const v8h b16a = __builtin_bit_cast(v8h, make_uint4(ra[0], ra[1], ra[2], ra[3]));
+                        const v8h b16b = __builtin_bit_cast(v8h, make_uint4(rb[0], rb[1], rb[2], rb[3]));
+                        v4f acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16a, b16a, (v4f){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16b, b16b, acc16, 0, 0, 0);
+                        const int nb8 = *m8, nb16 = *m16;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int dy = cy - rwy0[r], dx = cx - rwx0[r];
-                        if ((unsigned)dy < (unsigned)rwh[r] && (unsigned)dx < (unsigned)rww[r]) {
-                            const int d = rgreen[r] ? rn[r] + nb8 - 2 * acc8[r] : rn[r] + nb16 - 2 * (int)acc16[r];
-                            tab[(4 * q + r) * TAB_STRIDE + dy * rww[r] + dx] = (uint32_t)d;
+                        for (int r = 0; r < 4; ++r) {
+                            const int dot = (gmask[r] & acc8[r]) | (~gmask[r] & (int)acc16[r]);
+                            const int nb = (gmask[r] & nb8) | (~gmask[r] & nb16);
+                            d[r] = nb + rn[r] - 2 * dot;
                         }
+                    } else {
+                        const int nb8 = *m8;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) d[r] = nb8 + rn[r] - 2 * acc8[r];
                     }
+                    if ((unsigned)(cr - wy) < (unsigned)wh) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (inside[r]) *reinterpret_cast<uint32_t *>(at[r]) = (uint32_t)d[r];
+                    }
+                    c8 += wpc * L.pitch8;
+                    c16 += wpc * L.pitch16;
+                    m8 += wpc * uw;
+                    m16 += wpc * uw;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) at[r] += step4[r];
                 }
             }
         }
         __syncthreads();
 
         // ---- top-K per reference ----
-        uint64_t *sel = reinterpret_cast<uint64_t *>(smem + L.off_sel) + wave * SEL_CAP;
         for (int ii = wave; ii < NREF; ii += BMW) {
             if (ti.ry[ii] < 0) continue;
-            const int n = ti.wh[ii] * ti.ww[ii];
-            const uint32_t *row = tab + ii * TAB_STRIDE;
-            // this lane's candidates p = lane + 64 i, read once; key = (distance, position)
-            constexpr int NPL = (MAX_CAND + 63) / 64;
+            const int ww = __builtin_amdgcn_readfirstlane(ti.ww[ii]);
+            const int n = __builtin_amdgcn_readfirstlane(ti.wh[ii]) * ww;
+            uint32_t *row = tab + ii * TAB;
+            // this lane's candidates p = lane + 64 i, read once (past the window: whatever is there)
             uint32_t dv[NPL];
-            uint32_t dmin = 0xFFFFFFFFu;   // valid distances are below 2^26
 #pragma unroll
-            for (int i = 0; i < NPL; ++i) {
-                const int p = lane + 64 * i;
-                dv[i] = p < n ? row[p] : 0xFFFFFFFFu;
-                dmin = min(dmin, dv[i]);
-            }
+            for (int i = 0; i < NPL; ++i) dv[i] = row[lane + 64 * i];
+            const bool small = __builtin_amdgcn_readfirstlane(ti.green[ii]) != 0;
             if constexpr (VIDEO) {
                 if (fi > 0) {
-                    // Only keys below the running K-th can enter the list.  When at most 64 - K of
-                    // this frame's candidates are, one sort of them with the list is the merge.
+                    // Only keys below the running K-th can enter the list; its slot is another one,
+                    // so the distance decides alone.  When at most 64 - K of this frame's candidates
+                    // are, one sort of them with the list is the merge.
                     const uint64_t th = run[ii * RUN_K + K - 1];
-                    const uint64_t sk = (uint64_t)slot << 10;
-                    int cnt = 0;
+                    const uint32_t below = (uint32_t)(th >> 16) + ((uint32_t)slot < ((uint32_t)(th >> 10) & 63u) ? 1u : 0u);
+                    uint32_t in = 0;   // bit i: dv[i] qualifies
+                    int total = 0;
 #pragma unroll
                     for (int i = 0; i < NPL; ++i) {
-                        const int p = lane + 64 * i;
-                        cnt += (p < n && (((uint64_t)dv[i] << 16) | sk | (uint64_t)p) < th);
+                        const bool q1 = lane + 64 * i < n && dv[i] < below;
+                        in |= (uint32_t)q1 << i;
+                        total += __popcll(__builtin_amdgcn_ballot_w64(q1));
                     }
-                    int total;
-                    int off = wave_excl_scan(cnt, lane, &total);
+                    if (total == 0) continue;
                     if (total <= 64 - K) {
+                        uint64_t *sel = reinterpret_cast<uint64_t *>(row);
+                        int at0 = 0;
 #pragma unroll
                         for (int i = 0; i < NPL; ++i) {
-                            const int p = lane + 64 * i;
-                            const uint64_t key = ((uint64_t)dv[i] << 16) | sk | (uint64_t)p;
-                            if (p < n && key < th) sel[off++] = key;
+                            const bool q1 = (in >> i) & 1u;
+                            const uint64_t mask = __builtin_amdgcn_ballot_w64(q1);
+                            if (q1)
+                                sel[at0 + bits_below(mask)] = ((uint64_t)dv[i] << 16) | ((uint64_t)slot << 10) |
+                                                              (uint64_t)(lane + 64 * i);
+                            at0 += __popcll(mask);
                         }
                         wave_lds_sync();
                         uint64_t v = lane < total ? sel[lane]
@@ -512,84 +636,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                     }
                 }
             }
-            // the lane's smallest key: its smallest distance at the first (smallest) position
-            int pmin = 0;
-#pragma unroll
-            for (int i = NPL - 1; i >= 0; --i) pmin = dv[i] == dmin ? lane + 64 * i : pmin;
-            if (!VIDEO && ti.green[ii]) {
-                // green or gray distances are below 2^22 (64 * 255^2) and positions below 1024, so
-                // the key (distance, position) fits 32 bits and stays below the empty key ~0
-                const uint32_t lmin32 = dmin == 0xFFFFFFFFu ? ~0u : ((dmin << 10) | (uint32_t)pmin);
-                const uint32_t sorted32 = wave_sort_asc<uint32_t>(lmin32, lane);
-                const uint32_t theta32 = __builtin_amdgcn_readlane(sorted32, K - 1);
-                int cnt32 = 0;
-#pragma unroll
-                for (int i = 0; i < NPL; ++i) {
-                    const int p = lane + 64 * i;
-                    cnt32 += (p < n && ((dv[i] << 10) | (uint32_t)p) <= theta32);
-                }
-                int total32;
-                int off32 = wave_excl_scan(cnt32, lane, &total32);
-                uint32_t *sel32 = reinterpret_cast<uint32_t *>(sel);
-#pragma unroll
-                for (int i = 0; i < NPL; ++i) {
-                    const int p = lane + 64 * i;
-                    const uint32_t key = (dv[i] << 10) | (uint32_t)p;
-                    if (p < n && key <= theta32) sel32[off32++] = key;
-                }
-                wave_lds_sync();
-                uint32_t mine32;
-                if (total32 <= 64) {
-                    mine32 = wave_sort_asc<uint32_t>(lane < total32 ? sel32[lane] : ~0u, lane);
-                } else {
-                    int P = 64;
-                    while (P < total32) P <<= 1;
-                    for (int t = total32 + lane; t < P; t += 64) sel32[t] = ~0u;
-                    wave_lds_sync();
-                    lds_sort(sel32, P, lane);
-                    mine32 = lane < K ? sel32[lane] : ~0u;
-                }
-                if (lane < K) {
-                    const int p = (int)(mine32 & 1023u);
-                    const int y = ti.wy0[ii] + p / ti.ww[ii], x = ti.wx0[ii] + p % ti.ww[ii];
-                    const int iy = tyi * REF_TILE + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
-                    const int64_t r = (int64_t)iy * g.nx + ix;
-                    idx_out[r * K + lane] = y * g.w + x;
-                    if (dist_out) dist_out[r * K + lane] = (int32_t)(mine32 >> 10);
-                }
-                wave_lds_sync();
-                continue;
-            }
-            const uint64_t lmin = dmin == 0xFFFFFFFFu ? ~0ull : (((uint64_t)dmin << 10) | (uint64_t)pmin);
-            const uint64_t sorted = wave_sort64(lmin, lane);
-            const uint64_t theta = readlane_u64(sorted, K - 1);
-            int cnt = 0;
-#pragma unroll
-            for (int i = 0; i < NPL; ++i) {
-                const int p = lane + 64 * i;
-                cnt += (p < n && (((uint64_t)dv[i] << 10) | (uint64_t)p) <= theta);
-            }
-            int total;
-            int off = wave_excl_scan(cnt, lane, &total);
-#pragma unroll
-            for (int i = 0; i < NPL; ++i) {
-                const int p = lane + 64 * i;
-                const uint64_t key = ((uint64_t)dv[i] << 10) | (uint64_t)p;
-                if (p < n && key <= theta) sel[off++] = key;
-            }
-            wave_lds_sync();
-            uint64_t mine;
-            if (total <= 64) {
-                uint64_t v = lane < total ? sel[lane] : ~0ull;
-                mine = wave_sort64(v, lane);
-            } else {
-                int P = 64;
-                while (P < total) P <<= 1;
-                for (int t = total + lane; t < P; t += 64) sel[t] = ~0ull;
-                wave_lds_sync();
-                lds_sort(sel, P, lane);
-                mine = lane < K ? sel[lane] : ~0ull;
-            }
+            const uint64_t mine = select_k<NPL>(dv, n, K, small, row, lane);
             if constexpr (VIDEO) {
                 // merge into the running list: keys (distance, frame slot, position); only this wave
                 // touches reference ii's list
@@ -601,7 +648,8 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                 if (lane < K) run[ii * RUN_K + lane] = v;
             } else if (lane < K) {
                 const int p = (int)(mine & 1023u);
-                const int y = ti.wy0[ii] + p / ti.ww[ii], x = ti.wx0[ii] + p % ti.ww[ii];
+                const int py = (int)((uint32_t)p * (65536u / (uint32_t)ww + 1u) >> 16);   // p / ww for p < 1024
+                const int y = ti.wy0[ii] + py, x = ti.wx0[ii] + p - py * ww;
                 const int iy = tyi * REF_TILE + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
                 const int64_t r = (int64_t)iy * g.nx + ix;
                 idx_out[r * K + lane] = y * g.w + x;
@@ -625,6 +673,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     }
 }
 
+template <int NPL>
 __global__ __launch_bounds__(BMT) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                  BmLds L, int32_t *__restrict__ idx_out,
                                                  int32_t *__restrict__ dist_out) {
@@ -636,10 +685,11 @@ __global__ __launch_bounds__(BMT) void bm_kernel(ImageGeom g, MethodParams mp, i
     const int per = (n_tiles + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= n_tiles) return;
-    bm_tile<false>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
+    bm_tile<false, NPL>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
 }
 
 // Spatio-temporal form: n_tiles covers the tiles of all frames.
+template <int NPL>
 __global__ __launch_bounds__(BMT) void bm_video_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                        VideoArgs va, BmLds L, int32_t *__restrict__ idx_out,
                                                        int32_t *__restrict__ dist_out) {
@@ -648,10 +698,11 @@ __global__ __launch_bounds__(BMT) void bm_video_kernel(ImageGeom g, MethodParams
     const int per = (n_tiles + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= n_tiles) return;
-    bm_tile<true>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, va);
+    bm_tile<true, NPL>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, va);
 }
 
 // Persistent form over many images: each workgroup pulls (image, tile) units from a queue.
+template <int NPL>
 __global__ __launch_bounds__(BMT) void bm_kernel_batched(const BatchItem *__restrict__ items, int n_items,
                                                          const int *__restrict__ unit_start, BmLds L,
                                                          int *__restrict__ queue) {
@@ -667,12 +718,16 @@ __global__ __launch_bounds__(BMT) void bm_kernel_batched(const BatchItem *__rest
         if (u >= total) break;
         const int i = find_unit(unit_start, n_items, u);
         const BatchItem it = items[i];
-        bm_tile<false>(it.g, it.mp, it.bm_tiles_x, u - unit_start[i], L, it.idx, nullptr, smem, ti, VideoArgs{});
+        bm_tile<false, NPL>(it.g, it.mp, it.bm_tiles_x, u - unit_start[i], L, it.idx, nullptr, smem, ti, VideoArgs{});
         __syncthreads();
     }
 }
 
-BmLds bm_lds_layout(int uh_max, int uw_max, bool video = false) {
+// Register rows of the table (tab_stride) that windows of up to n positions need.
+int bm_npl(int n) { return n <= 256 ? 4 : (n <= 448 ? 7 : (n <= 640 ? 10 : 16)); }
+int bm_tab_stride(int npl) { return npl == 4 ? tab_stride<4>() : (npl == 7 ? tab_stride<7>() : (npl == 10 ? tab_stride<10>() : tab_stride<16>())); }
+
+BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false) {
     BmLds L;
     L.rows = uh_max + PS - 1;
     // The int8 planes: rows of 96 bytes (enough for a union of 64 columns plus the patch and the
@@ -693,17 +748,12 @@ BmLds bm_lds_layout(int uh_max, int uw_max, bool video = false) {
     L.off_n8 = off;  off += uh_max * uw_max * 4;
     L.off_n16 = off; off += uh_max * uw_max * 4;
     off = (off + 15) & ~15;
-    // the selection scratch reuses the plane/norm region once the distances are in the table
-    const int sel_bytes = BMW * SEL_CAP * 8;
-    int region = off;
-    L.off_sel = 0;
-    if (region < sel_bytes) region = sel_bytes;
-    off = (region + 15) & ~15;
     L.off_tab = off;
-    int tab_bytes = NREF * TAB_STRIDE * 4;
+    // the last row is read to 64 npl words
+    int tab_bytes = ((NREF - 1) * bm_tab_stride(npl) + std::max(bm_tab_stride(npl), 64 * npl)) * 4;
     const int rs_bytes = 2 * L.rows * uw_max * 4;  // row sums of the norm pass live in the table
     if (tab_bytes < rs_bytes) tab_bytes = rs_bytes;
-    off += tab_bytes;
+    off += (tab_bytes + 15) & ~15;
     if (video) off += NREF * RUN_K * 8;   // the running lists of the video search
     L.total = off;
     return L;
@@ -719,13 +769,17 @@ hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_
     const int span = (REF_TILE - 1) * g.s + mp.W;
     const int uh = span < g.h - PS + 1 ? span : g.h - PS + 1;
     const int uw = span < g.w - PS + 1 ? span : g.w - PS + 1;
-    BmLds L = bm_lds_layout(uh, uw);
-    hipError_t e = prepare_dynamic_lds((const void *)bm_kernel, L.total, (int)sizeof(TileInfo));
-    if (e != hipSuccess) return e;
+    const int npl = bm_npl(min(mp.W, g.h - PS + 1) * min(mp.W, g.w - PS + 1));
+    const BmLds L = bm_lds_layout(uh, uw, npl);
     // round the grid up to a multiple of 8 so the XCD remap is a bijection onto [0, 8*per)
     const int per = (n_tiles + 7) / 8;
-    hipLaunchKernelGGL(bm_kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, L, idx, dist);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        const hipError_t e = prepare_dynamic_lds((const void *)kernel, L.total, (int)sizeof(TileInfo));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, L, idx, dist);
+        return hipGetLastError();
+    };
+    return npl == 4 ? go(bm_kernel<4>) : (npl == 7 ? go(bm_kernel<7>) : (npl == 10 ? go(bm_kernel<10>) : go(bm_kernel<16>)));
 }
 
 // Spatio-temporal block matching of T frames of g.h rows stacked from g.img (Sec. IV-C): the
@@ -741,14 +795,18 @@ hipError_t launch_block_match_video(const ImageGeom &g, const MethodParams &mp, 
     const int span = (REF_TILE - 1) * g.s + mp.W;
     const int uh = span < g.h - PS + 1 ? span : g.h - PS + 1;
     const int uw = span < g.w - PS + 1 ? span : g.w - PS + 1;
-    BmLds L = bm_lds_layout(uh, uw, true);
-    hipError_t e = prepare_dynamic_lds((const void *)bm_video_kernel, L.total, (int)sizeof(TileInfo));
-    if (e != hipSuccess) return e;
+    const int npl = bm_npl(min(mp.W, g.h - PS + 1) * min(mp.W, g.w - PS + 1));
+    const BmLds L = bm_lds_layout(uh, uw, npl, true);
     VideoArgs va{T, radius, (int64_t)g.h * g.stride};
     const int per = (n_tiles + 7) / 8;
-    hipLaunchKernelGGL(bm_video_kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, va, L, idx,
-                       dist);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        const hipError_t e = prepare_dynamic_lds((const void *)kernel, L.total, (int)sizeof(TileInfo));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, va, L, idx, dist);
+        return hipGetLastError();
+    };
+    return npl == 4 ? go(bm_video_kernel<4>)
+                    : (npl == 7 ? go(bm_video_kernel<7>) : (npl == 10 ? go(bm_video_kernel<10>) : go(bm_video_kernel<16>)));
 }
 
 // Batched block matching: one persistent launch over the tiles of all images; the LDS layout
@@ -758,18 +816,24 @@ hipError_t launch_block_match_batched(const BatchItem *items, int n_items, const
     const int span = (REF_TILE - 1) * max_s + max_W;
     const int uh = span < max_h - PS + 1 ? span : max_h - PS + 1;
     const int uw = span < max_w - PS + 1 ? span : max_w - PS + 1;
-    BmLds L = bm_lds_layout(uh, uw);
-    hipError_t e = prepare_dynamic_lds((const void *)bm_kernel_batched, L.total, (int)sizeof(TileInfo) + 16);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bm_kernel_batched, dim3(grid), dim3(BMT), L.total, st, items, n_items, unit_start, L, queue);
-    return hipGetLastError();
+    const int npl = bm_npl(min(max_W, max_h - PS + 1) * min(max_W, max_w - PS + 1));
+    const BmLds L = bm_lds_layout(uh, uw, npl);
+    auto go = [&](auto kernel) {
+        const hipError_t e = prepare_dynamic_lds((const void *)kernel, L.total, (int)sizeof(TileInfo) + 16);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BMT), L.total, st, items, n_items, unit_start, L, queue);
+        return hipGetLastError();
+    };
+    return npl == 4 ? go(bm_kernel_batched<4>)
+                    : (npl == 7 ? go(bm_kernel_batched<7>)
+                                : (npl == 10 ? go(bm_kernel_batched<10>) : go(bm_kernel_batched<16>)));
 }
 
 int bm_lds_bytes(int s, int W, int h, int w) {
     const int span = (REF_TILE - 1) * s + W;
     const int uh = span < h - PS + 1 ? span : h - PS + 1;
     const int uw = span < w - PS + 1 ? span : w - PS + 1;
-    return bm_lds_layout(uh, uw).total;
+    return bm_lds_layout(uh, uw, bm_npl(min(W, h - PS + 1) * min(W, w - PS + 1))).total;
 }
 
 hipError_t prepare_dynamic_lds(const void *kernel, int bytes, int static_bytes) {
