@@ -2284,13 +2284,13 @@ htsvd_status htsvd_denoise_bands(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
     bm.frag_inv = bm.frag_fwd + (size_t)(bands / 2 + 1) * 512;
     {
         StageScope sc(ctx, HTSVD_STAGE_FILTER, st);
-        if ((e = launch_band_filter(bm, d_in, in_stride, h, w, bands, idx, n_ref, mp.K, s_lo * mult, ctx->band_cap,
-                                    (char *)ctx->ws + off_ws, d_out, out_stride, st)) != hipSuccess)
+        if ((e = launch_band_filter(bm, d_in, in_stride, h, w, bands, idx, g.s, mp.W, mp.K, s_lo * mult,
+                                    ctx->band_cap, (char *)ctx->ws + off_ws, d_out, out_stride, st)) != hipSuccess)
             return hip_fail(e, "band filter");
         if (any_severe) {
             float *alt = (float *)((char *)ctx->ws + off_auto);
             uint8_t *sel = (uint8_t *)ctx->ws + off_sel;
-            if ((e = launch_band_filter(bm, d_in, in_stride, h, w, bands, idx, n_ref, mp.K, s_hi * mult,
+            if ((e = launch_band_filter(bm, d_in, in_stride, h, w, bands, idx, g.s, mp.W, mp.K, s_hi * mult,
                                         ctx->band_cap, (char *)ctx->ws + off_ws, alt, (int64_t)w * bands, st)) !=
                     hipSuccess ||
                 (e = hipMemcpyAsync(sel, severe.data(), bands, hipMemcpyHostToDevice, st)) != hipSuccess ||

@@ -366,8 +366,8 @@ hipError_t launch_select_bands(const float *alt, int64_t alt_stride, const uint8
 // The filter works in chunks of groups whose FP64 patch matrices stay below cap bytes each.
 size_t band_ws_bytes(int h, int w, int B, int K, int64_t n_group, int64_t cap);
 hipError_t launch_band_filter(const BandMaps &bm, const uint8_t *cube, int64_t stride, int h, int w, int B,
-                              const int32_t *idx, int64_t n_group, int K, double tau, int64_t cap, void *ws,
-                              float *out, int64_t out_stride, hipStream_t st);
+                              const int32_t *idx, int s, int W, int K, double tau, int64_t cap, void *ws, float *out,
+                              int64_t out_stride, hipStream_t st);
 
 // RA-Haar-tSVD refinement network (ra.hip).
 int ra_hidden(int c);

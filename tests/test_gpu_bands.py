@@ -242,3 +242,27 @@ def test_learned_pair_at_the_ends_of_the_band_counts(dn, h, w, bands, stride):
     learned = dn.denoise_bands(d, 20.0, p)
     ht.htsvd_set_basis(dn.ctx, 8, bands, U, V)
     assert float((learned - dn.denoise_bands(d, 20.0, p)).abs().max()) <= 1e-4
+
+
+# both ends of the band DFT's row blocks (31 | 32, 63 | 64), two bands, every group size, reference
+# tiles of 4, 2 and 1, thresholds that keep every row, some rows, or row 0 alone, and a row whose
+# sums pass 2048 (black and white noise)
+@pytest.mark.parametrize("bands,K,s,W,h,w", [
+    (2, 4, 2, 9, 24, 31), (4, 32, 3, 21, 40, 33), (30, 16, 8, 31, 50, 61), (31, 32, 4, 31, 47, 70),
+    (31, 8, 11, 31, 64, 53), (32, 8, 4, 15, 33, 40), (63, 4, 5, 9, 31, 36), (64, 16, 4, 21, 40, 32),
+])
+@pytest.mark.parametrize("sigma", [0.01, 12.0, 4000.0])
+@pytest.mark.parametrize("harsh", [False, True])
+def test_band_rows_at_the_edges(dn, bands, K, s, W, h, w, sigma, harsh):
+    """Estimates in FP64, their sums in units of 2^-16 and the mean as a float: within 2^-15 of the
+    oracle, as long as every keep or kill decision agrees."""
+    import paper_2512_23569_amd as ht
+    noisy = synth.add_awgn(synth.make_hsi(h, w, bands, 130 + bands), 12.0, 131)
+    if harsh:
+        noisy = np.where(np.random.default_rng(5).random(noisy.shape) < 0.5, 0, 255).astype(np.uint8)
+    U, V = lb.learn(noisy, 8, 4)
+    ht.htsvd_set_basis(dn.ctx, 8, bands, oracle.to_slices(U), oracle.to_slices(V))
+    idx, _ = oracle.block_match(oracle.band_guide(noisy), 8, s, W, K)
+    ref = oracle.filter_groups(noisy, idx, U, V, float(np.float32(sigma)) * np.sqrt(2.0 * np.log(bands * K * 64)))
+    out = dn.denoise_bands(_dev(noisy), sigma, dn.params(1, stride=s, window=W, K=K)).cpu().numpy()
+    assert np.abs(out - ref).max() <= 2.0 ** -15
