@@ -153,18 +153,28 @@ __global__ __launch_bounds__(GR_THREADS) void gram_kernel(const uint8_t *__restr
 // The same sums for a runtime channel count C (hyperspectral bands, up to 64), taken before the
 // regrouping by column: the row sums over the vectors v = X(y..y+7, x+j, :) of every reference
 // (y, x) and offset j, the column sums over X(y+i, x..x+7, :), without weights.  A block owns a
-// 64 x 64 tile pair (ta <= tb) of the A x A matrix (A = 8C) and a slice of the vectors; it stages
-// 64 vectors at a time in LDS, the bytes of 4 consecutive vectors packed in one word per entry
-// (P[group][entry]), and each thread adds a 4 x 4 block of entries with v_dot4_u32_u8 (four
-// byte products per instruction).  Per chunk the 32-bit partial is at most 64 * 255^2; the
-// blocks add 64-bit totals with integer atomics (exact, so in any order).
+// 64 x 64 tile pair (ta <= tb) of the A x A matrix (A = 8C) and a slice of the vectors.  It stages
+// 64 vectors at a time in LDS, entry by entry (8 bands of 4 vectors per thread, the bytes transposed
+// in registers), as v - 128 so that v_mfma_i32_16x16x64_i8 takes them: a wave's product of 16
+// entries with all 64 over the 64 vectors is four instructions, and five more with ones in place of
+// one side give the sums that undo the shift,
+//   sum v v' = sum (v-128)(v'-128) + 128 (sum (v-128) + sum (v'-128)) + 128^2 n.
+// The products are a small part of it: it is bound by the latency of the staging loads (the next
+// chunk's are issued ahead) and by the 64-bit atomics at its end, 0.13 us per block.  63 x 63
+// references, 31 bands: 75 us with 256 blocks, 89 with 512, 147 with 1,024 (212 us with byte loads and
+// v_dot4); 126 x 126 references: 259, 186 and 242 us (434).  Four teams of waves per block that add
+// their sums in LDS before the atomics were slower (107 us with 256).  32-bit partials hold GB_MAX chunks
+// (64 128^2 each); the blocks add 64-bit totals with integer atomics (exact, so in any order).
 constexpr int GB_VEC = 64;            // vectors per staged chunk
-constexpr int GB_GROUPS = GB_VEC / 4;
+constexpr int GB_MAX = 1024;          // chunks per block
+constexpr int GB_PITCH = 80;          // bytes per staged entry (64 and 4 banks)
+
+typedef int gv4i __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void gram_bands_kernel(const uint8_t *__restrict__ img, int64_t stride, int h,
                                                          int w, int C, int s, int ny, int nx,
                                                          unsigned long long *__restrict__ out) {
-    __shared__ uint32_t P[2][GB_GROUPS][64];
+    __shared__ __align__(16) unsigned char P[2][2][64 * GB_PITCH];   // (buffer, tile side)
     const int A = 8 * C;
     const int g = blockIdx.y;
     // tile pair (ta, tb), ta <= tb, row-major over the upper triangle of the tile grid
@@ -175,59 +185,92 @@ __global__ __launch_bounds__(256) void gram_bands_kernel(const uint8_t *__restri
         ++ta;
     }
     const int tb = ta + rem;
-    const int64_t n_vec = (int64_t)ny * nx * 8;
-    const int64_t n_chunks = (n_vec + GB_VEC - 1) / GB_VEC;
+    const int64_t n_ref = (int64_t)ny * nx;
+    const int64_t n_chunks = (n_ref * 8 + GB_VEC - 1) / GB_VEC;
     const int64_t c_begin = n_chunks * blockIdx.z / gridDim.z, c_end = n_chunks * (blockIdx.z + 1) / gridDim.z;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    unsigned long long tot[4][4] = {};
-    for (int64_t ck = c_begin; ck < c_end; ++ck) {
-        // staging: 2 x 16 x 64 words, one per (tile side, 4-vector group, entry)
-        for (int t = threadIdx.x; t < 2 * GB_GROUPS * 64; t += 256) {
-            const int side = t / (GB_GROUPS * 64), k = (t / 64) % GB_GROUPS, ai = t % 64;
-            const int a = (side ? tb : ta) * 64 + ai;
-            const int64_t q = ck * GB_VEC + 4 * k;   // first of 4 vectors with the same reference
-            uint32_t word = 0;
-            if (a < A && q < n_vec) {
-                const int iy = (int)(q / ((int64_t)nx * 8)), rm = (int)(q % ((int64_t)nx * 8));
-                const int ix = rm / 8, off = rm % 8, ch = a / 8, e = a % 8;
-                const int y = ref_pos(iy, ny, h, s), x = ref_pos(ix, nx, w, s);
-                // g = 0: entry e is the row offset, the 4 vectors are columns x+off..x+off+3;
-                // g = 1: entry e is the column offset, the 4 vectors are rows y+off..y+off+3
-                const uint8_t *px = g == 0 ? img + (int64_t)(y + e) * stride + (int64_t)(x + off) * C + ch
-                                           : img + (int64_t)(y + off) * stride + (int64_t)(x + e) * C + ch;
-                const int64_t step = g == 0 ? C : stride;
-                word = (uint32_t)px[0] | ((uint32_t)px[step] << 8) | ((uint32_t)px[2 * step] << 16) |
-                       ((uint32_t)px[3 * step] << 24);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // staging task: 4 vectors 4k .. 4k + 3 (of one reference) at entry offset e, the 8 bands of its side
+    const int k = tid & 15, e = tid >> 4 & 7, side = tid >> 7;
+    const int b0 = 8 * (side ? tb : ta), n_band = min(8, C - b0);
+    uint32_t lo[4], hi[4];
+    auto load = [&](int64_t ck) {
+        const int64_t r = ck * 8 + (k >> 1);
+        if (r < n_ref) {   // past the slice: loaded, not used
+            const int iy = (int)((uint32_t)r / (uint32_t)nx), ix = (int)r - iy * nx, off = 4 * (k & 1);
+            const int y = ref_pos(iy, ny, h, s), x = ref_pos(ix, nx, w, s);
+            // g = 0: entry e is the row offset, the 4 vectors are columns x+off..x+off+3;
+            // g = 1: entry e is the column offset, the 4 vectors are rows y+off..y+off+3
+            const uint8_t *px = g == 0 ? img + (int64_t)(y + e) * stride + (int64_t)(x + off) * C
+                                       : img + (int64_t)(y + off) * stride + (int64_t)(x + e) * C;
+            const int64_t step = g == 0 ? C : stride;
+            if (C >= 8) {   // the last bands of a tube: its last 8 bytes, shifted
+                const int at = b0 + n_band - 8, sh = 8 * (8 - n_band);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    uint64_t t;
+                    __builtin_memcpy(&t, px + v * step + at, 8);
+                    t = (t >> sh) ^ 0x8080808080808080ull;
+                    lo[v] = (uint32_t)t;
+                    hi[v] = (uint32_t)(t >> 32);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    uint64_t t = 0;
+                    for (int b = 0; b < C; ++b) t |= (uint64_t)px[v * step + b] << (8 * b);
+                    t ^= 0x8080808080808080ull;
+                    lo[v] = (uint32_t)t;
+                    hi[v] = (uint32_t)(t >> 32);
+                }
             }
-            P[side][k][ai] = word;
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) lo[v] = hi[v] = 0;   // adds nothing
         }
-        __syncthreads();
-        uint32_t acc[4][4] = {};
-#pragma unroll 4
-        for (int k = 0; k < GB_GROUPS; ++k) {
-            const uint4 pa = *reinterpret_cast<const uint4 *>(&P[0][k][ty * 4]);
-            const uint4 pb = *reinterpret_cast<const uint4 *>(&P[1][k][tx * 4]);
-            const uint32_t va[4] = {pa.x, pa.y, pa.z, pa.w}, vb[4] = {pb.x, pb.y, pb.z, pb.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_udot4(va[i], vb[j], acc[i][j], false);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) tot[i][j] += acc[i][j];
-        __syncthreads();
-    }
-    unsigned long long *og = out + (size_t)g * C * C * 64;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
+    };
+    // bytes of 4 vectors at one band, for 4 bands: word b of the entry's rows b*8 + e
+    auto store4 = [&](const uint32_t (&v)[4], unsigned char *d) {
+        const uint32_t t0 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u), t1 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
+        const uint32_t t2 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u), t3 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
+        *reinterpret_cast<uint32_t *>(d) = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+        *reinterpret_cast<uint32_t *>(d + 8 * GB_PITCH) = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+        *reinterpret_cast<uint32_t *>(d + 16 * GB_PITCH) = __builtin_amdgcn_perm(t3, t2, 0x05040100u);
+        *reinterpret_cast<uint32_t *>(d + 24 * GB_PITCH) = __builtin_amdgcn_perm(t3, t2, 0x07060302u);
+    };
+    const int col = lane & 15, q = lane >> 4;
+    const gv4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    gv4i acc[4] = {}, sum_b[4] = {}, sum_a = {};
+    load(c_begin);
+    for (int64_t ck = c_begin; ck < c_end; ++ck) {
+        unsigned char(*buf)[64 * GB_PITCH] = P[(ck - c_begin) & 1];
+        store4(lo, buf[side] + e * GB_PITCH + 4 * k);
+        store4(hi, buf[side] + (32 + e) * GB_PITCH + 4 * k);
+        load(ck + 1);
+        __syncthreads();   // the other buffer was read before the barrier of the chunk between
+        const gv4i a = *reinterpret_cast<const gv4i *>(buf[0] + (16 * wave + col) * GB_PITCH + 16 * q);
+        sum_a = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, ones, sum_a, 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int a = ta * 64 + ty * 4 + i, b = tb * 64 + tx * 4 + j;
-            if (a >= A || b >= A || tot[i][j] == 0) continue;
-            atomicAdd(og + ((a / 8) * C + b / 8) * 64 + (a % 8) * 8 + b % 8, tot[i][j]);
-            if (ta != tb) atomicAdd(og + ((b / 8) * C + a / 8) * 64 + (b % 8) * 8 + a % 8, tot[i][j]);
+            const gv4i b = *reinterpret_cast<const gv4i *>(buf[1] + (16 * j + col) * GB_PITCH + 16 * q);
+            acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, acc[j], 0, 0, 0);
+            sum_b[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b, sum_b[j], 0, 0, 0);
+        }
+    }
+    const int64_t n = min(n_ref * 8, c_end * GB_VEC) - c_begin * GB_VEC;
+    if (n <= 0) return;
+    unsigned long long *og = out + (size_t)g * C * C * 64;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int x = ta * 64 + 16 * wave + 4 * q + r, y = tb * 64 + 16 * j + col;
+            if (x >= A || y >= A) continue;
+            const unsigned long long t =
+                (unsigned long long)((int64_t)acc[j][r] + 128 * ((int64_t)sum_a[r] + sum_b[j][r]) + 16384 * n);
+            if (t == 0) continue;
+            // staged entry x holds row or column offset x mod 8 of band x / 8
+            atomicAdd(og + ((x / 8) * C + y / 8) * 64 + (x % 8) * 8 + y % 8, t);
+            if (ta != tb) atomicAdd(og + ((y / 8) * C + x / 8) * 64 + (y % 8) * 8 + x % 8, t);
         }
 }
 
@@ -422,9 +465,11 @@ hipError_t launch_gram(const uint8_t *img, int64_t stride, int h, int w, int c, 
     if (e != hipSuccess) return e;
     if (c != 1 && c != 3) {
         const int nt = (8 * c + 63) / 64, n_tp = nt * (nt + 1) / 2;
-        // vector slices for about 1024 workgroups, each with at least 8 chunks
+        // vector slices for 256 to 512 workgroups of about 40 chunks, each with at least 8 and at most GB_MAX
         const int64_t n_chunks = ((int64_t)ny * nx * 8 + GB_VEC - 1) / GB_VEC;
-        const int64_t zs = std::max<int64_t>(1, std::min<int64_t>((1024 + 2 * n_tp - 1) / (2 * n_tp), n_chunks / 8));
+        const int64_t blocks = std::min<int64_t>(512, std::max<int64_t>(256, n_chunks * 2 * n_tp / 40));
+        const int64_t zs = std::max<int64_t>(
+            {1, std::min<int64_t>((blocks + 2 * n_tp - 1) / (2 * n_tp), n_chunks / 8), (n_chunks + GB_MAX - 1) / GB_MAX});
         hipLaunchKernelGGL(gram_bands_kernel, dim3((unsigned)n_tp, 2, (unsigned)zs), dim3(256), 0, st, img, stride, h,
                            w, c, s, ny, nx, reinterpret_cast<unsigned long long *>(out));
         return hipGetLastError();

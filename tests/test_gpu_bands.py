@@ -266,3 +266,12 @@ def test_band_rows_at_the_edges(dn, bands, K, s, W, h, w, sigma, harsh):
     ref = oracle.filter_groups(noisy, idx, U, V, float(np.float32(sigma)) * np.sqrt(2.0 * np.log(bands * K * 64)))
     out = dn.denoise_bands(_dev(noisy), sigma, dn.params(1, stride=s, window=W, K=K)).cpu().numpy()
     assert np.abs(out - ref).max() <= 2.0 ** -15
+
+
+@pytest.mark.parametrize("h,w,bands,s", [(8, 9, 2, 1), (33, 40, 8, 4), (20, 70, 9, 1), (61, 37, 63, 5), (90, 80, 64, 1)])
+def test_band_gram_sums_at_the_edges(dn, h, w, bands, s):
+    """Whole numbers: fewer than 8 bands, a last tile with one band or all 8, one chunk of vectors and
+    many slices, the largest values."""
+    for cube in (synth.add_awgn(synth.make_hsi(h, w, bands, 140 + bands), 40.0, 141), np.full((h, w, bands), 255, np.uint8)):
+        G = dn.basis_gram(_dev(cube), stride=s)
+        assert np.array_equal(G.cpu().numpy(), lb.channel_gram(cube, 8, s))
