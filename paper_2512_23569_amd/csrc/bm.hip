@@ -28,12 +28,14 @@
 // and position, the keys were counted before they were compacted, and channel sums took 64-bit
 // keys).  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions, so that
 // small windows neither walk empty table rows nor hold LDS for them: 1536 x 2048 gray, window 21,
-// 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 1,784 us.
+// 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 981 us.
 //
 // Video (Sec. IV-C): the frames are stacked vertically, and a reference's candidates are the
 // positions of its clipped window in every frame within a temporal radius.  The workgroup keeps
-// the reference patches of its own frame in registers, stages one frame after another, and
-// merges each frame's K best (distance, frame slot, position) keys into a running list in LDS.
+// the reference patches of its own frame in registers and stages one frame after another.  Where
+// a row of the table holds the windows of all frames, position frame slot x window + place, a
+// reference selects once at the end; else each frame's K best (distance, frame slot, position) keys
+// are merged into a running list in LDS.
 #include <algorithm>
 
 #include "common.h"
@@ -81,7 +83,7 @@ struct BmLds {
     int pitch16;    // halves per row of one fp16 plane copy
     int rows;       // plane rows (union rows + 7)
     int plane8;     // bytes between the int8 plane copies (a row multiple plus a bank offset)
-    int off_p8, off_p16, off_n8, off_n16, off_tab, total;   // video: running lists last
+    int off_p8, off_p16, off_n8, off_n16, off_tab, off_rs, total;   // video: running lists last
 };
 
 __device__ inline uint32_t lds_u32(const unsigned char *base, int byte_off) {
@@ -236,13 +238,16 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
     return sel[lane];
 }
 
-// Groups of the 16 references of tile b (VIDEO: tile b of the frames' tiles, frame-major).
-template <bool VIDEO, int NPL>
+// Groups of the 16 references of tile b (VIDEO: tile b of the frames' tiles, frame-major; ONE: the
+// table holds the windows of all its frames and a reference selects once).
+template <bool VIDEO, int NPL, bool ONE = false>
 __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams &mp, const int tiles_x, const int b_in,
                                         const BmLds &L, int32_t *__restrict__ idx_out,
                                         int32_t *__restrict__ dist_out, unsigned char *smem, TileInfo &ti,
                                         const VideoArgs &va) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tid_f = threadIdx.x;
+    asm volatile("" : "+v"(tid_f));   // nothing per thread is kept from tile to tile
+    const int tid = tid_f, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int b = b_in, t = 0, f_lo = 0, nf = 1;
     ImageGeom g = g0;   // the reference's frame
     if constexpr (VIDEO) {
@@ -316,7 +321,6 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     // Per-lane state of the distance phase, kept across the frames of a video search: the A
     // fragments of reference i16 and the window and norm of the 4 references of this lane's
     // accumulators.
-    const int i16 = lane & 15, q = lane >> 4;
     v4i a8;
     v8h a16a = {}, a16b = {};
     bool any_sum = false;
@@ -327,6 +331,9 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     const int K = mp.K;
 
     for (int fi = 0; fi < nf; ++fi) {
+        // addresses are made anew for each frame: kept over the loop they cost 50 registers
+        if constexpr (VIDEO) asm volatile("" : "+v"(tid_f));
+        const int tid = tid_f, lane = tid & 63, i16 = lane & 15, q = lane >> 4;
         int slot = 0;
         const uint8_t *fimg = g.img;
         if constexpr (VIDEO) {
@@ -334,7 +341,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             const int f = fi == 0 ? t : f_lo + fi - 1 + (f_lo + fi - 1 >= t ? 1 : 0);
             slot = f - f_lo;
             fimg = g0.img + (int64_t)f * va.frame_bytes;
-            if (fi > 0) __syncthreads();   // the last frame's table and selection scratch are reused
+            if (fi > 0) __syncthreads();   // the last frame's planes and table or selection scratch are reused
         }
 
         // ---- stage the shifted planes: one thread per (row, group of 4 columns) ----
@@ -408,7 +415,8 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
         // Reads past the last valid output stay inside the staged planes and the table; the
         // outputs they feed are not stored.
         {
-            int32_t *rs8 = reinterpret_cast<int32_t *>(tab);          // prow x uw, tab is free now
+            // prow x uw; but for the windows of earlier frames the table is free now
+            int32_t *rs8 = reinterpret_cast<int32_t *>(ONE ? smem + L.off_rs : smem + L.off_tab);
             int32_t *rs16 = rs8 + prow * uw;
             const int ng = (uw + 3) >> 2;
             for (int e = tid; e < prow * ng; e += BMT) {
@@ -537,7 +545,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             for (int r = 0; r < 4; ++r) {
                 const int dx = cc0 - (ti.wx0[r] - ux0), ww = ti.ry[r] >= 0 ? ti.ww[r] : 0;
                 inside[r] = (unsigned)dx < (unsigned)ww;
-                at[r] = reinterpret_cast<unsigned char *>(tab + (4 * q + r) * TAB + (cr0 - wy) * ww + dx);
+                at[r] = reinterpret_cast<unsigned char *>(tab + (4 * q + r) * TAB + ((ONE ? slot * wh : 0) + cr0 - wy) * ww + dx);
                 step4[r] = 4 * wpc * ww;
             }
             const unsigned char *c8 = p8 + (cc & 3) * plane8 + (cr0 + 2 * q) * L.pitch8 + (cc & ~3);
@@ -585,20 +593,21 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                 }
             }
         }
+        if (ONE && fi + 1 < nf) continue;   // the next frame's staging begins with a barrier
         __syncthreads();
 
         // ---- top-K per reference ----
         for (int ii = wave; ii < NREF; ii += BMW) {
             if (ti.ry[ii] < 0) continue;
             const int ww = __builtin_amdgcn_readfirstlane(ti.ww[ii]);
-            const int n = __builtin_amdgcn_readfirstlane(ti.wh[ii]) * ww;
+            const int n = __builtin_amdgcn_readfirstlane(ti.wh[ii]) * ww * (ONE ? nf : 1);
             uint32_t *row = tab + ii * TAB;
             // this lane's candidates p = lane + 64 i, read once (past the window: whatever is there)
             uint32_t dv[NPL];
 #pragma unroll
             for (int i = 0; i < NPL; ++i) dv[i] = row[lane + 64 * i];
             const bool small = __builtin_amdgcn_readfirstlane(ti.green[ii]) != 0;
-            if constexpr (VIDEO) {
+            if constexpr (VIDEO && !ONE) {
                 if (fi > 0) {
                     // Only keys below the running K-th can enter the list; its slot is another one,
                     // so the distance decides alone.  When at most 64 - K of this frame's candidates
@@ -637,7 +646,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                 }
             }
             const uint64_t mine = select_k<NPL>(dv, n, K, small, row, lane);
-            if constexpr (VIDEO) {
+            if constexpr (VIDEO && !ONE) {
                 // merge into the running list: keys (distance, frame slot, position); only this wave
                 // touches reference ii's list
                 uint64_t v = lane < K ? (((mine >> 10) << 16) | ((uint64_t)slot << 10) | (mine & 1023u)) : ~0ull;
@@ -649,17 +658,24 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             } else if (lane < K) {
                 const int p = (int)(mine & 1023u);
                 const int py = (int)((uint32_t)p * (65536u / (uint32_t)ww + 1u) >> 16);   // p / ww for p < 1024
-                const int y = ti.wy0[ii] + py, x = ti.wx0[ii] + p - py * ww;
+                int y = ti.wy0[ii] + py;
+                const int x = ti.wx0[ii] + p - py * ww;
                 const int iy = tyi * REF_TILE + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
-                const int64_t r = (int64_t)iy * g.nx + ix;
+                int64_t r = (int64_t)iy * g.nx + ix;
+                if constexpr (ONE) {   // py runs through the rows of all frames' windows
+                    const int wh = ti.wh[ii], f = py / wh;
+                    y += (f_lo + f) * g.h - f * wh;
+                    r += (int64_t)t * g.ny * g.nx;
+                }
                 idx_out[r * K + lane] = y * g.w + x;
                 if (dist_out) dist_out[r * K + lane] = (int32_t)(mine >> 10);
             }
             wave_lds_sync();
         }
+        if constexpr (ONE) break;
     }   // frames
 
-    if constexpr (VIDEO) {
+    if constexpr (VIDEO && !ONE) {
         for (int ii = wave; ii < NREF; ii += BMW) {
             if (ti.ry[ii] < 0 || lane >= K) continue;
             const uint64_t key = run[ii * RUN_K + lane];
@@ -689,8 +705,10 @@ __global__ __launch_bounds__(BMT) void bm_kernel(ImageGeom g, MethodParams mp, i
 }
 
 // Spatio-temporal form: n_tiles covers the tiles of all frames.
-template <int NPL>
-__global__ __launch_bounds__(BMT) void bm_video_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
+// 64 registers, so that two workgroups share a CU where the LDS allows: while one waits at a barrier
+// the other works.  Rows of 16 keys per lane do not fit them.
+template <int NPL, bool ONE>
+__global__ __launch_bounds__(BMT, ONE && NPL < 16 ? 8 : 4) void bm_video_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                        VideoArgs va, BmLds L, int32_t *__restrict__ idx_out,
                                                        int32_t *__restrict__ dist_out) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -698,12 +716,12 @@ __global__ __launch_bounds__(BMT) void bm_video_kernel(ImageGeom g, MethodParams
     const int per = (n_tiles + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= n_tiles) return;
-    bm_tile<true, NPL>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, va);
+    bm_tile<true, NPL, ONE>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, va);
 }
 
 // Persistent form over many images: each workgroup pulls (image, tile) units from a queue.
 template <int NPL>
-__global__ __launch_bounds__(BMT) void bm_kernel_batched(const BatchItem *__restrict__ items, int n_items,
+__global__ __launch_bounds__(BMT, NPL == 16 ? 4 : 8) void bm_kernel_batched(const BatchItem *__restrict__ items, int n_items,
                                                          const int *__restrict__ unit_start, BmLds L,
                                                          int *__restrict__ queue) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -725,9 +743,9 @@ __global__ __launch_bounds__(BMT) void bm_kernel_batched(const BatchItem *__rest
 
 // Register rows of the table (tab_stride) that windows of up to n positions need.
 int bm_npl(int n) { return n <= 256 ? 4 : (n <= 448 ? 7 : (n <= 640 ? 10 : 16)); }
-int bm_tab_stride(int npl) { return npl == 4 ? tab_stride<4>() : (npl == 7 ? tab_stride<7>() : (npl == 10 ? tab_stride<10>() : tab_stride<16>())); }
+int bm_tab_stride(int npl) { return npl == 11 ? tab_stride<11>() : npl == 4 ? tab_stride<4>() : (npl == 7 ? tab_stride<7>() : (npl == 10 ? tab_stride<10>() : tab_stride<16>())); }
 
-BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false) {
+BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool one = false) {
     BmLds L;
     L.rows = uh_max + PS - 1;
     // The int8 planes: rows of 96 bytes (enough for a union of 64 columns plus the patch and the
@@ -751,10 +769,14 @@ BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false) {
     L.off_tab = off;
     // the last row is read to 64 npl words
     int tab_bytes = ((NREF - 1) * bm_tab_stride(npl) + std::max(bm_tab_stride(npl), 64 * npl)) * 4;
-    const int rs_bytes = 2 * L.rows * uw_max * 4;  // row sums of the norm pass live in the table
-    if (tab_bytes < rs_bytes) tab_bytes = rs_bytes;
+    // row sums of the norm pass live in the table, unless that holds the windows of earlier frames
+    // (the columns of the norm pass read up to 3 rows past the last)
+    const int rs_bytes = 2 * L.rows * uw_max * 4 + (one ? 3 * uw_max * 4 : 0);
+    if (!one && tab_bytes < rs_bytes) tab_bytes = rs_bytes;
     off += (tab_bytes + 15) & ~15;
-    if (video) off += NREF * RUN_K * 8;   // the running lists of the video search
+    L.off_rs = off;
+    if (one) off += (rs_bytes + 15) & ~15;
+    if (video && !one) off += NREF * RUN_K * 8;   // the running lists of the video search
     L.total = off;
     return L;
 }
@@ -795,8 +817,16 @@ hipError_t launch_block_match_video(const ImageGeom &g, const MethodParams &mp, 
     const int span = (REF_TILE - 1) * g.s + mp.W;
     const int uh = span < g.h - PS + 1 ? span : g.h - PS + 1;
     const int uw = span < g.w - PS + 1 ? span : g.w - PS + 1;
-    const int npl = bm_npl(min(mp.W, g.h - PS + 1) * min(mp.W, g.w - PS + 1));
-    const BmLds L = bm_lds_layout(uh, uw, npl, true);
+    const int window = min(mp.W, g.h - PS + 1) * min(mp.W, g.w - PS + 1), frames = min(2 * radius + 1, T);
+    // One selection from the windows of all frames where they fit a row of the table and the table fits
+    // beside the planes: 981 us against 1,761 us with a selection per frame and merged lists (four 720 x
+    // 1280 frames, radius 1, window 15), of which 380 us are the second workgroup on a CU.
+    const bool fits = window * frames <= MAX_CAND;
+    const int npl_one = window * frames > 640 && window * frames <= 704 ? 11 : bm_npl(window * frames);
+    const BmLds L_one = bm_lds_layout(uh, uw, fits ? npl_one : 4, true, true);
+    const bool one = fits && L_one.total + (int)sizeof(TileInfo) <= 160 * 1024;
+    const int npl = one ? npl_one : bm_npl(window);
+    const BmLds L = one ? L_one : bm_lds_layout(uh, uw, npl, true);
     VideoArgs va{T, radius, (int64_t)g.h * g.stride};
     const int per = (n_tiles + 7) / 8;
     auto go = [&](auto kernel) {
@@ -805,8 +835,17 @@ hipError_t launch_block_match_video(const ImageGeom &g, const MethodParams &mp, 
         hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, va, L, idx, dist);
         return hipGetLastError();
     };
-    return npl == 4 ? go(bm_video_kernel<4>)
-                    : (npl == 7 ? go(bm_video_kernel<7>) : (npl == 10 ? go(bm_video_kernel<10>) : go(bm_video_kernel<16>)));
+    if (one)
+        switch (npl) {
+            case 4: return go(bm_video_kernel<4, true>);
+            case 7: return go(bm_video_kernel<7, true>);
+            case 10: return go(bm_video_kernel<10, true>);
+            case 11: return go(bm_video_kernel<11, true>);
+            default: return go(bm_video_kernel<16, true>);
+        }
+    return npl == 4 ? go(bm_video_kernel<4, false>)
+                    : (npl == 7 ? go(bm_video_kernel<7, false>)
+                                : (npl == 10 ? go(bm_video_kernel<10, false>) : go(bm_video_kernel<16, false>)));
 }
 
 // Batched block matching: one persistent launch over the tiles of all images; the LDS layout

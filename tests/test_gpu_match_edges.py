@@ -59,7 +59,7 @@ def test_groups_equal_the_oracle(dn, window, stride, K, kind, c):
     assert np.array_equal(dist.cpu().numpy(), od)
 
 
-@pytest.mark.parametrize("window", [7, 21, 25, 31])
+@pytest.mark.parametrize("window", [7, 13, 15, 17, 21, 25, 31])
 @pytest.mark.parametrize("kind", ["stripes", "wide_stripes", "red_blue"])
 def test_video_groups_equal_the_oracle(dn, window, kind):
     frames = np.stack([_image(kind, 40, 51, 3, 7 * t + window) for t in range(3)])
