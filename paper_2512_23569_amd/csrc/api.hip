@@ -17,7 +17,6 @@
 
 namespace htsvd {
 hipError_t launch_fill_const(double *p, int n, double v, hipStream_t st);
-int bm_lds_bytes(int s, int W, int h, int w);
 }  // namespace htsvd
 
 using namespace htsvd;
@@ -1524,7 +1523,6 @@ htsvd_status plan_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *imgs, cons
         b.out = x.d_out;
         b.out_stride = x.out_stride;
         b.bm_tiles_x = (b.g.nx + REF_TILE - 1) / REF_TILE;
-        b.bm_tiles = ((b.g.ny + REF_TILE - 1) / REF_TILE) * b.bm_tiles_x;
         b.n_ref = (int64_t)b.g.ny * b.g.nx;
         b.n_tiles_sigma = (int64_t)((b.g.h + T - 1) / T) * ((b.g.w + T - 1) / T);
         b.learned = x.sigma == HTSVD_SIGMA_AUTO && p->estimator == 1;
@@ -1589,7 +1587,9 @@ htsvd_status plan_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *imgs, cons
     P.off_mom = off;
     off = align256(off + sizeof(int32_t) * sigma_mom_ints() * mom_units);
     int64_t px = 0, refs = 0, bm = 0;
-    for (const BatchImage &b : P.im) {
+    const int bm_rows = bm_tile_rows(P.max_s, P.max_W, P.max_h, P.max_w);
+    for (BatchImage &b : P.im) {
+        b.bm_tiles = (b.g.ny + bm_rows - 1) / bm_rows * b.bm_tiles_x;
         px += (int64_t)b.g.h * b.g.w;
         refs += b.n_ref;
         bm += b.bm_tiles;
@@ -1930,7 +1930,7 @@ htsvd_status htsvd_denoise_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *i
                                           (const double *)(D + o_mult), ls)) != hipSuccess)
             return hip_fail(e2, "tau");
         if ((e2 = launch_block_match_batched(d_items, ni, (const int *)(D + o_bm), P.max_s, P.max_W, P.max_h, P.max_w,
-                                             d_q, std::min(grid, bm_start[ni]), ls)) != hipSuccess)
+                                             d_q, grid, bm_start[ni], ls)) != hipSuccess)
             return hip_fail(e2, "batched block matching");
         // images whose noise level is estimated or adjusted: the network per learned image, then
         // every sub-image stage in one launch over all images

@@ -6,8 +6,9 @@
 // Distances are squared Euclidean and exact.  Algorithm 1 "Grouping" keeps the K
 // smallest, ordered by (distance, row, column).
 //
-// Mapping.  One workgroup (16 waves, four per SIMD) owns a 4x4 tile of references.  The union of their
-// search windows (at most 64x64 candidate positions) is staged in LDS as
+// Mapping.  One workgroup (16 waves) owns a 4x4 tile of references, or with windows past 640
+// positions and steps up to 4 a 3x4 tile (12 waves), so that two workgroups share a CU.  The union of
+// their search windows (at most 64x64 candidate positions) is staged in LDS as
 //   - the shifted green (or gray) plane x-128 in int8, in 4 byte-shifted copies so any
 //     8-pixel row segment is a 4-byte-aligned pair of dwords, and
 //   - the shifted channel-sum plane R+G+B-384 in fp16 (exact: |v| <= 384), in 2 copies.
@@ -26,7 +27,8 @@
 // wherever their range allows.  1,205 vector instructions per reference of a 12 MP image with
 // window 31, 4.20 ms (1,575 and 4.70 ms when both sides of each window were tested per reference
 // and position, the keys were counted before they were compacted, and channel sums took 64-bit
-// keys).  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions, so that
+// keys).  The rest is the waits at the barriers between a tile's phases, which a second workgroup on
+// the CU fills: 3.44 ms.  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions, so that
 // small windows neither walk empty table rows nor hold LDS for them: 1536 x 2048 gray, window 21,
 // 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 981 us.
 //
@@ -188,7 +190,7 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
         for (int i = 0; i < NPL; ++i) {
             const bool in = key[i] <= theta;
             const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
-            if (in) row[total + bits_below(mask)] = small ? key[i] : ((dv[i] - dmin) << 10) | (uint32_t)(lane + 64 * i);
+            if (in) row[total + bits_below(mask)] = small ? key[i] : (((key[i] >> 6) - dmin) << 10) | (uint32_t)(lane + 64 * i);
             total += __popcll(mask);
         }
         wave_lds_sync();
@@ -212,13 +214,13 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
         }
         return small ? (uint64_t)v : ((uint64_t)((v >> 10) + dmin) << 10) | (v & 1023u);
     }
-    // the K-th smallest of the exact lane minima, under which at most RUN_K lanes hold keys
+    // (the distances are in the coarse keys)  The K-th smallest of the exact lane minima, under which at most RUN_K lanes hold keys
     uint64_t *sel = reinterpret_cast<uint64_t *>(row);
     uint64_t mm = ~0ull;
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
         const int p = lane + 64 * i;
-        const uint64_t k64 = ((uint64_t)dv[i] << 10) | (uint64_t)p;
+        const uint64_t k64 = ((uint64_t)(key[i] >> 6) << 10) | (uint64_t)p;
         mm = p < n && k64 < mm ? k64 : mm;
     }
     const uint64_t bound = readlane_u64(wave_sort64(mm, lane), K - 1);
@@ -226,7 +228,7 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
         const int p = lane + 64 * i;
-        const uint64_t k64 = ((uint64_t)dv[i] << 10) | (uint64_t)p;
+        const uint64_t k64 = ((uint64_t)(key[i] >> 6) << 10) | (uint64_t)p;
         const bool in = p < n && k64 <= bound;
         const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
         if (in) sel[total + bits_below(mask)] = k64;
@@ -238,20 +240,21 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
     return sel[lane];
 }
 
-// Groups of the 16 references of tile b (VIDEO: tile b of the frames' tiles, frame-major; ONE: the
+// Groups of the 4 TR references of tile b, TR rows of 4, by as many wavefronts (VIDEO: tile b of the frames' tiles, frame-major; ONE: the
 // table holds the windows of all its frames and a reference selects once).
-template <bool VIDEO, int NPL, bool ONE = false>
+template <bool VIDEO, int NPL, bool ONE = false, int TR = REF_TILE>
 __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams &mp, const int tiles_x, const int b_in,
                                         const BmLds &L, int32_t *__restrict__ idx_out,
                                         int32_t *__restrict__ dist_out, unsigned char *smem, TileInfo &ti,
                                         const VideoArgs &va) {
+    constexpr int NW = 4 * TR, NR = 4 * TR, THREADS = 64 * NW;   // wavefronts, references
     int tid_f = threadIdx.x;
     asm volatile("" : "+v"(tid_f));   // nothing per thread is kept from tile to tile
     const int tid = tid_f, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int b = b_in, t = 0, f_lo = 0, nf = 1;
     ImageGeom g = g0;   // the reference's frame
     if constexpr (VIDEO) {
-        const int tiles_frame = ((g0.ny + REF_TILE - 1) / REF_TILE) * tiles_x;
+        const int tiles_frame = ((g0.ny + TR - 1) / TR) * tiles_x;
         t = b_in / tiles_frame;
         b = b_in - t * tiles_frame;
         g.img = g0.img + (int64_t)t * va.frame_bytes;
@@ -264,15 +267,15 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     // ---- tile geometry ----
     // The union of the 16 windows in closed form (positions increase along each side), so every
     // thread has it at once and the staging loads need not wait for the per-reference table.
-    const int iya = tyi * REF_TILE, iyb = min(iya + REF_TILE, g.ny) - 1;
+    const int iya = tyi * TR, iyb = min(iya + TR, g.ny) - 1;
     const int ixa = txi * REF_TILE, ixb = min(ixa + REF_TILE, g.nx) - 1;
     const int uy0 = max(0, ref_pos(iya, g.ny, g.h, g.s) - R);
     const int ux0 = max(0, ref_pos(ixa, g.nx, g.w, g.s) - R);
     const int uh = min(g.h - PS, ref_pos(iyb, g.ny, g.h, g.s) + R) - uy0 + 1;
     const int uw = min(g.w - PS, ref_pos(ixb, g.nx, g.w, g.s) + R) - ux0 + 1;
     if (tid < NREF) {
-        const int iy = tyi * REF_TILE + tid / REF_TILE, ix = txi * REF_TILE + tid % REF_TILE;
-        if (iy < g.ny && ix < g.nx) {
+        const int iy = iya + tid / REF_TILE, ix = txi * REF_TILE + tid % REF_TILE;
+        if (tid < NR && iy < g.ny && ix < g.nx) {
             const int y = ref_pos(iy, g.ny, g.h, g.s), x = ref_pos(ix, g.nx, g.w, g.s);
             const int y0 = max(0, y - R), y1 = min(g.h - PS, y + R);
             const int x0 = max(0, x - R), x1 = min(g.w - PS, x + R);
@@ -290,7 +293,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
         const int i = tid >> 4, sub = tid & 15;   // 16 threads per reference (the first 256 threads)
         int nr = 0, ng = 0, nb = 0;
         const int iy = iya + i / REF_TILE, ix = ixa + i % REF_TILE;
-        if (i < NREF && iy < g.ny && ix < g.nx) {
+        if (i < NR && iy < g.ny && ix < g.nx) {
             const int ry = ref_pos(iy, g.ny, g.h, g.s), rx = ref_pos(ix, g.nx, g.w, g.s);
             for (int p = sub; p < PS * PS; p += 16) {
                 const uint8_t *px = g.img + (int64_t)(ry + p / PS) * g.stride + (int64_t)(rx + p % PS) * 3;
@@ -353,7 +356,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             const uint8_t *img_end = fimg + (int64_t)(g.h - 1) * g.stride + (int64_t)g.w * g.c;
             uint32_t *p8w = reinterpret_cast<uint32_t *>(p8);
             uint32_t *p16w = reinterpret_cast<uint32_t *>(p16);
-            for (int e = tid; e < prow * nw; e += BMT) {
+            for (int e = tid; e < prow * nw; e += THREADS) {
                 const int r = e / nw, w4 = 4 * (e - r * nw);
                 const int npx = min(7, pcol - w4);
                 const uint8_t *a = fimg + (int64_t)(uy0 + r) * g.stride + (int64_t)(ux0 + w4) * g.c;
@@ -419,7 +422,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             int32_t *rs8 = reinterpret_cast<int32_t *>(ONE ? smem + L.off_rs : smem + L.off_tab);
             int32_t *rs16 = rs8 + prow * uw;
             const int ng = (uw + 3) >> 2;
-            for (int e = tid; e < prow * ng; e += BMT) {
+            for (int e = tid; e < prow * ng; e += THREADS) {
                 const int r = e / ng, c0 = 4 * (e - r * ng);
                 int q8[11], q16[11];
                 {
@@ -465,7 +468,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             }
             __syncthreads();
             const int nr4 = (uh + 3) >> 2;
-            for (int e = tid; e < nr4 * uw; e += BMT) {
+            for (int e = tid; e < nr4 * uw; e += THREADS) {
                 const int r4 = 4 * (e / uw), col = e - (r4 >> 2) * uw;
                 int c8[11], c16[11];
 #pragma unroll
@@ -534,7 +537,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             // rows of their windows go with q and the columns with r; position (dy, dx) of reference
             // 4 q + r is table byte 4 (dy ww + dx) of its row.
             const int ncb = (uw + 15) >> 4;   // 1 .. 4
-            const int wpc = ncb == 1 ? 16 : (ncb == 2 ? 8 : (ncb == 3 ? 5 : 4));   // waves per block of columns
+            const int wpc = ncb == 1 ? NW : (ncb == 2 ? NW / 2 : (ncb == 3 ? NW / 3 : NW / 4));   // waves per block of columns
             const int cb = (wave >= wpc) + (wave >= 2 * wpc) + (wave >= 3 * wpc), cr0 = wave - cb * wpc;
             const int cc0 = 16 * cb + i16, cc = min(cc0, uw - 1);
             const int wy = ti.wy0[4 * q] - uy0, wh = ti.ry[4 * q] >= 0 ? ti.wh[4 * q] : 0;
@@ -597,7 +600,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
         __syncthreads();
 
         // ---- top-K per reference ----
-        for (int ii = wave; ii < NREF; ii += BMW) {
+        for (int ii = wave; ii < NR; ii += NW) {
             if (ti.ry[ii] < 0) continue;
             const int ww = __builtin_amdgcn_readfirstlane(ti.ww[ii]);
             const int n = __builtin_amdgcn_readfirstlane(ti.wh[ii]) * ww * (ONE ? nf : 1);
@@ -660,7 +663,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                 const int py = (int)((uint32_t)p * (65536u / (uint32_t)ww + 1u) >> 16);   // p / ww for p < 1024
                 int y = ti.wy0[ii] + py;
                 const int x = ti.wx0[ii] + p - py * ww;
-                const int iy = tyi * REF_TILE + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
+                const int iy = iya + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
                 int64_t r = (int64_t)iy * g.nx + ix;
                 if constexpr (ONE) {   // py runs through the rows of all frames' windows
                     const int wh = ti.wh[ii], f = py / wh;
@@ -676,12 +679,12 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     }   // frames
 
     if constexpr (VIDEO && !ONE) {
-        for (int ii = wave; ii < NREF; ii += BMW) {
+        for (int ii = wave; ii < NR; ii += NW) {
             if (ti.ry[ii] < 0 || lane >= K) continue;
             const uint64_t key = run[ii * RUN_K + lane];
             const int p = (int)(key & 1023u), f = f_lo + (int)((key >> 10) & 63u);
             const int y = ti.wy0[ii] + p / ti.ww[ii], x = ti.wx0[ii] + p % ti.ww[ii];
-            const int iy = tyi * REF_TILE + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
+            const int iy = iya + ii / REF_TILE, ix = txi * REF_TILE + ii % REF_TILE;
             const int64_t r = ((int64_t)t * g.ny + iy) * g.nx + ix;
             idx_out[r * K + lane] = (f * g.h + y) * g.w + x;
             if (dist_out) dist_out[r * K + lane] = (int32_t)(key >> 16);
@@ -689,8 +692,8 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     }
 }
 
-template <int NPL>
-__global__ __launch_bounds__(BMT) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
+template <int NPL, int TR = REF_TILE>
+__global__ __launch_bounds__(256 * TR, TR == REF_TILE ? 4 : 6) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                  BmLds L, int32_t *__restrict__ idx_out,
                                                  int32_t *__restrict__ dist_out) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -701,7 +704,7 @@ __global__ __launch_bounds__(BMT) void bm_kernel(ImageGeom g, MethodParams mp, i
     const int per = (n_tiles + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= n_tiles) return;
-    bm_tile<false, NPL>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
+    bm_tile<false, NPL, false, TR>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
 }
 
 // Spatio-temporal form: n_tiles covers the tiles of all frames.
@@ -720,10 +723,10 @@ __global__ __launch_bounds__(BMT, ONE && NPL < 16 ? 8 : 4) void bm_video_kernel(
 }
 
 // Persistent form over many images: each workgroup pulls (image, tile) units from a queue.
-template <int NPL>
-__global__ __launch_bounds__(BMT, NPL == 16 ? 4 : 8) void bm_kernel_batched(const BatchItem *__restrict__ items, int n_items,
-                                                         const int *__restrict__ unit_start, BmLds L,
-                                                         int *__restrict__ queue) {
+template <int NPL, int TR = REF_TILE>
+__global__ __launch_bounds__(256 * TR, NPL < 16 ? 8 : (TR < REF_TILE ? 6 : 4)) void bm_kernel_batched(
+    const BatchItem *__restrict__ items, int n_items, const int *__restrict__ unit_start, BmLds L,
+    int *__restrict__ queue) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ TileInfo ti;
     __shared__ int s_u;
@@ -736,7 +739,7 @@ __global__ __launch_bounds__(BMT, NPL == 16 ? 4 : 8) void bm_kernel_batched(cons
         if (u >= total) break;
         const int i = find_unit(unit_start, n_items, u);
         const BatchItem it = items[i];
-        bm_tile<false, NPL>(it.g, it.mp, it.bm_tiles_x, u - unit_start[i], L, it.idx, nullptr, smem, ti, VideoArgs{});
+        bm_tile<false, NPL, false, TR>(it.g, it.mp, it.bm_tiles_x, u - unit_start[i], L, it.idx, nullptr, smem, ti, VideoArgs{});
         __syncthreads();
     }
 }
@@ -745,7 +748,7 @@ __global__ __launch_bounds__(BMT, NPL == 16 ? 4 : 8) void bm_kernel_batched(cons
 int bm_npl(int n) { return n <= 256 ? 4 : (n <= 448 ? 7 : (n <= 640 ? 10 : 16)); }
 int bm_tab_stride(int npl) { return npl == 11 ? tab_stride<11>() : npl == 4 ? tab_stride<4>() : (npl == 7 ? tab_stride<7>() : (npl == 10 ? tab_stride<10>() : tab_stride<16>())); }
 
-BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool one = false) {
+BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool one = false, int tile_rows = REF_TILE) {
     BmLds L;
     L.rows = uh_max + PS - 1;
     // The int8 planes: rows of 96 bytes (enough for a union of 64 columns plus the patch and the
@@ -755,7 +758,7 @@ BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool on
     // reads per bank against 2 to 4 for tightly packed rows, whether 32 or 64 banks serve a
     // half or a whole wave).
     const int pitch_min = ((uw_max + PS + 3) / 4) * 4 + 4;
-    L.pitch8 = pitch_min > 96 ? pitch_min : 96;
+    L.pitch8 = pitch_min > 96 || tile_rows < REF_TILE ? pitch_min : 96;
     L.plane8 = L.rows * L.pitch8 + 16;
     L.pitch16 = ((uw_max + PS + 1) / 2) * 2 + 2;
     int off = 0;
@@ -768,7 +771,7 @@ BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool on
     off = (off + 15) & ~15;
     L.off_tab = off;
     // the last row is read to 64 npl words
-    int tab_bytes = ((NREF - 1) * bm_tab_stride(npl) + std::max(bm_tab_stride(npl), 64 * npl)) * 4;
+    int tab_bytes = ((4 * tile_rows - 1) * bm_tab_stride(npl) + std::max(bm_tab_stride(npl), 64 * npl)) * 4;
     // row sums of the norm pass live in the table, unless that holds the windows of earlier frames
     // (the columns of the norm pass read up to 3 rows past the last)
     const int rs_bytes = 2 * L.rows * uw_max * 4 + (one ? 3 * uw_max * 4 : 0);
@@ -783,25 +786,60 @@ BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool on
 
 }  // namespace
 
+namespace {
+
+// Launch shape for images up to h x w, steps up to s and windows up to W: register rows, rows of
+// references per tile, LDS layout and whether two workgroups fit a CU.
+struct BmShape {
+    int npl, rows;
+    BmLds L;
+    bool two;
+};
+
+BmShape bm_shape(int s, int W, int h, int w) {
+    BmShape r;
+    // largest union of windows over a tile: 3 grid steps plus the window, capped by the image
+    const int uw = min((REF_TILE - 1) * s + W, w - PS + 1);
+    r.npl = bm_npl(min(W, h - PS + 1) * min(W, w - PS + 1));
+    auto layout = [&](int rows) {
+        r.rows = rows;
+        r.L = bm_lds_layout(min((rows - 1) * s + W, h - PS + 1), uw, r.npl, false, false, rows);
+        r.two = 2 * (r.L.total + (int)sizeof(TileInfo) + 64) <= 160 * 1024;
+    };
+    // The phases of a tile are separated by barriers, and only another workgroup fills the waits
+    // behind them.  The table of 16 references with windows past 640 positions takes 62 KB and leaves no
+    // room for a second one; 12 references with 12 waves do up to step 4: 12 MP, window 31, step 3, 4.15 ->
+    // 3.44 ms, 512 x 512, step 4, 87 -> 68 us, though a tile's staging and matrix products serve fewer.
+    // Where two tiles of 12 do not fit either, 16 references share the staging.
+    if (r.npl == 16) layout(3);
+    if (r.npl < 16 || !r.two) layout(REF_TILE);
+    return r;
+}
+
+}  // namespace
+
+int bm_tile_rows(int s, int W, int h, int w) { return bm_shape(s, W, h, w).rows; }
+
 hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_t *idx, int32_t *dist,
                               hipStream_t st) {
-    const int tiles_y = (g.ny + REF_TILE - 1) / REF_TILE, tiles_x = (g.nx + REF_TILE - 1) / REF_TILE;
-    const int n_tiles = tiles_y * tiles_x;
-    // largest union of windows over a tile: 3 grid steps plus the window, capped by the image
-    const int span = (REF_TILE - 1) * g.s + mp.W;
-    const int uh = span < g.h - PS + 1 ? span : g.h - PS + 1;
-    const int uw = span < g.w - PS + 1 ? span : g.w - PS + 1;
-    const int npl = bm_npl(min(mp.W, g.h - PS + 1) * min(mp.W, g.w - PS + 1));
-    const BmLds L = bm_lds_layout(uh, uw, npl);
+    const BmShape sh = bm_shape(g.s, mp.W, g.h, g.w);
+    const int tiles_x = (g.nx + REF_TILE - 1) / REF_TILE;
+    const int n_tiles = (g.ny + sh.rows - 1) / sh.rows * tiles_x;
     // round the grid up to a multiple of 8 so the XCD remap is a bijection onto [0, 8*per)
     const int per = (n_tiles + 7) / 8;
     auto go = [&](auto kernel) {
-        const hipError_t e = prepare_dynamic_lds((const void *)kernel, L.total, (int)sizeof(TileInfo));
+        const hipError_t e = prepare_dynamic_lds((const void *)kernel, sh.L.total, (int)sizeof(TileInfo));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(BMT), L.total, st, g, mp, tiles_x, n_tiles, L, idx, dist);
+        hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(256 * sh.rows), sh.L.total, st, g, mp, tiles_x, n_tiles, sh.L, idx,
+                           dist);
         return hipGetLastError();
     };
-    return npl == 4 ? go(bm_kernel<4>) : (npl == 7 ? go(bm_kernel<7>) : (npl == 10 ? go(bm_kernel<10>) : go(bm_kernel<16>)));
+    switch (sh.npl) {
+        case 4: return go(bm_kernel<4>);
+        case 7: return go(bm_kernel<7>);
+        case 10: return go(bm_kernel<10>);
+        default: return sh.rows == 3 ? go(bm_kernel<16, 3>) : go(bm_kernel<16>);
+    }
 }
 
 // Spatio-temporal block matching of T frames of g.h rows stacked from g.img (Sec. IV-C): the
@@ -848,31 +886,25 @@ hipError_t launch_block_match_video(const ImageGeom &g, const MethodParams &mp, 
                                 : (npl == 10 ? go(bm_video_kernel<10, false>) : go(bm_video_kernel<16, false>)));
 }
 
-// Batched block matching: one persistent launch over the tiles of all images; the LDS layout
-// is the largest any image of the batch needs.
+// Batched block matching: one persistent launch over the tiles of all images (bm_tile_rows of the
+// same limits to a tile), `grid` workgroups or, where two fit a CU, twice as many; the LDS layout is
+// the largest any image of the batch needs.
 hipError_t launch_block_match_batched(const BatchItem *items, int n_items, const int *unit_start, int max_s,
-                                      int max_W, int max_h, int max_w, int *queue, int grid, hipStream_t st) {
-    const int span = (REF_TILE - 1) * max_s + max_W;
-    const int uh = span < max_h - PS + 1 ? span : max_h - PS + 1;
-    const int uw = span < max_w - PS + 1 ? span : max_w - PS + 1;
-    const int npl = bm_npl(min(max_W, max_h - PS + 1) * min(max_W, max_w - PS + 1));
-    const BmLds L = bm_lds_layout(uh, uw, npl);
+                                      int max_W, int max_h, int max_w, int *queue, int grid, int units, hipStream_t st) {
+    const BmShape sh = bm_shape(max_s, max_W, max_h, max_w);
+    const int n = min(sh.two ? 2 * grid : grid, units);
     auto go = [&](auto kernel) {
-        const hipError_t e = prepare_dynamic_lds((const void *)kernel, L.total, (int)sizeof(TileInfo) + 16);
+        const hipError_t e = prepare_dynamic_lds((const void *)kernel, sh.L.total, (int)sizeof(TileInfo) + 16);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BMT), L.total, st, items, n_items, unit_start, L, queue);
+        hipLaunchKernelGGL(kernel, dim3(n), dim3(256 * sh.rows), sh.L.total, st, items, n_items, unit_start, sh.L, queue);
         return hipGetLastError();
     };
-    return npl == 4 ? go(bm_kernel_batched<4>)
-                    : (npl == 7 ? go(bm_kernel_batched<7>)
-                                : (npl == 10 ? go(bm_kernel_batched<10>) : go(bm_kernel_batched<16>)));
-}
-
-int bm_lds_bytes(int s, int W, int h, int w) {
-    const int span = (REF_TILE - 1) * s + W;
-    const int uh = span < h - PS + 1 ? span : h - PS + 1;
-    const int uw = span < w - PS + 1 ? span : w - PS + 1;
-    return bm_lds_layout(uh, uw, bm_npl(min(W, h - PS + 1) * min(W, w - PS + 1))).total;
+    switch (sh.npl) {
+        case 4: return go(bm_kernel_batched<4>);
+        case 7: return go(bm_kernel_batched<7>);
+        case 10: return go(bm_kernel_batched<10>);
+        default: return sh.rows == 3 ? go(bm_kernel_batched<16, 3>) : go(bm_kernel_batched<16>);
+    }
 }
 
 hipError_t prepare_dynamic_lds(const void *kernel, int bytes, int static_bytes) {

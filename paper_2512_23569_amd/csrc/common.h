@@ -269,7 +269,9 @@ hipError_t launch_vote(const ImageGeom &g, const MethodParams &mp, const int32_t
 
 // ---- batched (persistent, work-queue) forms ----
 hipError_t launch_block_match_batched(const BatchItem *items, int n_items, const int *unit_start, int max_s,
-                                      int max_W, int max_h, int max_w, int *queue, int grid, hipStream_t st);
+                                      int max_W, int max_h, int max_w, int *queue, int grid, int units, hipStream_t st);
+// Rows of references per tile of block matching (REF_TILE columns), for images, steps and windows up to these.
+int bm_tile_rows(int s, int W, int h, int w);
 hipError_t launch_filter_batched(int C, int K, const BatchItem *items, int n_items, const int *unit_start, int lds,
                                  const BasisDev &b, unsigned long long *gc, int *queue, int grid, hipStream_t st);
 hipError_t launch_gather_batched(int C, const BatchItem *items, int n_items, const int *pix_start, int total_px,
