@@ -457,9 +457,10 @@ htsvd_status run_cnn_map(htsvd_ctx *ctx, const ImageGeom &g, hipStream_t st, con
     return HTSVD_OK;
 }
 
-htsvd_status run_bm(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &mp, const Ws &w, hipStream_t st) {
+htsvd_status run_bm(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &mp, const Ws &w, hipStream_t st,
+                    const BmExtra &extra = BmExtra{}) {
     StageScope sc(ctx, HTSVD_STAGE_BM, st);
-    hipError_t e = launch_block_match(g, mp, w.idx, nullptr, st);
+    hipError_t e = launch_block_match(g, mp, w.idx, nullptr, st, extra);
     if (e != hipSuccess) return hip_fail(e, "block matching");
     return HTSVD_OK;
 }
@@ -472,6 +473,7 @@ htsvd_status run_sigma(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &m
     const int T = p->subimage;
     const int n_tiles = ((g.h + T - 1) / T) * ((g.w + T - 1) / T);
     hipError_t e;
+    const double *sigma2 = nullptr;
     if (sigma > 0.f) {
         if ((e = launch_fill_const(w.sig_est, n_tiles, (double)sigma, st)) != hipSuccess) return hip_fail(e, "sigma");
     } else if (p->estimator == 1) {
@@ -479,11 +481,15 @@ htsvd_status run_sigma(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &m
         if ((e = launch_sigma_est(g, T, w.mom, w.cov, w.sig_plain, st)) != hipSuccess) return hip_fail(e, "sigma estimation");
         if ((e = launch_learned_judge(g, T, zmap, w.sig_plain, JUDGE_RATIO, w.use_plain, w.sig_est, st)) != hipSuccess)
             return hip_fail(e, "sigma judge");
+    } else if (p->adaptive) {   // the vote combines the channels
+        if ((e = launch_sigma2_units(g, T, 0, n_tiles * g.c, w.mom, w.cov, st)) != hipSuccess)
+            return hip_fail(e, "sigma estimation");
+        sigma2 = w.cov;
     } else {
         if ((e = launch_sigma_est(g, T, w.mom, w.cov, w.sig_est, st)) != hipSuccess) return hip_fail(e, "sigma estimation");
     }
     if (p->adaptive) {
-        if ((e = launch_vote(g, mp, w.idx, T, p->n_vote, p->vote_seed, p->gamma_rank, p->beta, w.sig_est,
+        if ((e = launch_vote(g, mp, w.idx, T, p->n_vote, p->vote_seed, p->gamma_rank, p->beta, sigma2, w.sig_est,
                              w.sig_hat, w.votes, st)) != hipSuccess)
             return hip_fail(e, "vote");
     } else {
@@ -495,13 +501,14 @@ htsvd_status run_sigma(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &m
     return HTSVD_OK;
 }
 
+// cleared: an earlier launch of the call has set the counters to zero.
 htsvd_status run_filter(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &mp, const Ws &w,
-                        const double *tau, float *d_out, int64_t out_stride, hipStream_t st,
+                        const double *tau, float *d_out, int64_t out_stride, hipStream_t st, bool cleared,
                         const float *ra_d = nullptr, const uint8_t *ra_flag = nullptr) {
     hipError_t e;
     {
         StageScope sc(ctx, HTSVD_STAGE_CLEAR, st);
-        if ((e = launch_zero(ctx->d_guard, 2 * sizeof(unsigned long long), st)) != hipSuccess)
+        if (!cleared && (e = launch_zero(ctx->d_guard, 2 * sizeof(unsigned long long), st)) != hipSuccess)
             return hip_fail(e, "zero counters");
     }
     {
@@ -1106,7 +1113,9 @@ htsvd_status htsvd_denoise_tau(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
     if ((s = ensure_ws(ctx, off_ra + (p->ra ? ra_ws_bytes(g) : 0))) != HTSVD_OK) return s;
     Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile);
     hipStream_t st = (hipStream_t)stream;
-    if ((s = run_bm(ctx, g, mp, wk, st)) != HTSVD_OK) return s;
+    BmExtra extra;
+    extra.guard = ctx->d_guard;
+    if ((s = run_bm(ctx, g, mp, wk, st, extra)) != HTSVD_OK) return s;
     const float *ra_d = nullptr;
     const uint8_t *ra_f = nullptr;
     if (p->ra) {
@@ -1115,7 +1124,7 @@ htsvd_status htsvd_denoise_tau(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
             HTSVD_OK)
             return s;
     }
-    return run_filter(ctx, g, mp, wk, d_tau_ref, d_out, out_stride, st, ra_d, ra_f);
+    return run_filter(ctx, g, mp, wk, d_tau_ref, d_out, out_stride, st, true, ra_d, ra_f);
 }
 
 }  // extern "C"
@@ -1159,11 +1168,15 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     hipStream_t st = (hipStream_t)stream;
     const float *zmap = nullptr;
     if (learned && (s = run_cnn_map(ctx, g, st, &zmap)) != HTSVD_OK) return s;
-    if ((s = run_bm(ctx, g, mp, wk, st)) != HTSVD_OK) return s;
-    hipError_t e;
+    BmExtra extra;   // one threshold for all references is written along with the groups
+    extra.guard = ctx->d_guard;
     if (sigma > 0.f && !p->adaptive) {
-        e = launch_fill_tau(wk.tau, (int64_t)g.ny * g.nx, nullptr, (double)sigma, mult, g, tile, st);
-    } else {
+        extra.tau = wk.tau;
+        extra.value = (double)sigma * mult;
+    }
+    if ((s = run_bm(ctx, g, mp, wk, st, extra)) != HTSVD_OK) return s;
+    hipError_t e = hipSuccess;
+    if (!extra.tau) {
         if ((s = run_sigma(ctx, g, mp, p, sigma, wk, zmap, st)) != HTSVD_OK) return s;
         if (learned)
             e = launch_fill_tau_learned(wk.tau, g, tile, zmap, wk.use_plain, wk.sig_est, wk.sig_hat, mult, st);
@@ -1176,7 +1189,7 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     if (p->ra && (s = run_ra(ctx, g, mp, wk, wk.tau, (char *)ctx->ws + off_ra, mult, p->ra_sigma, st, &ra_d, &ra_f)) !=
                      HTSVD_OK)
         return s;
-    return run_filter(ctx, g, mp, wk, wk.tau, d_out, out_stride, st, ra_d, ra_f);
+    return run_filter(ctx, g, mp, wk, wk.tau, d_out, out_stride, st, true, ra_d, ra_f);
 }
 
 }  // namespace
@@ -1252,9 +1265,9 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
             wi.idx = idx_pre;
         }
         const double mult = p->tau_mult > 0.0 ? p->tau_mult : default_mult(c, it.K);
-        if ((e = launch_fill_tau(wk.tau, n_ref, nullptr, (double)it.sigma, mult, g, tile, st)) != hipSuccess)
+        if ((e = launch_fill_tau(wk.tau, n_ref, nullptr, (double)it.sigma, mult, g, tile, st, ctx->d_guard)) != hipSuccess)
             return hip_fail(e, "tau");
-        if ((s = run_filter(ctx, g, mpi, wi, wk.tau, it.d_out, it.out_stride, st)) != HTSVD_OK) return s;
+        if ((s = run_filter(ctx, g, mpi, wi, wk.tau, it.d_out, it.out_stride, st, true)) != HTSVD_OK) return s;
     }
     return HTSVD_OK;
 }

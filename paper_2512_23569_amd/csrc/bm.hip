@@ -695,7 +695,7 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
 template <int NPL, int TR = REF_TILE>
 __global__ __launch_bounds__(256 * TR, TR == REF_TILE ? 4 : 6) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                  BmLds L, int32_t *__restrict__ idx_out,
-                                                 int32_t *__restrict__ dist_out) {
+                                                 int32_t *__restrict__ dist_out, BmExtra extra) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ TileInfo ti;
     // XCD-aware order: consecutive workgroups are dealt round-robin over the 8 XCDs; give
@@ -704,6 +704,11 @@ __global__ __launch_bounds__(256 * TR, TR == REF_TILE ? 4 : 6) void bm_kernel(Im
     const int per = (n_tiles + 7) / 8;
     const int b = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (b >= n_tiles) return;
+    if (extra.guard && blockIdx.x == 0 && threadIdx.x < 2) extra.guard[threadIdx.x] = 0;
+    if (extra.tau && threadIdx.x < 4 * TR) {
+        const int iy = b / tiles_x * TR + threadIdx.x / REF_TILE, ix = b % tiles_x * REF_TILE + threadIdx.x % REF_TILE;
+        if (iy < g.ny && ix < g.nx) extra.tau[(int64_t)iy * g.nx + ix] = extra.value;
+    }
     bm_tile<false, NPL, false, TR>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
 }
 
@@ -821,7 +826,7 @@ BmShape bm_shape(int s, int W, int h, int w) {
 int bm_tile_rows(int s, int W, int h, int w) { return bm_shape(s, W, h, w).rows; }
 
 hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_t *idx, int32_t *dist,
-                              hipStream_t st) {
+                              hipStream_t st, const BmExtra &extra) {
     const BmShape sh = bm_shape(g.s, mp.W, g.h, g.w);
     const int tiles_x = (g.nx + REF_TILE - 1) / REF_TILE;
     const int n_tiles = (g.ny + sh.rows - 1) / sh.rows * tiles_x;
@@ -831,7 +836,7 @@ hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_
         const hipError_t e = prepare_dynamic_lds((const void *)kernel, sh.L.total, (int)sizeof(TileInfo));
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3(8 * per), dim3(256 * sh.rows), sh.L.total, st, g, mp, tiles_x, n_tiles, sh.L, idx,
-                           dist);
+                           dist, extra);
         return hipGetLastError();
     };
     switch (sh.npl) {

@@ -244,12 +244,20 @@ __device__ __host__ inline void region_cols(const ImageGeom &g, const TileGeom &
 hipError_t prepare_dynamic_lds(const void *kernel, int bytes, int static_bytes);
 
 // Launchers (stream-ordered, no synchronisation).
+// Small values that a launch sets along the way, each a launch of its own otherwise (3 to 5 us): the
+// thresholds of all references to one value, and the filter's two counters to zero.
+struct BmExtra {
+    double *tau = nullptr;
+    double value = 0.0;
+    unsigned long long *guard = nullptr;
+};
 hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_t *idx, int32_t *dist,
-                              hipStream_t st);
+                              hipStream_t st, const BmExtra &extra = BmExtra{});
 hipError_t launch_block_match_video(const ImageGeom &g, const MethodParams &mp, int T, int radius, int32_t *idx,
                                     int32_t *dist, hipStream_t st);
 hipError_t launch_fill_tau(double *tau_ref, int64_t n_ref, const double *sigma_tile, double sigma_const,
-                           double mult, const ImageGeom &g, int tile, hipStream_t st);
+                           double mult, const ImageGeom &g, int tile, hipStream_t st,
+                           unsigned long long *guard = nullptr);   // guard: two counters set to zero
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 // out[r*kout + k] = in[r*kin + k] for k < kout <= kin.
 hipError_t launch_idx_prefix(const int32_t *in, int kin, int32_t *out, int kout, int64_t n_ref, hipStream_t st);
@@ -263,9 +271,10 @@ hipError_t launch_sigma2_units(const ImageGeom &g, int tile, int unit0, int n_un
                                hipStream_t st);
 hipError_t launch_sigma_est(const ImageGeom &g, int tile, int32_t *mom, double *cov_work, double *sigma_est,
                             hipStream_t st);
+// sigma2: the variances of launch_sigma2_units, combined into sigma_est here, or null (sigma_est given).
 hipError_t launch_vote(const ImageGeom &g, const MethodParams &mp, const int32_t *idx, int tile, int n_vote,
-                       uint64_t seed, int gamma_rank, double beta, const double *sigma_est, double *sigma_hat,
-                       int32_t *votes, hipStream_t st);
+                       uint64_t seed, int gamma_rank, double beta, const double *sigma2, double *sigma_est,
+                       double *sigma_hat, int32_t *votes, hipStream_t st);
 
 // ---- batched (persistent, work-queue) forms ----
 hipError_t launch_block_match_batched(const BatchItem *items, int n_items, const int *unit_start, int max_s,

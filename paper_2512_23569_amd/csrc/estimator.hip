@@ -481,8 +481,7 @@ struct VoteShared {
 template <int K>
 __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, const int32_t *__restrict__ idx,
                                  int idx_stride, int T, int t, int n_vote, uint64_t seed, int gamma_rank, double beta,
-                                 const double *__restrict__ sigma_est, double *__restrict__ sigma_hat,
-                                 int32_t *__restrict__ votes) {
+                                 const double se, double *__restrict__ sigma_hat, int32_t *__restrict__ votes) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ntx = (g.w + T - 1) / T;
     const int ty = t / ntx, tx = t % ntx;
@@ -497,7 +496,6 @@ __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, 
     __syncthreads();
     const int nyr = s_iy1 - s_iy0 + 1, nxr = s_ix1 - s_ix0 + 1;
     const int64_t n_t = (s_iy0 < 0 || s_ix0 < 0) ? 0 : (int64_t)nyr * nxr;
-    const double se = sigma_est[t];
     if (n_t == 0) {
         if (tid == 0) { sigma_hat[t] = se; if (votes) votes[t] = 0; }
         return;
@@ -569,10 +567,12 @@ __device__ __forceinline__ void vote_tile(VoteShared<K> &sh, const ImageGeom g, 
 template <int K>
 __global__ __launch_bounds__(64 * VOTE_WAVES) void vote_kernel(ImageGeom g, const int32_t *__restrict__ idx, int T, int n_vote,
                                                    uint64_t seed, int gamma_rank, double beta,
-                                                   const double *__restrict__ sigma_est, double *__restrict__ sigma_hat,
-                                                   int32_t *__restrict__ votes) {
+                                                   const double *__restrict__ sigma2, double *__restrict__ sigma_est,
+                                                   double *__restrict__ sigma_hat, int32_t *__restrict__ votes) {
     __shared__ VoteShared<K> sh;
-    vote_tile<K>(sh, g, idx, K, T, blockIdx.x, n_vote, seed, gamma_rank, beta, sigma_est, sigma_hat, votes);
+    const double se = sigma2 ? combine_sigma_tile(sigma2, g.c, blockIdx.x) : sigma_est[blockIdx.x];
+    if (sigma2 && threadIdx.x == 0) sigma_est[blockIdx.x] = se;
+    vote_tile<K>(sh, g, idx, K, T, blockIdx.x, n_vote, seed, gamma_rank, beta, se, sigma_hat, votes);
 }
 
 template <int K>
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(64 * VOTE_WAVES) void vote_kernel_batched(const Sig
     // an image whose group size is chosen on the device is listed for both sizes; the launch of
     // the other size leaves it (the condition is uniform over the workgroup)
     if (it.ksel && *it.ksel != K) return;
-    vote_tile<K>(sh, it.g, it.idx, it.K, T, blockIdx.x - start[j], n_vote, seed, gamma_rank, beta, it.sig_est,
+    vote_tile<K>(sh, it.g, it.idx, it.K, T, blockIdx.x - start[j], n_vote, seed, gamma_rank, beta, it.sig_est[blockIdx.x - start[j]],
                  it.sig_hat, it.votes);
 }
 
@@ -636,13 +636,13 @@ hipError_t launch_fill_const(double *p, int n, double v, hipStream_t st) {
 }
 
 hipError_t launch_vote(const ImageGeom &g, const MethodParams &mp, const int32_t *idx, int tile, int n_vote,
-                       uint64_t seed, int gamma_rank, double beta, const double *sigma_est, double *sigma_hat,
-                       int32_t *votes, hipStream_t st) {
+                       uint64_t seed, int gamma_rank, double beta, const double *sigma2, double *sigma_est,
+                       double *sigma_hat, int32_t *votes, hipStream_t st) {
     const int n_tiles = ((g.h + tile - 1) / tile) * ((g.w + tile - 1) / tile);
 #define HV_CASE(KK)                                                                                              \
     if (mp.K == KK) {                                                                                            \
         hipLaunchKernelGGL(vote_kernel<KK>, dim3(n_tiles), dim3(64 * VOTE_WAVES), 0, st, g, idx, tile, n_vote, seed, gamma_rank, \
-                           beta, sigma_est, sigma_hat, votes);                                                   \
+                           beta, sigma2, sigma_est, sigma_hat, votes);                                           \
         return hipGetLastError();                                                                                \
     }
     HV_CASE(4) HV_CASE(8) HV_CASE(16) HV_CASE(32)

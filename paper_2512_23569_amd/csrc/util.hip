@@ -17,8 +17,9 @@ __global__ void zero_words_kernel(uint32_t *p, int64_t n) {
 }
 
 __global__ void fill_tau_kernel(double *tau, int64_t n_ref, const double *sigma_tile, double sigma_const,
-                                double mult, ImageGeom g, int tile) {
+                                double mult, ImageGeom g, int tile, unsigned long long *guard) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r == 0 && guard) guard[0] = guard[1] = 0;
     if (r >= n_ref) return;
     double s = sigma_const;
     if (sigma_tile) {
@@ -237,9 +238,9 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
 }
 
 hipError_t launch_fill_tau(double *tau_ref, int64_t n_ref, const double *sigma_tile, double sigma_const,
-                           double mult, const ImageGeom &g, int tile, hipStream_t st) {
+                           double mult, const ImageGeom &g, int tile, hipStream_t st, unsigned long long *guard) {
     hipLaunchKernelGGL(fill_tau_kernel, dim3((unsigned)((n_ref + 255) / 256)), dim3(256), 0, st, tau_ref, n_ref,
-                       sigma_tile, sigma_const, mult, g, tile);
+                       sigma_tile, sigma_const, mult, g, tile, guard);
     return hipGetLastError();
 }
 
