@@ -64,3 +64,17 @@ def test_more_values_at_the_threshold_than_the_list_holds(dn, basis1, basis3, c,
         out = dn.denoise_tau(torch.from_numpy(img).cuda(), torch.from_numpy(taus).cuda(), p).cpu().numpy()
         ref = oracle.denoise(img, U, V, taus, s=4, W=15, K=K)
         assert np.abs(out - ref).max() <= TOL
+
+
+# the counts of a video's pixels are made by tiles of 64 x 16 of the stacked frames
+@pytest.mark.parametrize("T,h,w", [(1, 15, 63), (2, 16, 64), (3, 21, 65), (2, 40, 130)])
+@pytest.mark.parametrize("c", [1, 3])
+def test_video_count_tiles(dn, basis1, basis3, T, h, w, c):
+    v = np.stack([synth.add_awgn(synth.make_clean(h, w, c, 7), 20.0, 30 + t) for t in range(T)])
+    p = dn.params(c, stride=4, window=7, K=8)
+    out = dn.denoise_video(torch.from_numpy(v).cuda(), 20.0, p, radius=1).cpu().numpy()
+    idx, _ = oracle.block_match_video(v, 8, 4, 7, 8, 1)
+    U, V = basis3 if c == 3 else basis1
+    stacked = v.reshape((T * h,) + v.shape[2:])
+    ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, 8)).reshape(v.shape)
+    assert np.abs(out - ref).max() <= TOL
