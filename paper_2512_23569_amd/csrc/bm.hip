@@ -240,9 +240,15 @@ __device__ __forceinline__ uint64_t select_k(const uint32_t (&dv)[NPL], const in
     return sel[lane];
 }
 
+// Whether the columns that blocks of 16 leave over are few enough to be taken a row per lane.  Such a
+// step makes its addresses anew, hence the factor 2.
+__host__ __device__ inline bool turn_columns(int uh, int uw) {
+    return (uw & 15) && 2 * (uw & 15) * ((uh + 15) >> 4) < uh;
+}
+
 // Groups of the 4 TR references of tile b, TR rows of 4, by as many wavefronts (VIDEO: tile b of the frames' tiles, frame-major; ONE: the
 // table holds the windows of all its frames and a reference selects once).
-template <bool VIDEO, int NPL, bool ONE = false, int TR = REF_TILE>
+template <bool VIDEO, int NPL, bool ONE = false, int TR = REF_TILE, bool TURN = false>
 __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams &mp, const int tiles_x, const int b_in,
                                         const BmLds &L, int32_t *__restrict__ idx_out,
                                         int32_t *__restrict__ dist_out, unsigned char *smem, TileInfo &ti,
@@ -536,8 +542,10 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
             // union's coordinates the references 4 q + r lie in row q and column r of the tile, so the
             // rows of their windows go with q and the columns with r; position (dy, dx) of reference
             // 4 q + r is table byte 4 (dy ww + dx) of its row.
-            const int ncb = (uw + 15) >> 4;   // 1 .. 4
-            const int wpc = ncb == 1 ? NW : (ncb == 2 ? NW / 2 : (ncb == 3 ? NW / 3 : NW / 4));   // waves per block of columns
+            // TURN: where few columns are left over, a lane takes a row of one of them instead.
+            const bool turned = TURN && turn_columns(uh, uw);
+            const int ncb = turned ? uw >> 4 : (uw + 15) >> 4;   // 0 .. 4
+            const int wpc = ncb <= 1 ? NW : (ncb == 2 ? NW / 2 : (ncb == 3 ? NW / 3 : NW / 4));   // waves per block of columns
             const int cb = (wave >= wpc) + (wave >= 2 * wpc) + (wave >= 3 * wpc), cr0 = wave - cb * wpc;
             const int cc0 = 16 * cb + i16, cc = min(cc0, uw - 1);
             const int wy = ti.wy0[4 * q] - uy0, wh = ti.ry[4 * q] >= 0 ? ti.wh[4 * q] : 0;
@@ -593,6 +601,41 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
                     m16 += wpc * uw;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) at[r] += step4[r];
+                }
+            }
+            if (TURN && turned) {
+                const int rows16 = (uh + 15) >> 4;
+#pragma unroll 1
+                for (int it = NW - 1 - wave; it < (uw & 15) * rows16; it += NW) {
+                    int i16 = lane & 15, q = lane >> 4;
+                    asm volatile("" : "+v"(i16), "+v"(q));   // nothing of this is made before the loop above
+                    const int c = (uw & ~15) + it / rows16, row = 16 * (it % rows16) + i16, cr = min(row, uh - 1);
+                    const unsigned char *t8 = p8 + (c & 3) * plane8 + (cr + 2 * q) * L.pitch8 + (c & ~3);
+                    const uint32_t *w8a = reinterpret_cast<const uint32_t *>(t8);
+                    const uint32_t *w8b = reinterpret_cast<const uint32_t *>(t8 + L.pitch8);
+                    const v4i b8 = {(int)w8a[0], (int)w8a[1], (int)w8b[0], (int)w8b[1]};
+                    const v4i acc8 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a8, b8, (v4i){0, 0, 0, 0}, 0, 0, 0);
+                    v4f acc16 = {0.f, 0.f, 0.f, 0.f};
+                    if (any_sum) {
+                        const _Float16 *t16 = p16 + (c & 1) * plane16 + (cr + q) * L.pitch16 + (c & ~1);
+                        const uint32_t *ra = reinterpret_cast<const uint32_t *>(t16);
+                        const uint32_t *rb = reinterpret_cast<const uint32_t *>(t16 + 4 * L.pitch16);
+                        const v8h b16a = __builtin_bit_cast(v8h, make_uint4(ra[0], ra[1], ra[2], ra[3]));
+                        const v8h b16b = __builtin_bit_cast(v8h, make_uint4(rb[0], rb[1], rb[2], rb[3]));
+                        acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16a, b16a, acc16, 0, 0, 0);
+                        acc16 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a16b, b16b, acc16, 0, 0, 0);
+                    }
+                    const int nb8 = n8[cr * uw + c], nb16 = any_sum ? n16[cr * uw + c] : 0;
+                    if ((unsigned)(row - wy) < (unsigned)wh) {   // the windows end within the union
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int dx = c - (ti.wx0[r] - ux0), ww = ti.ry[r] >= 0 ? ti.ww[r] : 0;
+                            const int dot = (gmask[r] & acc8[r]) | (~gmask[r] & (int)acc16[r]);
+                            const int nb = (gmask[r] & nb8) | (~gmask[r] & nb16);
+                            if ((unsigned)dx < (unsigned)ww)
+                                tab[(4 * q + r) * TAB + (row - wy) * ww + dx] = (uint32_t)(nb + rn[r] - 2 * dot);
+                        }
+                    }
                 }
             }
         }
@@ -692,8 +735,8 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     }
 }
 
-template <int NPL, int TR = REF_TILE>
-__global__ __launch_bounds__(256 * TR, TR == REF_TILE ? 4 : 6) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
+template <int NPL, int TR = REF_TILE, bool TURN = false>
+__global__ __launch_bounds__(256 * TR, TURN ? 8 : (TR == REF_TILE ? 4 : 6)) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                  BmLds L, int32_t *__restrict__ idx_out,
                                                  int32_t *__restrict__ dist_out, BmExtra extra) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -709,7 +752,7 @@ __global__ __launch_bounds__(256 * TR, TR == REF_TILE ? 4 : 6) void bm_kernel(Im
         const int iy = b / tiles_x * TR + threadIdx.x / REF_TILE, ix = b % tiles_x * REF_TILE + threadIdx.x % REF_TILE;
         if (iy < g.ny && ix < g.nx) extra.tau[(int64_t)iy * g.nx + ix] = extra.value;
     }
-    bm_tile<false, NPL, false, TR>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
+    bm_tile<false, NPL, false, TR, TURN>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
 }
 
 // Spatio-temporal form: n_tiles covers the tiles of all frames.
@@ -839,10 +882,16 @@ hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_
                            dist, extra);
         return hipGetLastError();
     };
+    // Window 21 at step 4 has a union of 33 columns: without a third block for the last one alone the
+    // matching of 1536 x 2048 gray takes 322 us instead of 425, of 509 x 763 RGB 92 instead of 118.  The
+    // form spills 7 registers, which costs a lone tile per workgroup slot more than it gains (256 x
+    // 256 gray: 16.2 against 15.3), so it needs two rounds.
+    const bool turn = n_tiles > 512 && turn_columns(min((REF_TILE - 1) * g.s + mp.W, g.h - PS + 1),
+                                                    min((REF_TILE - 1) * g.s + mp.W, g.w - PS + 1));
     switch (sh.npl) {
-        case 4: return go(bm_kernel<4>);
-        case 7: return go(bm_kernel<7>);
-        case 10: return go(bm_kernel<10>);
+        case 4: return turn ? go(bm_kernel<4, REF_TILE, true>) : go(bm_kernel<4>);
+        case 7: return turn ? go(bm_kernel<7, REF_TILE, true>) : go(bm_kernel<7>);
+        case 10: return turn ? go(bm_kernel<10, REF_TILE, true>) : go(bm_kernel<10>);
         default: return sh.rows == 3 ? go(bm_kernel<16, 3>) : go(bm_kernel<16>);
     }
 }

@@ -67,3 +67,14 @@ def test_video_groups_equal_the_oracle(dn, window, kind):
     oi, od = oracle.block_match_video(frames, 8, 5, window, 16, 1)
     assert np.array_equal(idx.cpu().numpy(), oi)
     assert np.array_equal(dist.cpu().numpy(), od)
+
+
+# unions of 33 and 17 columns with more tiles than two per CU: the column left over goes a row per lane
+@pytest.mark.parametrize("h,w,window,stride", [(431, 301, 21, 4), (330, 420, 27, 2), (270, 300, 11, 2), (300, 270, 15, 1)])
+@pytest.mark.parametrize("c", [1, 3])
+def test_groups_with_a_column_left_over(dn, h, w, window, stride, c):
+    img = _image("mixed", h, w, c, window)
+    idx, dist = dn.block_match(torch.from_numpy(img).cuda(), dn.params(c, stride=stride, window=window, K=16))
+    oi, od = oracle.block_match(img, 8, stride, window, 16)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(dist.cpu().numpy(), od)
