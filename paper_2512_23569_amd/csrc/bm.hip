@@ -882,12 +882,11 @@ hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_
                            dist, extra);
         return hipGetLastError();
     };
-    // Window 21 at step 4 has a union of 33 columns: without a third block for the last one alone the
-    // matching of 1536 x 2048 gray takes 322 us instead of 425, of 509 x 763 RGB 92 instead of 118.  The
-    // form spills 7 registers, which costs a lone tile per workgroup slot more than it gains (256 x
-    // 256 gray: 16.2 against 15.3), so it needs two rounds.
-    const bool turn = n_tiles > 512 && turn_columns(min((REF_TILE - 1) * g.s + mp.W, g.h - PS + 1),
-                                                    min((REF_TILE - 1) * g.s + mp.W, g.w - PS + 1));
+    // The form of 64 registers lets two workgroups share a CU: 509 x 763 RGB, window 21, 92 us instead of
+    // 118, and with the column left over of a union of 33 (window 21 at step 4) 1536 x 2048 gray 322 instead
+    // of 425.  It spills 7 to 11 registers, which costs a lone tile per workgroup slot more than it gains
+    // (256 x 256 gray: 16.2 against 15.3), so it needs more than two rounds.
+    const bool turn = n_tiles > 512;
     switch (sh.npl) {
         case 4: return turn ? go(bm_kernel<4, REF_TILE, true>) : go(bm_kernel<4>);
         case 7: return turn ? go(bm_kernel<7, REF_TILE, true>) : go(bm_kernel<7>);
