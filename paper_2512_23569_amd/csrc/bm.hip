@@ -421,8 +421,8 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
 
         // ---- squared norms at every candidate position (horizontal then vertical 8-sums) ----
         // Four consecutive outputs per thread from one window of 11 values, sliding (exact integers).
-        // Reads past the last valid output stay inside the staged planes and the table; the
-        // outputs they feed are not stored.
+        // Reads past the last valid output stay inside the staged planes and the row sums' place (see
+        // bm_lds_layout); the outputs they feed are not stored.
         {
             // prow x uw; but for the windows of earlier frames the table is free now
             int32_t *rs8 = reinterpret_cast<int32_t *>(ONE ? smem + L.off_rs : smem + L.off_tab);
@@ -820,9 +820,9 @@ BmLds bm_lds_layout(int uh_max, int uw_max, int npl, bool video = false, bool on
     L.off_tab = off;
     // the last row is read to 64 npl words
     int tab_bytes = ((4 * tile_rows - 1) * bm_tab_stride(npl) + std::max(bm_tab_stride(npl), 64 * npl)) * 4;
-    // row sums of the norm pass live in the table, unless that holds the windows of earlier frames
-    // (the columns of the norm pass read up to 3 rows past the last)
-    const int rs_bytes = 2 * L.rows * uw_max * 4 + (one ? 3 * uw_max * 4 : 0);
+    // row sums of the norm pass live in the table, unless that holds the windows of earlier frames;
+    // its columns read up to 3 rows past the last
+    const int rs_bytes = (2 * L.rows + 3) * uw_max * 4;
     if (!one && tab_bytes < rs_bytes) tab_bytes = rs_bytes;
     off += (tab_bytes + 15) & ~15;
     L.off_rs = off;

@@ -1,0 +1,98 @@
+"""Checks of the launches that the library's calls make, over the stand-in runtime of fake_hip.py.
+Each check runs in a process of its own (test_launches.py)."""
+import ctypes
+import re
+
+import fake_hip
+
+IN, OUT = 1 << 43, 1 << 42     # addresses of an input and an output that nothing reads
+
+
+class BmLds(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("pitch8", "pitch16", "rows", "plane8", "off_p8", "off_p16", "off_n8",
+                                              "off_n16", "off_tab", "off_rs", "total")]
+
+
+def windows_and_steps():
+    """Every accepted (window, step)."""
+    return [(W, s) for W in range(3, 32, 2) for s in range(1, (64 - W) // 3 + 1)]
+
+
+def _match_lds(launch, layout, W, s, h, w, frames):
+    """Every LDS access of a matching launch lies within the array it is meant for."""
+    L = launch.arg(layout, BmLds)
+    where = (launch.name, W, s, h, w, frames)
+    npl = int(re.search(r"ILi(\d+)E", launch.name).group(1))
+    one = "video" in launch.name and "Lb1E" in launch.name
+    rows = launch.block[0] // 256
+    assert launch.lds == L.total <= 160 * 1024, where
+    tab_stride = 964 if npl == 16 else 64 * npl + 4
+    n = min(W, h - 7) * min(W, w - 7) * (frames if one else 1)
+    uh, uw = min((rows - 1) * s + W, h - 7), min((REF_TILE - 1) * s + W, w - 7)
+    prow, pcol = uh + 7, uw + 7
+    staged = (pcol + 3) // 4 * 4
+    plane16 = L.rows * L.pitch16
+    last4 = (uw + 3) // 4 * 4 - 4
+    # staging: rows of the planes, the last row of the last copy
+    assert staged <= L.pitch8 and staged <= L.pitch16 and prow <= L.rows, where
+    assert L.off_p8 + 3 * L.plane8 + (prow - 1) * L.pitch8 + staged <= L.off_p16, where
+    assert L.off_p16 + 2 * (plane16 + (prow - 1) * L.pitch16 + staged) <= L.off_n8, where
+    # rows of the norm pass: 11 values from each fourth column, in whole words
+    assert L.off_p8 + (prow - 1) * L.pitch8 + last4 + 12 <= L.off_p16, where
+    assert L.off_p16 + 2 * ((prow - 1) * L.pitch16 + last4 + 12) <= L.off_n8, where
+    # its columns: 11 row sums from each fourth row, of both planes
+    sums = L.off_rs if one else L.off_tab
+    end = L.total if one or "video" not in launch.name else L.total - 16 * 32 * 8
+    for u in range(max(1, uh - 3), uh + 1):
+        last = 4 * ((u + 3) // 4) - 4 + 10
+        assert sums + 4 * ((u + 7) * uw + last * uw + uw) <= end, where
+    assert L.off_n8 + 4 * uh * uw <= L.off_n16 and L.off_n16 + 4 * uh * uw <= L.off_tab, where
+    # operands of the distances
+    assert L.off_p8 + 3 * L.plane8 + (uh + 6) * L.pitch8 + (uw - 1) // 4 * 4 + 8 <= L.off_p16, where
+    assert L.off_p16 + 2 * (plane16 + (uh + 6) * L.pitch16 + (uw - 1) // 2 * 2 + 8) <= L.off_n8, where
+    # the table: a window to a row, whole register rows read
+    assert n <= 64 * npl and n <= tab_stride, where
+    assert L.off_tab + 4 * ((4 * rows - 1) * tab_stride + max(tab_stride, 64 * npl)) <= (L.off_rs if one else end), where
+
+
+REF_TILE = 4
+
+
+def match_lds():
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    # images and frames larger than any union of windows, and sides that cut it to its parts
+    sizes = [(200, 200), (38, 200), (200, 39), (46, 47), (64, 70), (15, 200), (200, 9)]
+    for W, s in windows_and_steps():
+        for h, w in sizes:
+            p = f.params(1, stride=s, window=W, K=4)
+            ref = ctypes.byref(p)
+            seen = []
+            f.watch = lambda l: seen.append(l) or _match_lds(l, 4, W, s, h, w, 1)
+            f.call("htsvd_block_match", ctx, IN, h, w, 1, w, ref, OUT, OUT, None)
+            assert len(seen) == 1
+            for T, radius in ((1, 0), (3, 1), (7, 2), (70, 31)):
+                seen = []
+                f.watch = lambda l: seen.append(l) or _match_lds(l, 5, W, s, h, w, min(2 * radius + 1, T))
+                f.call("htsvd_block_match_video", ctx, IN, T, h, w, 1, w, radius, ref, OUT, OUT, None)
+                assert len(seen) == 1
+
+
+def match_lds_batched():
+    f = fake_hip.FakeHip()
+    ctx = f.context((1,))
+    ht = f.ht
+    opts = ht.htsvd_batch_opts(0, 1, 0.0, 0)
+    for W, s in windows_and_steps():
+        if ((W - 1) // 2 + 1) ** 2 < 4:
+            continue
+        p = f.params(1, stride=s, window=W, K=4)
+        for (h, w), other in (((200, 200), (40, 40)), ((38, 200), (15, 70)), ((46, 47), (46, 47))):
+            imgs = (ht.htsvd_image * 2)(*[ht.htsvd_image(IN, a, b, 1, b, 20.0, 4, OUT, b) for a, b in ((h, w), other)])
+
+            def look(l):
+                if "bm_kernel_batched" in l.name:   # an image's own tiles lie in the layout of the largest
+                    _match_lds(l, 3, W, s, max(h, other[0]), max(w, other[1]), 1)
+
+            f.watch = look
+            f.call("htsvd_denoise_batch", ctx, 2, imgs, ctypes.byref(p), ctypes.byref(opts), None)

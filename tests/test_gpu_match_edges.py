@@ -78,3 +78,16 @@ def test_groups_with_a_column_left_over(dn, h, w, window, stride, c):
     oi, od = oracle.block_match(img, 8, stride, window, 16)
     assert np.array_equal(idx.cpu().numpy(), oi)
     assert np.array_equal(dist.cpu().numpy(), od)
+
+
+# steps wide enough that the row sums of the norm pass, not the table, size the table's place
+@pytest.mark.parametrize("window,stride", [(7, 14), (15, 9), (15, 13), (15, 16), (21, 12), (21, 14)])
+@pytest.mark.parametrize("c", [1, 3])
+def test_groups_at_wide_steps(dn, window, stride, c):
+    img = _image("mixed", 117, 141, c, window)
+    x = torch.from_numpy(img).cuda()
+    p = dn.params(c, stride=stride, window=window, K=16)
+    idx, dist = dn.block_match(x, p)
+    oi, od = oracle.block_match(img, 8, stride, window, 16)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(dist.cpu().numpy(), od)

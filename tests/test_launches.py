@@ -1,0 +1,10 @@
+"""What the library's calls launch: sizes and layouts over everything that the calls accept, checked
+on the host (launch_checks.py) without a GPU."""
+import pytest
+
+import fake_hip
+
+
+@pytest.mark.parametrize("check", ["match_lds", "match_lds_batched"])
+def test_launches(check):
+    fake_hip.run("launch_checks", check + "()")
