@@ -112,11 +112,13 @@ htsvd_status htsvd_basis_gram(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, in
  * V_hat^(f) those of C_col = sum_P P_hat^H P_hat over all reference patches of the grid of
  * step `stride`, by descending eigenvalue, each with the phase that makes its entry of largest
  * modulus (the first among equals) real and positive; slices f and c-f are conjugate, so U and
- * V are real.  The sums run on the device (see htsvd_basis_gram); the 8x8 eigendecompositions
- * run on the host.  h_U, h_V (host, ps*ps*c FP64 each, slice-major as in htsvd_set_basis) receive
+ * V are real.  The sums run on the device (see htsvd_basis_gram), and so do the 8x8
+ * eigendecompositions of a cube's slices (c = 2 or 4 .. 64); those of c = 1 and 3 run on the host.
+ * h_U, h_V (host, ps*ps*c FP64 each, slice-major as in htsvd_set_basis) receive
  * the pair when not NULL.  Synchronises `stream`; like htsvd_set_basis, it must not overlap a
  * running call that uses the basis for c channels.  Errors as htsvd_basis_gram, plus those of
- * htsvd_set_basis and HTSVD_EDEVICE / HTSVD_ENOMEM from the device. */
+ * htsvd_set_basis and HTSVD_EDEVICE / HTSVD_ENOMEM from the device; the basis of a cube that was
+ * installed before then stays installed (also where htsvd_set_basis fails). */
 htsvd_status htsvd_learn_basis(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_t w, int32_t c,
                                int64_t in_stride, int32_t ps, int32_t stride, double *h_U, double *h_V,
                                void *stream);

@@ -112,6 +112,8 @@ struct htsvd_ctx {
     int bands = 0;                          // band count of the hyperspectral basis (0: none)
     double *d_band_maps = nullptr;          // its D, Dinv and slice maps (FP64)
     size_t band_maps_n = 0;                 // its capacity (doubles)
+    double *d_band_next = nullptr;          // the next basis is made here (see install_maps)
+    size_t band_next_n = 0;
     int64_t band_cap = (int64_t)4 << 30;    // bytes per patch matrix of one pass of the band filter
     // Optional per-stage timing with HIP events recorded on the call's stream.
     bool timing = false;
@@ -599,23 +601,30 @@ htsvd_status build_band_maps(int B, const double *h_U, const double *h_V, std::v
     return HTSVD_OK;
 }
 
-// Uploads maps into *d (replacing what it held).  Synchronises the device first.
-// The maps' buffer, for n doubles, with no call still using it.
-htsvd_status ensure_maps(htsvd_ctx *ctx, size_t n) {
+// Buffer for the maps of a new basis, n doubles, with no call still using it.  The installed basis
+// stays in use until install_maps, so a call that fails in between leaves it as it was.
+htsvd_status ensure_next_maps(htsvd_ctx *ctx, size_t n) {
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "synchronise before basis upload");
-    if (ctx->band_maps_n >= n) return HTSVD_OK;
-    if (ctx->d_band_maps) (void)hipFree(ctx->d_band_maps);
-    ctx->d_band_maps = nullptr;
-    ctx->band_maps_n = 0;
-    if (hipMalloc(&ctx->d_band_maps, sizeof(double) * n) != hipSuccess) {
-        ctx->d_band_maps = nullptr;
+    if (ctx->band_next_n >= n) return HTSVD_OK;
+    if (ctx->d_band_next) (void)hipFree(ctx->d_band_next);
+    ctx->d_band_next = nullptr;
+    ctx->band_next_n = 0;
+    if (hipMalloc(&ctx->d_band_next, sizeof(double) * n) != hipSuccess) {
+        ctx->d_band_next = nullptr;
         (void)hipGetLastError();
         return fail(HTSVD_ENOMEM, "basis allocation");
     }
-    ctx->band_maps_n = n;
+    ctx->band_next_n = n;
     return HTSVD_OK;
+}
+
+// Makes the maps in d_band_next (complete on the device) the basis for B bands.
+void install_maps(htsvd_ctx *ctx, int B) {
+    std::swap(ctx->d_band_maps, ctx->d_band_next);
+    std::swap(ctx->band_maps_n, ctx->band_next_n);
+    ctx->bands = B;
 }
 
 size_t band_maps_doubles(int B) { return (size_t)2 * band_nb(B) * band_nb(B) + (size_t)2 * (B / 2 + 1) * 512; }
@@ -624,11 +633,10 @@ htsvd_status set_basis_bands(htsvd_ctx *ctx, int B, const double *h_U, const dou
     std::vector<double> maps;
     htsvd_status s = build_band_maps(B, h_U, h_V, maps);
     if (s != HTSVD_OK) return s;
-    ctx->bands = 0;
-    if ((s = ensure_maps(ctx, maps.size())) != HTSVD_OK) return s;
-    const hipError_t e = hipMemcpy(ctx->d_band_maps, maps.data(), sizeof(double) * maps.size(), hipMemcpyHostToDevice);
+    if ((s = ensure_next_maps(ctx, maps.size())) != HTSVD_OK) return s;
+    const hipError_t e = hipMemcpy(ctx->d_band_next, maps.data(), sizeof(double) * maps.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "basis upload");
-    ctx->bands = B;
+    install_maps(ctx, B);
     return HTSVD_OK;
 }
 
@@ -817,6 +825,7 @@ void htsvd_destroy(htsvd_ctx *ctx) {
     if (ctx->d_guard) (void)hipFree(ctx->d_guard);
     if (ctx->d_gram) (void)hipFree(ctx->d_gram);
     if (ctx->d_band_maps) (void)hipFree(ctx->d_band_maps);
+    if (ctx->d_band_next) (void)hipFree(ctx->d_band_next);
     for (int i = 0; i < 2; ++i) {
         RaState &r = ctx->ra[i];
         for (void *q : {(void *)r.w, (void *)r.m, (void *)r.v, (void *)r.grad, (void *)r.frag, (void *)r.frag3t,
@@ -1052,22 +1061,19 @@ htsvd_status htsvd_learn_basis(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
         ctx->d_gram_n = std::max<size_t>(gram_n, 2 * 9 * 64);
     }
     hipStream_t st = (hipStream_t)stream;
-    if (on_device) {
-        if ((s = ensure_maps(ctx, band_maps_doubles(c))) != HTSVD_OK) return s;
-        ctx->bands = 0;
-    }
+    if (on_device && (s = ensure_next_maps(ctx, band_maps_doubles(c))) != HTSVD_OK) return s;
     if ((e = launch_gram(d_in, in_stride, h, w, c, stride, ctx->d_gram, st)) != hipSuccess)
         return hip_fail(e, "Gram sums");
     if (on_device) {
         double *uv = nullptr;
-        if ((e = launch_band_learn(ctx->d_gram, c, band_nb(c), ctx->d_gram + sums_n, ctx->d_band_maps, &uv, st)) !=
+        if ((e = launch_band_learn(ctx->d_gram, c, band_nb(c), ctx->d_gram + sums_n, ctx->d_band_next, &uv, st)) !=
             hipSuccess)
             return hip_fail(e, "basis");
         std::vector<double> UV((size_t)2 * 64 * c);
         if ((e = hipMemcpyAsync(UV.data(), uv, sizeof(double) * UV.size(), hipMemcpyDeviceToHost, st)) != hipSuccess ||
             (e = hipStreamSynchronize(st)) != hipSuccess)
             return hip_fail(e, "basis download");
-        ctx->bands = c;
+        install_maps(ctx, c);
         if (h_U) memcpy(h_U, UV.data(), sizeof(double) * 64 * c);
         if (h_V) memcpy(h_V, UV.data() + (size_t)64 * c, sizeof(double) * 64 * c);
         return HTSVD_OK;

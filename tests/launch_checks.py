@@ -96,3 +96,67 @@ def match_lds_batched():
 
             f.watch = look
             f.call("htsvd_denoise_batch", ctx, 2, imgs, ctypes.byref(p), ctypes.byref(opts), None)
+
+
+def failed_basis_keeps_the_installed_one():
+    """A basis for another band count that runs out of memory or cannot launch leaves the installed
+    one, and its maps, in use."""
+    import numpy as np
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    ht = f.ht
+    eye = np.zeros((64, 8, 8))
+    eye[0] = np.eye(8)
+    h = w = 40
+    p = f.params(1, stride=4, window=15, K=4)
+
+    def denoise(bands):
+        maps = []
+
+        def look(l):
+            if "band_rows_kernel" in l.name:
+                maps.extend(l.arg(i, ctypes.c_uint64) for i in (6, 7, 8, 9))
+
+        f.watch = look
+        f.call("htsvd_denoise_bands", ctx, IN, h, w, bands, w * bands, ctypes.c_float(20.0), ctypes.byref(p), OUT,
+               w * bands, None)
+        assert len(maps) == 4 and all(f.holds(a) for a in maps), (bands, maps)
+
+    def learn(bands, expect=0):
+        f.call("htsvd_learn_basis", ctx, IN, h, w, bands, w * bands, 8, 4, None, None, None, expect=expect)
+
+    def install(bands, expect=0):
+        U = np.ascontiguousarray(eye[:bands])
+        f.call("htsvd_set_basis", ctx, 8, bands, U.ctypes.data, U.ctypes.data, expect=expect)
+
+    small = 4
+    for first in (install, learn):
+        for second in (install, learn):
+            for big in (20, 64):
+                first(small)
+                denoise(small)
+                allocations = 0
+                for fail in range(8):   # the first, second, ... allocation of the call fails
+                    f.c.fake_fail_malloc(fail)
+                    before = len(f.live)
+                    done = getattr(f.L, "htsvd_set_basis" if second is install else "htsvd_learn_basis")
+                    U = np.ascontiguousarray(eye[:big])
+                    args = (ctx, 8, big, U.ctypes.data, U.ctypes.data) if second is install else \
+                        (ctx, IN, h, w, big, w * big, 8, 4, None, None, None)
+                    status = done(*args)
+                    f.c.fake_fail_malloc(-1)
+                    if status == 0:
+                        denoise(big)
+                        break
+                    assert status == ht.HTSVD_ENOMEM, (status, before)
+                    allocations += 1
+                    denoise(small)
+                f.c.fake_fail_launches(1)
+                learn(big // 2, expect=ht.HTSVD_EDEVICE)
+                f.c.fake_fail_launches(0)
+                denoise(big)
+                learn(big)
+                denoise(big)
+    ht.htsvd_destroy(ctx)
+    # everything but the fixed scratch array was given back
+    assert sorted(f.live.values()) == [64 << 20], f.live
