@@ -1090,9 +1090,11 @@ __global__ void ga_gather_kernel(const int *__restrict__ regions, TileGeom tg, V
         const int plane = region_plane(tg);
         const int tyf = (vt.ny_frame + tg.TY - 1) / tg.TY;
         const int span_y = tg.TY * s, span_x = tg.TX * s;
-        // tiles whose region rows r0 .. r0 + RH - 1 can hold y: r0 = max(0, first reference row - R)
-        const int ty_hi = min(tyf - 1, (y + tg.R) / span_y + 1), ty_lo = max(0, (y + tg.R - vt.RH) / span_y - 1);
-        const int tx_hi = min(tg.tiles_x - 1, (x + tg.R) / span_x + 1), tx_lo = max(0, (x + tg.R - vt.RW) / span_x - 1);
+        // tiles whose region rows r0 .. r0 + RH - 1 can hold y: r0 = max(0, first reference row - R), and
+        // the windows end R + 7 past the last reference (RH, which ends at the frame, says less: a tile
+        // whose r0 is 0 may reach every row of a small frame)
+        const int ty_hi = min(tyf - 1, (y + tg.R) / span_y + 1), ty_lo = max(0, (y - tg.R - PS - span_y) / span_y - 1);
+        const int tx_hi = min(tg.tiles_x - 1, (x + tg.R) / span_x + 1), tx_lo = max(0, (x - tg.R - PS - span_x) / span_x - 1);
         long long acc[C];
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) acc[ch] = 0;

@@ -78,3 +78,21 @@ def test_video_count_tiles(dn, basis1, basis3, T, h, w, c):
     stacked = v.reshape((T * h,) + v.shape[2:])
     ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, 8)).reshape(v.shape)
     assert np.abs(out - ref).max() <= TOL
+
+
+# frames smaller than a window's reach, with tiles of few references: a pixel then lies in the regions of
+# tiles many places before its own
+@pytest.mark.parametrize("T,h,w,radius,stride,window,K", [
+    (1, 70, 16, 0, 1, 27, 32), (2, 19, 13, 0, 2, 31, 32), (3, 12, 33, 1, 2, 27, 32), (2, 33, 12, 1, 1, 31, 8),
+    (3, 21, 22, 2, 1, 31, 16), (2, 40, 41, 1, 1, 31, 32), (6, 30, 70, 2, 2, 31, 32),
+])
+@pytest.mark.parametrize("c", [1, 3])
+def test_video_frames_smaller_than_the_windows(dn, basis1, basis3, T, h, w, radius, stride, window, K, c):
+    v = np.stack([synth.add_awgn(synth.make_clean(h, w, c, 7), 20.0, 30 + t) for t in range(T)])
+    p = dn.params(c, stride=stride, window=window, K=K)
+    out = dn.denoise_video(torch.from_numpy(v).cuda(), 20.0, p, radius=radius).cpu().numpy()
+    idx, _ = oracle.block_match_video(v, 8, stride, window, K, radius)
+    U, V = basis3 if c == 3 else basis1
+    stacked = v.reshape((T * h,) + v.shape[2:])
+    ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, K)).reshape(v.shape)
+    assert np.abs(out - ref).max() <= TOL
