@@ -374,6 +374,11 @@ __device__ inline h4 to_h4(f4 v) { return __builtin_convertvector(v, h4); }
 //      the lanes swap bits 3 and 5 in between;
 //   3. E(e, b) and O(e, b), the even and odd part of the coefficients, from Y stored as
 //      [row][re, im][e][f]: the larger of |E + O| and |E - O| is |E| + |O|.
+// The test takes 20 us however few rows there are, and up to 2,048 rows go through the FP64 transform in
+// one round of the workgroups, with a time that goes with the bands: 968 rows of 31 bands 76 us for the
+// call with the test and 60 without (16 bands: 72 and 54), 1,936 rows 88 and 82, 3,600 rows 95 and 111
+// (16 bands: 90 and 95; 7 bands: 79 and 82).  Passes of more rows than this are tested.
+inline int test_min_rows(int B) { return 2048 + 64 * (31 - B); }
 constexpr int TEST_ROWS = 8;         // rows per wave and pass: one list reservation
 constexpr int TEST_F = 544;          // bytes per frequency of Z' (512 and 8 banks)
 __global__ __launch_bounds__(256, 3) void band_test_kernel(int B, int nb, int K, int64_t n_row,
@@ -652,6 +657,12 @@ struct BandAgg {
     int TR, RH, RW;   // tile side and capacity (rows, columns) of its pixels
 };
 
+// A tile's groups go through one workgroup one after the other (16 groups of 32 members: 40 us), so tiles
+// shrink where a pass has few of them: 27 x 36 x 5, K 32, 75 us for the call with tiles of 4 x 4 and 42
+// with single references; 48 x 48 x 31, K 16, 82 and 68; 64 x 64 x 31, K 32, 136 and (2 x 2) 114.  At
+// 256 workgroups instead of 64 smaller tiles add more to memory than they gain (64 x 64 x 31: 126).
+constexpr int ADD_BLOCKS = 64;
+
 template <int K>
 __global__ __launch_bounds__(1024) void band_add_kernel(const BandAgg a, int B, const int32_t *__restrict__ idx,
                                                         const double *__restrict__ S, int64_t g0, int64_t ng, int ty0,
@@ -774,21 +785,24 @@ unsigned nb(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 template <int K>
 hipError_t launch_pass(const BandMaps &bm, const uint8_t *cube, int64_t stride, int B, const int32_t *idx, int64_t g0,
-                       int64_t ng, double tau, const BandAgg &a, double *S, int *list, int64_t chunk_rows, unsigned long long *acc, int *cnt,
+                       int64_t ng, double tau, const BandAgg &a, double *S, int *n_list, unsigned long long *acc, int *cnt,
                        hipStream_t st) {
     const auto haar = B == 2 ? band_haar_kernel<K, true> : band_haar_kernel<K, false>;
     hipLaunchKernelGGL(haar, dim3((unsigned)ng), dim3(256), 0, st, cube, stride, a.w, B, idx, S);
     const auto rows = B <= 31 ? band_rows_kernel<1> : (B <= 63 ? band_rows_kernel<2> : band_rows_kernel<3>);
     // workgroups that go through the rows: three per CU, then four (FB = 1) or two are resident
-    int *n_list = list + chunk_rows;
-    if (B <= 31) {
-        const hipError_t e = launch_zero(n_list, sizeof(int), st);
-        if (e != hipSuccess) return e;
+    int *list = n_list + 1;
+    const bool test = B <= 31 && ng * K > test_min_rows(B);
+    if (test) {
+        if (g0 > 0) {   // zero before the first pass
+            const hipError_t e = launch_zero(n_list, sizeof(int), st);
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL(band_test_kernel, dim3(std::min<unsigned>(nb(ng * K, 4 * TEST_ROWS), 768)), dim3(256), 0, st, B,
                            bm.nb, K, ng * K, bm.D, bm.frag_fwd, tau, S, list, n_list);
     }
     const unsigned grid = std::min<unsigned>(nb(ng * K, BandTile<1>::PP), B <= 31 ? 1024 : 512);
-    hipLaunchKernelGGL(rows, dim3(grid), dim3(256), 0, st, B, bm.nb, K, ng * K, B <= 31 ? list : nullptr, n_list, bm.D,
+    hipLaunchKernelGGL(rows, dim3(grid), dim3(256), 0, st, B, bm.nb, K, ng * K, test ? list : nullptr, n_list, bm.D,
                        bm.Dinv, bm.frag_fwd, bm.frag_inv, tau, S);
     const int tiles_x = (a.nx + a.TR - 1) / a.TR;
     const int ty0 = (int)(g0 / a.nx) / a.TR, ty1 = (int)((g0 + ng - 1) / a.nx) / a.TR;
@@ -815,10 +829,11 @@ hipError_t launch_band_guide(const uint8_t *cube, int64_t stride, int h, int w, 
     return hipGetLastError();
 }
 
-// Groups per pass of the filter: the FP64 patch matrix S stays below cap bytes.
+// Groups per pass of the filter: the FP64 patch matrix S stays below 3 cap bytes, at least one group.
+// A pass is 3 or 5 launches of 35 to 60 us however few groups it has, so it takes what it may.
 int64_t band_chunk_groups(int B, int K, int64_t n_group, int64_t cap) {
     const int64_t per = (int64_t)K * 64 * B * (int64_t)sizeof(double);
-    return std::max<int64_t>(1, std::min<int64_t>(n_group, cap / per));
+    return std::max<int64_t>(1, std::min<int64_t>(n_group, cap / per * 3));
 }
 
 size_t band_ws_bytes(int h, int w, int B, int K, int64_t n_group, int64_t cap) {
@@ -835,29 +850,31 @@ hipError_t launch_band_filter(const BandMaps &bm, const uint8_t *cube, int64_t s
                               int64_t out_stride, hipStream_t st) {
     if (bm.nb != band_nb(B)) return hipErrorInvalidValue;
     BandAgg a = {h, w, s, ref_count(h, s), ref_count(w, s), (W - 1) / 2, 4, 0, 0};
-    // the largest tile of references whose pixels fit 128 KB of LDS (one reference takes at most 98)
+    const int64_t n_group = (int64_t)a.ny * a.nx, chunk = band_chunk_groups(B, K, n_group, cap);
+    // the largest tile of references whose pixels fit 128 KB of LDS (one reference takes at most 98) and
+    // of which a pass has ADD_BLOCKS
     for (;; a.TR >>= 1) {
         a.RH = (int)std::min<int64_t>(h, (int64_t)(a.TR - 1) * s + 2 * a.R + PS);
         a.RW = (int)std::min<int64_t>(w, (int64_t)(a.TR - 1) * s + 2 * a.R + PS);
-        if (a.TR == 1 || (int64_t)a.RH * a.RW * (8 * 8 + 4) <= 128 * 1024) break;
+        if (a.TR == 1 || ((int64_t)a.RH * a.RW * (8 * 8 + 4) <= 128 * 1024 &&
+                          std::min(n_group, chunk) * nb(B, 8) >= (int64_t)ADD_BLOCKS * a.TR * a.TR))
+            break;
     }
-    const int64_t n_group = (int64_t)a.ny * a.nx, chunk = band_chunk_groups(B, K, n_group, cap);
     const size_t mat = ((sizeof(double) * (size_t)(chunk * K) * 64 * B) + 255) & ~(size_t)255;
     double *S = (double *)ws;
     unsigned long long *acc = (unsigned long long *)((char *)ws + mat);
     int *cnt = (int *)((char *)acc + (((size_t)h * w * B * 8 + 255) & ~(size_t)255));
-    int *list = (int *)((char *)cnt + (((size_t)h * w * 4 + 255) & ~(size_t)255));   // rows of a pass, and their number
+    int *n_list = (int *)((char *)cnt + (((size_t)h * w * 4 + 255) & ~(size_t)255));   // number of listed rows, then these
     hipError_t e;
-    if ((e = launch_zero(acc, (size_t)h * w * B * 8, st)) != hipSuccess) return e;
-    if ((e = launch_zero(cnt, (size_t)h * w * 4, st)) != hipSuccess) return e;
+    if ((e = launch_zero(acc, (size_t)((char *)(n_list + 1) - (char *)acc), st)) != hipSuccess) return e;
     for (int64_t g0 = 0; g0 < n_group; g0 += chunk) {
         const int64_t ng = std::min<int64_t>(chunk, n_group - g0);
         const int32_t *ix = idx + g0 * K;
         switch (K) {
-            case 4: e = launch_pass<4>(bm, cube, stride, B, ix, g0, ng, tau, a, S, list, chunk * K, acc, cnt, st); break;
-            case 8: e = launch_pass<8>(bm, cube, stride, B, ix, g0, ng, tau, a, S, list, chunk * K, acc, cnt, st); break;
-            case 16: e = launch_pass<16>(bm, cube, stride, B, ix, g0, ng, tau, a, S, list, chunk * K, acc, cnt, st); break;
-            case 32: e = launch_pass<32>(bm, cube, stride, B, ix, g0, ng, tau, a, S, list, chunk * K, acc, cnt, st); break;
+            case 4: e = launch_pass<4>(bm, cube, stride, B, ix, g0, ng, tau, a, S, n_list, acc, cnt, st); break;
+            case 8: e = launch_pass<8>(bm, cube, stride, B, ix, g0, ng, tau, a, S, n_list, acc, cnt, st); break;
+            case 16: e = launch_pass<16>(bm, cube, stride, B, ix, g0, ng, tau, a, S, n_list, acc, cnt, st); break;
+            case 32: e = launch_pass<32>(bm, cube, stride, B, ix, g0, ng, tau, a, S, n_list, acc, cnt, st); break;
             default: return hipErrorInvalidValue;
         }
         if (e != hipSuccess) return e;

@@ -231,10 +231,16 @@ hipError_t launch_idx_prefix(const int32_t *in, int kin, int32_t *out, int kout,
 }
 
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
-    const int64_t n = (int64_t)(bytes / 4);
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (uint32_t *)p, n);
-    return hipGetLastError();
+    uint32_t *w = (uint32_t *)p;
+    for (int64_t n = (int64_t)(bytes / 4); n > 0;) {   // a launch has less than 2^32 threads
+        const int64_t m = n < (int64_t)1 << 31 ? n : (int64_t)1 << 31;
+        hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, w, m);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        w += m;
+        n -= m;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_fill_tau(double *tau_ref, int64_t n_ref, const double *sigma_tile, double sigma_const,

@@ -160,3 +160,64 @@ def failed_basis_keeps_the_installed_one():
     ht.htsvd_destroy(ctx)
     # everything but the fixed scratch array was given back
     assert sorted(f.live.values()) == [64 << 20], f.live
+
+
+def _install_unit_basis(f, ctx, bands):
+    import numpy as np
+    U = np.zeros((bands, 8, 8))
+    U[0] = np.eye(8)
+    f.call("htsvd_set_basis", ctx, 8, bands, U.ctypes.data, U.ctypes.data)
+
+
+def _denoise_bands(f, ctx, h, w, bands, p):
+    return f.call("htsvd_denoise_bands", ctx, IN, h, w, bands, w * bands, ctypes.c_float(20.0), ctypes.byref(p), OUT,
+                  w * bands, None)
+
+
+def band_passes():
+    """Passes of the band filter: their patch matrix within three times the cap or a single group, every
+    row in one of them, and the row test only in passes of many rows of at most 31 bands."""
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    for bands in (2, 5, 16, 30, 31, 32, 64):
+        _install_unit_basis(f, ctx, bands)
+        for cap in (1 << 20, 1 << 24, 4 << 30, 2 ** 63 - 1):
+            f.call("htsvd_set_band_memory", ctx, ctypes.c_int64(cap))
+            for h, w, s, K, W in ((15, 30, 4, 8, 15), (48, 48, 4, 16, 21), (64, 60, 2, 32, 15), (9, 300, 1, 4, 31)):
+                p = f.params(1, stride=s, window=W, K=K)
+                rows, tested = [], []
+
+                def look(l):
+                    if "band_test_kernel" in l.name:
+                        tested.append(l.arg(3, ctypes.c_int64))
+                        assert bands <= 31 and tested[-1] > 2048 + 64 * (31 - bands)
+                    if "band_rows_kernel" in l.name:
+                        rows.append(l.arg(3, ctypes.c_int64))
+                        listed = bands <= 31 and rows[-1] > 2048 + 64 * (31 - bands)
+                        assert bool(l.arg(4, ctypes.c_uint64)) == listed and (not listed or tested[-1] == rows[-1])
+
+                f.watch = look
+                launches = _denoise_bands(f, ctx, h, w, bands, p)
+                n_ref = f.L.htsvd_ref_count(h, 8, s) * f.L.htsvd_ref_count(w, 8, s)
+                assert sum(rows) == n_ref * K, (bands, cap, h, w)
+                assert all(r * 64 * bands * 8 <= 3 * cap or r == K for r in rows)
+                assert len(launches) <= 4 + 3 * len(rows) + 2 * len(tested)
+
+
+def zeroed_memory():
+    """Memory of more than 2^31 words is cleared by several launches, each of less than 2^32 threads."""
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    bands, h, w = 64, 4096, 4095
+    _install_unit_basis(f, ctx, bands)
+    words = []
+
+    def look(l):
+        assert l.grid[0] * l.block[0] < 1 << 32, (l.name, l.grid, l.block)
+        if "zero_words" in l.name:
+            words.append((l.arg(0, ctypes.c_uint64), l.arg(1, ctypes.c_int64)))
+
+    f.watch = look
+    _denoise_bands(f, ctx, h, w, bands, f.params(1, stride=16, window=15, K=4))
+    assert sum(n for _, n in words) >= 2 * h * w * bands + h * w
+    assert words[0][0] + 4 * words[0][1] == words[1][0]

@@ -275,3 +275,26 @@ def test_band_gram_sums_at_the_edges(dn, h, w, bands, s):
     for cube in (synth.add_awgn(synth.make_hsi(h, w, bands, 140 + bands), 40.0, 141), np.full((h, w, bands), 255, np.uint8)):
         G = dn.basis_gram(_dev(cube), stride=s)
         assert np.array_equal(G.cpu().numpy(), lb.channel_gram(cube, 8, s))
+
+
+@pytest.mark.parametrize("bands,K,s", [(2, 8, 2), (4, 32, 3), (5, 16, 2), (16, 4, 1), (30, 8, 2), (31, 32, 3)])
+@pytest.mark.parametrize("sigma", [0.5, 20.0, 200.0])
+@pytest.mark.parametrize("harsh", [False, True])
+def test_band_rows_with_and_without_the_row_test(dn, bands, K, s, sigma, harsh):
+    """Rows of one pass go through the fp16 row test, those of passes cut short by the memory cap (at
+    most 3,072 rows each) straight to the FP64 transform: the same decisions, hence the same bits."""
+    import paper_2512_23569_amd as ht
+    noisy = synth.add_awgn(synth.make_hsi(66, 61, bands, 150 + bands), 20.0, 151)
+    if harsh:
+        noisy = np.where(np.random.default_rng(6).random(noisy.shape) < 0.5, 0, 255).astype(np.uint8)
+    d = _dev(noisy)
+    dn.learn_basis(d, stride=s)
+    p = dn.params(1, stride=s, window=15, K=K)
+    one = dn.denoise_bands(d, sigma, p)
+    ht.htsvd_set_band_memory(dn.ctx, 1 << 20)
+    try:
+        many = dn.denoise_bands(d, sigma, p)
+    finally:
+        ht.htsvd_set_band_memory(dn.ctx, 4 << 30)
+    torch.cuda.synchronize()
+    assert torch.equal(one, many)
