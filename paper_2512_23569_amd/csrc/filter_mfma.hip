@@ -1030,17 +1030,19 @@ __global__ void ga_normalize_kernel(const unsigned long long *__restrict__ gacc,
         o[ch] = n > 0 ? (float)((double)(long long)gacc[e * C + ch] * inv) : (float)px[ch];
 }
 
-// Patches covering each pixel of a 64 x 16 tile at (Y0, x0) of a hh x w image, from the patches by
+// Patches covering each pixel of a 64 x 4 tile at (Y0, x0) of a hh x w image, from the patches by
 // top-left pixel: 8 x 8 box sums, separable, in LDS (256 threads; 64 loads per pixel took most of the
-// 229 us of the gather of four 720 x 1280 frames, 112 us so).  Thread t gets the counts of pixels
-// (Y0 + t / 64 + 4 k, x0 + t % 64).
-constexpr int BOX_W = 64, BOX_H = 16;
+// 229 us of the gather of four 720 x 1280 frames, 112 us so).  Thread t gets the count of pixel
+// (Y0 + t / 64, x0 + t % 64).  Tiles of 16 rows, 4 pixels to a thread, load less around them, but a
+// pixel's sum over its regions waits for memory at every one, and small frames then have too few threads:
+// four 150 x 200 frames 41 us so and 16 with 4 rows (24 with the 64 loads), three of 70 x 70 at step 1
+// 250 and 71 (68); four of 720 x 1280 the same.
+constexpr int BOX_W = 64, BOX_H = 4;
 struct BoxShared {
     int hist[BOX_H + PS - 1][BOX_W + PS - 1];
     int row[BOX_H + PS - 1][BOX_W];
 };
-__device__ __forceinline__ void box_counts(BoxShared &sh, const int *__restrict__ ghist, int hh, int w, int Y0, int x0,
-                                           int (&n)[BOX_H / 4]) {
+__device__ __forceinline__ int box_count(BoxShared &sh, const int *__restrict__ ghist, int hh, int w, int Y0, int x0) {
     constexpr int RW = BOX_W + PS - 1, RH = BOX_H + PS - 1;
     for (int t = threadIdx.x; t < RH * RW; t += 256) {
         const int r = t / RW, c = t - r * RW, Y = Y0 - (PS - 1) + r, x = x0 - (PS - 1) + c;
@@ -1055,13 +1057,10 @@ __device__ __forceinline__ void box_counts(BoxShared &sh, const int *__restrict_
         sh.row[r][c] = a;
     }
     __syncthreads();
+    int a = 0;
 #pragma unroll
-    for (int k = 0; k < BOX_H / 4; ++k) {
-        int a = 0;
-#pragma unroll
-        for (int d = 0; d < PS; ++d) a += sh.row[(threadIdx.x >> 6) + 4 * k + d][threadIdx.x & 63];
-        n[k] = a;
-    }
+    for (int d = 0; d < PS; ++d) a += sh.row[(threadIdx.x >> 6) + d][threadIdx.x & 63];
+    return a;
 }
 
 // Slot regions (GA == 2): pixel (f, y, x) of the stacked frames sums, over the frames t within
@@ -1070,53 +1069,50 @@ __device__ __forceinline__ void box_counts(BoxShared &sh, const int *__restrict_
 template <int C>
 __global__ void ga_gather_kernel(const int *__restrict__ regions, TileGeom tg, VideoTiling vt, int s, int nx,
                                  const int *__restrict__ ghist, const uint8_t *__restrict__ img, int64_t stride,
-                                 int w, float *__restrict__ out, int64_t out_stride) {
+                                 int w, int box0, float *__restrict__ out, int64_t out_stride) {
     __shared__ BoxShared sh;
     const int hh = vt.T * vt.h_frame, tiles = (w + BOX_W - 1) / BOX_W;
-    const int Y0 = (int)(blockIdx.x / tiles) * BOX_H, x = (int)(blockIdx.x % tiles) * BOX_W + (threadIdx.x & 63);
-    int cnt[BOX_H / 4];
-    box_counts(sh, ghist, hh, w, Y0, x - (threadIdx.x & 63), cnt);
-    for (int k = 0; k < BOX_H / 4; ++k) {
-        const int Y = Y0 + (threadIdx.x >> 6) + 4 * k, n = cnt[k];
-        if (Y >= hh || x >= w) continue;
-        const int f = Y / vt.h_frame, y = Y - f * vt.h_frame;
-        float *o = out + (int64_t)Y * out_stride + (int64_t)x * C;
-        const uint8_t *px = img + (int64_t)Y * stride + (int64_t)x * C;
-        if (n == 0) {
+    const int box = box0 + (int)blockIdx.x, Y0 = box / tiles * BOX_H, x0 = box % tiles * BOX_W;
+    const int n = box_count(sh, ghist, hh, w, Y0, x0);
+    const int Y = Y0 + (threadIdx.x >> 6), x = x0 + (threadIdx.x & 63);
+    if (Y >= hh || x >= w) return;
+    const int f = Y / vt.h_frame, y = Y - f * vt.h_frame;
+    float *o = out + (int64_t)Y * out_stride + (int64_t)x * C;
+    const uint8_t *px = img + (int64_t)Y * stride + (int64_t)x * C;
+    if (n == 0) {
 #pragma unroll
-            for (int ch = 0; ch < C; ++ch) o[ch] = (float)px[ch];
-            continue;
-        }
-        const int plane = region_plane(tg);
-        const int tyf = (vt.ny_frame + tg.TY - 1) / tg.TY;
-        const int span_y = tg.TY * s, span_x = tg.TX * s;
-        // tiles whose region rows r0 .. r0 + RH - 1 can hold y: r0 = max(0, first reference row - R), and
-        // the windows end R + 7 past the last reference (RH, which ends at the frame, says less: a tile
-        // whose r0 is 0 may reach every row of a small frame)
-        const int ty_hi = min(tyf - 1, (y + tg.R) / span_y + 1), ty_lo = max(0, (y - tg.R - PS - span_y) / span_y - 1);
-        const int tx_hi = min(tg.tiles_x - 1, (x + tg.R) / span_x + 1), tx_lo = max(0, (x - tg.R - PS - span_x) / span_x - 1);
-        long long acc[C];
+        for (int ch = 0; ch < C; ++ch) o[ch] = (float)px[ch];
+        return;
+    }
+    const int plane = region_plane(tg);
+    const int tyf = (vt.ny_frame + tg.TY - 1) / tg.TY;
+    const int span_y = tg.TY * s, span_x = tg.TX * s;
+    // tiles whose region rows r0 .. r0 + RH - 1 can hold y: r0 = max(0, first reference row - R), and
+    // the windows end R + 7 past the last reference (RH, which ends at the frame, says less: a tile
+    // whose r0 is 0 may reach every row of a small frame)
+    const int ty_hi = min(tyf - 1, (y + tg.R) / span_y + 1), ty_lo = max(0, (y - tg.R - PS - span_y) / span_y - 1);
+    const int tx_hi = min(tg.tiles_x - 1, (x + tg.R) / span_x + 1), tx_lo = max(0, (x - tg.R - PS - span_x) / span_x - 1);
+    long long acc[C];
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch) acc[ch] = 0;
-        for (int t = max(0, f - vt.radius); t <= min(vt.T - 1, f + vt.radius); ++t) {
-            const int slot = f - max(0, t - vt.radius);
-            for (int tyl = ty_lo; tyl <= ty_hi; ++tyl) {
-                const int r0 = max(0, ref_pos(tyl * tg.TY, vt.ny_frame, vt.h_frame, s) - tg.R);
-                if (y < r0 || y >= r0 + vt.RH) continue;
-                for (int tx = tx_lo; tx <= tx_hi; ++tx) {
-                    const int c0 = max(0, ref_pos(tx * tg.TX, nx, w, s) - tg.R);
-                    if (x < c0 || x >= c0 + vt.RW) continue;
-                    const int *src = regions + ((int64_t)(t * tyf + tyl) * tg.tiles_x + tx) * C * plane +
-                                     ((slot * vt.RH + (y - r0)) * tg.RP + (x - c0)) * C;
+    for (int ch = 0; ch < C; ++ch) acc[ch] = 0;
+    for (int t = max(0, f - vt.radius); t <= min(vt.T - 1, f + vt.radius); ++t) {
+        const int slot = f - max(0, t - vt.radius);
+        for (int tyl = ty_lo; tyl <= ty_hi; ++tyl) {
+            const int r0 = max(0, ref_pos(tyl * tg.TY, vt.ny_frame, vt.h_frame, s) - tg.R);
+            if (y < r0 || y >= r0 + vt.RH) continue;
+            for (int tx = tx_lo; tx <= tx_hi; ++tx) {
+                const int c0 = max(0, ref_pos(tx * tg.TX, nx, w, s) - tg.R);
+                if (x < c0 || x >= c0 + vt.RW) continue;
+                const int *src = regions + ((int64_t)(t * tyf + tyl) * tg.tiles_x + tx) * C * plane +
+                                 ((slot * vt.RH + (y - r0)) * tg.RP + (x - c0)) * C;
 #pragma unroll
-                    for (int ch = 0; ch < C; ++ch) acc[ch] += src[ch];
-                }
+                for (int ch = 0; ch < C; ++ch) acc[ch] += src[ch];
             }
         }
-        const double inv = 1.0 / ((double)n * (double)(1 << tg.FS));
-#pragma unroll
-        for (int ch = 0; ch < C; ++ch) o[ch] = (float)((double)acc[ch] * inv);
     }
+    const double inv = 1.0 / ((double)n * (double)(1 << tg.FS));
+#pragma unroll
+    for (int ch = 0; ch < C; ++ch) o[ch] = (float)((double)acc[ch] * inv);
 }
 
 template <int C>
@@ -1372,13 +1368,12 @@ hipError_t launch_filter_mfma_global(const ImageGeom &g, int T, int radius, int 
     const int64_t n = (int64_t)g.h * g.w;
     const unsigned grid = (unsigned)((n + 255) / 256);
     if (side > 0) {
-        const unsigned boxes = (unsigned)((g.w + BOX_W - 1) / BOX_W) * (unsigned)((g.h + BOX_H - 1) / BOX_H);
-        if (g.c == 3)
-            hipLaunchKernelGGL(ga_gather_kernel<3>, dim3(boxes), dim3(256), 0, st, (const int *)accum, tg, vt, g.s, g.nx,
-                               ghist, g.img, g.stride, g.w, out, out_stride);
-        else
-            hipLaunchKernelGGL(ga_gather_kernel<1>, dim3(boxes), dim3(256), 0, st, (const int *)accum, tg, vt, g.s, g.nx,
-                               ghist, g.img, g.stride, g.w, out, out_stride);
+        const int n_box = ((g.w + BOX_W - 1) / BOX_W) * ((g.h + BOX_H - 1) / BOX_H);   // 2^25 at most (2^30 pixels)
+        for (int b0 = 0; b0 < n_box; b0 += 1 << 23) {   // a launch has less than 2^32 threads
+            const auto gather = g.c == 3 ? ga_gather_kernel<3> : ga_gather_kernel<1>;
+            hipLaunchKernelGGL(gather, dim3((unsigned)min(n_box - b0, 1 << 23)), dim3(256), 0, st, (const int *)accum, tg,
+                               vt, g.s, g.nx, ghist, g.img, g.stride, g.w, b0, out, out_stride);
+        }
     } else if (g.c == 3) {
         hipLaunchKernelGGL(ga_normalize_kernel<3>, dim3(grid), dim3(256), 0, st, gacc, ghist, g.img, g.stride, g.h,
                            g.w, tg.FS, out, out_stride);

@@ -221,3 +221,23 @@ def zeroed_memory():
     _denoise_bands(f, ctx, h, w, bands, f.params(1, stride=16, window=15, K=4))
     assert sum(n for _, n in words) >= 2 * h * w * bands + h * w
     assert words[0][0] + 4 * words[0][1] == words[1][0]
+
+
+def _within_limits(l):
+    """Launch limits of the device: threads along each side, blocks along y and z, threads and LDS of a
+    block."""
+    for n, b, most in zip(l.grid, l.block, ((1 << 32) - 1, 65535, 65535)):
+        assert 0 < n * b < 1 << 32 and (n <= most), (l.name, l.grid, l.block)
+    assert l.block[0] * l.block[1] * l.block[2] <= 1024 and l.lds <= 160 * 1024, (l.name, l.block, l.lds)
+
+
+def large_videos():
+    """Videos of up to 2^30 pixels of any shape."""
+    f = fake_hip.FakeHip()
+    ctx = f.context((1,))
+    f.watch = _within_limits
+    for T, h, w, s, W in ((1, 1 << 27, 8, 19, 7), (1, 8, 1 << 27, 19, 7), (1 << 13, 256, 500, 4, 15), (4, 1 << 14, 16000, 4, 15)):
+        p = f.params(1, stride=s, window=W, K=4)
+        launches = f.call("htsvd_denoise_video", ctx, IN, T, h, w, 1, w, 1, ctypes.c_float(20.0), ctypes.byref(p), OUT,
+                          w, None)
+        assert any("gather" in l.name or "normalize" in l.name for l in launches)
