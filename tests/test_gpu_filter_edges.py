@@ -96,3 +96,19 @@ def test_video_frames_smaller_than_the_windows(dn, basis1, basis3, T, h, w, radi
     stacked = v.reshape((T * h,) + v.shape[2:])
     ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, K)).reshape(v.shape)
     assert np.abs(out - ref).max() <= TOL
+
+
+# so many frames within the radius that their regions do not fit in LDS: sums straight to memory, with steps
+# and tiles cut short by the last group
+@pytest.mark.parametrize("K", [4, 8, 16, 32])
+@pytest.mark.parametrize("c", [1, 3])
+def test_video_sums_in_memory(dn, basis1, basis3, K, c):
+    T, h, w = 64, 27, 30
+    v = np.stack([synth.add_awgn(synth.make_clean(h, w, c, 7), 20.0, 30 + t) for t in range(T)])
+    p = dn.params(c, stride=7, window=17, K=K)
+    out = dn.denoise_video(torch.from_numpy(v).cuda(), 20.0, p, radius=31).cpu().numpy()
+    idx, _ = oracle.block_match_video(v, 8, 7, 17, K, 31)
+    U, V = basis3 if c == 3 else basis1
+    stacked = v.reshape((T * h,) + v.shape[2:])
+    ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, K)).reshape(v.shape)
+    assert np.abs(out - ref).max() <= TOL
