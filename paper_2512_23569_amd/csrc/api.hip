@@ -2372,11 +2372,19 @@ htsvd_status htsvd_denoise_video(htsvd_ctx *ctx, const uint8_t *d_in, int32_t T,
     const int64_t n_frame = (int64_t)g.ny * g.nx, n_ref = (int64_t)gv.ny * gv.nx, npx = (int64_t)gv.h * w;
     const size_t off_tau = align256(sizeof(int32_t) * n_ref * mp.K);
     const size_t off_acc = off_tau + align256(sizeof(double) * n_ref);
-    const size_t off_hist = off_acc + align256(filter_mfma_global_bytes(gv, T, radius, mp.W, mp.K));
-    const size_t off_ra = off_hist + align256(sizeof(int) * npx);
-    const size_t off_frame = off_ra + (p->ra ? align256(ra_ws_bytes(gv)) : 0);
     const size_t frame_ws = per_frame ? plan_ws(nullptr, g, mp.W, mp.K, tile).total : 0;
-    if ((s = ensure_ws(ctx, off_frame + frame_ws)) != HTSVD_OK) return s;
+    // the sums straight to memory take 8 bytes per value; regions may take thousands, so a call that has no
+    // room for them goes without
+    size_t off_hist, off_ra, off_frame;
+    bool direct = false;
+    for (;; direct = true) {
+        off_hist = off_acc + align256(filter_mfma_global_bytes(gv, T, radius, mp.W, mp.K, direct));
+        off_ra = off_hist + align256(sizeof(int) * npx);
+        off_frame = off_ra + (p->ra ? align256(ra_ws_bytes(gv)) : 0);
+        s = ensure_ws(ctx, off_frame + frame_ws);
+        if (s == HTSVD_OK) break;
+        if (s != HTSVD_ENOMEM || direct) return s;
+    }
     char *ws = (char *)ctx->ws;
     int32_t *idx = (int32_t *)ws;
     double *tau = (double *)(ws + off_tau);
@@ -2428,7 +2436,7 @@ htsvd_status htsvd_denoise_video(htsvd_ctx *ctx, const uint8_t *d_in, int32_t T,
     {
         StageScope sc(ctx, HTSVD_STAGE_FILTER, st);
         if ((e = launch_filter_mfma_global(gv, T, radius, mp.W, mp.K, ctx->basis[c == 3], idx, tau, accum, ghist,
-                                           ctx->d_guard, d_out, out_stride, st, ra_d, ra_f)) != hipSuccess)
+                                           ctx->d_guard, d_out, out_stride, st, ra_d, ra_f, direct)) != hipSuccess)
             return hip_fail(e, "video filter");
     }
     return HTSVD_OK;

@@ -297,6 +297,8 @@ double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share);
 size_t filter_region_bytes(const TileGeom &tg, int c);
 hipError_t launch_gather(const ImageGeom &g, const TileGeom &tg, const float *regions, float *out, int64_t out_stride,
                          hipStream_t st);
+// Whether `planes` planes of rows x cols words, rows padded to 8 modulo 16 words, fit in LDS beside 65 KB.
+bool padded_region_fits(int planes, int rows, int cols);
 int filter_lds_bytes_for(const TileGeom &tg, int C, int K);
 // matrix-core filter (filter_mfma.hip)
 int filter_mfma_lds_bytes(const TileGeom &tg, int C);

@@ -91,6 +91,10 @@ size_t region_bytes(const TileGeom &tg, int c) {
 
 int filter_lds_budget() { return 160 * 1024 - filter_mfma_static_bytes() - 64; }
 
+bool padded_region_fits(int planes, int rows, int cols) {
+    return (int64_t)planes * rows * (cols + (24 - cols % 16) % 16) * 4 + 65 * 1024 <= filter_lds_budget();
+}
+
 int filter_lds_bytes_for(const TileGeom &tg, int C, int K) {
     (void)K;
     return filter_mfma_lds_bytes(tg, C);

@@ -36,6 +36,8 @@
 //             instead, with a histogram of patch positions for the counts.
 //
 // c = 1 uses the single 64 x 64 map and no channel DFT.
+#include <algorithm>
+
 #include "common.h"
 
 namespace htsvd {
@@ -269,7 +271,8 @@ __device__ inline int to_fixed(float v, float scale) { return (int)(to_fixed_bia
 // keeps TY TX K 1024 2^FS below 2^31, and only tilings with a shift of at least GA_MIN_FS.
 constexpr int GA_FS = 12;
 constexpr int GA_MIN_FS = 10;
-constexpr int GA_MAX_TILE = 8;   // largest tile side of the slot regions
+constexpr int GA_PADDED_MIN_FS = 9;   // of the tiles that set the least shift
+constexpr int GA_MAX_TILE = 8;   // largest tile side of the slot regions, and that of the sums in memory
 
 // Geometry of a video for the global aggregation: frames of h_frame rows stacked vertically,
 // ny_frame reference rows each; with slot regions (GA == 2) a tile's references lie in one
@@ -1308,23 +1311,47 @@ static int ga_shift(int side, int K) {
     return fs;
 }
 
+// Shift that slot regions keep at least: that of the largest tile whose slots, rows padded to 8 modulo 16
+// words, fit in LDS beside 65 KB (or of the sums in memory where none does), whatever side the estimated
+// time would take.
+static int ga_least_shift(int C, int K, int h_frame, int w, int s, int R, int nslot) {
+    for (int side = GA_MAX_TILE; side >= 1; --side) {
+        const int reach = (side - 1) * s + 2 * R + PS;
+        if (ga_shift(side, K) >= GA_PADDED_MIN_FS && padded_region_fits(C, nslot * min(reach, h_frame), min(reach, w)))
+            return max(GA_MIN_FS, ga_shift(side, K));
+    }
+    return GA_FS;
+}
+
 // Tiling of the video filter: the tile side (<= GA_MAX_TILE) with the lowest estimated time among
-// those whose fixed-point shift is at least GA_MIN_FS and whose slot region fits in LDS beside the
-// tables; 0 when none does (direct global aggregation).
+// those whose fixed-point shift is at least ga_least_shift and whose slot region fits in LDS beside the
+// tables; 0 where the sums straight to memory are estimated to take less.  Besides the filter and the
+// regions' way to memory (as for one image): the gather reads 300 region pixels per nanosecond, but a
+// thread waits some 0.7 us at each of its own; sums in memory take 118 values per nanosecond (RGB) or 78
+// (gray), one pixel's about 0.3 us each, and two launches more.  Measured with either forced, filter and gather: six 200 x 300 RGB frames, radius 2, window 31, K
+// 32: 2,096 us with single references to a region (2.1 GB), 1,168 without; twenty 128 x 128 gray frames,
+// radius 10: 2,376 (2.5 GB) and 518; ten 200 x 300 RGB frames, radius 3, window 21, K 32: 930 (2 x 2) and
+// 1,856; four 720 x 1280 RGB frames, radius 1: 1,953 (7 x 7) and 11,944.
 static int video_tile_side(int C, int K, int T, int ny_frame, int nx, int h_frame, int w, int s, int W, int nslot,
                            VideoTiling *vt) {
     const int R = (W - 1) / 2;
+    const int least = ga_least_shift(C, K, h_frame, w, s, R, nslot);
+    const double pixels = (double)T * h_frame * w, added = (double)T * ny_frame * nx * K * 64;
+    const int64_t units = (int64_t)((T * ny_frame + GA_MAX_TILE - 1) / GA_MAX_TILE) * ((nx + GA_MAX_TILE - 1) / GA_MAX_TILE);
     int best = 0;
-    double best_cost = 0.0;
+    double best_cost = 10.0 + std::max({C == 3 ? added * 3 / 118e3 : added / 78e3, 0.3 * added / pixels,
+                                        filter_tiles_cost(C, K, units, GA_MAX_TILE * GA_MAX_TILE, 1.0)});
     for (int side = 1; side <= GA_MAX_TILE; ++side) {
         const int RH = min((side - 1) * s + 2 * R + PS, h_frame), RW = min((side - 1) * s + 2 * R + PS, w);
         const int RP = region_pitch(RW);
-        const int bytes = filter_mfma_group_bytes(C) + C * ((nslot * RH * RP + 3) & ~3) * 4;
-        if (ga_shift(side, K) < GA_MIN_FS || bytes > filter_lds_budget()) break;
+        const int64_t bytes = filter_mfma_group_bytes(C) + (int64_t)C * (((int64_t)nslot * RH * RP + 3) & ~3) * 4;
+        if (ga_shift(side, K) < least || bytes > filter_lds_budget()) break;
         const int64_t n_tiles = (int64_t)T * ((ny_frame + side - 1) / side) * ((nx + side - 1) / side);
+        const double visits = (double)n_tiles * nslot * RH * RW;
         const double cost = filter_tiles_cost(C, K, n_tiles, side * side, 1.0) +
-                            (double)n_tiles * nslot * RH * RP * C * 4 / 2.5e6;
-        if (best == 0 || cost <= best_cost) {
+                            (double)n_tiles * nslot * RH * RP * C * 4 / 2.5e6 +
+                            std::max(visits / 300e3, 0.7 * visits / pixels);
+        if (cost <= best_cost) {
             best = side;
             best_cost = cost;
             vt->RH = RH;
@@ -1357,7 +1384,7 @@ static int plan_video(const ImageGeom &g, int T, int radius, int W, int K, bool 
         tg->RW = vt->RW;
         tg->RP = vt->RP;
     } else {          // direct: 8 x 8 references of the stacked grid per scheduling unit
-        tg->TY = tg->TX = 8;
+        tg->TY = tg->TX = GA_MAX_TILE;
         tg->tiles_y = (g.ny + tg->TY - 1) / tg->TY;
         tg->tiles_x = (g.nx + tg->TX - 1) / tg->TX;
     }

@@ -14,10 +14,12 @@ typedef void (*memory_cb)(int alloc, uint64_t addr, size_t bytes);
 static launch_cb on_launch;
 static memory_cb on_memory;
 static long malloc_left = -1;   /* allocations until one fails, -1: none does */
+static long malloc_fail;        /* allocations that fail before the others succeed */
 static int launch_error;        /* what every launch returns to hipGetLastError */
 
 void fake_set(launch_cb l, memory_cb m) { on_launch = l; on_memory = m; }
 void fake_fail_malloc(long after) { malloc_left = after; }
+void fake_fail_next(long n) { malloc_fail = n; }
 void fake_fail_launches(int error) { launch_error = error; }
 
 enum { MAX_KERNELS = 4096 };
@@ -57,7 +59,10 @@ const char *hipGetErrorString(int e) { (void)e; return "stand-in error"; }
 
 static uint64_t next_addr = (uint64_t)1 << 44;
 int hipMalloc(void **p, size_t n) {
-    if (malloc_left == 0) return 2;   /* out of memory */
+    if (malloc_left == 0 || malloc_fail > 0) {   /* out of memory */
+        if (malloc_fail > 0) --malloc_fail;
+        return 2;
+    }
     if (malloc_left > 0) --malloc_left;
     *p = (void *)next_addr;
     if (on_memory) on_memory(1, next_addr, n);

@@ -25,7 +25,8 @@ class Launch:
         self.name, self.grid, self.block, self.lds, self._args = name, grid, block, lds, args
 
     def arg(self, i, ctype):
-        return ctypes.cast(self._args[i], ctypes.POINTER(ctype))[0]
+        value = ctypes.cast(self._args[i], ctypes.POINTER(ctype))[0]
+        return type(value).from_buffer_copy(value) if isinstance(value, ctypes.Structure) else value
 
 
 class FakeHip:
@@ -39,7 +40,7 @@ class FakeHip:
         mcb = ctypes.CFUNCTYPE(None, ctypes.c_int, ctypes.c_uint64, ctypes.c_size_t)
         self._cb = (lcb(self._launch), mcb(self._memory))
         self.c.fake_set(*self._cb)
-        self.c.fake_fail_malloc.argtypes = [ctypes.c_long]
+        self.c.fake_fail_malloc.argtypes = self.c.fake_fail_next.argtypes = [ctypes.c_long]
         self.launches = []
         self.live = {}       # address -> bytes of the device memory held
         self.watch = None    # called with every launch

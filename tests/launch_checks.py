@@ -241,3 +241,77 @@ def large_videos():
         launches = f.call("htsvd_denoise_video", ctx, IN, T, h, w, 1, w, 1, ctypes.c_float(20.0), ctypes.byref(p), OUT,
                           w, None)
         assert any("gather" in l.name or "normalize" in l.name for l in launches)
+
+
+class TileGeom(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("TY", "TX", "tiles_y", "tiles_x", "RH", "RW", "RP", "FS", "R")]
+
+
+def _padded_fits(planes, rows, cols):
+    """Planes with rows padded to 8 modulo 16 words beside 65 KB of tables, in the LDS of a workgroup
+    without the lists' 6,184 bytes and 80 to spare."""
+    return planes * rows * (cols + (24 - cols % 16) % 16) * 4 + 65 * 1024 <= 160 * 1024 - 6184 - 80
+
+
+def _shift(contributions, least):
+    """Largest shift up to 12 at which so many contributions of 1024 stay below 2^31, and >= least."""
+    return max([f for f in range(13) if contributions * 1024 * 2 ** f < 2 ** 31 - 1], default=0) >= least
+
+
+def _video_least_shift(c, K, T, h, w, s, W, radius):
+    """Shift of the largest tile of at most 8 x 8 references whose padded slots fit, 9 at least; of the
+    sums in memory where none does."""
+    nslot, reach = min(2 * radius + 1, T), W - 1 + 8
+    for side in range(8, 0, -1):
+        n = (side - 1) * s + reach
+        if _shift(side * side * K, 9) and _padded_fits(c, nslot * min(n, h), min(n, w)):
+            return max(f for f in range(13) if _shift(side * side * K, f))
+    return 12
+
+
+def video_sums():
+    """The video filter's sums are never coarser than those of the largest tile that fits with padded
+    rows, its regions fit in LDS, and without memory for them the sums go straight to memory."""
+    import random
+    f = fake_hip.FakeHip()
+    ctx = f.context()
+    ht = f.ht
+    rng = random.Random(5)
+    forms = set()
+    for _ in range(4000):
+        T, h, w = rng.randint(1, 40), int(8 * 2 ** rng.uniform(0, 7)), int(8 * 2 ** rng.uniform(0, 7))
+        c, K, (W, s) = rng.choice((1, 3)), rng.choice((4, 8, 16, 32)), rng.choice(windows_and_steps())
+        radius = rng.choice((0, 1, 1, 2, 2, 3, 5, 10, 31))
+        if min(W // 2 + 1, h - 7) * min(W // 2 + 1, w - 7) < K:
+            continue
+        where = (T, h, w, c, K, W, s, radius)
+        seen = []
+
+        def look(l):
+            if "filter_mfma_ga" in l.name:
+                seen.append((re.search(r"ELi(\d)EEE", l.name).group(1), l.arg(1, TileGeom), l.lds))
+                assert l.lds + 6184 <= 160 * 1024, where
+
+        f.watch = look
+        p = f.params(c, stride=s, window=W, K=K)
+        args = (ctx, IN, T, h, w, c, w * c, radius, ctypes.c_float(20.0), ctypes.byref(p), OUT, w * c, None)
+        f.call("htsvd_denoise_video", *args)
+        (form, tg, _), = seen
+        forms.add(form)
+        assert tg.FS >= _video_least_shift(c, K, T, h, w, s, W, radius), where + (tg.FS, tg.TY)
+        if form == "2":
+            assert _shift(tg.TY * tg.TX * K, tg.FS), where + (tg.TY, tg.TX, tg.FS)
+        if rng.random() < 0.02:   # the first allocation of a new context's workspace fails
+            other = ht.htsvd_create(0)
+            ht.htsvd_set_basis(other, 8, c, *ht.load_basis_slices(c))
+            del seen[:]
+            f.c.fake_fail_malloc(0)
+            status = f.L.htsvd_denoise_video(other, *args[1:])
+            f.c.fake_fail_malloc(-1)
+            assert status == ht.HTSVD_ENOMEM and not seen
+            f.c.fake_fail_next(1)
+            f.call("htsvd_denoise_video", other, *args[1:])
+            f.c.fake_fail_next(0)
+            assert [x[0] for x in seen] == ["1"], where
+            ht.htsvd_destroy(other)
+    assert forms == {"1", "2"}
