@@ -262,9 +262,9 @@ struct Ws {
     size_t total;
 };
 
-Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile, bool compact = false) {
+Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile, FilterTiles pick = FilterTiles::FASTEST) {
     Ws w;
-    w.tg = plan_filter_tiles(g, W, K, 0, 1.0, compact);
+    w.tg = plan_filter_tiles(g, W, K, 0, 1.0, pick);
     const int64_t n_ref = (int64_t)g.ny * g.nx;
     const int64_t n_tiles = (int64_t)((g.h + tile - 1) / tile) * ((g.w + tile - 1) / tile);
     size_t off = 0;
@@ -1156,12 +1156,13 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
     const size_t off_ra = align256(w0.total);
     void *base = fixed_ws;
-    bool compact = false;
+    FilterTiles pick = FilterTiles::FASTEST;
     if (fixed_ws) {
         if (learned) return fail(HTSVD_ENOTSUP, "the no-allocation call takes the plain estimator or a known sigma");
         if (p->ra) return fail(HTSVD_ENOTSUP, "the no-allocation call does not run RA-Haar-tSVD");
-        // the tiles that take the least memory where the fastest ones do not fit
-        if (w0.total > fixed_cap) w0 = plan_ws(nullptr, g, mp.W, mp.K, tile, compact = true);
+        // tiles that take less memory where the fastest ones do not fit
+        for (const FilterTiles less : {FilterTiles::SMALL, FilterTiles::SMALLEST})
+            if (w0.total > fixed_cap) w0 = plan_ws(nullptr, g, mp.W, mp.K, tile, pick = less);
         if (w0.total > fixed_cap)
             return fail(HTSVD_ENOMEM, "the image needs " + std::to_string(w0.total) + " bytes of scratch; the "
                                       "fixed array holds " + std::to_string(fixed_cap));
@@ -1169,7 +1170,7 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
         if ((s = ensure_ws(ctx, off_ra + (p->ra ? ra_ws_bytes(g) : 0))) != HTSVD_OK) return s;
         base = ctx->ws;
     }
-    Ws wk = plan_ws(base, g, mp.W, mp.K, tile, compact);
+    Ws wk = plan_ws(base, g, mp.W, mp.K, tile, pick);
     const double mult = p->tau_mult > 0.0 ? p->tau_mult : default_mult(c, mp.K);
     hipStream_t st = (hipStream_t)stream;
     const float *zmap = nullptr;

@@ -291,8 +291,10 @@ hipError_t launch_select_k(const BatchItem *items, const int *auto_list, int n_a
 hipError_t launch_fill_tau_batched(const BatchItem *items, int n_items, const int *ref_start, int total_refs,
                                    const double *sigma, const double *mult, hipStream_t st);
 // Reference tiling of the filter: square tiles (side <= max_side, 0 = 16) for `share` of the GPU,
-// or (compact) those with the smallest regions.
-TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share = 1.0, bool compact = false);
+// or those with smaller regions.
+enum class FilterTiles { FASTEST, SMALL, SMALLEST };
+TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share = 1.0,
+                           FilterTiles pick = FilterTiles::FASTEST);
 double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share);
 size_t filter_region_bytes(const TileGeom &tg, int c);
 hipError_t launch_gather(const ImageGeom &g, const TileGeom &tg, const float *regions, float *out, int64_t out_stride,

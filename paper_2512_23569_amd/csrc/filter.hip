@@ -130,20 +130,36 @@ double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share) 
     return (double)((n_tiles + cu - 1) / cu) * (c == 3 ? 14.5 * steps + 18.0 : 4.6 * steps + 9.0);
 }
 
+// Shift that a tiling's sums keep at least: that of the largest tile whose region, rows padded to 8 modulo
+// 16 words, fits in LDS beside 65 KB.  The choice by time alone takes larger tiles where the LDS allows,
+// with sums in coarser units (RGB, K 8, window 21, step 3: side 16 and 2^-9 instead of 15 and 2^-10).
+int least_shift(const ImageGeom &g, int W, int K, int max_side) {
+    int T = max_side > 0 ? min(max_side, 16) : 16;
+    for (; T > 1; --T) {
+        const int reach = (T - 1) * g.s + (W - 1) + PS;
+        if (accumulation_shift(T, K) >= FX_MIN_SHIFT && padded_region_fits(g.c + 1, min(reach, g.h), min(reach, g.w)))
+            break;
+    }
+    return accumulation_shift(T, K);
+}
+
 // The tile side with the lowest estimated time among those whose region fits in LDS beside the
-// tables and whose sums keep FX_MIN_SHIFT: small images take small tiles, so that every CU has
+// tables and whose sums keep least_shift: small images take small tiles, so that every CU has
 // one, large ones the largest, whose regions overlap least.  The regions' way through memory
 // (written and read once, about 2.5 bytes per nanosecond and direction over the whole GPU at
 // these sizes) is added.  64 x 72 RGB at K 16: 108 us at the largest side (one tile), 29 at side 4;
-// 256 x 256 gray: 49 against 20.  compact: the side whose regions, without
-// padding, take the least memory instead (for the fixed scratch of the no-allocation call).
-TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share, bool compact) {
+// 256 x 256 gray: 49 against 20.  For the fixed scratch of the no-allocation call, SMALL: the side whose
+// regions, without padding, take the least memory instead; SMALLEST: the same with the shifts down to
+// FX_MIN_SHIFT.
+TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, double share, FilterTiles pick) {
+    const bool compact = pick != FilterTiles::FASTEST;
+    const int least = pick == FilterTiles::SMALLEST ? FX_MIN_SHIFT : least_shift(g, W, K, max_side);
     TileGeom best = tiles_of(g, W, 1, compact);
     double best_cost = 0.0;
     const int top = min(max_side > 0 ? min(max_side, 16) : 16, max(g.ny, g.nx));
     for (int T = 1; T <= top; ++T) {
         const TileGeom tg = tiles_of(g, W, T, compact);
-        if (T > 1 && (accumulation_shift(T, K) < FX_MIN_SHIFT || filter_mfma_lds_bytes(tg, g.c) > filter_lds_budget()))
+        if (T > 1 && (accumulation_shift(T, K) < least || filter_mfma_lds_bytes(tg, g.c) > filter_lds_budget()))
             break;
         const double bytes = (double)region_bytes(tg, g.c);
         const double cost = compact ? bytes

@@ -315,3 +315,54 @@ def video_sums():
             assert [x[0] for x in seen] == ["1"], where
             ht.htsvd_destroy(other)
     assert forms == {"1", "2"}
+
+
+def _image_least_shift(c, K, h, w, s, W, max_side=16):
+    """Shift of the largest tile whose padded region fits, 9 at least."""
+    for side in range(max_side, 0, -1):
+        n = (side - 1) * s + W - 1 + 8
+        if side == 1 or (_shift(side * side * K, 9) and _padded_fits(c + 1, min(n, h), min(n, w))):
+            return max(f for f in range(13) if _shift(side * side * K, f))
+
+
+def image_sums():
+    """The filter's sums are never coarser than those of the largest tile that fits with padded rows, for
+    one image and for a sweep; the call with fixed scratch takes coarser ones only where nothing else
+    fits.  Regions fit in LDS."""
+    import random
+    f = fake_hip.FakeHip()
+    ctx = f.context()
+    ht = f.ht
+    rng = random.Random(6)
+    coarse = refused = 0
+    for _ in range(6000):
+        h, w = int(8 * 2 ** rng.uniform(0, 9)), int(8 * 2 ** rng.uniform(0, 9))
+        c, K, (W, s) = rng.choice((1, 3)), rng.choice((4, 8, 16, 32)), rng.choice(windows_and_steps())
+        if min(W // 2 + 1, h - 7) * min(W // 2 + 1, w - 7) < K:
+            continue
+        p = f.params(c, stride=s, window=W, K=K)
+        least = {k: _image_least_shift(c, k, h, w, s, W) for k in (4, 8, 16, 32)}
+        seen = []
+
+        def look(l):
+            if "filter_mfma_kernel" in l.name and "batched" not in l.name:
+                seen.append((l.arg(2, ctypes.c_int), l.arg(1, TileGeom)))
+                assert l.lds + 6184 <= 160 * 1024
+
+        f.watch = look
+        image = (ctx, IN, h, w, c, w * c, ctypes.c_float(20.0), ctypes.byref(p), OUT, w * c, None)
+        f.call("htsvd_denoise", *image)
+        Ks = [k for k in (4, 8, 16, 32) if k <= K]
+        items = (ht.htsvd_sweep_item * len(Ks))(*[ht.htsvd_sweep_item(20.0, k, OUT, w * c) for k in Ks])
+        f.call("htsvd_denoise_sweep", ctx, IN, h, w, c, w * c, len(Ks), items, ctypes.byref(p), None)
+        assert len(seen) == 1 + len(Ks)
+        for k, tg in seen:
+            assert tg.FS >= least[k] and _shift(tg.TY * tg.TX * k, tg.FS), (h, w, c, k, W, s, tg.FS, tg.TY)
+        del seen[:]
+        if f.call("htsvd_denoise_noalloc", *image, expect=None) is None:
+            refused += 1
+            continue
+        (k, tg), = seen
+        coarse += tg.FS < least[k]
+        assert _shift(tg.TY * tg.TX * k, max(9, tg.FS))
+    assert coarse < 20 and refused > 100, (coarse, refused)
