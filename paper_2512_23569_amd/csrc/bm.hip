@@ -28,7 +28,8 @@
 // window 31, 4.20 ms (1,575 and 4.70 ms when both sides of each window were tested per reference
 // and position, the keys were counted before they were compacted, and channel sums took 64-bit
 // keys).  The rest is the waits at the barriers between a tile's phases, which a second workgroup on
-// the CU fills: 3.44 ms.  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions, so that
+// the CU fills: 3.44 ms.  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions (the
+// windows of all frames of a video also for up to 704: window 15 in three frames), so that
 // small windows neither walk empty table rows nor hold LDS for them: 1536 x 2048 gray, window 21,
 // 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 981 us.
 //
@@ -735,8 +736,10 @@ __device__ __forceinline__ void bm_tile(const ImageGeom &g0, const MethodParams 
     }
 }
 
-template <int NPL, int TR = REF_TILE, bool TURN = false>
-__global__ __launch_bounds__(256 * TR, TURN ? 8 : (TR == REF_TILE ? 4 : 6)) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
+// MANY: the form of 64 registers for many tiles of which two share a CU; only this one has the rows per
+// lane for the columns left over, whose registers cost the others more than they gain.
+template <int NPL, int TR = REF_TILE, bool MANY = false>
+__global__ __launch_bounds__(256 * TR, MANY ? 8 : (TR == REF_TILE ? 4 : 6)) void bm_kernel(ImageGeom g, MethodParams mp, int tiles_x, int n_tiles,
                                                  BmLds L, int32_t *__restrict__ idx_out,
                                                  int32_t *__restrict__ dist_out, BmExtra extra) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(256 * TR, TURN ? 8 : (TR == REF_TILE ? 4 : 6)) void
         const int iy = b / tiles_x * TR + threadIdx.x / REF_TILE, ix = b % tiles_x * REF_TILE + threadIdx.x % REF_TILE;
         if (iy < g.ny && ix < g.nx) extra.tau[(int64_t)iy * g.nx + ix] = extra.value;
     }
-    bm_tile<false, NPL, false, TR, TURN>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
+    bm_tile<false, NPL, false, TR, MANY>(g, mp, tiles_x, b, L, idx_out, dist_out, smem, ti, VideoArgs{});
 }
 
 // Spatio-temporal form: n_tiles covers the tiles of all frames.
@@ -882,15 +885,16 @@ hipError_t launch_block_match(const ImageGeom &g, const MethodParams &mp, int32_
                            dist, extra);
         return hipGetLastError();
     };
-    // The form of 64 registers lets two workgroups share a CU: 509 x 763 RGB, window 21, 92 us instead of
-    // 118, and with the column left over of a union of 33 (window 21 at step 4) 1536 x 2048 gray 322 instead
-    // of 425.  It spills 7 to 11 registers, which costs a lone tile per workgroup slot more than it gains
-    // (256 x 256 gray: 16.2 against 15.3), so it needs more than two rounds.
-    const bool turn = n_tiles > 512;
+    // The form of 64 registers lets two workgroups share a CU where the LDS does: 509 x 763 RGB, window 21,
+    // 91 us instead of 118, and with the column left over of a union of 33 (window 21 at step 4) 1536 x 2048
+    // gray 322 instead of 425.  It spills 7 to 11 registers, which costs a workgroup alone on its CU more
+    // than it gains: 256 x 256 gray 16.2 us against 15.3 (so it takes more than two rounds, 512 tiles), and
+    // tiles of more than 80 KB (900 x 900 gray, window 25, step 6) 73.8 against 69.1.
+    const bool many = n_tiles > 512 && sh.two;
     switch (sh.npl) {
-        case 4: return turn ? go(bm_kernel<4, REF_TILE, true>) : go(bm_kernel<4>);
-        case 7: return turn ? go(bm_kernel<7, REF_TILE, true>) : go(bm_kernel<7>);
-        case 10: return turn ? go(bm_kernel<10, REF_TILE, true>) : go(bm_kernel<10>);
+        case 4: return many ? go(bm_kernel<4, REF_TILE, true>) : go(bm_kernel<4>);
+        case 7: return many ? go(bm_kernel<7, REF_TILE, true>) : go(bm_kernel<7>);
+        case 10: return many ? go(bm_kernel<10, REF_TILE, true>) : go(bm_kernel<10>);
         default: return sh.rows == 3 ? go(bm_kernel<16, 3>) : go(bm_kernel<16>);
     }
 }

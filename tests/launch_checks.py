@@ -366,3 +366,22 @@ def image_sums():
         coarse += tg.FS < least[k]
         assert _shift(tg.TY * tg.TX * k, max(9, tg.FS))
     assert coarse < 20 and refused > 100, (coarse, refused)
+
+
+def match_forms():
+    """The matcher's 64-register form runs for more than 512 tiles of which two share a CU, for every window
+    class up to 640 positions, and only there."""
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    forms = set()
+    for W, s in windows_and_steps():
+        for side in (8 + 80 * s, 8 + 120 * s, 600):
+            p = f.params(1, stride=s, window=W, K=4)
+            (l,) = f.call("htsvd_block_match", ctx, IN, side, side, 1, side, ctypes.byref(p), OUT, None, None)
+            npl, rows, many = re.search(r"bm_kernelILi(\d+)ELi(\d)ELb(\d)E", l.name).groups()
+            n_ref = f.L.htsvd_ref_count(side, 8, s)
+            tiles = -(-n_ref // int(rows)) * -(-n_ref // 4)
+            two = 2 * (l.lds + 452 + 64) <= 160 * 1024   # 452 bytes of tile geometry, and some to round up
+            assert (many == "1") == (tiles > 512 and two and npl != "16"), (W, s, side, l.name, l.lds)
+            forms.add((npl, many))
+    assert {(n, m) for n in ("4", "7", "10") for m in "01"} <= forms

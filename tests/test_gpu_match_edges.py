@@ -91,3 +91,15 @@ def test_groups_at_wide_steps(dn, window, stride, c):
     oi, od = oracle.block_match(img, 8, stride, window, 16)
     assert np.array_equal(idx.cpu().numpy(), oi)
     assert np.array_equal(dist.cpu().numpy(), od)
+
+
+# more than 512 tiles of windows of 23 and 25: unions without and with columns left over by blocks of 16, and
+# tiles too large for two of them to share a CU
+@pytest.mark.parametrize("h,w,window,stride", [(300, 290, 23, 3), (380, 420, 23, 4), (290, 301, 25, 3), (590, 600, 25, 6)])
+@pytest.mark.parametrize("c", [1, 3])
+def test_groups_of_many_tiles(dn, h, w, window, stride, c):
+    img = _image("mixed", h, w, c, window)
+    idx, dist = dn.block_match(torch.from_numpy(img).cuda(), dn.params(c, stride=stride, window=window, K=32))
+    oi, od = oracle.block_match(img, 8, stride, window, 32)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(dist.cpu().numpy(), od)
