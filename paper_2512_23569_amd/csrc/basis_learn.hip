@@ -173,7 +173,7 @@ typedef int gv4i __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void gram_bands_kernel(const uint8_t *__restrict__ img, int64_t stride, int h,
                                                          int w, int C, int s, int ny, int nx,
-                                                         unsigned long long *__restrict__ out) {
+                                                         unsigned long long *__restrict__ out, int z0, int zs) {
     __shared__ __align__(16) unsigned char P[2][2][64 * GB_PITCH];   // (buffer, tile side)
     const int A = 8 * C;
     const int g = blockIdx.y;
@@ -187,7 +187,8 @@ __global__ __launch_bounds__(256) void gram_bands_kernel(const uint8_t *__restri
     const int tb = ta + rem;
     const int64_t n_ref = (int64_t)ny * nx;
     const int64_t n_chunks = (n_ref * 8 + GB_VEC - 1) / GB_VEC;
-    const int64_t c_begin = n_chunks * blockIdx.z / gridDim.z, c_end = n_chunks * (blockIdx.z + 1) / gridDim.z;
+    const int z = z0 + (int)blockIdx.z;   // slice of zs
+    const int64_t c_begin = n_chunks * z / zs, c_end = n_chunks * (z + 1) / zs;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // staging task: 4 vectors 4k .. 4k + 3 (of one reference) at entry offset e, the 8 bands of its side
     const int k = tid & 15, e = tid >> 4 & 7, side = tid >> 7;
@@ -470,9 +471,13 @@ hipError_t launch_gram(const uint8_t *img, int64_t stride, int h, int w, int c, 
         const int64_t blocks = std::min<int64_t>(512, std::max<int64_t>(256, n_chunks * 2 * n_tp / 40));
         const int64_t zs = std::max<int64_t>(
             {1, std::min<int64_t>((blocks + 2 * n_tp - 1) / (2 * n_tp), n_chunks / 8), (n_chunks + GB_MAX - 1) / GB_MAX});
-        hipLaunchKernelGGL(gram_bands_kernel, dim3((unsigned)n_tp, 2, (unsigned)zs), dim3(256), 0, st, img, stride, h,
-                           w, c, s, ny, nx, reinterpret_cast<unsigned long long *>(out));
-        return hipGetLastError();
+        for (int64_t z0 = 0; z0 < zs; z0 += 65535) {   // blocks along z of a launch
+            hipLaunchKernelGGL(gram_bands_kernel, dim3((unsigned)n_tp, 2, (unsigned)std::min<int64_t>(65535, zs - z0)),
+                               dim3(256), 0, st, img, stride, h, w, c, s, ny, nx,
+                               reinterpret_cast<unsigned long long *>(out), (int)z0, (int)zs);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     const int64_t n_vec = std::max<int64_t>((int64_t)ny * w, (int64_t)nx * h);
     const int nb = (int)std::min<int64_t>(GR_MAX_BLOCKS, (n_vec + GR_CHUNK - 1) / GR_CHUNK);

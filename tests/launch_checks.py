@@ -385,3 +385,25 @@ def match_forms():
             assert (many == "1") == (tiles > 512 and two and npl != "16"), (W, s, side, l.name, l.lds)
             forms.add((npl, many))
     assert {(n, m) for n in ("4", "7", "10") for m in "01"} <= forms
+
+
+def large_cubes():
+    """Gram sums of cubes of up to 2^30 pixels at every step: launches within the device's limits, which
+    take every chunk of 64 vectors once, at most 1,024 of them per workgroup."""
+    f = fake_hip.FakeHip()
+    ctx = f.context(())
+    for bands in (2, 9, 64):
+        for h, w, s in ((1 << 15, 1 << 15, 1), (1 << 15, 1 << 15, 4), (1 << 27, 8, 1), (8, 1 << 20, 1), (9, 9, 1)):
+            slices = []
+
+            def look(l):
+                _within_limits(l)
+                if "gram_bands" in l.name:
+                    slices.append((l.arg(9, ctypes.c_int), l.arg(10, ctypes.c_int), l.grid[2]))
+
+            f.watch = look
+            f.call("htsvd_basis_gram", ctx, IN, h, w, bands, ctypes.c_int64(w * bands), 8, s, OUT, None)
+            total = slices[0][1]
+            assert [z0 for z0, _, _ in slices] == list(range(0, total, 65535)) and sum(n for _, _, n in slices) == total
+            chunks = -(-f.L.htsvd_ref_count(h, 8, s) * f.L.htsvd_ref_count(w, 8, s) // 8)
+            assert -(-chunks // total) <= 1024

@@ -298,3 +298,23 @@ def test_band_rows_with_and_without_the_row_test(dn, bands, K, s, sigma, harsh):
         ht.htsvd_set_band_memory(dn.ctx, 4 << 30)
     torch.cuda.synchronize()
     assert torch.equal(one, many)
+
+
+def test_band_gram_sums_of_more_slices_than_one_launch_takes(dn):
+    """23,200 x 23,200 x 2 at every position: more slices of vectors than a launch has blocks along z.  A
+    constant cube, whose sums are known, with one other value in its last corner."""
+    n, v = 23200, 199
+    d = torch.full((n, n, 2), v, dtype=torch.uint8, device="cuda")
+    d[n - 1, n - 1, 1] = 7
+    G = dn.basis_gram(d, stride=1).cpu().numpy()
+    want = np.full((2, 2, 2, 8, 8), (n - 7) ** 2 * 8 * v * v, np.int64)
+    # the corner is pixel (7, 7) of the last patch alone: one vector along rows and one along columns
+    for g in range(2):
+        for i in range(7):
+            for a in range(2):
+                want[g, 1, a, 7, i] += (7 - v) * v
+                want[g, a, 1, i, 7] += (7 - v) * v
+        want[g, 1, 0, 7, 7] += (7 - v) * v
+        want[g, 0, 1, 7, 7] += (7 - v) * v
+        want[g, 1, 1, 7, 7] += 7 * 7 - v * v
+    assert np.array_equal(G, want)
