@@ -176,7 +176,7 @@ htsvd_status htsvd_denoise_tau(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
 htsvd_status htsvd_band_guide(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_t w, int32_t bands,
                               int64_t in_stride, uint8_t *d_guide, void *stream);
 /* Memory of htsvd_denoise_bands: its groups are filtered in passes whose FP64 patch
- * matrix (K*64*bands doubles per group) stays below three times `bytes` (default 4 GiB, at least
+ * matrix (K*64*bands doubles per group) stays below `bytes` (default 4 GiB, at least
  * 1 MiB, at least one group per pass).  The output does not depend on it. */
 htsvd_status htsvd_set_band_memory(htsvd_ctx *ctx, int64_t bytes);
 /* Band-wise noise levels (Sec. IV-D): sigma_b of every band, the mean over the band's 128 x 128

@@ -114,7 +114,7 @@ struct htsvd_ctx {
     size_t band_maps_n = 0;                 // its capacity (doubles)
     double *d_band_next = nullptr;          // the next basis is made here (see install_maps)
     size_t band_next_n = 0;
-    int64_t band_cap = (int64_t)4 << 30;    // a third of the bytes of the patch matrix of one pass of the band filter
+    int64_t band_cap = (int64_t)4 << 30;    // bytes of the patch matrix of one pass of the band filter
     // Optional per-stage timing with HIP events recorded on the call's stream.
     bool timing = false;
     hipEvent_t ev[2 * HTSVD_N_STAGES] = {};

@@ -829,11 +829,10 @@ hipError_t launch_band_guide(const uint8_t *cube, int64_t stride, int h, int w, 
     return hipGetLastError();
 }
 
-// Groups per pass of the filter: the FP64 patch matrix S stays below 3 cap bytes, at least one group.
-// A pass is 3 or 5 launches of 35 to 60 us however few groups it has, so it takes what it may.
+// Groups per pass of the filter: the FP64 patch matrix S stays below cap bytes, at least one group.
 int64_t band_chunk_groups(int B, int K, int64_t n_group, int64_t cap) {
     const int64_t per = (int64_t)K * 64 * B * (int64_t)sizeof(double);
-    return std::max<int64_t>(1, std::min<int64_t>(n_group, cap / per * 3));
+    return std::max<int64_t>(1, std::min<int64_t>(n_group, cap / per));
 }
 
 size_t band_ws_bytes(int h, int w, int B, int K, int64_t n_group, int64_t cap) {

@@ -378,7 +378,7 @@ hipError_t launch_scale_tau(const double *tau, double *out, int64_t n, const int
 hipError_t launch_band_guide(const uint8_t *cube, int64_t stride, int h, int w, int B, uint8_t *guide, hipStream_t st);
 hipError_t launch_select_bands(const float *alt, int64_t alt_stride, const uint8_t *sel, int h, int w, int B,
                                float *out, int64_t out_stride, hipStream_t st);
-// The filter works in chunks of groups whose FP64 patch matrix stays below 3 cap bytes.
+// The filter works in chunks of groups whose FP64 patch matrix stays below cap bytes.
 size_t band_ws_bytes(int h, int w, int B, int K, int64_t n_group, int64_t cap);
 hipError_t launch_band_filter(const BandMaps &bm, const uint8_t *cube, int64_t stride, int h, int w, int B,
                               const int32_t *idx, int s, int W, int K, double tau, int64_t cap, void *ws, float *out,

@@ -175,8 +175,8 @@ def _denoise_bands(f, ctx, h, w, bands, p):
 
 
 def band_passes():
-    """Passes of the band filter: their patch matrix within three times the cap or a single group, every
-    row in one of them, and the row test only in passes of many rows of at most 31 bands."""
+    """Passes of the band filter: their patch matrix within the cap or a single group, every row in one of
+    them, and the row test only in passes of many rows of at most 31 bands."""
     f = fake_hip.FakeHip()
     ctx = f.context(())
     for bands in (2, 5, 16, 30, 31, 32, 64):
@@ -200,7 +200,7 @@ def band_passes():
                 launches = _denoise_bands(f, ctx, h, w, bands, p)
                 n_ref = f.L.htsvd_ref_count(h, 8, s) * f.L.htsvd_ref_count(w, 8, s)
                 assert sum(rows) == n_ref * K, (bands, cap, h, w)
-                assert all(r * 64 * bands * 8 <= 3 * cap or r == K for r in rows)
+                assert all(r * 64 * bands * 8 <= cap or r == K for r in rows)
                 assert len(launches) <= 4 + 3 * len(rows) + 2 * len(tested)
 
 

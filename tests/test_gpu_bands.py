@@ -282,7 +282,7 @@ def test_band_gram_sums_at_the_edges(dn, h, w, bands, s):
 @pytest.mark.parametrize("harsh", [False, True])
 def test_band_rows_with_and_without_the_row_test(dn, bands, K, s, sigma, harsh):
     """Rows of one pass go through the fp16 row test, those of passes cut short by the memory cap (at
-    most 3,072 rows each) straight to the FP64 transform: the same decisions, hence the same bits."""
+    most 1,024 rows each) straight to the FP64 transform: the same decisions, hence the same bits."""
     import paper_2512_23569_amd as ht
     noisy = synth.add_awgn(synth.make_hsi(66, 61, bands, 150 + bands), 20.0, 151)
     if harsh:
