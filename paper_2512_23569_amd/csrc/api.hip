@@ -287,6 +287,16 @@ Ws plan_ws(void *base, const ImageGeom &g, int W, int K, int tile, FilterTiles p
     return w;
 }
 
+// The workspace for bytes(pick) with the fastest tiles, or with tiles whose regions take less where the
+// device has no room for those.
+template <typename Bytes>
+htsvd_status ensure_ws_tiles(htsvd_ctx *ctx, FilterTiles *pick, const Bytes &bytes) {
+    *pick = FilterTiles::FASTEST;
+    htsvd_status s = ensure_ws(ctx, bytes(*pick));
+    if (s == HTSVD_ENOMEM) s = ensure_ws(ctx, bytes(*pick = FilterTiles::SMALL));
+    return s;
+}
+
 // Stage timing: an event pair per stage; the elapsed time of the previous pair is
 // harvested (after it completed) when the stage is recorded again or on request.
 void harvest(htsvd_ctx *ctx, int s) {
@@ -1114,10 +1124,14 @@ htsvd_status htsvd_denoise_tau(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
     if (!d_tau_ref || !d_out) return fail(HTSVD_EINVAL, "null tau or output");
     if (out_stride < (int64_t)w * c) return fail(HTSVD_EINVAL, "out_stride < w*c");
     const int tile = p->subimage > 0 ? p->subimage : 128;
-    Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
-    const size_t off_ra = align256(w0.total);
-    if ((s = ensure_ws(ctx, off_ra + (p->ra ? ra_ws_bytes(g) : 0))) != HTSVD_OK) return s;
-    Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile);
+    FilterTiles pick;
+    size_t off_ra = 0;
+    s = ensure_ws_tiles(ctx, &pick, [&](FilterTiles t) {
+        off_ra = align256(plan_ws(nullptr, g, mp.W, mp.K, tile, t).total);
+        return off_ra + (p->ra ? ra_ws_bytes(g) : 0);
+    });
+    if (s != HTSVD_OK) return s;
+    Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile, pick);
     hipStream_t st = (hipStream_t)stream;
     BmExtra extra;
     extra.guard = ctx->d_guard;
@@ -1153,11 +1167,11 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     if (p->estimator != 0 && p->estimator != 1) return fail(HTSVD_EINVAL, "estimator must be 0 or 1");
     const bool learned = sigma == HTSVD_SIGMA_AUTO && p->estimator == 1;
     const int tile = p->subimage;
-    Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
-    const size_t off_ra = align256(w0.total);
+    size_t off_ra = 0;
     void *base = fixed_ws;
     FilterTiles pick = FilterTiles::FASTEST;
     if (fixed_ws) {
+        Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
         if (learned) return fail(HTSVD_ENOTSUP, "the no-allocation call takes the plain estimator or a known sigma");
         if (p->ra) return fail(HTSVD_ENOTSUP, "the no-allocation call does not run RA-Haar-tSVD");
         // tiles that take less memory where the fastest ones do not fit
@@ -1167,7 +1181,11 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
             return fail(HTSVD_ENOMEM, "the image needs " + std::to_string(w0.total) + " bytes of scratch; the "
                                       "fixed array holds " + std::to_string(fixed_cap));
     } else {
-        if ((s = ensure_ws(ctx, off_ra + (p->ra ? ra_ws_bytes(g) : 0))) != HTSVD_OK) return s;
+        s = ensure_ws_tiles(ctx, &pick, [&](FilterTiles t) {
+            off_ra = align256(plan_ws(nullptr, g, mp.W, mp.K, tile, t).total);
+            return off_ra + (p->ra ? ra_ws_bytes(g) : 0);
+        });
+        if (s != HTSVD_OK) return s;
         base = ctx->ws;
     }
     Ws wk = plan_ws(base, g, mp.W, mp.K, tile, pick);
@@ -1230,7 +1248,6 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
     if (p->adaptive) return fail(HTSVD_ENOTSUP, "sweeps take known sigma without the vote (adaptive = 0)");
     if (p->ra) return fail(HTSVD_ENOTSUP, "RA-Haar-tSVD runs in htsvd_denoise and htsvd_denoise_tau");
     bool need_prefix = false;
-    size_t region_max = 0;
     for (int i = 0; i < n; ++i) {
         const htsvd_sweep_item &it = items[i];
         if (!(it.sigma > 0.f) || !std::isfinite(it.sigma)) return fail(HTSVD_EINVAL, "sweep sigma must be > 0");
@@ -1239,17 +1256,23 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
         if (!it.d_out) return fail(HTSVD_EINVAL, "null sweep output");
         if (it.out_stride < (int64_t)w * c) return fail(HTSVD_EINVAL, "out_stride < w*c");
         need_prefix |= it.K < mp.K;
-        region_max = std::max(region_max, filter_region_bytes(plan_filter_tiles(g, mp.W, it.K, 0), c));
     }
     const int tile = p->subimage;
     const int64_t n_ref = (int64_t)g.ny * g.nx;
     // Workspace: the single-call layout for p->K, then the prefix groups and a region buffer
     // sized for the largest tiling among the settings.
-    const Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
-    const size_t off_pre = align256(w0.total);
-    const size_t off_reg = off_pre + align256(need_prefix ? sizeof(int32_t) * n_ref * (mp.K / 2) : 0);
-    if ((s = ensure_ws(ctx, off_reg + region_max)) != HTSVD_OK) return s;
-    const Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile);
+    FilterTiles pick;
+    size_t off_pre = 0, off_reg = 0;
+    s = ensure_ws_tiles(ctx, &pick, [&](FilterTiles t) {
+        size_t region_max = 0;
+        for (int i = 0; i < n; ++i)
+            region_max = std::max(region_max, filter_region_bytes(plan_filter_tiles(g, mp.W, items[i].K, 0, 1.0, t), c));
+        off_pre = align256(plan_ws(nullptr, g, mp.W, mp.K, tile, t).total);
+        off_reg = off_pre + align256(need_prefix ? sizeof(int32_t) * n_ref * (mp.K / 2) : 0);
+        return off_reg + region_max;
+    });
+    if (s != HTSVD_OK) return s;
+    const Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile, pick);
     int32_t *idx_pre = (int32_t *)((char *)ctx->ws + off_pre);
     float *regions = (float *)((char *)ctx->ws + off_reg);
     hipStream_t st = (hipStream_t)stream;
@@ -1262,7 +1285,7 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
         mpi.K = it.K;
         Ws wi = wk;
         wi.regions = regions;
-        wi.tg = plan_filter_tiles(g, mp.W, it.K, 0);
+        wi.tg = plan_filter_tiles(g, mp.W, it.K, 0, 1.0, pick);
         if (it.K < mp.K) {
             if (pre_k != it.K) {
                 if ((e = launch_idx_prefix(wk.idx, mp.K, idx_pre, it.K, n_ref, st)) != hipSuccess)
@@ -1290,9 +1313,9 @@ htsvd_status htsvd_estimate_sigma(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h
     if (p->estimator != 0 && p->estimator != 1) return fail(HTSVD_EINVAL, "estimator must be 0 or 1");
     const bool learned = sigma == HTSVD_SIGMA_AUTO && p->estimator == 1;
     const int tile = p->subimage;
-    Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile);
+    Ws w0 = plan_ws(nullptr, g, mp.W, mp.K, tile, FilterTiles::SMALL);   // nothing is filtered
     if ((s = ensure_ws(ctx, w0.total)) != HTSVD_OK) return s;
-    Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile);
+    Ws wk = plan_ws(ctx->ws, g, mp.W, mp.K, tile, FilterTiles::SMALL);
     hipStream_t st = (hipStream_t)stream;
     const float *zmap = nullptr;
     if (learned && (s = run_cnn_map(ctx, g, st, &zmap)) != HTSVD_OK) return s;
@@ -1523,7 +1546,7 @@ struct BatchPlan {
 };
 
 htsvd_status plan_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *imgs, const htsvd_params *p, int tile_side,
-                        BatchPlan *bp) {
+                        FilterTiles pick, BatchPlan *bp) {
     BatchPlan &P = *bp;
     const int T = p->subimage;
     for (int i = 0; i < n; ++i) {
@@ -1558,8 +1581,8 @@ htsvd_status plan_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *imgs, cons
         if (b.auto_k) work_k[16] += b.n_ref;
     }
     for (BatchImage &b : P.im) {
-        b.tg = plan_filter_tiles(b.g, b.mp.W, b.mp.K, tile_side, (double)b.n_ref / work_k[b.mp.K]);
-        b.tg_alt = plan_filter_tiles(b.g, b.mp.W, 16, tile_side, (double)b.n_ref / std::max(work_k[16], b.n_ref));
+        b.tg = plan_filter_tiles(b.g, b.mp.W, b.mp.K, tile_side, (double)b.n_ref / work_k[b.mp.K], pick);
+        b.tg_alt = plan_filter_tiles(b.g, b.mp.W, 16, tile_side, (double)b.n_ref / std::max(work_k[16], b.n_ref), pick);
     }
     // largest images first: their units enter the work queues first and the tail is short
     std::stable_sort(P.im.begin(), P.im.end(), [](const BatchImage &a, const BatchImage &b) {
@@ -1687,7 +1710,7 @@ htsvd_status htsvd_denoise_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *i
 
     ctx->batch.k_plan.clear();   // valid again once this batch is planned
     BatchPlan P;
-    htsvd_status s = plan_batch(ctx, n, imgs, p, o.tile_side, &P);
+    htsvd_status s = plan_batch(ctx, n, imgs, p, o.tile_side, FilterTiles::FASTEST, &P);
     if (s != HTSVD_OK) return s;
     const int ni = (int)P.im.size();
     const int C = P.im[0].g.c;
@@ -1698,7 +1721,13 @@ htsvd_status htsvd_denoise_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *i
         if (ctx->cnn.c != C) return fail(HTSVD_EINVAL, "network channel count differs from the images'");
         if ((s = ensure_cnn_ws(ctx, P.cnn_ws)) != HTSVD_OK) return s;
     }
-    if ((s = ensure_ws(ctx, P.ws_total)) != HTSVD_OK) return s;
+    s = ensure_ws(ctx, P.ws_total);
+    if (s == HTSVD_ENOMEM) {   // with regions that take less, as ensure_ws_tiles
+        P = BatchPlan();
+        if ((s = plan_batch(ctx, n, imgs, p, o.tile_side, FilterTiles::SMALL, &P)) != HTSVD_OK) return s;
+        s = ensure_ws(ctx, P.ws_total);
+    }
+    if (s != HTSVD_OK) return s;
 
     // descriptor tables (host), then one upload
     std::vector<BatchItem> items(ni);
@@ -2373,7 +2402,7 @@ htsvd_status htsvd_denoise_video(htsvd_ctx *ctx, const uint8_t *d_in, int32_t T,
     const int64_t n_frame = (int64_t)g.ny * g.nx, n_ref = (int64_t)gv.ny * gv.nx, npx = (int64_t)gv.h * w;
     const size_t off_tau = align256(sizeof(int32_t) * n_ref * mp.K);
     const size_t off_acc = off_tau + align256(sizeof(double) * n_ref);
-    const size_t frame_ws = per_frame ? plan_ws(nullptr, g, mp.W, mp.K, tile).total : 0;
+    const size_t frame_ws = per_frame ? plan_ws(nullptr, g, mp.W, mp.K, tile, FilterTiles::SMALL).total : 0;
     // the sums straight to memory take 8 bytes per value; regions may take thousands, so a call that has no
     // room for them goes without
     size_t off_hist, off_ra, off_frame;
@@ -2408,7 +2437,7 @@ htsvd_status htsvd_denoise_video(htsvd_ctx *ctx, const uint8_t *d_in, int32_t T,
         for (int t = 0; t < T; ++t) {
             ImageGeom gt = g;
             gt.img = d_in + (int64_t)t * h * in_stride;
-            Ws wt = plan_ws(ws + off_frame, gt, mp.W, mp.K, tile);
+            Ws wt = plan_ws(ws + off_frame, gt, mp.W, mp.K, tile, FilterTiles::SMALL);
             const float *zmap = nullptr;
             if (learned && (s = run_cnn_map(ctx, gt, st, &zmap)) != HTSVD_OK) return s;
             if ((s = run_bm(ctx, gt, mp, wt, st)) != HTSVD_OK) return s;

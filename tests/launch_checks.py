@@ -407,3 +407,37 @@ def large_cubes():
             assert [z0 for z0, _, _ in slices] == list(range(0, total, 65535)) and sum(n for _, _, n in slices) == total
             chunks = -(-f.L.htsvd_ref_count(h, 8, s) * f.L.htsvd_ref_count(w, 8, s) // 8)
             assert -(-chunks // total) <= 1024
+
+
+def without_memory_for_the_fastest_tiles():
+    """A call whose workspace does not fit with the fastest tiles runs with smaller regions, and fails only
+    without room for these."""
+    import random
+    f = fake_hip.FakeHip()
+    ht = f.ht
+    rng = random.Random(7)
+    for _ in range(400):
+        h, w = int(8 * 2 ** rng.uniform(0, 8)), int(8 * 2 ** rng.uniform(0, 8))
+        c, K, (W, s) = rng.choice((1, 3)), rng.choice((4, 16, 32)), rng.choice(windows_and_steps())
+        if min(W // 2 + 1, h - 7) * min(W // 2 + 1, w - 7) < K:
+            continue
+        p = f.params(c, stride=s, window=W, K=K)
+        image = ht.htsvd_image(IN, h, w, c, w * c, 20.0, K, OUT, w * c)
+        item = ht.htsvd_sweep_item(20.0, K, OUT, w * c)
+        opts = ht.htsvd_batch_opts(0, 1, 0.0, 0)
+        calls = [("htsvd_denoise", (IN, h, w, c, w * c, ctypes.c_float(20.0), ctypes.byref(p), OUT, w * c, None)),
+                 ("htsvd_denoise_tau", (IN, h, w, c, w * c, IN, ctypes.byref(p), OUT, w * c, None)),
+                 ("htsvd_denoise_sweep", (IN, h, w, c, w * c, 1, ctypes.byref(item), ctypes.byref(p), None)),
+                 ("htsvd_denoise_batch", (1, ctypes.byref(image), ctypes.byref(p), ctypes.byref(opts), None))]
+        for name, args in calls:
+            sizes = []
+            for fail in (0, 1, 2):
+                ctx = ht.htsvd_create(0)
+                ht.htsvd_set_basis(ctx, 8, c, *ht.load_basis_slices(c))
+                held = sum(f.live.values())
+                f.c.fake_fail_next(fail)
+                f.call(name, ctx, *args, expect=0 if fail < 2 else ht.HTSVD_ENOMEM)
+                f.c.fake_fail_next(0)
+                sizes.append(sum(f.live.values()) - held)
+                ht.htsvd_destroy(ctx)
+            assert sizes[1] <= sizes[0], (name, h, w, c, K, W, s, sizes)
