@@ -112,3 +112,42 @@ def test_video_sums_in_memory(dn, basis1, basis3, K, c):
     stacked = v.reshape((T * h,) + v.shape[2:])
     ref = oracle.filter_groups(stacked, idx, U, V, 20.0 * oracle.tau_multiplier(c, K)).reshape(v.shape)
     assert np.abs(out - ref).max() <= TOL
+
+
+# The list of values near the threshold (within 0.05 of it) holds 64 of each wave's pass over 32 patches x 16
+# columns of every slice; the FP32 value decides the rest.  An image of few ones has many equal and small
+# coefficients; the threshold lies in a gap of them that is wider than the FP32 values' error (their rows'
+# norms stay below 8, so 2^-22 of the split basis and 2^-24 of each of up to 192 partial sums are below 1e-4).
+@pytest.mark.parametrize("over", [True, False])
+@pytest.mark.parametrize("K", [4, 8, 16, 32])
+@pytest.mark.parametrize("c", [1, 3])
+def test_values_near_the_threshold(dn, basis1, basis3, c, K, over):
+    rng = np.random.default_rng(K + c)
+    img = (rng.random((20, 24, c)) < 1 / 32).astype(np.uint8)
+    img = img if c == 3 else img[:, :, 0]
+    U, V = basis3 if c == 3 else basis1
+    idx, _ = oracle.block_match(img, 8, 7, 15, K)
+    a = img.reshape(20, 24, c).astype(np.float64)
+    patches = [[oracle.patch_forward(U, V, a[i // 24:i // 24 + 8, i % 24:i % 24 + 8]) for i in row] for row in idx]
+    S = np.abs(np.einsum("mk,gkijc->gmijc", oracle.haar(K), np.array(patches)))
+    v = np.sort(S.ravel())
+    v = v[np.searchsorted(v, 0.06):]
+    best, tau = 0, 0.0
+    for j in np.nonzero(np.diff(v) > 2.4e-4)[0]:
+        t = (v[j] + v[j + 1]) / 2
+        per_group = (np.abs(S - t) < 0.05).reshape(len(S), K, 4, 16, c).sum((1, 3, 4))
+        # over: more than 64 in the average pass of 32 / K groups; else at most 64 in any, but some
+        n = per_group.mean(0).max() * (32 // K) if K < 32 else per_group.max()
+        if not over:
+            most = np.sort(per_group, axis=0)[-(32 // K):].sum(0).max()
+            n = per_group.sum() if most <= 64 else 0
+        if n > best:
+            best, tau = n, t
+    assert best > (64 if over else 0)
+    p = dn.params(c, stride=7, window=15, K=K)
+    out = dn.denoise_tau(torch.from_numpy(img).cuda(), torch.full((len(S),), tau, dtype=torch.float64,
+                                                                  device="cuda"), p).cpu().numpy()
+    in_list, beyond = dn.guard_count()
+    assert (np.abs(S - tau) < 0.05 - 1e-4).sum() <= in_list + beyond <= (np.abs(S - tau) < 0.05 + 1e-4).sum()
+    assert in_list > 0 and (beyond > 0) == over
+    assert np.abs(out - oracle.denoise(img, U, V, tau, s=7, W=15, K=K)).max() <= TOL
