@@ -513,16 +513,11 @@ htsvd_status run_sigma(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &m
     return HTSVD_OK;
 }
 
-// cleared: an earlier launch of the call has set the counters to zero.
 htsvd_status run_filter(htsvd_ctx *ctx, const ImageGeom &g, const MethodParams &mp, const Ws &w,
-                        const double *tau, float *d_out, int64_t out_stride, hipStream_t st, bool cleared,
+                        const double *tau, float *d_out, int64_t out_stride, hipStream_t st,
                         const float *ra_d = nullptr, const uint8_t *ra_flag = nullptr) {
     hipError_t e;
-    {
-        StageScope sc(ctx, HTSVD_STAGE_CLEAR, st);
-        if (!cleared && (e = launch_zero(ctx->d_guard, 2 * sizeof(unsigned long long), st)) != hipSuccess)
-            return hip_fail(e, "zero counters");
-    }
+    { StageScope sc(ctx, HTSVD_STAGE_CLEAR, st); }   // the counters were cleared by an earlier launch of the call
     {
         StageScope sc(ctx, HTSVD_STAGE_FILTER, st);
         if ((e = launch_filter_mfma(g, w.tg, mp.K, ctx->basis[g.c == 3], w.idx, tau, w.regions, ctx->d_guard, st, ra_d,
@@ -1144,7 +1139,7 @@ htsvd_status htsvd_denoise_tau(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, i
             HTSVD_OK)
             return s;
     }
-    return run_filter(ctx, g, mp, wk, d_tau_ref, d_out, out_stride, st, true, ra_d, ra_f);
+    return run_filter(ctx, g, mp, wk, d_tau_ref, d_out, out_stride, st, ra_d, ra_f);
 }
 
 }  // extern "C"
@@ -1214,7 +1209,7 @@ htsvd_status denoise_impl(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_
     if (p->ra && (s = run_ra(ctx, g, mp, wk, wk.tau, (char *)ctx->ws + off_ra, mult, p->ra_sigma, st, &ra_d, &ra_f)) !=
                      HTSVD_OK)
         return s;
-    return run_filter(ctx, g, mp, wk, wk.tau, d_out, out_stride, st, true, ra_d, ra_f);
+    return run_filter(ctx, g, mp, wk, wk.tau, d_out, out_stride, st, ra_d, ra_f);
 }
 
 }  // namespace
@@ -1297,7 +1292,7 @@ htsvd_status htsvd_denoise_sweep(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h,
         const double mult = p->tau_mult > 0.0 ? p->tau_mult : default_mult(c, it.K);
         if ((e = launch_fill_tau(wk.tau, n_ref, nullptr, (double)it.sigma, mult, g, tile, st, ctx->d_guard)) != hipSuccess)
             return hip_fail(e, "tau");
-        if ((s = run_filter(ctx, g, mpi, wi, wk.tau, it.d_out, it.out_stride, st, true)) != HTSVD_OK) return s;
+        if ((s = run_filter(ctx, g, mpi, wi, wk.tau, it.d_out, it.out_stride, st)) != HTSVD_OK) return s;
     }
     return HTSVD_OK;
 }
@@ -1785,7 +1780,7 @@ htsvd_status htsvd_denoise_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *i
             cls_items[k].push_back(it);
             cls_src[k].push_back(i);
             cls_start[k].push_back(cls_start[k].back() + it.tg.tiles_y * it.tg.tiles_x);
-            cls_lds[k] = std::max(cls_lds[k], filter_lds_bytes_for(it.tg, C, K));
+            cls_lds[k] = std::max(cls_lds[k], filter_mfma_lds_bytes(it.tg, C));
         }
     }
     std::vector<size_t> o_citems(P.classes.size()), o_cstart(P.classes.size());
@@ -2030,9 +2025,10 @@ htsvd_status htsvd_denoise_batch(htsvd_ctx *ctx, int32_t n, const htsvd_image *i
         }
         for (size_t k = 0; k < P.classes.size(); ++k) {
             const int units = cls_start[k].back();
-            if ((e2 = launch_filter_batched(C, P.classes[k], (const BatchItem *)(D + o_citems[k]), (int)cls_items[k].size(),
-                                            (const int *)(D + o_cstart[k]), cls_lds[k], ctx->basis[C == 3], ctx->d_guard,
-                                            d_q + 1 + k, std::min(grid, units), ls)) != hipSuccess)
+            if ((e2 = launch_filter_mfma_batched(C, P.classes[k], (const BatchItem *)(D + o_citems[k]),
+                                                 (int)cls_items[k].size(), (const int *)(D + o_cstart[k]), cls_lds[k],
+                                                 ctx->basis[C == 3], ctx->d_guard, d_q + 1 + k, std::min(grid, units),
+                                                 ls)) != hipSuccess)
                 return hip_fail(e2, "batched filtering");
         }
         if ((e2 = launch_gather_batched(C, d_items, ni, (const int *)(D + o_pix), pix_start[ni], ls)) != hipSuccess)

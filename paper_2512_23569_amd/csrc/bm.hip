@@ -107,17 +107,6 @@ __device__ inline uint64_t readlane_u64(uint64_t v, int l) {
 // Ascending sort of one u64 per lane across the 64 lanes of a wave.
 __device__ inline uint64_t wave_sort64(uint64_t v, int lane) { return wave_sort_asc<uint64_t>(v, lane); }
 
-__device__ inline int wave_excl_scan(int v, int lane, int *total) {
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    *total = __shfl(x, 63);
-    return x - v;
-}
-
 // Ascending bitonic sort of n keys in LDS by one wave, in the form whose comparators are all
 // ascending (see wave_sort_asc), so that the places from n to the next power of two can be taken as
 // larger than any key without existing.

@@ -281,8 +281,6 @@ hipError_t launch_block_match_batched(const BatchItem *items, int n_items, const
                                       int max_W, int max_h, int max_w, int *queue, int grid, int units, hipStream_t st);
 // Rows of references per tile of block matching (REF_TILE columns), for images, steps and windows up to these.
 int bm_tile_rows(int s, int W, int h, int w);
-hipError_t launch_filter_batched(int C, int K, const BatchItem *items, int n_items, const int *unit_start, int lds,
-                                 const BasisDev &b, unsigned long long *gc, int *queue, int grid, hipStream_t st);
 hipError_t launch_gather_batched(int C, const BatchItem *items, int n_items, const int *pix_start, int total_px,
                                  hipStream_t st);
 int select_k_chunks(int64_t max_refs);
@@ -301,7 +299,6 @@ hipError_t launch_gather(const ImageGeom &g, const TileGeom &tg, const float *re
                          hipStream_t st);
 // Whether `planes` planes of rows x cols words, rows padded to 8 modulo 16 words, fit in LDS beside 65 KB.
 bool padded_region_fits(int planes, int rows, int cols);
-int filter_lds_bytes_for(const TileGeom &tg, int C, int K);
 // matrix-core filter (filter_mfma.hip)
 int filter_mfma_lds_bytes(const TileGeom &tg, int C);
 int filter_mfma_group_bytes(int C);  // LDS besides the region

@@ -95,11 +95,6 @@ bool padded_region_fits(int planes, int rows, int cols) {
     return (int64_t)planes * rows * (cols + (24 - cols % 16) % 16) * 4 + 65 * 1024 <= filter_lds_budget();
 }
 
-int filter_lds_bytes_for(const TileGeom &tg, int C, int K) {
-    (void)K;
-    return filter_mfma_lds_bytes(tg, C);
-}
-
 // Fixed-point shift of the region sums: a pixel of a tile's region receives at most T^2 K
 // contributions (every member of every group of the tile), each clamped to |v| <= 1024, so
 // T^2 K 1024 2^FS must stay below 2^31.  Tiles are capped so that FS >= 9: a contribution
@@ -117,13 +112,14 @@ int accumulation_shift(int T, int K) {
     return fs;
 }
 
-// Estimated microseconds of the filter over n_tiles tiles of refs references (K members each), on
-// `share` of the 256 CUs: one workgroup of 8 waves per CU takes whole tiles, a wave takes 32
-// patches per step, and a tile costs a fixed time besides (clearing and writing its region, the
-// first loads of its patches, waves that wait for the last one).  Measured with the tile side
-// forced: 512 x 512 RGB, stride 4, window 31, K 32: 187, 188, 164, 146, 203 us at side 4, 5, 6, 8,
-// 10, which is rounds (steps 14.5 + 18); 1536 x 2048 gray, K 16: 538, 412, 332, 320 us at side
-// 4, 6, 8, 11, rounds (steps 4.6 + 9).
+// Estimated microseconds of the filter over n_tiles tiles of refs references (K members each), on `share` of
+// the GPU's 256 CUs (asked of no device: a plan is the same wherever it is made, and a partition with fewer
+// CUs only gets tiles that suit the whole GPU): one workgroup of 8 waves per CU takes whole tiles, a wave takes
+// 32 patches per step, and a tile costs a fixed time besides (clearing and writing its region, the first loads
+// of its patches, waves that wait for the last one).  The constants come from these two shapes, with the tile
+// side forced: 512 x 512 RGB, stride 4, window 31, K 32: 187, 188, 164, 146, 203 us at side 4, 5, 6, 8, 10,
+// which is rounds (steps 14.5 + 18); 1536 x 2048 gray, K 16: 538, 412, 332, 320 us at side 4, 6, 8, 11, rounds
+// (steps 4.6 + 9).
 double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share) {
     const int64_t cu = max((int64_t)1, (int64_t)(256 * share + 0.5));
     const double steps = max(1.0, (double)refs * K / 32 / 8);
@@ -175,11 +171,6 @@ TileGeom plan_filter_tiles(const ImageGeom &g, int W, int K, int max_side, doubl
 }
 
 size_t filter_region_bytes(const TileGeom &tg, int c) { return region_bytes(tg, c); }
-
-hipError_t launch_filter_batched(int C, int K, const BatchItem *items, int n_items, const int *unit_start, int lds,
-                                 const BasisDev &b, unsigned long long *gc, int *queue, int grid, hipStream_t st) {
-    return launch_filter_mfma_batched(C, K, items, n_items, unit_start, lds, b, gc, queue, grid, st);
-}
 
 hipError_t launch_gather_batched(int C, const BatchItem *items, int n_items, const int *pix_start, int total_px,
                                  hipStream_t st) {

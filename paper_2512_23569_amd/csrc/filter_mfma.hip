@@ -362,8 +362,8 @@ __device__ __forceinline__ FilterLds<C> filter_lds_init(float *smem, const v8h *
 // row side by side instead of one after the other.
 template <int C, bool RA = false, int GA = 0>
 __device__ __forceinline__ void filter_tile_mfma(const ImageGeom &g, const TileGeom &tg, const FilterLds<C> &L,
-                                                 const v8h *__restrict__ FG, const double *__restrict__ T64,
-                                                 const int K, const int32_t *__restrict__ idx, const int idx_stride,
+                                                 const double *__restrict__ T64, const int K,
+                                                 const int32_t *__restrict__ idx, const int idx_stride,
                                                  const double *__restrict__ tau_ref, const double tau_mul,
                                                  float *__restrict__ regions,
                                                  unsigned long long *__restrict__ guard_count, const int tile,
@@ -1021,7 +1021,7 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_kernel(ImageGeom g, TileG
     for (int v = blockIdx.x; v < 8 * per; v += gridDim.x) {
         const int tile = (v & 7) * per + (v >> 3);
         if (tile >= n_tiles) continue;
-        filter_tile_mfma<C, RA>(g, tg, L, F, T64, K, idx, K, tau_ref, 1.0, regions, guard_count, tile, sh, ra_d,
+        filter_tile_mfma<C, RA>(g, tg, L, T64, K, idx, K, tau_ref, 1.0, regions, guard_count, tile, sh, ra_d,
                                 ra_flag);
         __syncthreads();
     }
@@ -1049,7 +1049,7 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_ga_kernel(ImageGeom g, Ti
     for (int v = blockIdx.x; v < 8 * per; v += gridDim.x) {
         const int tile = (v & 7) * per + (v >> 3);
         if (tile >= n_tiles) continue;
-        filter_tile_mfma<C, RA, GA>(g, tg, L, F, T64, K, idx, K, tau_ref, 1.0, nullptr, guard_count, tile, sh, ra_d,
+        filter_tile_mfma<C, RA, GA>(g, tg, L, T64, K, idx, K, tau_ref, 1.0, nullptr, guard_count, tile, sh, ra_d,
                                     ra_flag, gacc, ghist, vt);
         __syncthreads();
     }
@@ -1196,7 +1196,7 @@ __global__ __launch_bounds__(MW * 64) void filter_mfma_kernel_batched(const Batc
         if (u >= total) break;
         const int i = find_unit(unit_start, n_items, u);
         const BatchItem it = items[i];
-        filter_tile_mfma<C>(it.g, it.tg, L, F, T64, K, it.idx, it.idx_stride, it.tau, it.tau_mul, it.regions,
+        filter_tile_mfma<C>(it.g, it.tg, L, T64, K, it.idx, it.idx_stride, it.tau, it.tau_mul, it.regions,
                             guard_count, u - unit_start[i], sh);
         __syncthreads();
     }
