@@ -43,7 +43,9 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // The real band DFT separates into cosines of the even part of a tube, x_b + x_{B-b}, and sines of
 // the odd part, x_b - x_{B-b} (b < NF = B / 2 + 1; x_0, and x_{B/2} of an even B, stand alone), each
 // half as many rows and columns as the whole DFT: a quarter of the products each.  FB is the number
-// of 16-row blocks of the cosines: 1 for B <= 31, 2 up to 63, 3 for 64.
+// of 16-row blocks of the cosines: 1 for B <= 31, 2 up to 63, 3 for 64; and 0 for 32 bands, one block and a
+// 17th cosine, which lanes sum from the operands of the block (with a second block, of that row alone,
+// the call for 256 x 256 x 32 at K 16 and noise 10 took 2.40 ms instead of 1.42).
 //
 // The workgroup's patches and the LDS layout of their spectra: value (i, j) of component c of patch p
 // at Z[p*ZP + c*64 + zpos(c, i, j)], component f the real part of frequency f and IM + f its
@@ -52,9 +54,15 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // banks of 4 bytes: a wave's 32-lane halves reach 32 distinct double slots).
 template <int FB> struct BandTile {
     static constexpr int PP = 2;                            // patches per workgroup (256 threads), two waves each
-    static constexpr int KS = FB == 3 ? 9 : 4 * FB;         // k-steps of a cosine product
-    static constexpr int IM = (FB == 3 ? 33 : 16 * FB) - 1; // frequency 0 has no imaginary part
-    static constexpr int ZP = (FB == 1 ? 31 : (FB == 2 ? 63 : 64)) * 64 + 16;   // doubles per patch
+    static constexpr int CB = FB == 0 ? 1 : FB;
+    static constexpr int KS = FB == 3 ? 9 : FB == 0 ? 5 : 4 * FB;   // k-steps of a cosine product
+    static constexpr int KS1 = FB == 0 ? 4 : KS;                    // of a sine product
+    // component of the imaginary part of frequency f, which frequency 0 has not, less f; odd where that costs
+    // nothing, so that both parts of a frequency keep free of bank conflicts
+    static constexpr int IM = FB == 3 ? 32 : FB == 0 ? 17 : 16 * FB - 1;
+    static constexpr int ZP = (FB == 0 ? 33 : FB == 1 ? 31 : (FB == 2 ? 63 : 64)) * 64 + 16;   // doubles per patch
+    static constexpr bool OPS = FB < 2;                             // operands in LDS
+    static constexpr int N_OPS = OPS ? 4 * KS * 64 + (FB == 0 ? 2 * 4 * KS : 0) : 1;
 };
 
 __device__ inline int zpos(int c, int i, int j) {
@@ -73,7 +81,7 @@ __device__ inline int re_row(int f, int B) { return f == 0 ? 0 : (2 * f == B ? B
 // as rows, bands as columns), or of its inverse.  Rows and columns beyond NF repeat the last: those
 // rows are not used, those columns meet zeros.  Read from memory a lane's rows lie apart, and the first
 // cache's lookups bound the whole kernel (926 us for all of 63,504 rows of 31 bands; from LDS, with
-// the next row's sums loaded ahead, 797), so for FB = 1 a workgroup keeps them in LDS.
+// the next row's sums loaded ahead, 797), so for one block a workgroup keeps them in LDS.
 template <int FB, bool INV>
 __device__ __forceinline__ void band_operand(const double *__restrict__ M, int B, int nb, int part, int cb, int lane,
                                              double (&a)[BandTile<FB>::KS]) {
@@ -88,10 +96,23 @@ __device__ __forceinline__ void band_operand(const double *__restrict__ M, int B
 }
 
 // The same from LDS.
-template <bool INV>
-__device__ __forceinline__ void band_operand_lds(const double *ops, int part, int lane, double (&a)[4]) {
+template <int FB, bool INV>
+__device__ __forceinline__ void band_operand_lds(const double *ops, int part, int lane, double (&a)[BandTile<FB>::KS]) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) a[s] = ops[((2 * INV + part) * 4 + s) * 64 + lane];
+    for (int s = 0; s < BandTile<FB>::KS; ++s) a[s] = ops[((2 * INV + part) * BandTile<FB>::KS + s) * 64 + lane];
+}
+
+// Row 16 of the cosine product of 32 bands, or of its inverse, in every lane of a position: columns 4 s + q by
+// the lanes q, whose sums are added.
+template <bool INV>
+__device__ __forceinline__ double band_last(const double *ops, const double (&x)[BandTile<0>::KS], int q) {
+    constexpr int KS = BandTile<0>::KS;
+    const double *a = ops + 4 * KS * 64 + 4 * KS * INV + q;
+    double t = 0.0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) t = fma(a[4 * s], x[s], t);
+    t += __shfl_xor(t, 16);
+    return t + __shfl_xor(t, 32);
 }
 
 // Band DFT of a wave's 32 positions: component c of e from the even and odd parts x of its tube.
@@ -104,11 +125,11 @@ __device__ __forceinline__ void band_dft(const double *__restrict__ D, const dou
     for (int part = 0; part < 2; ++part) {
         const int rows = part ? NS : NF;
 #pragma unroll
-        for (int cb = 0; cb < FB; ++cb) {
+        for (int cb = 0; cb < BandTile<FB>::CB; ++cb) {
             if (FB > 1 && 16 * cb >= rows) continue;
             double a[BandTile<FB>::KS];
-            if constexpr (FB == 1)
-                band_operand_lds<false>(ops, part, lane, a);
+            if constexpr (BandTile<FB>::OPS)
+                band_operand_lds<FB, false>(ops, part, lane, a);
             else
                 band_operand<FB, false>(D, B, nb, part, cb, lane, a);
 #pragma unroll
@@ -116,14 +137,20 @@ __device__ __forceinline__ void band_dft(const double *__restrict__ D, const dou
                 const int e = 32 * half + 16 * u + col;
                 dbl4 t = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int s = 0; s < BandTile<FB>::KS; ++s)
-                    if (FB == 1 || 4 * s < rows) t = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], x[part][u][s], t, 0, 0, 0);
+                for (int s = 0; s < (part ? BandTile<FB>::KS1 : BandTile<FB>::KS); ++s)
+                    if (FB < 2 || 4 * s < rows) t = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], x[part][u][s], t, 0, 0, 0);
                 // the parity of a component is that of q (of its imaginary part, the other): constant steps
                 const int c0 = (part ? BandTile<FB>::IM : 0) + 16 * cb + q;
                 double *zc = z + c0 * 64 + zpos(c0, e >> 3, e & 7);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)   // FB = 1: rows past the last frequency land in slots nobody reads
-                    if ((FB == 1 || 16 * cb + q + 4 * r < rows) && (!part || cb || r || q)) zc[r * 256] = t[r];
+                    if ((FB < 2 || 16 * cb + q + 4 * r < rows) && (!part || cb || r || q)) zc[r * 256] = t[r];
+                if constexpr (FB == 0) {
+                    if (part == 0) {
+                        const double last = band_last<false>(ops, x[0][u], q);
+                        if (q == 0) z[16 * 64 + zpos(16, e >> 3, e & 7)] = last;
+                    }
+                }
             }
         }
     }
@@ -145,26 +172,26 @@ __device__ __forceinline__ void band_idft(const double *__restrict__ Dinv, const
             for (int s = 0; s < KS; ++s) {
                 const int f = 4 * s + q, e = 32 * half + 16 * u + col, c0 = (part ? BandTile<FB>::IM : 0) + q;
                 const bool in = f >= part && f < (part ? NS : NF);
-                const int c = FB < 3 || in ? c0 + 4 * s : c0;   // 64 bands: 4 s + q may pass the last slot
+                const int c = FB == 1 || FB == 2 || in ? c0 + 4 * s : c0;   // 32 and 64 bands: 4 s + q may pass the last slot
                 const double t = z[c * 64 + zpos(c0, e >> 3, e & 7)];
                 v[part][u][s] = in ? t : 0.0;
             }
 #pragma unroll
-    for (int cb = 0; cb < FB; ++cb) {
+    for (int cb = 0; cb < BandTile<FB>::CB; ++cb) {
         dbl4 t[2][2];
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
             double a[KS];
-            if constexpr (FB == 1)
-                band_operand_lds<true>(ops, part, lane, a);
+            if constexpr (BandTile<FB>::OPS)
+                band_operand_lds<FB, true>(ops, part, lane, a);
             else
                 band_operand<FB, true>(Dinv, B, nb, part, cb, lane, a);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 t[part][u] = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int s = 0; s < KS; ++s)
-                    if (FB == 1 || 4 * s < (part ? NS : NF))
+                for (int s = 0; s < (part ? BandTile<FB>::KS1 : KS); ++s)
+                    if (FB < 2 || 4 * s < (part ? NS : NF))
                         t[part][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], v[part][u][s], t[part][u], 0, 0, 0);
             }
         }
@@ -176,6 +203,13 @@ __device__ __forceinline__ void band_idft(const double *__restrict__ Dinv, const
                     y[0][u][4 * cb + r] = t[0][u][r] + t[1][u][r];
                     y[1][u][4 * cb + r] = t[0][u][r] - t[1][u][r];
                 }
+    }
+    if constexpr (FB == 0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {   // band 16 has no odd part; lanes q > 0 hold no band here
+            y[0][u][4] = band_last<true>(ops, v[0][u], q);
+            y[1][u][4] = 0.0;
+        }
     }
 }
 
@@ -537,27 +571,35 @@ __global__ __launch_bounds__(256, 3) void band_test_kernel(int B, int nb, int K,
 // back with the factors swapped.  The coefficients never leave the registers; a row without kept
 // coefficients stores only its mark.
 template <int FB>
-__global__ __launch_bounds__(256, FB == 1 ? 4 : 2) void band_rows_kernel(
+__global__ __launch_bounds__(256, FB == 1 ? 4 : FB == 0 ? 3 : 2) void band_rows_kernel(
     int B, int nb, int K, int64_t n_rows, const int *__restrict__ list, const int *__restrict__ n_list,
     const double *__restrict__ D, const double *__restrict__ Dinv, const double *__restrict__ frag_fwd,
     const double *__restrict__ frag_inv, double tau, double *__restrict__ S) {
     using T = BandTile<FB>;
     __shared__ double Z[T::PP * T::ZP];
-    __shared__ double ops[FB == 1 ? 4 * 4 * 64 : 1];
+    __shared__ double ops[T::N_OPS];
     __shared__ int kept[2][T::PP];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), p = wave & 1, half = wave >> 1;
     const int NF = B / 2 + 1, KS = (NF + 3) >> 2;
     int lane = tid & 63;
     double *z = Z + p * T::ZP;
     if (tid < 2 * T::PP) kept[tid / T::PP][tid % T::PP] = 0;
-    if constexpr (FB == 1) {   // wave = (inverse, part)
+    if constexpr (T::OPS) {   // wave = (inverse, part)
         double a[T::KS];
         if (wave < 2)
             band_operand<FB, false>(D, B, nb, wave, 0, lane, a);
         else
             band_operand<FB, true>(Dinv, B, nb, wave - 2, 0, lane, a);
 #pragma unroll
-        for (int s = 0; s < T::KS; ++s) ops[(wave * 4 + s) * 64 + lane] = a[s];
+        for (int s = 0; s < T::KS; ++s) ops[(wave * T::KS + s) * 64 + lane] = a[s];
+        if constexpr (FB == 0) {   // row 16 of both, zero beyond its 17 columns
+            if (tid < 2 * 4 * T::KS) {
+                const bool inv = tid >= 4 * T::KS;
+                const int k = tid - (inv ? 4 * T::KS : 0), c = min(k, 16);
+                const double d = inv ? Dinv[16 * nb + re_row(c, 32)] : D[re_row(16, 32) * nb + c];
+                ops[4 * T::KS * 64 + tid] = k > 16 ? 0.0 : d;
+            }
+        }
     }
     __syncthreads();
 
@@ -789,8 +831,11 @@ hipError_t launch_pass(const BandMaps &bm, const uint8_t *cube, int64_t stride, 
                        hipStream_t st) {
     const auto haar = B == 2 ? band_haar_kernel<K, true> : band_haar_kernel<K, false>;
     hipLaunchKernelGGL(haar, dim3((unsigned)ng), dim3(256), 0, st, cube, stride, a.w, B, idx, S);
-    const auto rows = B <= 31 ? band_rows_kernel<1> : (B <= 63 ? band_rows_kernel<2> : band_rows_kernel<3>);
-    // workgroups that go through the rows: three per CU, then four (FB = 1) or two are resident
+    const auto rows = B <= 31   ? band_rows_kernel<1>
+                      : B == 32 ? band_rows_kernel<0>
+                      : B <= 63 ? band_rows_kernel<2>
+                                : band_rows_kernel<3>;
+    // workgroups that go through the rows: three per CU, then four (FB = 1), three (0) or two are resident
     int *list = n_list + 1;
     const bool test = B <= 31 && ng * K > test_min_rows(B);
     if (test) {
@@ -801,7 +846,7 @@ hipError_t launch_pass(const BandMaps &bm, const uint8_t *cube, int64_t stride, 
         hipLaunchKernelGGL(band_test_kernel, dim3(std::min<unsigned>(nb(ng * K, 4 * TEST_ROWS), 768)), dim3(256), 0, st, B,
                            bm.nb, K, ng * K, bm.D, bm.frag_fwd, tau, S, list, n_list);
     }
-    const unsigned grid = std::min<unsigned>(nb(ng * K, BandTile<1>::PP), B <= 31 ? 1024 : 512);
+    const unsigned grid = std::min<unsigned>(nb(ng * K, BandTile<1>::PP), B <= 31 ? 1024 : B == 32 ? 768 : 512);
     hipLaunchKernelGGL(rows, dim3(grid), dim3(256), 0, st, B, bm.nb, K, ng * K, test ? list : nullptr, n_list, bm.D,
                        bm.Dinv, bm.frag_fwd, bm.frag_inv, tau, S);
     const int tiles_x = (a.nx + a.TR - 1) / a.TR;

@@ -318,3 +318,22 @@ def test_band_gram_sums_of_more_slices_than_one_launch_takes(dn):
         want[g, 0, 1, 7, 7] += (7 - v) * v
         want[g, 1, 1, 7, 7] += 7 * 7 - v * v
     assert np.array_equal(G, want)
+
+
+# 32 bands have a 17th cosine beside the DFT's block of 16: a single group, one round of the workgroups and
+# several (1,536 rows each), rows that keep everything, some or nothing
+@pytest.mark.parametrize("K,s,W,h,w", [(4, 4, 15, 11, 8), (4, 3, 9, 21, 30), (16, 2, 15, 30, 41), (32, 3, 21, 40, 33)])
+@pytest.mark.parametrize("sigma", [0.01, 12.0, 4000.0])
+@pytest.mark.parametrize("harsh", [False, True])
+def test_32_bands(dn, K, s, W, h, w, sigma, harsh):
+    """As test_band_rows_at_the_edges: within 2^-15 of the oracle."""
+    import paper_2512_23569_amd as ht
+    noisy = synth.add_awgn(synth.make_hsi(h, w, 32, 160 + K), 12.0, 161)
+    if harsh:
+        noisy = np.where(np.random.default_rng(7).random(noisy.shape) < 0.5, 0, 255).astype(np.uint8)
+    U, V = lb.learn(noisy, 8, 3)
+    ht.htsvd_set_basis(dn.ctx, 8, 32, oracle.to_slices(U), oracle.to_slices(V))
+    idx, _ = oracle.block_match(oracle.band_guide(noisy), 8, s, W, K)
+    ref = oracle.filter_groups(noisy, idx, U, V, float(np.float32(sigma)) * np.sqrt(2.0 * np.log(32 * K * 64)))
+    out = dn.denoise_bands(_dev(noisy), sigma, dn.params(1, stride=s, window=W, K=K)).cpu().numpy()
+    assert np.abs(out - ref).max() <= 2.0 ** -15
