@@ -101,7 +101,7 @@ htsvd_status htsvd_set_basis(htsvd_ctx *ctx, int32_t ps, int32_t c, const double
  *   d_gram[((0*c + a)*c + b)*64 + i*8 + k] = sum_P sum_j P(i, j, a) P(k, j, b)   (patch rows)
  *   d_gram[((1*c + a)*c + b)*64 + i*8 + k] = sum_P sum_j P(j, i, a) P(j, k, b)   (patch columns)
  * Exact integers.  Asynchronous on `stream` (clears d_gram first); the caller owns d_gram.
- * Errors: HTSVD_EINVAL (null pointers, c not 1/3, stride < 1, in_stride < w*c), HTSVD_ENOTSUP
+ * Errors: HTSVD_EINVAL (null pointers, c not 1 .. 64, stride < 1, in_stride < w*c), HTSVD_ENOTSUP
  * (ps != 8, more than 2^30 pixels), HTSVD_ESHAPE (image smaller than one patch). */
 htsvd_status htsvd_basis_gram(htsvd_ctx *ctx, const uint8_t *d_in, int32_t h, int32_t w, int32_t c,
                               int64_t in_stride, int32_t ps, int32_t stride, int64_t *d_gram, void *stream);

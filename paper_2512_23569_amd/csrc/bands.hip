@@ -172,7 +172,8 @@ __device__ __forceinline__ void band_idft(const double *__restrict__ Dinv, const
             for (int s = 0; s < KS; ++s) {
                 const int f = 4 * s + q, e = 32 * half + 16 * u + col, c0 = (part ? BandTile<FB>::IM : 0) + q;
                 const bool in = f >= part && f < (part ? NS : NF);
-                const int c = FB == 1 || FB == 2 || in ? c0 + 4 * s : c0;   // 32 and 64 bands: 4 s + q may pass the last slot
+                // 32 and 64 bands: 4 s + q may pass the last slot
+                const int c = FB == 1 || FB == 2 || in ? c0 + 4 * s : c0;
                 const double t = z[c * 64 + zpos(c0, e >> 3, e & 7)];
                 v[part][u][s] = in ? t : 0.0;
             }
@@ -394,8 +395,9 @@ __device__ inline h4 to_h4(f4 v) { return __builtin_convertvector(v, h4); }
 // Bound.  All three stages are written with orthonormal factors (the DFT scaled by c_f = sqrt(2 / B),
 // sqrt(1 / B) at frequencies 0 and B / 2; unitary slices), so an error vector reaches one coefficient
 // with at most its 2-norm.  With u = 2^-11 and |x| the norm of the row: the DFT's factors are split
-// into two halves and whole numbers up to 2048 are exact in fp16 (else u sqrt(1 + 3 / B) sqrt(B) |x|
-// for their rounding, by Cauchy's inequality per component); each of the two slice products errs by
+// into two halves and whole numbers up to 2048 are exact in fp16 (else their rounding adds u |x| at most, as
+// the DFT of the folded row has a spectral norm of 1 at most; 1.1 sqrt(B) u |x| is taken, which is more for
+// every B); each of the two slice products errs by
 // u per entry of its factor, 16 entries of unit norm to a row: 4 u |x|; each of the three
 // results stored as fp16 adds u |x|; the last factor u |x|.  Sum 12 u |x|, 13 with the second-order and
 // FP32 terms, and 0.02 for values below fp16's normal range.  Infinities and NaN count as large.
@@ -567,9 +569,9 @@ __global__ __launch_bounds__(256, 3) void band_test_kernel(int B, int nb, int K,
 }
 
 // The t-product of two of the listed Haar rows, or of all of them where there is no list (Eq. 19), the
-// hard threshold |s| >= tau (Eq. 20) and, where a coefficient is kept, the inverse t-product (Eq. 21): U_hat_f^H P_hat_f V_hat_f per frequency and
-// back with the factors swapped.  The coefficients never leave the registers; a row without kept
-// coefficients stores only its mark.
+// hard threshold |s| >= tau (Eq. 20) and, where a coefficient is kept, the inverse t-product (Eq. 21):
+// U_hat_f^H P_hat_f V_hat_f per frequency and back with the factors swapped.  The coefficients never leave
+// the registers; a row without kept coefficients stores only its mark.
 template <int FB>
 __global__ __launch_bounds__(256, FB == 1 ? 4 : FB == 0 ? 3 : 2) void band_rows_kernel(
     int B, int nb, int K, int64_t n_rows, const int *__restrict__ list, const int *__restrict__ n_list,

@@ -24,11 +24,11 @@
 // It is bound by vector instructions, so the work per candidate is kept to few: in the distance
 // phase a wave takes a fixed block of columns and steps through the rows, so that addresses advance
 // by constants and a window's columns are tested once, and the keys sorted are 32 bits wide
-// wherever their range allows.  1,205 vector instructions per reference of a 12 MP image with
-// window 31, 4.20 ms (1,575 and 4.70 ms when both sides of each window were tested per reference
-// and position, the keys were counted before they were compacted, and channel sums took 64-bit
-// keys).  The rest is the waits at the barriers between a tile's phases, which a second workgroup on
-// the CU fills: 3.44 ms.  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions (the
+// wherever their range allows: 12 MP, step 3, window 31, noise known, 4.70 -> 4.20 ms (when both sides of
+// each window were tested per reference and position, the keys were counted before they were
+// compacted, and channel sums took 64-bit keys).  The waits at the barriers between a tile's phases are
+// filled by a second workgroup on the CU: 3.44 ms.  With it vector instructions are active in 88% of the
+// cycles, 1,649 per reference (noise 50, 12 references to a tile).  The kernels are compiled for windows of up to 256, 448, 640 and 961 positions (the
 // windows of all frames of a video also for up to 704: window 15 in three frames), so that
 // small windows neither walk empty table rows nor hold LDS for them: 1536 x 2048 gray, window 21,
 // 560 -> 423 us; four 720 x 1280 frames with window 15, 2,505 -> 981 us.

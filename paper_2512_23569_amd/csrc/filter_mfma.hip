@@ -1328,10 +1328,11 @@ static int ga_least_shift(int C, int K, int h_frame, int w, int s, int R, int ns
 // tables; 0 where the sums straight to memory are estimated to take less.  Besides the filter and the
 // regions' way to memory (as for one image): the gather reads 300 region pixels per nanosecond, but a
 // thread waits some 0.7 us at each of its own; sums in memory take 118 values per nanosecond (RGB) or 78
-// (gray), one pixel's about 0.3 us each, and two launches more.  Measured with either forced, filter and gather: six 200 x 300 RGB frames, radius 2, window 31, K
-// 32: 2,096 us with single references to a region (2.1 GB), 1,168 without; twenty 128 x 128 gray frames,
-// radius 10: 2,376 (2.5 GB) and 518; ten 200 x 300 RGB frames, radius 3, window 21, K 32: 930 (2 x 2) and
-// 1,856; four 720 x 1280 RGB frames, radius 1: 1,953 (7 x 7) and 11,944.
+// (gray), one pixel's about 0.3 us each, and two launches more.  Measured with either forced, filter and
+// gather: six 200 x 300 RGB frames, radius 2, window 31, K 32: 2,096 us with single references to a region
+// (2.1 GB), 1,168 without; twenty 128 x 128 gray frames, radius 10: 2,376 (2.5 GB) and 518; ten 200 x 300
+// RGB frames, radius 3, window 21, K 32: 930 (2 x 2) and 1,856; four 720 x 1280 RGB frames, radius 1: 1,953
+// (7 x 7) and 11,944.
 static int video_tile_side(int C, int K, int T, int ny_frame, int nx, int h_frame, int w, int s, int W, int nslot,
                            VideoTiling *vt) {
     const int R = (W - 1) / 2;
