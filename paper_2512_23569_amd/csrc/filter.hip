@@ -8,6 +8,8 @@
 // covering each pixel.  The gather kernel then sums, for every pixel, the (at most a few)
 // regions covering it and divides (uniform weights, "average" aggregation); a pixel no patch
 // covers keeps its noisy value.
+#include <algorithm>
+
 #include "common.h"
 
 namespace htsvd {
@@ -116,13 +118,13 @@ int accumulation_shift(int T, int K) {
 // the GPU's 256 CUs (asked of no device: a plan is the same wherever it is made, and a partition with fewer
 // CUs only gets tiles that suit the whole GPU): one workgroup of 8 waves per CU takes whole tiles, a wave takes
 // 32 patches per step, and a tile costs a fixed time besides (clearing and writing its region, the first loads
-// of its patches, waves that wait for the last one).  The constants come from these two shapes, with the tile
-// side forced: 512 x 512 RGB, stride 4, window 31, K 32: 187, 188, 164, 146, 203 us at side 4, 5, 6, 8, 10,
-// which is rounds (steps 14.5 + 18); 1536 x 2048 gray, K 16: 538, 412, 332, 320 us at side 4, 6, 8, 11, rounds
-// (steps 4.6 + 9).
+// of its patches, waves that wait for the last one).  Whole steps that every wave takes are counted, not the
+// last one of some.  The constants come from two shapes, with the tile side forced: 512 x 512 RGB, stride 4,
+// window 31, K 32: 187, 188, 164, 146, 203 us at side 4, 5, 6, 8, 10, rounds (steps 14.5 + 18) = 188, 185, 152,
+// 134, 192; 1536 x 2048 gray, K 16: 538, 412, 332, 320 us at side 4, 6, 8, 11, rounds (steps 4.6 + 9).
 double filter_tiles_cost(int c, int K, int64_t n_tiles, int refs, double share) {
-    const int64_t cu = max((int64_t)1, (int64_t)(256 * share + 0.5));
-    const double steps = max(1.0, (double)refs * K / 32 / 8);
+    const int64_t cu = std::max<int64_t>(1, (int64_t)(256 * share + 0.5));
+    const int64_t steps = std::max(1, refs * K / (32 * 8));
     return (double)((n_tiles + cu - 1) / cu) * (c == 3 ? 14.5 * steps + 18.0 : 4.6 * steps + 9.0);
 }
 
